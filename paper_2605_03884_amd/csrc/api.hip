@@ -240,9 +240,10 @@ static qkv_card_header_t make_header(const qkv_desc_t* desc, const CardGeom& g, 
 }
 
 static int plan_card(const qkv_desc_t* desc, const uint8_t* bits_dev, const CardGeom& g, const uint64_t n[4], uint8_t* card,
-              hipStream_t s, uint32_t flags = 0) {
+              hipStream_t s, uint32_t flags = 0, const uint8_t* card_in = nullptr, uint64_t card_in_bytes = 0,
+              uint32_t* status_in = nullptr) {
   const qkv_card_header_t h = make_header(desc, g, n, flags);
-  return launch_classify(bits_dev, g, h, card, s) == hipSuccess ? QKV_OK : QKV_ERR_HIP;
+  return launch_classify(bits_dev, g, h, card, s, card_in, card_in_bytes, status_in) == hipSuccess ? QKV_OK : QKV_ERR_HIP;
 }
 
 // Scores and a budget to widths and a planned card, one launch.  `counts_out` gets the budget's class counts.
@@ -353,7 +354,7 @@ int qkv_requantize(const void* card_in_dev, uint64_t card_in_bytes, const qkv_de
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint8_t* card = static_cast<uint8_t*>(card_out_dev);
-  rc = plan_card(desc, bits_dev, g, n, card, s);
+  rc = plan_card(desc, bits_dev, g, n, card, s, 0, static_cast<const uint8_t*>(card_in_dev), card_in_bytes, status_dev);
   if (rc) return rc;
   if (launch_requant(static_cast<const uint8_t*>(card_in_dev), card_in_bytes, g, card, status_dev, s) != hipSuccess)
     return QKV_ERR_HIP;

@@ -10,8 +10,12 @@
 // per-thread counters then gives every token its slot, so the bucketing is stable
 // (increasing token index inside a class).  The work is bound by instruction issue, not by
 // memory, which is why it is spread over several compute units instead of one.
-// Workgroup 0 also writes the header and zeroes the pad bytes of every section.
+// Workgroup 0 also writes the header and zeroes the pad bytes of every section, and, where the card
+// is made from another one (requantization), the verdict on that card's header into the caller's
+// status word: the kernel that follows on the stream only adds to it (a launch of its own for the
+// verdict cost 4.6 us of 215).
 #include "qkv_common.h"
+#include "qkv_decode.h"
 #include "qkv_plan.h"
 
 namespace qkv {
@@ -21,8 +25,6 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWaveSize;
 constexpr uint32_t kPerThread = 8;
 constexpr uint32_t kPerBlock = kThreads * kPerThread;
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Number of bytes of w equal to the byte replicated in `pattern` (exact, no carries between bytes).
 __device__ inline uint32_t count_bytes_equal(uint64_t w, uint64_t pattern) {
@@ -64,7 +66,9 @@ __device__ inline void block_sums(uint32_t (&v)[N], uint32_t lane, uint32_t wave
 
 __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __restrict__ bits, CardGeom g,
                                                            qkv_card_header_t header, PadTable pads,
-                                                           uint8_t* __restrict__ card, bool aligned) {
+                                                           uint8_t* __restrict__ card, bool aligned,
+                                                           const uint8_t* card_in, uint64_t card_in_bytes,
+                                                           uint32_t* status_in) {
   __shared__ uint32_t sum_slots[7][kWaves];
   __shared__ uint32_t slots[kWaves];
   const uint32_t tid = threadIdx.x;
@@ -158,15 +162,22 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
   uint32_t status = (valid != T) ? QKV_STATUS_BAD_BITS : 0u;
   if (tot0 != g.n[0] || tot1 != g.n[1] || tot2 != g.n[2] || tot3 != g.n[3]) status |= QKV_STATUS_BAD_COUNTS;
   write_header_and_pads(card, header, pads, status, tid);
+  if (status_in) {
+    CardGeom in;
+    const bool ok = card_geometry_from_header(card_in, card_in_bytes, g.layers, g.kv_heads, g.head_dim, g.group_size, T, in);
+    if (tid == 0) *status_in = ok ? 0u : QKV_STATUS_BAD_HEADER;
+  }
 }
 
 }  // namespace
 
 hipError_t launch_classify(const uint8_t* bits, const CardGeom& geom, const qkv_card_header_t& header,
-                           uint8_t* card, hipStream_t stream) {
+                           uint8_t* card, hipStream_t stream, const uint8_t* card_in, uint64_t card_in_bytes,
+                           uint32_t* status_in) {
   const bool aligned = reinterpret_cast<uintptr_t>(bits) % 8 == 0;
   const uint32_t blocks = (geom.tokens + kPerBlock - 1) / kPerBlock;
-  hipLaunchKernelGGL(classify_kernel, dim3(blocks), dim3(kThreads), 0, stream, bits, geom, header, make_pad_table(geom), card, aligned);
+  hipLaunchKernelGGL(classify_kernel, dim3(blocks), dim3(kThreads), 0, stream, bits, geom, header, make_pad_table(geom), card, aligned,
+                     card_in, card_in_bytes, status_in);
   return hipGetLastError();
 }
 

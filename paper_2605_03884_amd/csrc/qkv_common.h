@@ -142,8 +142,10 @@ __device__ inline uint32_t find_bucket(const uint32_t* hist, uint32_t lane, uint
 int grid_blocks(uint64_t tiles);
 
 // Kernel launchers (one per source file).  All enqueue on `stream` and return a hipError_t.
+// card_in, status_in: the card this one is made from and where the verdict on its header goes, or null.
 hipError_t launch_classify(const uint8_t* bits, const CardGeom& geom, const qkv_card_header_t& header,
-                           uint8_t* card, hipStream_t stream);
+                           uint8_t* card, hipStream_t stream, const uint8_t* card_in = nullptr, uint64_t card_in_bytes = 0,
+                           uint32_t* status_in = nullptr);
 hipError_t launch_pack(const CardGeom& geom, const void* k, const void* v, uint8_t* card, bool keys_per_channel,
                        hipStream_t stream);
 hipError_t launch_unpack(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, void* k_out, void* v_out,

@@ -36,15 +36,8 @@ struct RequantArgs {
   uint64_t tokens;
   CardGeom out;                 // the outgoing card's geometry (host-known counts)
   uint8_t* card_out;
-  uint32_t* status;             // may be null
+  uint32_t* status;             // may be null; holds the verdict on the incoming header already (classify_kernel)
 };
-
-__global__ void requant_status_kernel(RequantArgs a) {
-  CardGeom g;
-  const bool ok = card_geometry_from_header(a.card_in, a.card_in_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size,
-                                            a.tokens, g);
-  if (threadIdx.x == 0 && blockIdx.x == 0) *a.status = ok ? 0u : QKV_STATUS_BAD_HEADER;
-}
 
 // The 32 values (16 packed pairs) of span q of the row (plane p, slot) of old class CO of the incoming card.
 // One instance per old class, so that every geometry field is picked at compile time.
@@ -233,11 +226,6 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
   a.out = out;
   a.card_out = card_out;
   a.status = status;
-  if (status) {
-    hipLaunchKernelGGL(requant_status_kernel, dim3(1), dim3(kWaveSize), 0, stream, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   uint64_t tiles = 0;                           // turns: 64 rows each
   for (int c = 0; c < 4; ++c) tiles += ((uint64_t)out.planes * out.n[c] + kWaveSize - 1u) / kWaveSize;
   if (tiles == 0) return hipSuccess;

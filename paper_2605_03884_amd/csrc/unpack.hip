@@ -28,6 +28,7 @@ struct UnpackArgs {
   uint8_t* k_out;
   uint8_t* v_out;
   uint32_t* status;                                  // may be null
+  uint32_t check_blocks;                             // 1: workgroup 0 reports for all (verdict_in_grid), the others are silent
 };
 
 // Injection into per-layer caches: the same tiles, but only the planes of a layer range,
@@ -42,6 +43,7 @@ struct InjectArgs {
   uint64_t head_stride, token_stride;                // bytes
   uint32_t rope;                                     // 1: rotate the keys with cs[]
   uint32_t* status;                                  // may be null
+  uint32_t check_blocks;                             // as in UnpackArgs
   uint64_t k_layer[QKV_INJECT_MAX_LAYERS];           // where token 0 of head 0 of layer layer_begin + i goes
   uint64_t v_layer[QKV_INJECT_MAX_LAYERS];
   float cs[128][2];                                  // (cos, sin) of the shift for pair index i < head_dim / 2
@@ -68,6 +70,41 @@ __device__ inline bool tables_agree(const uint8_t* card, const CardGeom& g, int 
   const uint32_t width = card[g.off_bits + t];
   const uint32_t slot = reinterpret_cast<const uint32_t*>(card + g.off_slot)[t];
   return width == width_of_class(c) && slot == j;
+}
+
+// The shapes the per-channel tiles are written for (the header has been accepted).
+__device__ inline bool kc_shape(const CardGeom& g) {
+  const bool uniform = g.n[0] == g.tokens || g.n[1] == g.tokens || g.n[2] == g.tokens;
+  const uint32_t tile_tokens = kTileChunks >> g.lpr_shift;
+  return uniform && g.group_size == 32u && g.head_dim <= 128u && g.tokens % max(32u, tile_tokens) == 0u;
+}
+
+// The caller's status word, written by one workgroup of the grid: the header's verdict, and whether any entry of
+// order[] disagrees with the other two tables - the same entries the tiles meet and skip, each looked at once
+// instead of once per plane.  A kernel of its own in front of the grid cost 1.8 us on an idle GPU and 4.7 us
+// behind another kernel (of 75 us for a handoff of 1K tokens); here the check runs beside the tiles.  Four
+// entries per thread and load, two loads in flight: about 2 us per 2048 tokens.
+__device__ inline void report_status(const uint8_t* card, const CardGeom& g, bool header_ok, bool check, uint32_t* status) {
+  uint32_t bad = 0;
+  if (header_ok && check) {
+    const u32x4* order = reinterpret_cast<const u32x4*>(card + g.off_order);       // the section is padded to 256 bytes
+    const uint32_t* slots = reinterpret_cast<const uint32_t*>(card + g.off_slot);
+#pragma unroll 2
+    for (uint32_t j0 = 4u * threadIdx.x; j0 < g.tokens; j0 += 4u * kBlockThreads) {
+      const u32x4 t4 = order[j0 >> 2];
+#pragma unroll
+      for (uint32_t e = 0; e < 4u; ++e) {
+        const uint32_t j = j0 + e, t = t4[e];
+        const uint32_t c = (uint32_t)(j >= g.base[1]) + (uint32_t)(j >= g.base[2]) + (uint32_t)(j >= g.base[3]);
+        const uint32_t base = c == 0u ? 0u : c == 1u ? g.base[1] : c == 2u ? g.base[2] : g.base[3];
+        const uint32_t at = t < g.tokens ? t : 0u;
+        const uint32_t width = card[g.off_bits + at], slot = slots[at];
+        bad |= (uint32_t)(j < g.tokens && (t >= g.tokens || width != (2u << c) || slot != j - base));
+      }
+    }
+  }
+  const int any = __syncthreads_or((int)bad);
+  if (threadIdx.x == 0) *status = (header_ok ? 0u : QKV_STATUS_BAD_HEADER) | (any ? QKV_STATUS_BAD_ORDER : 0u);
 }
 
 // Address of the output row that row `lane` of the tile starting at segment row r0 goes to;
@@ -271,7 +308,7 @@ __device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_
   store_tile(my_row, lane, lpr_shift, data);
 }
 
-// Writes the header verdict; runs before the unpacking grid on the same stream.
+// Writes the header verdict; runs before the grid on the same stream where the grid does not report by itself.
 __global__ void unpack_status_kernel(UnpackArgs a) {
   CardGeom g;
   const bool ok = card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, g,
@@ -309,17 +346,19 @@ template <int G, bool KEEP, bool KC>
 __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
   __shared__ u32x4 lds[kWavesPerBlock][kTileChunks];
   CardGeom g;
-  if (!card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, g,
-                                 KC ? QKV_FLAG_KEYS_PER_CHANNEL : 0u)) return;          // uniform over the grid: every wave leaves
-  if (KC) {                                      // the shapes the per-channel tiles are written for
-    const bool uniform = g.n[0] == g.tokens || g.n[1] == g.tokens || g.n[2] == g.tokens;
-    const uint32_t tile_tokens = kTileChunks >> g.lpr_shift;
-    if (!uniform || g.group_size != 32u || g.head_dim > 128u || g.tokens % max(32u, tile_tokens) != 0u) return;
+  const bool header_ok = card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, g,
+                                                   KC ? QKV_FLAG_KEYS_PER_CHANNEL : 0u);
+  bool shape_ok = header_ok;
+  if (KC) shape_ok = header_ok && kc_shape(g);
+  if (blockIdx.x < a.check_blocks) {
+    report_status(a.card, g, header_ok, shape_ok, a.status);
+    return;
   }
+  if (!shape_ok) return;                         // uniform over the grid: every wave leaves
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = threadIdx.x >> 6;
-  const uint32_t gw = blockIdx.x * kWavesPerBlock + wave;
-  const uint32_t n_waves = gridDim.x * kWavesPerBlock;
+  const uint32_t gw = (blockIdx.x - a.check_blocks) * kWavesPerBlock + wave;
+  const uint32_t n_waves = (gridDim.x - a.check_blocks) * kWavesPerBlock;
   u32x4* my_lds = lds[wave];
 
   uint32_t bad = 0;
@@ -361,7 +400,7 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
       const uint64_t my_row = tile_row_address(a, g, 0, r0, end, lane, tile_rows, bad);
       unpack_tile<2, G, KEEP, false>(a.card, g, 0, r0, end, my_row, lane, my_lds, no_rope);
     }
-    if (bad && a.status) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
+    if (bad && a.status && a.check_blocks == 0u) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
     return;
   }
   // The card is walked from its end to its start: right after packing, its tail is what the
@@ -372,7 +411,7 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
   unpack_class<2, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
   unpack_class<1, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
   unpack_class<0, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
-  if (bad && a.status) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
+  if (bad && a.status && a.check_blocks == 0u) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
 }
 
 // Row address for injection: plane p of the card -> (K or V, layer, head) -> the caller's
@@ -432,17 +471,19 @@ template <int G, bool KEEP, bool ROPE, bool KC>
 __global__ __launch_bounds__(kBlockThreads) void inject_kernel(InjectArgs a) {
   __shared__ u32x4 lds[kWavesPerBlock][kTileChunks];
   CardGeom g;
-  if (!card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, g,
-                                 KC ? QKV_FLAG_KEYS_PER_CHANNEL : 0u)) return;
-  if (KC) {                                      // the shapes the per-channel tiles are written for
-    const bool uniform = g.n[0] == g.tokens || g.n[1] == g.tokens || g.n[2] == g.tokens;
-    const uint32_t tile_tokens = kTileChunks >> g.lpr_shift;
-    if (!uniform || g.group_size != 32u || g.head_dim > 128u || g.tokens % max(32u, tile_tokens) != 0u) return;
+  const bool header_ok = card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, g,
+                                                   KC ? QKV_FLAG_KEYS_PER_CHANNEL : 0u);
+  bool shape_ok = header_ok;
+  if (KC) shape_ok = header_ok && kc_shape(g);
+  if (blockIdx.x < a.check_blocks) {
+    report_status(a.card, g, header_ok, shape_ok, a.status);
+    return;
   }
+  if (!shape_ok) return;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = threadIdx.x >> 6;
-  const uint32_t gw = blockIdx.x * kWavesPerBlock + wave;
-  const uint32_t n_waves = gridDim.x * kWavesPerBlock;
+  const uint32_t gw = (blockIdx.x - a.check_blocks) * kWavesPerBlock + wave;
+  const uint32_t n_waves = (gridDim.x - a.check_blocks) * kWavesPerBlock;
   u32x4* my_lds = lds[wave];
 
   // chunk 64 k + lane of a tile is chunk (lane mod chunks-per-row) of its row, whatever k
@@ -467,7 +508,14 @@ __global__ __launch_bounds__(kBlockThreads) void inject_kernel(InjectArgs a) {
   inject_range<1, 0, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
   inject_range<0, 1, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
   inject_range<0, 0, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
-  if (bad && a.status) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
+  if (bad && a.status && a.check_blocks == 0u) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
+}
+
+// Whether the grid reports the status by itself.  One workgroup looks at 2048 tokens in about 2 us; its share must not
+// outlast the grid, which writes `planes` rows per token: at 64 planes of 128 values a 128K-token card takes
+// 490 us and its check 120 us, at 2 planes the grid would wait for the check.  Otherwise: a kernel in front.
+bool grid_reports(uint64_t planes, uint32_t head_dim, uint64_t tokens) {
+  return tokens <= 2048u || planes * head_dim >= 64u * 128u;
 }
 
 }  // namespace
@@ -483,7 +531,8 @@ hipError_t launch_unpack(const uint8_t* card, uint64_t card_bytes, const CardGeo
   a.k_out = static_cast<uint8_t*>(k_out);
   a.v_out = static_cast<uint8_t*>(v_out);
   a.status = status;
-  if (status) {
+  a.check_blocks = status && grid_reports(expect.planes, expect.head_dim, expect.tokens) ? 1u : 0u;
+  if (status && a.check_blocks == 0u) {
     hipLaunchKernelGGL(unpack_status_kernel, dim3(1), dim3(kWaveSize), 0, stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -493,7 +542,7 @@ hipError_t launch_unpack(const uint8_t* card, uint64_t card_bytes, const CardGeo
   const uint64_t rows = (uint64_t)expect.planes * expect.tokens;
   const uint64_t tiles = keys_per_channel ? (rows + tile_rows - 1) / tile_rows + 3
                                           : (uint64_t)expect.planes * ((expect.tokens + tile_rows - 1) / tile_rows + 3);
-  const dim3 grid(grid_blocks(tiles)), block(kBlockThreads);
+  const dim3 grid(grid_blocks(tiles) + a.check_blocks), block(kBlockThreads);
   const bool keep = card_bytes <= kCacheResidentCardBytes;
   if (keys_per_channel) {                        // group size 32 only (checked by the caller)
     if (keep) hipLaunchKernelGGL((unpack_kernel<32, true, true>), grid, block, 0, stream, a);
@@ -535,12 +584,13 @@ hipError_t launch_inject(const uint8_t* card, uint64_t card_bytes, const CardGeo
     a.cs[i][0] = used ? cos_sin[i][0] : 1.0f;
     a.cs[i][1] = used ? cos_sin[i][1] : 0.0f;
   }
-  if (status) {
+  a.check_blocks = status && grid_reports(2ull * layer_count * expect.kv_heads, expect.head_dim, expect.tokens) ? 1u : 0u;
+  if (status && a.check_blocks == 0u) {
     UnpackArgs u;
     u.card = card; u.card_bytes = card_bytes; u.flags = keys_per_channel ? QKV_FLAG_KEYS_PER_CHANNEL : 0u;
     u.layers = expect.layers; u.kv_heads = expect.kv_heads; u.head_dim = expect.head_dim; u.group_size = expect.group_size;
     u.tokens = expect.tokens;
-    u.k_out = nullptr; u.v_out = nullptr; u.status = status;
+    u.k_out = nullptr; u.v_out = nullptr; u.status = status; u.check_blocks = 0u;
     hipLaunchKernelGGL(unpack_status_kernel, dim3(1), dim3(kWaveSize), 0, stream, u);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -549,7 +599,7 @@ hipError_t launch_inject(const uint8_t* card, uint64_t card_bytes, const CardGeo
   const uint32_t tile_rows = kTileChunks >> expect.lpr_shift;
   const uint64_t rows = 2ull * layer_count * expect.kv_heads * expect.tokens;
   const uint64_t tiles = (rows + tile_rows - 1) / tile_rows + 8;
-  const dim3 grid(grid_blocks(tiles)), block(kBlockThreads);
+  const dim3 grid(grid_blocks(tiles) + a.check_blocks), block(kBlockThreads);
   const bool keep = card_bytes <= kCacheResidentCardBytes;
   if (keys_per_channel) {                        // group size 32 only (checked by the caller)
     switch ((keep ? 2 : 0) + (a.rope ? 1 : 0)) {
