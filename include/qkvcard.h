@@ -264,11 +264,12 @@ int qkv_card_fill(const qkv_desc_t* desc, const void* k_dev, const void* v_dev, 
                   void* card_dev, uint64_t card_capacity, void* stream);
 
 /*
- * Scores to a planned card in one launch (paper Sec. 3.3: the score decides the width under the
+ * Scores to a planned card in one step (paper Sec. 3.3: the score decides the width under the
  * budget; Sec. 4.2.1: the card's bit-width vector, sequence length, identifiers and average-bit
  * statistic).  Does what qkv_assign_bits followed by qkv_card_plan does - same widths, same
- * header, tables and pads, byte for byte - but in a single kernel: the workgroup that ranks the
- * scores already holds every token's width, so slots, order[] and the header follow at once.
+ * header, tables and pads, byte for byte - but without a second pass over the widths: whoever ranks
+ * the scores already holds every token's width, so slots, order[] and the header follow at once
+ * (one kernel up to 16384 tokens, a chain of five small ones beyond).
  *   desc:       host.  tokens < 2^31.
  *   scores_dev: device, float[T], 4-byte aligned (NaN is a precondition violation).
  *   bits_dev:   device, uint8_t[T], written; may be NULL (the widths are in the card anyway).

@@ -7,7 +7,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqkvcard.so")
 CLIENT_SRC = os.path.join(CSRC, "handoff_client.cpp")
 CLIENT = os.path.join(HERE, "handoff_client")          # a plain HIP host program that links the library
-SOURCES = ["api.hip", "classify.hip", "pack.hip", "unpack.hip", "assign.hip", "attend.hip", "controller.hip", "requant.hip"]
+SOURCES = ["api.hip", "classify.hip", "pack.hip", "unpack.hip", "assign.hip", "assign_long.hip", "attend.hip", "controller.hip", "requant.hip"]
 
 # -ffp-contract=off: every fused multiply-add in the kernels is written out, none is invented;
 # packed fp32 instructions are switched off on this target.

@@ -246,7 +246,7 @@ static int plan_card(const qkv_desc_t* desc, const uint8_t* bits_dev, const Card
   return launch_classify(bits_dev, g, h, card, s, card_in, card_in_bytes, status_in) == hipSuccess ? QKV_OK : QKV_ERR_HIP;
 }
 
-// Scores and a budget to widths and a planned card, one launch.  `counts_out` gets the budget's class counts.
+// Scores and a budget to widths and a planned card.  `counts_out` gets the budget's class counts.
 static int assign_and_plan(const qkv_desc_t* desc, const float* scores_dev, double avg_bits_budget, uint8_t* bits_dev,
                     int64_t counts_out[4], void* card_dev, uint64_t card_capacity, CardGeom& g, hipStream_t s) {
   int rc = check_desc(desc);
@@ -263,16 +263,7 @@ static int assign_and_plan(const qkv_desc_t* desc, const float* scores_dev, doub
                             (uint32_t)(counts[3] + counts[2] + counts[1])};
   const qkv_card_header_t h = make_header(desc, g, n, 0u);
   uint8_t* card = static_cast<uint8_t*>(card_dev);
-  if ((uint64_t)desc->tokens <= assign_plan_max_tokens()) {
-    if (launch_assign_plan(scores_dev, cuts, bits_dev, g, h, card, s) != hipSuccess) return QKV_ERR_HIP;
-  } else {
-    // Sequences beyond the one-launch kernel's reach: the allocator and the classification one after the
-    // other, same bytes.  Without a buffer from the caller the widths go straight to their place in the
-    // card, where the classification rewrites every byte with the value it read there.
-    uint8_t* widths = bits_dev ? bits_dev : card + g.off_bits;
-    if (launch_assign(scores_dev, (uint32_t)desc->tokens, cuts, widths, s) != hipSuccess) return QKV_ERR_HIP;
-    if (launch_classify(widths, g, h, card, s) != hipSuccess) return QKV_ERR_HIP;
-  }
+  if (launch_assign_plan(scores_dev, cuts, bits_dev, g, h, card, s) != hipSuccess) return QKV_ERR_HIP;
   std::memcpy(counts_out, counts, sizeof(counts));
   return QKV_OK;
 }

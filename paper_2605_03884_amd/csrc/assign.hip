@@ -18,8 +18,8 @@
 // first pass's histogram is kept in 16 copies against same-word atomics (real scores share sign
 // and exponent); later passes test a key against all three cut prefixes and skip the counting
 // code for waves that hold no match; cuts whose prefixes still coincide share one histogram; a
-// wave without ties needs three comparisons per key for the widths.  Beyond 32768 tokens an
-// older form takes over that re-reads the scores (they stay in cache) instead of holding keys.
+// wave without ties needs three comparisons per key for the widths.  Longer sequences
+// (kRankedMax, kPlanMax): assign_long.hip.
 //
 // Planning variant (PLAN): once the cut keys are known every thread knows the widths of its own
 // tokens, so a block-wide prefix count of the classes gives the stable slots, order[] and the
@@ -31,52 +31,22 @@
 // leave as whole lines.
 #include "qkv_common.h"
 #include "qkv_plan.h"
+#include "qkv_select.h"
 
 namespace qkv {
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads = 1024;
-constexpr int kWaves = kThreads / kWaveSize;
+constexpr int kThreads = kSelectThreads;
+constexpr int kWaves = kSelectWaves;
 constexpr int kCopies = 16;                  // of the first pass's histogram
-constexpr uint32_t kRankedMax = 32768;       // tokens the ranked kernels take: at most 32 per thread
+// Longest sequences one workgroup's registers take; assign_long.hip goes on.  With planning the line lies lower, because
+// the chain of launches there also spreads the tables' writing (measured, one workgroup against the chain: widths alone
+// 13 / 24 us at 16384 tokens, 26 / 27 at 32768; with planning 17 / 24 us at 16384, 28 / 25 at 20000, 33 / 26 at 32768).
+constexpr uint32_t kRankedMax = 32768;
+constexpr uint32_t kPlanMax = 16384;
 constexpr uint32_t kShareTokens = 2048;      // tokens whose tables one workgroup writes
-
-// What the planning variant needs beyond the allocator's arguments.
-struct PlanArgs {
-  CardGeom g;                  // built on the host from the budget's class counts
-  qkv_card_header_t header;    // as the host filled it (status 0)
-  PadTable pads;
-  uint8_t* card;
-  uint32_t share_waves;        // workgroup b writes the tables of the tokens of waves [b * share_waves, (b + 1) * share_waves)
-};
-
-// Key that grows as the rank grows: smaller key = better score.  -0 ranks below +0.
-__device__ inline uint32_t rank_key(float score) {
-  const uint32_t x = __float_as_uint(score);
-  const uint32_t up = (x & 0x80000000u) ? ~x : (x | 0x80000000u);   // ascending in the score
-  return ~up;
-}
-
-__device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-
-// Prefix over the waves of a workgroup.  tot[0 .. kWaves) are wave totals in LDS (written before the last
-// barrier); the result holds, in lanes 0 .. 15 of every wave, the inclusive running sum.  One LDS read and
-// four DPP steps: a loop of dependent LDS reads would cost a full LDS latency per wave.
-__device__ inline uint32_t scan_wave_totals(const uint32_t* tot, uint32_t lane) {
-  uint32_t v = tot[lane & (kWaves - 1u)];
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);    // row_shr:1
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);    // row_shr:2
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);    // row_shr:4
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);    // row_shr:8
-  return v;
-}
-// Sum of the totals of waves [0, w) from that running sum; w must be the same in every lane.
-__device__ inline uint32_t waves_below(uint32_t running, uint32_t w) {
-  const uint32_t at = uniform(w);
-  return at == 0u ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)running, (int)(at - 1u));
-}
 
 // T <= KPT * 1024: thread tid owns the tokens [tid * KPT, tid * KPT + KPT) and keeps their keys in registers.
 // PLAN: also write slot[], order[], the bits copy, header and pads of plan->card; `bits` may then be null.
@@ -340,100 +310,6 @@ __global__ __launch_bounds__(kThreads) void assign_plan_kernel(const float* __re
   ranked_body<KPT, true>(scores, plan.g.tokens, cut0, cut1, cut2, bits, aligned, &plan);
 }
 
-// Any T: the same selection with every sweep a loop over the scores and a first-pass histogram in 32 copies.
-__global__ __launch_bounds__(kThreads) void long_assign_kernel(const float* __restrict__ scores, uint32_t T, uint32_t cut0,
-                                                               uint32_t cut1, uint32_t cut2, uint8_t* __restrict__ bits) {
-  constexpr int kWide = 32;
-  __shared__ uint32_t wide[256 * kWide];     // first pass: bucket d, copy c at [d * 32 + c]
-  __shared__ uint32_t hist[3][256];
-  __shared__ uint32_t sel_prefix[3];
-  __shared__ uint32_t sel_left[3];
-  __shared__ uint32_t wave_tot[3][kWaves];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t lane = tid & 63u, wave = tid >> 6;
-  const uint32_t cut[3] = {cut0, cut1, cut2};
-  const uint32_t per = (T + kThreads - 1) / kThreads;
-  const uint32_t t0 = min(tid * per, T);
-  const uint32_t t1 = min(t0 + per, T);
-  auto for_each_key = [&](auto&& f) {
-#pragma unroll 4
-    for (uint32_t t = t0; t < t1; ++t) f(rank_key(scores[t]), t);
-  };
-  for (uint32_t i = tid; i < 256 * kWide; i += kThreads) wide[i] = 0;
-  __syncthreads();
-  for_each_key([&](uint32_t key, uint32_t) { atomicAdd(&wide[(key >> 24) * kWide + (lane & 31u)], 1u); });
-  __syncthreads();
-  if (tid < 256) {
-    uint32_t s = 0;
-#pragma unroll 8
-    for (int i = 0; i < kWide; ++i) s += wide[tid * kWide + ((i + tid) & 31u)];
-    hist[0][tid] = s;
-  }
-  __syncthreads();
-  if (wave < 3 && cut[wave] < T) {
-    uint32_t left = cut[wave];
-    const uint32_t d = find_bucket(hist[0], lane, left);
-    if (lane == 0) { sel_prefix[wave] = d << 24; sel_left[wave] = left; }
-  }
-  __syncthreads();
-#pragma unroll 1
-  for (int pass = 1; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    if (tid < 3 * 256) hist[tid >> 8][tid & 255u] = 0;
-    uint32_t pre[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) pre[c] = sel_prefix[c];
-    __syncthreads();
-    const uint32_t high_mask = 0xFFFFFFFFu << (shift + 8);
-    for_each_key([&](uint32_t key, uint32_t) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if (cut[c] < T && ((key ^ pre[c]) & high_mask) == 0) atomicAdd(&hist[c][(key >> shift) & 255u], 1u);
-      }
-    });
-    __syncthreads();
-    if (wave < 3 && cut[wave] < T) {
-      uint32_t left = sel_left[wave];
-      const uint32_t d = find_bucket(hist[wave], lane, left);
-      if (lane == 0) { sel_prefix[wave] |= d << shift; sel_left[wave] = left; }
-    }
-    __syncthreads();
-  }
-  uint32_t keyc[3], quota[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) { keyc[c] = sel_prefix[c]; quota[c] = sel_left[c]; }
-  uint32_t eq[3] = {0, 0, 0};
-  for_each_key([&](uint32_t key, uint32_t) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) eq[c] += (key == keyc[c]);
-  });
-  uint32_t run[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const uint32_t inc = wave_inclusive_scan(eq[c]);
-    run[c] = inc - eq[c];
-    if (lane == 63) wave_tot[c][wave] = inc;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    uint32_t before = 0;
-    for (uint32_t w = 0; w < wave; ++w) before += wave_tot[c][w];
-    run[c] += before;
-  }
-  for_each_key([&](uint32_t key, uint32_t t) {
-    bool before[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      if (cut[c] >= T) { before[c] = true; continue; }
-      const bool is_eq = key == keyc[c];
-      before[c] = key < keyc[c] || (is_eq && run[c] < quota[c]);
-      run[c] += is_eq;
-    }
-    bits[t] = (uint8_t)(before[0] ? 16u : before[1] ? 8u : before[2] ? 4u : 2u);
-  });
-}
-
 __global__ __launch_bounds__(256) void count_kernel(const uint8_t* __restrict__ bits, uint64_t T,
                                                     unsigned long long* __restrict__ counts4) {
   __shared__ uint32_t part[4];
@@ -457,8 +333,6 @@ __global__ void zero4_kernel(unsigned long long* p) {
 
 }  // namespace
 
-uint32_t assign_plan_max_tokens() { return kRankedMax; }
-
 namespace {
 // Keys per thread of the ranked kernels: the smallest of 1, 2, 4, 8, 16, 32 that covers `tokens` with 1024 threads.
 uint32_t keys_per_thread(uint32_t tokens) {
@@ -475,7 +349,7 @@ hipError_t launch_assign(const float* scores, uint32_t tokens, const uint32_t cu
 #define QKV_LAUNCH_ASSIGN(K) \
   hipLaunchKernelGGL(ranked_assign_kernel<K>, grid, block, 0, stream, scores, tokens, cuts[0], cuts[1], cuts[2], bits, aligned)
   if (tokens > kRankedMax) {
-    hipLaunchKernelGGL(long_assign_kernel, grid, block, 0, stream, scores, tokens, cuts[0], cuts[1], cuts[2], bits);
+    return launch_assign_long(scores, tokens, cuts, bits, stream);
   } else {
     switch (keys_per_thread(tokens)) {
       case 1: QKV_LAUNCH_ASSIGN(1); break;
@@ -490,20 +364,19 @@ hipError_t launch_assign(const float* scores, uint32_t tokens, const uint32_t cu
   return hipGetLastError();
 }
 
-// tokens <= assign_plan_max_tokens()
 hipError_t launch_assign_plan(const float* scores, const uint32_t cuts[3], uint8_t* bits, const CardGeom& geom,
                               const qkv_card_header_t& header, uint8_t* card, hipStream_t stream) {
+  const uint32_t tokens = geom.tokens;
+  if (tokens > kPlanMax) return launch_assign_plan_long(scores, cuts, bits, geom, header, card, stream);
   PlanArgs plan;
   plan.g = geom;
   plan.header = header;
   plan.pads = make_pad_table(geom);
   plan.card = card;
-  const uint32_t tokens = geom.tokens;
-  if (tokens > kRankedMax) return hipErrorInvalidValue;
   const bool aligned = reinterpret_cast<uintptr_t>(scores) % 16 == 0;
   // a share is whole waves and at most kShareTokens tokens
   const uint32_t kpt = keys_per_thread(tokens);
-  uint32_t share_waves = kShareTokens / (kpt * kWaveSize);             // >= 1 since kpt <= 32
+  uint32_t share_waves = kShareTokens / (kpt * kWaveSize);             // >= 2 since kpt <= 16
   if (share_waves > (uint32_t)kWaves) share_waves = kWaves;
   const uint32_t used_waves = ((tokens + kpt - 1) / kpt + kWaveSize - 1) / kWaveSize;
   plan.share_waves = share_waves;
@@ -515,8 +388,7 @@ hipError_t launch_assign_plan(const float* scores, const uint32_t cuts[3], uint8
     case 2: QKV_LAUNCH_PLAN(2); break;
     case 4: QKV_LAUNCH_PLAN(4); break;
     case 8: QKV_LAUNCH_PLAN(8); break;
-    case 16: QKV_LAUNCH_PLAN(16); break;
-    default: QKV_LAUNCH_PLAN(32); break;
+    default: QKV_LAUNCH_PLAN(16); break;
   }
 #undef QKV_LAUNCH_PLAN
   return hipGetLastError();

@@ -158,9 +158,12 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
                           uint32_t* status, hipStream_t stream);
 hipError_t launch_assign(const float* scores, uint32_t tokens, const uint32_t cuts[3], uint8_t* bits,
                          hipStream_t stream);
-uint32_t assign_plan_max_tokens();      // longest sequence launch_assign_plan takes
 hipError_t launch_assign_plan(const float* scores, const uint32_t cuts[3], uint8_t* bits, const CardGeom& geom,
                               const qkv_card_header_t& header, uint8_t* card, hipStream_t stream);
+// The same two for long sequences: more than 32768 and more than 16384 tokens (the launchers above go there by themselves).
+hipError_t launch_assign_long(const float* scores, uint32_t tokens, const uint32_t cuts[3], uint8_t* bits, hipStream_t stream);
+hipError_t launch_assign_plan_long(const float* scores, const uint32_t cuts[3], uint8_t* bits, const CardGeom& geom,
+                                   const qkv_card_header_t& header, uint8_t* card, hipStream_t stream);
 void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk, uint32_t* max_tasks);
 hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, const void* q,
                          uint32_t q_heads, float softmax_scale, float* out, float* lse, float* workspace,

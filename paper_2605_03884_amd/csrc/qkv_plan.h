@@ -37,6 +37,15 @@ inline PadTable make_pad_table(const CardGeom& g) {
   return t;
 }
 
+// What the allocator's planning variants need beyond its own arguments.
+struct PlanArgs {
+  CardGeom g;                  // built on the host from the budget's class counts
+  qkv_card_header_t header;    // as the host filled it (status 0)
+  PadTable pads;
+  uint8_t* card;
+  uint32_t share_waves;        // assign.hip: workgroup b writes the tables of the tokens of waves [b * share_waves, (b + 1) * share_waves)
+};
+
 // The 256 header bytes with `status` in place of the host's status word, and zeros in the pad
 // bytes behind every section.  Call with tid = 0 .. 255 at least; every tid writes at most one
 // header word and one byte per pad.
