@@ -106,28 +106,16 @@ __device__ inline void encode_span(const uint32_t (&w)[16], float neg_mn, float 
   for (int o = 0; o < W; ++o) out[o] -= magic_carry<W>();
 }
 
-// One span of 32 values (16 packed pairs): the extrema of its group (reduced over the GS lanes that share
-// it), scale and reciprocal as the quantizer defines them, and the span's codes.  Returns the pair as it
-// is stored: fp16 scale, then fp16 zero.
-template <int W, int GS>
-__device__ inline uint32_t quantize_span(const uint32_t (&w)[16], uint32_t (&out)[W]) {
+// Scale and reciprocal of a group with the given extrema (fp16 bits), as the quantizer defines them.  `clamp` says
+// whether some lane's codes could round above qmax.  Returns the scale's fp16 bits.
+template <int W>
+__device__ inline uint32_t group_scale(uint32_t mn_h, uint32_t mx_h, float& neg_mn, float& inv, bool& clamp) {
   constexpr float QMAXF = (float)((1 << W) - 1);
   constexpr float RCPQ = 1.0f / QMAXF;           // correctly rounded at compile time
-  // extrema of the span, then of the group
-  uint32_t m = pk_min(pk_min3(pk_min3(w[0], w[1], w[2]), pk_min3(w[3], w[4], w[5]), pk_min3(w[6], w[7], w[8])),
-                      pk_min3(pk_min3(w[9], w[10], w[11]), pk_min3(w[12], w[13], w[14]), w[15]));
-  uint32_t M = pk_max(pk_max3(pk_max3(w[0], w[1], w[2]), pk_max3(w[3], w[4], w[5]), pk_max3(w[6], w[7], w[8])),
-                      pk_max3(pk_max3(w[9], w[10], w[11]), pk_max3(w[12], w[13], w[14]), w[15]));
-  m = pk_min_halves(m);
-  M = pk_max_halves(M);
-  if (GS >= 2) { m = pk_min(m, dpp<kQuadXor1>(m)); M = pk_max(M, dpp<kQuadXor1>(M)); }
-  if (GS >= 4) { m = pk_min(m, dpp<kQuadXor2>(m)); M = pk_max(M, dpp<kQuadXor2>(M)); }
-  const uint32_t mn_h = m & 0xFFFFu;
-
   // scale = fp16(range / qmax), inv = 1 / scale: fp32, correctly rounded.
   // Quotient: q0 = range * (1/qmax) is within one ulp, its exact residual corrects it.
   const float fmn = half_bits_to_float(mn_h);
-  const float fmx = half_bits_to_float(M & 0xFFFFu);
+  const float fmx = half_bits_to_float(mx_h);
   const float range = fmx - fmn;
   const float q0 = range * RCPQ;
   float s32 = __builtin_fmaf(__builtin_fmaf(-q0, QMAXF, range), RCPQ, q0);
@@ -142,13 +130,40 @@ __device__ inline uint32_t quantize_span(const uint32_t (&w)[16], uint32_t (&out
   // the correctly rounded value.
   const float y0 = __builtin_amdgcn_rcpf(s);
   const float y1 = __builtin_fmaf(__builtin_fmaf(-s, y0, 1.0f), y0, y0);
-  const float inv = (s > 0.0f) ? y1 : 0.0f;
-
+  inv = (s > 0.0f) ? y1 : 0.0f;
+  neg_mn = -fmn;
   // The clamp to qmax can only act when the stored scale is an fp16 subnormal; otherwise
   // d * inv <= qmax * (1 + 2^-11 + ...) already rounds to at most qmax.
-  const bool needs_clamp = (s_h - 1u) < 0x3FFu;
-  if (__builtin_amdgcn_ballot_w64(needs_clamp) != 0) encode_span<W, true>(w, -fmn, inv, out);
-  else encode_span<W, false>(w, -fmn, inv, out);
+  clamp = __builtin_amdgcn_ballot_w64((s_h - 1u) < 0x3FFu) != 0;
+  return s_h;
+}
+
+// Extrema of a group out of its spans' extrema: both halves of m and M hold a span's own.
+template <int GS>
+__device__ inline void reduce_group(uint32_t& m, uint32_t& M) {
+  if (GS >= 2) { m = pk_min(m, dpp<kQuadXor1>(m)); M = pk_max(M, dpp<kQuadXor1>(M)); }
+  if (GS >= 4) { m = pk_min(m, dpp<kQuadXor2>(m)); M = pk_max(M, dpp<kQuadXor2>(M)); }
+}
+
+// One span of 32 values (16 packed pairs): the extrema of its group (reduced over the GS lanes that share
+// it), scale and reciprocal as the quantizer defines them, and the span's codes.  Returns the pair as it
+// is stored: fp16 scale, then fp16 zero.
+template <int W, int GS>
+__device__ inline uint32_t quantize_span(const uint32_t (&w)[16], uint32_t (&out)[W]) {
+  // extrema of the span, then of the group
+  uint32_t m = pk_min(pk_min3(pk_min3(w[0], w[1], w[2]), pk_min3(w[3], w[4], w[5]), pk_min3(w[6], w[7], w[8])),
+                      pk_min3(pk_min3(w[9], w[10], w[11]), pk_min3(w[12], w[13], w[14]), w[15]));
+  uint32_t M = pk_max(pk_max3(pk_max3(w[0], w[1], w[2]), pk_max3(w[3], w[4], w[5]), pk_max3(w[6], w[7], w[8])),
+                      pk_max3(pk_max3(w[9], w[10], w[11]), pk_max3(w[12], w[13], w[14]), w[15]));
+  m = pk_min_halves(m);
+  M = pk_max_halves(M);
+  reduce_group<GS>(m, M);
+  const uint32_t mn_h = m & 0xFFFFu;
+  float neg_mn, inv;
+  bool clamp;
+  const uint32_t s_h = group_scale<W>(mn_h, M & 0xFFFFu, neg_mn, inv, clamp);
+  if (clamp) encode_span<W, true>(w, neg_mn, inv, out);
+  else encode_span<W, false>(w, neg_mn, inv, out);
   return s_h | (mn_h << 16);
 }
 

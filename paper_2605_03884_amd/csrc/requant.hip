@@ -8,26 +8,38 @@
 // dense values only ever exist in registers.  The result is, byte for byte, the card that creation
 // would build from the injected cache.
 //
-// Work decomposition: the outgoing card's segments are walked as in card creation, a wave taking 64 rows
-// at a time, one per lane.  A lane finds its row's token through the outgoing card's order[] (written
-// by the classification kernel just before, on the same stream) and the token's old width and slot
-// through the incoming card's tables.  Neighbouring rows of an outgoing segment had different old
-// widths, and the decoders of different widths can only run one after the other under lane masks, so
-// the 64 rows are first sorted by old width (ballots and one cross-lane permutation); the rounds that
-// follow then see one width each, except where two widths meet.  The work is bound by instruction
-// issue, not by memory.  The only LDS is the selector table of the 2-bit decoder.
+// Work decomposition: a workgroup takes a window of 256 consecutive rows of one outgoing segment and does
+// it for one or more planes.  It looks the window's tokens up once (token through the outgoing card's
+// order[], written by the classification kernel just before, old width and slot through the incoming
+// card's tables), sorts them by old width into a list in LDS and cuts the list into rounds of at most 64
+// spans of one old width; the four waves deal the rounds of all planes among themselves, each with the
+// next round's loads in flight, and no round mixes widths.  The incoming card is read with plain loads
+// whatever its size: rows that leave for different widths share lines, and windows that run at the
+// same time find them in cache (nontemporal loads cost 26 % at 32K tokens).
+//
+// Spans that were 2-bit (most of a card at low budgets) are not expanded to 32 values at all: a group
+// has four decoded values, in order, so its extrema follow from which codes occur, the quantizer runs
+// on the four values, and the new codes are the old ones relabelled.
+//
+// What bounds it: vector instruction issue (about 70 % busy at 8K tokens), then requests for parts of lines.
+// Whole call, 8K tokens, budget 3 to 2.5, with the new widths' assignment: 199 us before (64 rows of one plane
+// sorted per wave, every span expanded to 32 values), 162 us now; 32K tokens, 6 to 4: 1162 and 853 us.
+// Windows of 512 rows: 171 and 936 us; without the next round's loads in flight: 172 and 877 us; a window
+// of 256 tokens over all widths at once, four waves dealing 16 width pairs: 221 and 1137 us.
 //
 // The incoming card is untrusted: header and offsets are rebuilt and checked on the device, table
 // entries are bounded before they are used.
 #include "qkv_common.h"
 #include "qkv_encode.h"
+#include "qkv_plan.h"
 
 namespace qkv {
 namespace {
 
-// The rows of a turn leave in sorted order, their pieces a few rounds apart: plain stores let the L2 put whole
-// lines together whatever the card's size (nontemporal ones cost 14 - 50 % on 1 - 2 GB cards).
-constexpr bool kMergeStores = true;
+constexpr uint32_t kWindow = 256;             // rows of an outgoing segment that a workgroup looks up and sorts
+constexpr uint32_t kMaxPlanes = 2;            // planes it does them for, at most
+constexpr uint32_t kOld = 5;                  // old classes 0 .. 3, and 4: not placed by the incoming tables
+constexpr uint32_t kMaxRounds = kWindow * 8u / kWaveSize + kOld;
 
 struct RequantArgs {
   const uint8_t* card_in;
@@ -37,181 +49,322 @@ struct RequantArgs {
   CardGeom out;                 // the outgoing card's geometry (host-known counts)
   uint8_t* card_out;
   uint32_t* status;             // may be null; holds the verdict on the incoming header already (classify_kernel)
+  uint32_t group_planes;        // planes per workgroup
 };
 
-// The 32 values (16 packed pairs) of span q of the row (plane p, slot) of old class CO of the incoming card.
-// One instance per old class, so that every geometry field is picked at compile time.
-template <int CO, int G, bool KEEP>
-__device__ __forceinline__ void decode_old_class(const uint8_t* card, const CardGeom& in, uint32_t p, uint32_t slot,
-                                                 uint32_t q, uint32_t spr_shift, const u32x2* table, uint32_t (&w)[16],
-                                                 uint32_t& bad) {
-  constexpr int GS = G / 32;
-  const uint32_t n_old = in.n[CO];
-  if (slot >= n_old) { bad = 1; return; }
-  const uint64_t gsp = (((uint64_t)p * n_old + slot) << spr_shift) + q;
-  if constexpr (CO == 3) {
-    const u32x4* src = reinterpret_cast<const u32x4*>(card + in.off_fp16 + gsp * 64u);
+// Bits chosen from a where mask is 1, from b where it is 0: one instruction.
+__device__ inline uint32_t bit_select(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
+
+// Whether relabel_span2 applies to every lane's pair: a scale that is no negative number, and finite values.
+__device__ inline bool can_relabel(uint32_t old_pair) {
+  const float s = half_bits_to_float(old_pair & 0xFFFFu), z = half_bits_to_float(old_pair >> 16);
+  const uint32_t x3 = decode_pair(2.0f, 3.0f, s, z) >> 16;
+  const bool odd = (old_pair & 0xFFFFu) > 0x7BFFu || (x3 & 0x7C00u) == 0x7C00u || (old_pair & 0x7C000000u) == 0x7C000000u;
+  return __builtin_amdgcn_ballot_w64(odd) == 0ull;
+}
+
+// 2-bit codes to W-bit codes.  The decoded values x_k = fp16(fma(k, scale, zero)) do not decrease with k (and are never
+// -0: scale and zero are multiples of the smallest fp16 step), so the span's extrema are those of the smallest and the
+// largest code that occurs; then four values go through the quantizer instead of 32.
+template <int W, int GS>
+__device__ __forceinline__ uint32_t relabel_span2(const uint32_t (&cw)[2], uint32_t old_pair, uint32_t (&out)[W]) {
+  const float s = half_bits_to_float(old_pair & 0xFFFFu), z = half_bits_to_float(old_pair >> 16);
+  const uint32_t x01 = decode_pair(0.0f, 1.0f, s, z), x23 = decode_pair(2.0f, 3.0f, s, z);
+  constexpr uint32_t kLow = 0x55555555u;
+  const uint32_t lo0 = cw[0] & kLow, lo1 = cw[1] & kLow, hi0 = (cw[0] >> 1) & kLow, hi1 = (cw[1] >> 1) & kLow;
+  const bool any_hi = (hi0 | hi1) != 0u, all_hi = (hi0 & hi1) == kLow;
+  // largest code: in the upper half if any high bit is set; there, or below, 1 more if such a code has its low bit set
+  const uint32_t top_lo = any_hi ? ((lo0 & hi0) | (lo1 & hi1)) : (lo0 | lo1);
+  const uint32_t x_top = any_hi ? x23 : x01;
+  const uint32_t mx = top_lo != 0u ? x_top >> 16 : x_top & 0xFFFFu;
+  // smallest code, the same way with "not set"
+  const uint32_t bot_lo = all_hi ? (lo0 & lo1) : ((lo0 | hi0) & (lo1 | hi1));      // 1 wherever a code of the lower half has its low bit set, or is of the upper half
+  const uint32_t x_bot = all_hi ? x23 : x01;
+  const uint32_t mn = bot_lo == kLow ? x_bot >> 16 : x_bot & 0xFFFFu;
+  uint32_t m = mn | (mn << 16), M = mx | (mx << 16);
+  reduce_group<GS>(m, M);
+  const uint32_t mn_h = m & 0xFFFFu;
+  float neg_mn, inv;
+  bool clamp;
+  const uint32_t s_h = group_scale<W>(mn_h, M & 0xFFFFu, neg_mn, inv, clamp);
+  // the four new codes, one per byte (those of values that do not occur may be anything)
+  uint32_t u[4];
+  u[0] = __float_as_uint(__builtin_fmaf(lo_plus(x01, neg_mn), inv, kMagic));
+  u[1] = __float_as_uint(__builtin_fmaf(hi_plus(x01, neg_mn), inv, kMagic));
+  u[2] = __float_as_uint(__builtin_fmaf(lo_plus(x23, neg_mn), inv, kMagic));
+  u[3] = __float_as_uint(__builtin_fmaf(hi_plus(x23, neg_mn), inv, kMagic));
+  if (clamp) {
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const u32x4 v = card_load<KEEP>(src + h);
-      w[4 * h] = v.x; w[4 * h + 1] = v.y; w[4 * h + 2] = v.z; w[4 * h + 3] = v.w;
+    for (int k = 0; k < 4; ++k) u[k] = min(u[k], kMagicBits + ((1u << W) - 1u));
+  }
+  const uint32_t c4 = __builtin_amdgcn_perm(__builtin_amdgcn_perm(u[3], u[2], 0x0C0C0400u),
+                                            __builtin_amdgcn_perm(u[1], u[0], 0x0C0C0400u), 0x05040100u);
+  if constexpr (W == 2) {
+    const uint32_t rep = __builtin_amdgcn_perm(0u, 0xFFAA5500u, c4 & 0x03030303u);     // byte k: code k four times
+    const uint32_t r0 = __builtin_amdgcn_perm(rep, rep, 0x00000000u), r1 = __builtin_amdgcn_perm(rep, rep, 0x01010101u);
+    const uint32_t r2 = __builtin_amdgcn_perm(rep, rep, 0x02020202u), r3 = __builtin_amdgcn_perm(rep, rep, 0x03030303u);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t lo = i ? lo1 : lo0, hi = i ? hi1 : hi0;
+      const uint32_t lo2 = lo | (lo << 1), hi2 = hi | (hi << 1);
+      out[i] = bit_select(hi2, bit_select(lo2, r3, r2), bit_select(lo2, r1, r0));
     }
   } else {
-    constexpr int W = CO == 0 ? 2 : CO == 1 ? 4 : 8;
-    const uint32_t pair = card_load<KEEP>(reinterpret_cast<const uint32_t*>(card + in.off_meta[CO]) + gsp / GS);
-    const float s = half_bits_to_float(pair & 0xFFFFu);
-    const float z = half_bits_to_float(pair >> 16);
-    const uint8_t* src = card + in.off_codes[CO] + gsp * (4u * W);
-    uint32_t cw[W];
-    if constexpr (W == 2) {
-      const u32x2 v = card_load<KEEP>(reinterpret_cast<const u32x2*>(src));
-      cw[0] = v.x; cw[1] = v.y;
-    } else {
 #pragma unroll
-      for (int h = 0; h < W / 4; ++h) {
-        const u32x4 v = card_load<KEEP>(reinterpret_cast<const u32x4*>(src) + h);
-        cw[4 * h] = v.x; cw[4 * h + 1] = v.y; cw[4 * h + 2] = v.z; cw[4 * h + 3] = v.w;
+    for (int i = 0; i < 2; ++i) {
+      uint32_t a[4];                                // a[k]: the new codes of positions k, 4 + k, 8 + k, 12 + k
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a[k] = __builtin_amdgcn_perm(0u, c4, (cw[i] >> (2 * k)) & 0x03030303u);
+      if constexpr (W == 4) {
+        const uint32_t even = a[0] | (a[1] << 4), odd = a[2] | (a[3] << 4);
+        out[2 * i] = __builtin_amdgcn_perm(odd, even, 0x05010400u);
+        out[2 * i + 1] = __builtin_amdgcn_perm(odd, even, 0x07030602u);
+      } else {
+        const uint32_t p01 = __builtin_amdgcn_perm(a[1], a[0], 0x05010400u), q01 = __builtin_amdgcn_perm(a[1], a[0], 0x07030602u);
+        const uint32_t p23 = __builtin_amdgcn_perm(a[3], a[2], 0x05010400u), q23 = __builtin_amdgcn_perm(a[3], a[2], 0x07030602u);
+        out[4 * i] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+        out[4 * i + 1] = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+        out[4 * i + 2] = __builtin_amdgcn_perm(q23, q01, 0x05040100u);
+        out[4 * i + 3] = __builtin_amdgcn_perm(q23, q01, 0x07060302u);
       }
     }
-    if constexpr (W == 2) decode_span2_select(cw, s, z, reinterpret_cast<const uint8_t*>(table), w);      // most spans at low budgets: by selection
-    else decode_span<W>(cw, s, z, w);
   }
+  return s_h | (mn_h << 16);
 }
 
-// What a lane knows about one row of a turn: where its values lie in the incoming card.
-struct RowDesc {
-  uint32_t cls;     // old class 0..3; 4: the tables point outside the incoming card (the row becomes zeros); 5: no row
-  uint32_t slot;    // the token's slot in its old segment
-  uint32_t plane;
+// A span as it lies in the incoming card: its codes (or its 32 raw values) and its pair.
+struct OldSpan {
+  uint32_t cw[16];
+  uint32_t pair;
 };
 
-// The rows of outgoing class C, 64 per wave and turn (one per lane), dealt round-robin and continuing
-// where the previous class stopped.  A turn first looks its 64 rows up (token through the outgoing
-// order[], old width and slot through the incoming tables), then sorts them by old class with six
-// ballots, so that the 64 spans of a round mostly share one decoder, and works through them in
-// head_dim / 32 rounds; lane l of round k takes span (k * 64 + l) mod (spans per row) of sorted row
-// (k * 64 + l) / (spans per row).  The next turn's look-ups are in flight meanwhile.
-template <int C, int G, bool KEEP>
-__device__ __forceinline__ void requant_class(const RequantArgs& a, const CardGeom& in, uint32_t gw, uint32_t n_waves, uint32_t lane,
-                                     const u32x2* table, uint32_t& cum, uint32_t& bad) {
+// Span `gsp` (row * spans per row + span) of old class CO.  By value: stores into one object out of several branches
+// end up as one store to a computed place in scratch memory.
+template <int CO, int G>
+__device__ __forceinline__ OldSpan fetch_old(const uint8_t* card, const CardGeom& in, uint64_t gsp) {
   constexpr int GS = G / 32;
+  constexpr int NW = CO == 3 ? 16 : (2 << CO);
+  const uint8_t* src = card + (CO == 3 ? in.off_fp16 : in.off_codes[CO < 3 ? CO : 0]) + gsp * (4u * NW);
+  OldSpan d;
+  if constexpr (NW == 2) {
+    const u32x2 v = card_load<true>(reinterpret_cast<const u32x2*>(src));
+    d.cw[0] = v.x; d.cw[1] = v.y;
+  } else {
+#pragma unroll
+    for (int h = 0; h < NW / 4; ++h) {
+      const u32x4 v = card_load<true>(reinterpret_cast<const u32x4*>(src) + h);
+      d.cw[4 * h] = v.x; d.cw[4 * h + 1] = v.y; d.cw[4 * h + 2] = v.z; d.cw[4 * h + 3] = v.w;
+    }
+  }
+  if constexpr (CO < 3) d.pair = card_load<true>(reinterpret_cast<const uint32_t*>(card + in.off_meta[CO < 3 ? CO : 0]) + gsp / GS);
+  return d;
+}
+
+template <int W>
+__device__ __forceinline__ void decode_old(const OldSpan& d, uint32_t (&w)[16]) {
+  uint32_t cw[W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) cw[i] = d.cw[i];
+  decode_span<W>(cw, half_bits_to_float(d.pair & 0xFFFFu), half_bits_to_float(d.pair >> 16), w);
+}
+
+// Stores the codes and the pair of span gsp of the outgoing class with width W.  Plain stores: the rows of a line may
+// leave in different rounds, and the L2 puts the line together.
+template <int W, int G>
+__device__ __forceinline__ void store_span(const RequantArgs& a, uint64_t gsp, uint32_t q, bool live, const uint32_t (&codes)[W], uint32_t pair) {
+  constexpr int GS = G / 32, C = W == 2 ? 0 : W == 4 ? 1 : 2;
+  if (!live) return;
+  uint8_t* dst = a.card_out + a.out.off_codes[C] + gsp * (4u * W);
+  if (W == 2) *reinterpret_cast<u32x2*>(dst) = (u32x2){codes[0], codes[1]};
+  if (W >= 4) *reinterpret_cast<u32x4*>(dst) = (u32x4){codes[0], codes[1], codes[2], codes[3]};
+  if (W == 8) *reinterpret_cast<u32x4*>(dst + 16) = (u32x4){codes[4], codes[5], codes[6], codes[7]};
+  if ((q & (GS - 1)) == 0) reinterpret_cast<uint32_t*>(a.card_out + a.out.off_meta[C])[gsp / GS] = pair;
+}
+
+template <int W, int G>
+__device__ __forceinline__ void relabel_store(const RequantArgs& a, const OldSpan& d, uint64_t gsp, uint32_t q, bool live) {
+  uint32_t codes[W];
+  const uint32_t cw[2] = {d.cw[0], d.cw[1]};
+  const uint32_t pair = relabel_span2<W, G / 32>(cw, d.pair, codes);
+  store_span<W, G>(a, gsp, q, live, codes, pair);
+}
+
+template <int W, int G>
+__device__ __forceinline__ void quantize_store(const RequantArgs& a, const uint32_t (&w)[16], uint64_t gsp, uint32_t q, bool live) {
+  uint32_t codes[W];
+  const uint32_t pair = quantize_span<W, G / 32>(w, codes);            // every lane takes part: groups span lanes
+  store_span<W, G>(a, gsp, q, live, codes, pair);
+}
+
+// A round: up to 64 spans of rows list[first .. first + rows) of old class `co`.
+struct Round {
+  uint32_t co, first, rows;
+};
+
+struct Shared {
+  u32x2 list[kWindow];                         // (slot in the incoming segment, row of the window), sorted by old class
+  uint32_t counts[kWindow / kWaveSize][8];
+  uint32_t round_list[kMaxRounds];             // co | rows << 8 | first << 16
+  uint32_t n_rounds;
+};
+
+// The rows [j0, j0 + kWindow) of outgoing class C in the planes [p0, p1).
+template <int C, int G>
+__device__ __forceinline__ void requant_window(const RequantArgs& a, const CardGeom& in, uint32_t j0, uint32_t p0, uint32_t p1,
+                                               Shared& sh) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const CardGeom& out = a.out;
-  const uint32_t n_new = out.n[C];
-  if (n_new == 0) return;
   const uint32_t spr_shift = out.lpr_shift - 2u;                       // log2(spans per row)
-  const uint32_t rounds = 1u << spr_shift;
-  const uint32_t n_rows = out.planes * n_new;                          // below 2^32 by the shape rules
-  const uint32_t tiles = (uint32_t)(((uint64_t)n_rows + kWaveSize - 1u) / kWaveSize);
-  const uint32_t* order_out = reinterpret_cast<const uint32_t*>(a.card_out + out.off_order) + out.base[C];
-  const uint32_t first = (gw + n_waves - cum) % n_waves;
+  const uint32_t n_new = out.n[C];
+  constexpr uint32_t kPer = kWindow / kBlockThreads;
 
-  auto look_up = [&](uint32_t i) -> RowDesc {
-    RowDesc d = {5u, 0u, 0u};
-    const uint64_t r64 = (uint64_t)i * kWaveSize + lane;
-    if (i < tiles && r64 < n_rows) {
-      const uint32_t r = (uint32_t)r64;
-      // plane without a division per lane: one for the turn's first row (the same in every lane), then at most
-      // one plane boundary inside the turn's 64 rows when the class has that many tokens
-      const uint32_t row_first = i * kWaveSize;
-      const uint32_t plane_first = row_first / n_new;
-      const uint32_t p = (n_new < (uint32_t)kWaveSize) ? r / n_new
-                                                       : plane_first + (r - plane_first * n_new >= n_new ? 1u : 0u);
-      d.plane = p;
-      d.cls = 4u;
-      const uint32_t t = order_out[r - p * n_new];
-      if (t < out.tokens) {
-        const uint32_t width = a.card_in[in.off_bits + t];
-        const uint32_t sl = reinterpret_cast<const uint32_t*>(a.card_in + in.off_slot)[t];
-        const bool ok = (width == 2 && sl < in.n[0]) || (width == 4 && sl < in.n[1]) || (width == 8 && sl < in.n[2]) ||
-                        (width == 16 && sl < in.n[3]);
-        if (ok) { d.cls = (width == 2) ? 0u : (width == 4) ? 1u : (width == 8) ? 2u : 3u; d.slot = sl; }
-      }
-    }
-    return d;
-  };
-
-  RowDesc next = look_up(first);
-  for (uint32_t i = first; i < tiles; i += n_waves) {
-    const RowDesc mine = next;
-    next = look_up(i + n_waves);                       // in flight while this turn is worked through
-    if (mine.cls == 4u) bad = 1;
-
-    // stable sort of the turn's rows by class: rank = rows of lower classes + rows of my class in lower lanes
-    uint32_t rank = 0, below = 0;
+  // ---- look the rows up and sort them by old class
+  uint32_t cls[kPer], slot[kPer], rank[kPer];                          // class 7: no row
+  bool bad = false;
+  {
+    const uint32_t* order = reinterpret_cast<const uint32_t*>(a.card_out + out.off_order) + out.base[C];
 #pragma unroll
-    for (uint32_t k = 0; k < 6u; ++k) {
-      const uint64_t m = __builtin_amdgcn_ballot_w64(mine.cls == k);
-      const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-      if (mine.cls == k) rank = below + before;
-      below += (uint32_t)__builtin_popcountll(m);
-    }
-    // lane s receives the row of rank s
-    const int to = (int)(rank * 4u);
-    const uint32_t s_id = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(lane | (mine.cls << 8)));
-    const uint32_t s_slot = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)mine.slot);
-    const uint32_t s_plane = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)mine.plane);
-
-#pragma unroll 1
-    for (uint32_t k = 0; k < rounds; ++k) {
-      const uint32_t x = k * kWaveSize + lane;
-      const int from = (int)((x >> spr_shift) * 4u);
-      const uint32_t q = x & (rounds - 1u);
-      const uint32_t id = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)s_id);
-      const uint32_t slot = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)s_slot);
-      const uint32_t p = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)s_plane);
-      const uint32_t cls = id >> 8;
-      if (__builtin_amdgcn_ballot_w64(cls < 5u) == 0) break;            // rows that do not exist sort last
-      const bool live = cls < 5u;
-      uint32_t w[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) w[j] = 0;
-      if (cls == 0u) decode_old_class<0, G, KEEP>(a.card_in, in, p, slot, q, spr_shift, table, w, bad);
-      else if (cls == 1u) decode_old_class<1, G, KEEP>(a.card_in, in, p, slot, q, spr_shift, table, w, bad);
-      else if (cls == 2u) decode_old_class<2, G, KEEP>(a.card_in, in, p, slot, q, spr_shift, table, w, bad);
-      else if (cls == 3u) decode_old_class<3, G, KEEP>(a.card_in, in, p, slot, q, spr_shift, table, w, bad);
-      const uint64_t gsp = ((((uint64_t)i * kWaveSize) + (id & 63u)) << spr_shift) + q;    // the span's place in the outgoing segment
-      if constexpr (C == 3) {
-        if (live) {
-          u32x4* dst = reinterpret_cast<u32x4*>(a.card_out + out.off_fp16 + gsp * 64u);
-#pragma unroll
-          for (int h = 0; h < 4; ++h) card_store<kMergeStores>(dst + h, (u32x4){w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]});
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t j = j0 + i * kBlockThreads + tid;
+      cls[i] = 7u; slot[i] = 0u;
+      if (j < n_new) {
+        cls[i] = 4u;
+        const uint32_t t = order[j];
+        if (t < out.tokens) {
+          const uint32_t width = a.card_in[in.off_bits + t];
+          const uint32_t sl = reinterpret_cast<const uint32_t*>(a.card_in + in.off_slot)[t];
+          const bool ok = (width == 2 && sl < in.n[0]) || (width == 4 && sl < in.n[1]) || (width == 8 && sl < in.n[2]) ||
+                          (width == 16 && sl < in.n[3]);
+          if (ok) { cls[i] = class_of(width); slot[i] = sl; }
         }
-      } else {
-        constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
-        uint32_t codes[W];
-        const uint32_t pair = quantize_span<W, GS>(w, codes);        // every lane takes part: groups span lanes
-        if (live) {
-          uint8_t* dst = a.card_out + out.off_codes[C] + gsp * (4u * W);
-          if (W == 2) card_store<kMergeStores>(reinterpret_cast<u32x2*>(dst), (u32x2){codes[0], codes[1]});
-          if (W >= 4) card_store<kMergeStores>(reinterpret_cast<u32x4*>(dst), (u32x4){codes[0], codes[1], codes[2], codes[3]});
-          if (W == 8) card_store<kMergeStores>(reinterpret_cast<u32x4*>(dst + 16), (u32x4){codes[4], codes[5], codes[6], codes[7]});
-          if ((gsp & (GS - 1)) == 0)
-            card_store<kMergeStores>(reinterpret_cast<uint32_t*>(a.card_out + out.off_meta[C]) + gsp / GS, pair);
-        }
+        bad |= cls[i] == 4u;
       }
     }
   }
-  cum = (cum + tiles) % n_waves;
+  if (bad && a.status) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    uint64_t same = ~0ull;                                             // lanes with this lane's class
+#pragma unroll
+    for (uint32_t bit = 1; bit < 8u; bit <<= 1) {
+      const uint64_t m = __builtin_amdgcn_ballot_w64((cls[i] & bit) != 0u);
+      same &= (cls[i] & bit) ? m : ~m;
+    }
+    rank[i] = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+    uint32_t* counts = sh.counts[i * kWavesPerBlock + wave];
+    if (lane < 8u) counts[lane] = 0u;
+    if (rank[i] == 0u) counts[cls[i]] = (uint32_t)__builtin_popcountll(same);
+  }
+  __syncthreads();
+  uint32_t start = 0;                                                  // lane = class: its first place in the list
+  {
+    uint32_t total = 0, lower[kPer] = {};                              // of that class: in the window, in front of this wave's rows
+#pragma unroll
+    for (uint32_t w = 0; w < kPer * (uint32_t)kWavesPerBlock; ++w) {
+      const uint32_t n = lane < kOld ? sh.counts[w][lane] : 0u;
+      total += n;
+#pragma unroll
+      for (uint32_t i = 0; i < kPer; ++i) lower[i] += w < i * kWavesPerBlock + wave ? n : 0u;
+    }
+    start = wave_inclusive_scan(total) - total;
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t at = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(cls[i] * 4u), (int)(start + lower[i])) + rank[i];
+      if (cls[i] < kOld) sh.list[at] = (u32x2){slot[i], i * (uint32_t)kBlockThreads + tid};
+    }
+    if (wave == 0) {
+      const uint32_t per_round = (uint32_t)kWaveSize >> spr_shift;     // rows
+      const uint32_t rounds = (total + per_round - 1u) / per_round;
+      const uint32_t inc = wave_inclusive_scan(rounds);
+      if (lane == 63) sh.n_rounds = inc;
+      for (uint32_t r = 0; r < rounds; ++r)
+        sh.round_list[inc - rounds + r] = lane | (min(per_round, total - r * per_round) << 8) | ((start + r * per_round) << 16);
+    }
+  }
+  __syncthreads();
+
+  const uint32_t rounds = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.n_rounds);
+  const uint32_t q = lane & ((1u << spr_shift) - 1u), row_of_lane = lane >> spr_shift;
+  const auto round_at = [&](uint32_t r) {
+    const uint32_t x = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.round_list[r]);
+    const Round d = {x & 255u, x >> 16, (x >> 8) & 255u};
+    return d;
+  };
+  const auto fetch = [&](const Round& d, uint32_t p, uint32_t in_slot) {
+    OldSpan o;
+    if (d.co == 0u) o = fetch_old<0, G>(a.card_in, in, ((uint64_t)(p * in.n[0] + in_slot) << spr_shift) + q);
+    else if (d.co == 1u) o = fetch_old<1, G>(a.card_in, in, ((uint64_t)(p * in.n[1] + in_slot) << spr_shift) + q);
+    else if (d.co == 2u) o = fetch_old<2, G>(a.card_in, in, ((uint64_t)(p * in.n[2] + in_slot) << spr_shift) + q);
+    else if (d.co == 3u) o = fetch_old<3, G>(a.card_in, in, ((uint64_t)(p * in.n[3] + in_slot) << spr_shift) + q);
+    return o;
+  };
+  uint32_t p = p0, r = wave;
+  while (r >= rounds) { r -= rounds; ++p; }
+  if (p >= p1) return;
+  Round next = round_at(r);
+  u32x2 next_e = sh.list[next.first + min(row_of_lane, next.rows - 1u)];     // lanes past the round's rows repeat its last one
+  OldSpan next_o = fetch(next, p, next_e.x);
+  while (true) {
+    const Round d = next;
+    const u32x2 e = next_e;
+    const OldSpan o = next_o;
+    const uint32_t plane = p;
+    r += kWavesPerBlock;
+    while (r >= rounds) { r -= rounds; ++p; }
+    const bool more = p < p1;
+    if (more) {
+      next = round_at(r);
+      next_e = sh.list[next.first + min(row_of_lane, next.rows - 1u)];
+      next_o = fetch(next, p, next_e.x);
+    }
+    const bool live = row_of_lane < d.rows;
+    const uint64_t gsp = ((uint64_t)(plane * n_new + j0 + e.y) << spr_shift) + q;
+    bool done = false;
+    if constexpr (C < 3) {
+      if (d.co == 0u && can_relabel(o.pair)) {
+        relabel_store<(2 << C), G>(a, o, gsp, q, live);
+        done = true;
+      }
+    }
+    if (!done) {
+      uint32_t w[16];
+      if (d.co == 0u) decode_old<2>(o, w);
+      else if (d.co == 1u) decode_old<4>(o, w);
+      else if (d.co == 2u) decode_old<8>(o, w);
+      else {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) w[j] = d.co == 3u ? o.cw[j] : 0u;
+      }
+      if constexpr (C < 3) {
+        quantize_store<(2 << C), G>(a, w, gsp, q, live);
+      } else if (live) {
+        u32x4* dst = reinterpret_cast<u32x4*>(a.card_out + out.off_fp16 + gsp * 64u);
+#pragma unroll
+        for (int h = 0; h < 4; ++h) dst[h] = (u32x4){w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]};
+      }
+    }
+    if (!more) break;
+  }
 }
 
-template <int G, bool KEEP>
+__host__ __device__ inline uint32_t windows_of(uint32_t n) { return (uint32_t)(((uint64_t)n + kWindow - 1u) / kWindow); }
+
+template <int G>
 __global__ __launch_bounds__(kBlockThreads) void requant_kernel(RequantArgs a) {
-  __shared__ u32x2 tables[kWavesPerBlock][256];      // selector tables of the 2-bit decoder
+  __shared__ Shared sh;
   CardGeom in;
   if (!card_geometry_from_header(a.card_in, a.card_in_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, in))
     return;                                   // uniform over the grid
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wave = threadIdx.x >> 6;
-  const uint32_t gw = blockIdx.x * kWavesPerBlock + wave;
-  const uint32_t n_waves = gridDim.x * kWavesPerBlock;
-  build_select_table(tables[wave], lane);      // each wave its own copy: no barrier, fewer bank conflicts
-  const u32x2* table = tables[wave];
-  uint32_t bad = 0, cum = 0;
-  requant_class<0, G, KEEP>(a, in, gw, n_waves, lane, table, cum, bad);
-  requant_class<1, G, KEEP>(a, in, gw, n_waves, lane, table, cum, bad);
-  requant_class<2, G, KEEP>(a, in, gw, n_waves, lane, table, cum, bad);
-  requant_class<3, G, KEEP>(a, in, gw, n_waves, lane, table, cum, bad);
-  if (bad && a.status) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
+  const uint32_t w0 = windows_of(a.out.n[0]), w1 = windows_of(a.out.n[1]), w2 = windows_of(a.out.n[2]), w3 = windows_of(a.out.n[3]);
+  const uint32_t per_group = w0 + w1 + w2 + w3;
+  const uint32_t group = blockIdx.x / per_group;
+  uint32_t k = blockIdx.x - group * per_group;
+  const uint32_t p0 = group * a.group_planes, p1 = min(p0 + a.group_planes, a.out.planes);
+  if (k < w0) requant_window<0, G>(a, in, k * kWindow, p0, p1, sh);
+  else if ((k -= w0) < w1) requant_window<1, G>(a, in, k * kWindow, p0, p1, sh);
+  else if ((k -= w1) < w2) requant_window<2, G>(a, in, k * kWindow, p0, p1, sh);
+  else requant_window<3, G>(a, in, (k - w2) * kWindow, p0, p1, sh);
 }
 
 }  // namespace
@@ -226,25 +379,21 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
   a.out = out;
   a.card_out = card_out;
   a.status = status;
-  uint64_t tiles = 0;                           // turns: 64 rows each
-  for (int c = 0; c < 4; ++c) tiles += ((uint64_t)out.planes * out.n[c] + kWaveSize - 1u) / kWaveSize;
-  if (tiles == 0) return hipSuccess;
-  // A wave's start-up (header checks, selector table) costs about as much as 128 spans, and the kernel is bound
-  // by instruction issue: several turns per wave once there are enough waves to fill the chip several times over
-  // (measured at 8K tokens: 261 us against 280 us with 128 spans per wave).
-  const uint64_t fill = 8192;
-  const uint64_t per_wave = out.head_dim >= 256u ? 1u : out.head_dim == 128u ? 2u : 4u;      // 512 spans
-  uint64_t waves = (tiles + per_wave - 1) / per_wave;
-  if (waves < fill) waves = tiles < fill ? tiles : fill;
-  const dim3 grid(grid_blocks(waves)), block(kBlockThreads);
-  const bool keep = out.total <= kCacheResidentCardBytes && card_in_bytes <= kCacheResidentCardBytes;
-  switch (out.group_size * 2 + (keep ? 1 : 0)) {
-    case 65: hipLaunchKernelGGL((requant_kernel<32, true>), grid, block, 0, stream, a); break;
-    case 64: hipLaunchKernelGGL((requant_kernel<32, false>), grid, block, 0, stream, a); break;
-    case 129: hipLaunchKernelGGL((requant_kernel<64, true>), grid, block, 0, stream, a); break;
-    case 128: hipLaunchKernelGGL((requant_kernel<64, false>), grid, block, 0, stream, a); break;
-    case 257: hipLaunchKernelGGL((requant_kernel<128, true>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((requant_kernel<128, false>), grid, block, 0, stream, a); break;
+  uint64_t windows = 0;
+  for (int c = 0; c < 4; ++c) windows += windows_of(out.n[c]);
+  // A workgroup's look-ups are worth sharing between planes while the chip stays full several times over and both cards
+  // sit in the memory-side cache (8K tokens, budget 3 to 2.5: 161.7 us with two planes, 165.4 with one); larger cards
+  // want a plane's windows, which share lines of the incoming card, to run at the same time (32K, 6 to 4: 853 us with
+  // one plane, 951 with four).
+  const bool resident = out.total <= kCacheResidentCardBytes && card_in_bytes <= kCacheResidentCardBytes;
+  uint32_t group = resident ? kMaxPlanes : 1u;
+  while (group > 1u && windows * ((out.planes + group - 1u) / group) < 8192u) group /= 2u;
+  a.group_planes = group;
+  const dim3 grid((uint32_t)(windows * ((out.planes + group - 1u) / group))), block(kBlockThreads);
+  switch (out.group_size) {
+    case 32: hipLaunchKernelGGL(requant_kernel<32>, grid, block, 0, stream, a); break;
+    case 64: hipLaunchKernelGGL(requant_kernel<64>, grid, block, 0, stream, a); break;
+    default: hipLaunchKernelGGL(requant_kernel<128>, grid, block, 0, stream, a); break;
   }
   return hipGetLastError();
 }

@@ -1,0 +1,81 @@
+"""Requantization at the edges of its windows (256 rows of an outgoing segment) and of its rounds, and the relabelling of
+2-bit groups against the chain through the dense cache for pairs that card creation would never write."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_03884_amd as qkv
+import qkv_synth
+from oracle import ref
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def hop(card, rd, bits_new, label):
+    """The call's card against the oracle's unpack + pack, byte for byte."""
+    print("[case] " + label, flush=True)
+    counts = ref.count_bits(bits_new).tolist()
+    k, v = ref.unpack_dequant(card, rd)
+    want = ref.quantize_pack(rd, k, v, bits_new, counts)
+    desc = qkv.Desc.make(rd.layers, rd.kv_heads, rd.tokens, rd.head_dim, rd.group_size)
+    out = torch.full((want.size,), 0xA5, dtype=torch.uint8, device=DEV)
+    status = torch.full((1,), 0x7777, dtype=torch.int32, device=DEV)
+    qkv.requantize(torch.from_numpy(card).to(DEV), desc, torch.from_numpy(bits_new).to(DEV), counts, out, status=status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    diff = np.flatnonzero(out.cpu().numpy() != want)
+    assert diff.size == 0, (label, "differs at %d bytes, first %d" % (diff.size, int(diff[0])))
+
+
+def draw_bits(T, rng, shares):
+    return rng.choice(np.array([2, 4, 8, 16], np.uint8), size=T, p=shares)
+
+
+@pytest.mark.parametrize("T,D,G", [(255, 128, 32), (256, 64, 32), (257, 256, 128), (513, 128, 64), (1, 64, 64), (700, 128, 128)])
+def test_window_edges(T, D, G):
+    rng = np.random.default_rng(T)
+    K, V = qkv_synth.make_kv(1, 3, T, D, T, "llama")
+    rd = ref.make_desc(1, 3, T, D, G)
+    mixes = {"even": [0.25] * 4, "low": [0.9, 0.06, 0.03, 0.01], "high": [0.0, 0.1, 0.3, 0.6]}
+    for na, a in mixes.items():
+        bits = draw_bits(T, rng, a)
+        card = ref.quantize_pack(rd, K.numpy().view(np.uint16), V.numpy().view(np.uint16), bits, ref.count_bits(bits).tolist())
+        for nb, b in mixes.items():
+            hop(card, rd, draw_bits(T, rng, b), "T=%d D=%d G=%d %s to %s" % (T, D, G, na, nb))
+
+
+@pytest.mark.parametrize("G", [32, 64, 128])
+@pytest.mark.parametrize("kind", ["normal", "subnormal scale", "zero scale", "negative scale", "one code", "two codes", "mixed"])
+def test_two_bit_groups_of_any_content(kind, G):
+    """2-bit cards with drawn pairs and codes; every decoded value stays finite."""
+    T, D, P = 96, 128, 2
+    rng = np.random.default_rng(len(kind) + G)
+    rd = ref.make_desc(1, 1, T, D, G)
+    zero = np.zeros((1, 1, T, D), np.uint16)
+    card = ref.quantize_pack(rd, zero, zero, np.full(T, 2, np.uint8), [T, 0, 0, 0])
+    off = ref.card_offsets(rd, [T, 0, 0, 0])
+    n_codes, n_pairs = P * T * D // 4, P * T * D // G
+    codes = rng.integers(0, 256, n_codes).astype(np.uint8)
+    scale = np.abs(rng.standard_normal(n_pairs) * 10.0 ** rng.integers(-3, 3, n_pairs)).astype(np.float16)
+    low = (rng.integers(1, 1024, n_pairs) * 2.0 ** -24).astype(np.float16)
+    zeros = (rng.standard_normal(n_pairs) * 10.0 ** rng.integers(-6, 4, n_pairs)).astype(np.float16)
+    pick = rng.integers(0, 4, n_pairs)
+    if kind == "subnormal scale":
+        scale = low
+        zeros = np.where(rng.random(n_pairs) < 0.5, zeros, (rng.integers(-3000, 3000, n_pairs) * 2.0 ** -24).astype(np.float16))
+    if kind == "zero scale":
+        scale[:] = 0
+        zeros[::3] = np.float16(-0.0)
+    if kind == "negative scale":
+        scale[::2] = -scale[::2]
+    if kind == "one code":
+        codes = np.repeat(pick * 0x55, n_codes // n_pairs).astype(np.uint8)
+    if kind == "two codes":
+        codes = np.where(rng.random(n_codes) < 0.9, np.repeat(pick * 0x55, n_codes // n_pairs), rng.integers(0, 4, n_codes) * 0x55).astype(np.uint8)
+    if kind == "mixed":
+        scale = np.choose(pick, [scale, low, np.zeros_like(scale), -scale])
+    card[off["codes2"]:off["codes2"] + n_codes] = codes
+    card[off["meta2"]:off["meta2"] + 4 * n_pairs] = np.stack([scale, zeros], axis=1).reshape(-1).view(np.uint8)
+    for width in (2, 4, 8, 16):
+        hop(card, rd, np.full(T, width, np.uint8), "2-bit, %s, G=%d to %d bits" % (kind, G, width))
