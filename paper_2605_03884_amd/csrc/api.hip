@@ -470,25 +470,29 @@ int qkv_inject_layers(const void* card_dev, uint64_t card_bytes, const qkv_desc_
 
 namespace {
 // Shape rules of the fused attention path and the floats of workspace it needs.
-static int attend_workspace_floats(const qkv_desc_t* expect, int32_t q_heads, uint64_t* floats) {
+// (floats: the least a call accepts; best: what it can use).
+static int attend_workspace_floats(const qkv_desc_t* expect, int32_t q_heads, uint64_t* floats, uint64_t* best = nullptr) {
   const int rc = check_desc(expect);
   if (rc) return rc;
   if (q_heads < expect->kv_heads || q_heads % expect->kv_heads != 0 || q_heads / expect->kv_heads > 16)
     return QKV_ERR_SHAPE;
   const uint32_t rep = (uint32_t)(q_heads / expect->kv_heads);
+  const uint64_t pairs = (uint64_t)expect->layers * (uint64_t)expect->kv_heads;
   uint32_t chunk = 0, max_tasks = 0;
-  attend_plan((uint64_t)expect->tokens, rep, (uint64_t)expect->layers * (uint64_t)expect->kv_heads, &chunk, &max_tasks);
-  *floats = (uint64_t)expect->layers * (uint64_t)expect->kv_heads * max_tasks * rep * ((uint32_t)expect->head_dim + 2u) + 4u;   // + verdict word
+  attend_plan((uint64_t)expect->tokens, rep, pairs, &chunk, &max_tasks);
+  const uint64_t per_task = pairs * rep * ((uint32_t)expect->head_dim + 2u);
+  *floats = max_tasks * per_task + 4u;   // + verdict word
+  if (best) *best = attend_more_tasks((uint64_t)expect->tokens, rep, pairs, (uint32_t)expect->head_dim, max_tasks) * per_task + 4u;
   return QKV_OK;
 }
 }  // namespace
 
 int qkv_card_attend_workspace(const qkv_desc_t* expect, int32_t q_heads, uint64_t* bytes_out) {
   if (!expect || !bytes_out) return QKV_ERR_NULL;
-  uint64_t floats = 0;
-  const int rc = attend_workspace_floats(expect, q_heads, &floats);
+  uint64_t least = 0, best = 0;
+  const int rc = attend_workspace_floats(expect, q_heads, &least, &best);
   if (rc) return rc;
-  *bytes_out = floats * sizeof(float);
+  *bytes_out = best * sizeof(float);
   return QKV_OK;
 }
 
@@ -528,7 +532,7 @@ int qkv_card_attend(const void* card_dev, uint64_t card_bytes, const qkv_desc_t*
   if (workspace_bytes < floats * sizeof(float)) return QKV_ERR_CAPACITY;
   if (reinterpret_cast<uintptr_t>(workspace_dev) % 16 != 0) return QKV_ERR_ALIGN;
   if (launch_attend(static_cast<const uint8_t*>(card_dev), card_bytes, g, q_dev, (uint32_t)q_heads, softmax_scale,
-                    out_dev, lse_dev, static_cast<float*>(workspace_dev), status_dev, false,
+                    out_dev, lse_dev, static_cast<float*>(workspace_dev), workspace_bytes, status_dev, false,
                     static_cast<hipStream_t>(stream)) != hipSuccess)
     return QKV_ERR_HIP;
   return QKV_OK;
@@ -546,7 +550,7 @@ int qkv_card_attend_kc(const void* card_dev, uint64_t card_bytes, const qkv_desc
   if (workspace_bytes < floats * sizeof(float)) return QKV_ERR_CAPACITY;
   if (reinterpret_cast<uintptr_t>(workspace_dev) % 16 != 0) return QKV_ERR_ALIGN;
   if (launch_attend(static_cast<const uint8_t*>(card_dev), card_bytes, g, q_dev, (uint32_t)q_heads, softmax_scale,
-                    out_dev, lse_dev, static_cast<float*>(workspace_dev), status_dev, true,
+                    out_dev, lse_dev, static_cast<float*>(workspace_dev), workspace_bytes, status_dev, true,
                     static_cast<hipStream_t>(stream)) != hipSuccess)
     return QKV_ERR_HIP;
   return QKV_OK;
@@ -563,7 +567,7 @@ int qkv_card_attend_static(const void* card_dev, uint64_t card_bytes, const qkv_
   float* scratch_at = nullptr;
   if (attend_static_scratch(&scratch_at) != hipSuccess) return QKV_ERR_HIP;
   if (launch_attend(static_cast<const uint8_t*>(card_dev), card_bytes, g, q_dev, (uint32_t)q_heads, softmax_scale,
-                    out_dev, lse_dev, scratch_at, status_dev, false, static_cast<hipStream_t>(stream)) != hipSuccess)
+                    out_dev, lse_dev, scratch_at, QKV_ATTEND_STATIC_SCRATCH_BYTES, status_dev, false, static_cast<hipStream_t>(stream)) != hipSuccess)
     return QKV_ERR_HIP;
   return QKV_OK;
 }

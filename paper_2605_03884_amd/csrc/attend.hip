@@ -61,7 +61,8 @@ struct AttendArgs {
   float* part_o;           // [L*H][max_tasks][R][D] unnormalised sums of p.V^
   float* part_ml;          // [L*H][max_tasks][R][2]  (m in log2 units, l); l = 0 marks an empty task
   uint32_t max_tasks;      // tasks per (layer, kv head) the workspace was sized for
-  uint32_t chunk;          // tokens per task
+  uint32_t chunk;          // tokens per task at most
+  uint32_t unit[4];        // tokens of a class that make up one unit of work, see task_rows
   float* out;              // fp32 [L][Hq][D]
   float* lse;              // fp32 [L][Hq] or null
   uint32_t* status;        // or null
@@ -695,6 +696,28 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
   }
 }
 
+// Rows a task of every class takes.  Long sequences: `chunk` of any class, the most LDS allows.  Where there are more
+// tasks than that needs, all of them get the same number of units: a unit is one group of rounds whose loads
+// are in flight together - fewer tokens at larger widths - so a task lasts about as long whatever its width,
+// and the longest one decides how long a short card takes (whole call, 1K tokens at budget 5, 256 pairs: 27.7 us with
+// 192 rows of any width a task, 23.9 us; 300 tokens: 18.3 and 15.2 us).
+// With s units a task there are at most sum (u_c + s - 1) / s tasks over the k classes present, so
+// s >= (sum u_c - k) / (max_tasks - k) keeps them within max_tasks.
+__device__ inline void task_rows(const AttendArgs& a, const CardGeom& g, uint32_t (&rows)[4]) {
+  uint32_t sum = 0, present = 0, most = ~0u;             // most: units that fit a task of every class present
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    if (g.n[c] == 0u) continue;
+    sum += (g.n[c] + a.unit[c] - 1u) / a.unit[c];
+    ++present;
+    most = min(most, a.chunk / a.unit[c]);
+  }
+  const uint32_t room = a.max_tasks - present;           // max_tasks is at least 4
+  const uint32_t share = room == 0u ? ~0u : max(1u, (sum - present + room - 1u) / room);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) rows[c] = share <= most ? share * a.unit[c] : a.chunk;
+}
+
 // KC: the card's key planes are grouped per channel (a uniform card at 2, 4 or 8 bits, group size 32).
 template <int G, bool NARROW, int DS, bool KC>
 __global__ __launch_bounds__(kAttendWaves * kWaveSize) __attribute__((amdgpu_waves_per_eu(2)))
@@ -728,14 +751,16 @@ void attend_kernel(AttendArgs a) {
   // which class and which rows this task covers
   int cls = -1;
   uint32_t j0 = 0, j1 = 0;
+  uint32_t rows[4];
+  task_rows(a, g, rows);
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const uint32_t chunks = (g.n[c] + a.chunk - 1) / a.chunk;
+    const uint32_t chunks = (g.n[c] + rows[c] - 1) / rows[c];
     if (cls < 0) {
       if (tau < chunks) {
         cls = c;
-        j0 = tau * a.chunk;
-        j1 = min(g.n[c], j0 + a.chunk);
+        j0 = tau * rows[c];
+        j1 = min(g.n[c], j0 + rows[c]);
       } else {
         tau -= chunks;
       }
@@ -762,48 +787,70 @@ void attend_kernel(AttendArgs a) {
   }
 }
 
-// Merges the partials of one (layer, query head): thread d owns output dimension d.  The
-// (m, l) pairs of all tasks are first gathered into LDS by parallel loads, so that the
-// weights cost no chain of dependent global loads.
-constexpr int kMergeBatch = 256;             // tasks whose (m, l) are held in LDS at a time
+// Merges the partials of one (layer, query head).  The tasks' weights relative to the common maximum are worked out once,
+// a thread per task; then every group of head_dim / 4 threads adds up its share of the tasks, four output
+// dimensions per thread, and the groups' sums are added in order.  Bound by the latency of one trip to the partials:
+// one thread per dimension walking over all tasks, with the weights' exponentials in the loop, took 7.6 us at 8K tokens
+// (25 tasks); this takes 6.4.
+constexpr int kMergeBatch = 256;             // tasks whose weights are held in LDS at a time
+constexpr int kMergeThreads = 256;
 
-__global__ __launch_bounds__(256) void attend_merge_kernel(AttendArgs a) {
-  __shared__ float ml_m[kMergeBatch], ml_l[kMergeBatch];
+__global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(AttendArgs a) {
+  __shared__ float weight[kMergeBatch];
+  __shared__ float part_max[kMergeThreads / kWaveSize], part_den[kMergeThreads / kWaveSize];
+  __shared__ f32x4 sums[kMergeThreads];
   if (*a.valid == 0) return;                           // header refused: outputs stay untouched
-  const uint32_t d = threadIdx.x, D = a.head_dim;      // one thread per output dimension
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, D = a.head_dim;
   const uint32_t lq = blockIdx.x;                      // l * Hq + hq
   const uint32_t l = lq / a.q_heads, hq = lq - l * a.q_heads;
   const uint32_t h = hq / a.rep, r = hq - h * a.rep;
   const uint64_t part0 = (uint64_t)(l * a.kv_heads + h) * a.max_tasks;
-  float M = -INFINITY, den = 0.f, num = 0.f;           // running maximum, and sums relative to it
+  const uint32_t per = D / 4u, split = kMergeThreads / per;      // threads per task's row, tasks at a time
+  const uint32_t mine = tid / per, d4 = tid - mine * per;
+  float M = -INFINITY, den = 0.f;                      // running maximum, and sums relative to it
+  f32x4 num = {0.f, 0.f, 0.f, 0.f};
   for (uint32_t t0 = 0; t0 < a.max_tasks; t0 += kMergeBatch) {
     const uint32_t nb = min((uint32_t)kMergeBatch, a.max_tasks - t0);
-    __syncthreads();
-    for (uint32_t t = d; t < nb; t += D) {
-      const float* ml = a.part_ml + ((part0 + t0 + t) * a.rep + r) * 2;
-      ml_m[t] = ml[0];
-      ml_l[t] = ml[1];
+    float m = -INFINITY, lt = 0.f;
+    if (tid < nb) {
+      const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + ((part0 + t0 + tid) * a.rep + r) * 2);
+      if (ml.y > 0.f) { m = ml.x; lt = ml.y; }         // an empty task counts for nothing
     }
+    float top = row_max16(m);
+    top = fmaxf(top, __shfl_xor(top, 16, kWaveSize));
+    top = fmaxf(top, __shfl_xor(top, 32, kWaveSize));
+    if (lane == 0) part_max[wave] = top;
     __syncthreads();
     float Mb = M;
-    for (uint32_t t = 0; t < nb; ++t) if (ml_l[t] > 0.f) Mb = fmaxf(Mb, ml_m[t]);
-    if (Mb == -INFINITY) continue;                     // nothing but empty tasks so far (uniform over the block)
-    const float rescale = __builtin_amdgcn_exp2f(M - Mb);   // 0 when M is still -inf
-    den *= rescale;
-    num *= rescale;
+#pragma unroll
+    for (int w = 0; w < kMergeThreads / kWaveSize; ++w) Mb = fmaxf(Mb, part_max[w]);
+    const float rescale = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
     M = Mb;
-    // loads first, unconditionally (an empty task's slot holds anything: it is read but not used)
-#pragma unroll 8
-    for (uint32_t t = 0; t < nb; ++t) {
-      const float v = a.part_o[((part0 + t0 + t) * a.rep + r) * D + d];
-      const float lt = ml_l[t];
-      const float w = __builtin_amdgcn_exp2f(ml_m[t] - M);
-      den += (lt > 0.f) ? w * lt : 0.f;
-      num += (lt > 0.f) ? w * v : 0.f;
+    const float w = lt > 0.f ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+    weight[tid] = w;
+    float wl = row_sum16(w * lt);
+    wl += __shfl_xor(wl, 16, kWaveSize);
+    wl += __shfl_xor(wl, 32, kWaveSize);
+    if (lane == 0) part_den[wave] = wl;
+    __syncthreads();
+    den *= rescale;
+#pragma unroll
+    for (int x = 0; x < kMergeThreads / kWaveSize; ++x) den += part_den[x];
+    num *= rescale;
+#pragma unroll 4
+    for (uint32_t t = mine; t < nb; t += split) {
+      const float wt = weight[t];
+      if (wt != 0.f) num += wt * *reinterpret_cast<const f32x4*>(a.part_o + ((part0 + t0 + t) * a.rep + r) * D + 4u * d4);
     }
+    if (t0 + kMergeBatch < a.max_tasks) __syncthreads();        // the weights are written again
   }
-  a.out[(uint64_t)lq * D + d] = num / den;
-  if (d == 0 && a.lse) a.lse[lq] = (M + __builtin_log2f(den)) * 0.69314718055994530942f;
+  sums[tid] = num;
+  __syncthreads();
+  if (tid < per) {
+    for (uint32_t x = 1; x < split; ++x) num += sums[x * per + tid];
+    *reinterpret_cast<f32x4*>(a.out + (uint64_t)lq * D + 4u * tid) = num / den;
+  }
+  if (tid == 0 && a.lse) a.lse[lq] = (M + __builtin_log2f(den)) * 0.69314718055994530942f;
 }
 
 }  // namespace
@@ -824,6 +871,22 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
   while (c > 192u && pairs * ((tokens + c - 1) / c + 2u) < slots) c -= 192u;
   *chunk = c;
   *max_tasks = (uint32_t)((tokens + *chunk - 1) / *chunk) + 3u;   // every class may end with a partly filled task
+}
+
+// The number of tasks that short sequences are better cut into, where the workspace has room for their partials: one
+// per wave slot of the chip, but no more than there are units of work at a middling mix of widths (an empty task still
+// costs its dispatch).  Up to 4 query heads per kv head and head_dim 128: beyond, a task's fixed part is heavier, and the
+// call got slower (3877 tokens with 8 heads 29.6 -> 31.9 us, 6000 tokens at head_dim 256 61.4 -> 62.4).  Not beyond the fixed scratch array, so that the call that uses it cuts
+// its tasks - and rounds its sums - like the one with a workspace.
+uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t head_dim, uint32_t max_tasks) {
+  if (rep > 4u || head_dim > 128u) return max_tasks;
+  const uint64_t slots = 256u * 4u * 4u;
+  uint64_t want = slots / pairs;
+  const uint64_t useful = tokens / 48u + 3u;
+  if (want > useful) want = useful;
+  const uint64_t fits = (QKV_ATTEND_STATIC_SCRATCH_BYTES / sizeof(float) - 4u) / (pairs * rep * (head_dim + 2u));
+  if (want > fits) want = fits;
+  return want > max_tasks ? (uint32_t)want : max_tasks;
 }
 
 // ---- scratch for callers that cannot allocate -------------------------------------------------
@@ -859,7 +922,7 @@ hipError_t attend_static_scratch(float** ptr) {
 
 hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, const void* q,
                          uint32_t q_heads, float softmax_scale, float* out, float* lse, float* workspace,
-                         uint32_t* status, bool keys_per_channel, hipStream_t stream) {
+                         uint64_t workspace_bytes, uint32_t* status, bool keys_per_channel, hipStream_t stream) {
   AttendArgs a;
   a.card = card;
   a.card_bytes = card_bytes;
@@ -872,6 +935,17 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
   attend_plan(expect.tokens, a.rep, (uint64_t)expect.layers * expect.kv_heads, &a.chunk, &a.max_tasks);
   const uint64_t pairs = (uint64_t)expect.layers * expect.kv_heads;
   const uint32_t D = expect.head_dim;
+  {
+    const uint32_t more = attend_more_tasks(expect.tokens, a.rep, pairs, D, a.max_tasks);
+    if (workspace_bytes >= (pairs * more * a.rep * (D + 2u) + 4u) * sizeof(float)) a.max_tasks = more;
+  }
+  // a group of rounds whose loads are in flight together: 4, 3, 2 or 1 rounds of 16 tokens; keys grouped per channel are
+  // scored up to 128 tokens at a time, in whole blocks of 32
+  const bool wide_units = keys_per_channel && a.chunk >= 128u;
+  a.unit[0] = wide_units ? 128u : 64u;
+  a.unit[1] = keys_per_channel ? (a.chunk >= 96u ? 96u : 64u) : 48u;
+  a.unit[2] = wide_units ? 128u : 32u;
+  a.unit[3] = 16u;
   a.part_o = workspace;
   a.part_ml = workspace + pairs * a.max_tasks * a.rep * D;
   a.valid = reinterpret_cast<uint32_t*>(workspace + pairs * a.max_tasks * a.rep * (D + 2u));
@@ -905,7 +979,7 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
 #undef QKV_LAUNCH_ATTEND
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attend_merge_kernel, dim3(expect.layers * q_heads), dim3(D), 0, stream, a);
+  hipLaunchKernelGGL(attend_merge_kernel, dim3(expect.layers * q_heads), dim3(kMergeThreads), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -1,0 +1,70 @@
+"""How attention over a short card cuts its tasks: every class alone and mixed, token counts at the edges of the units (64, 48,
+32 and 16 tokens by width), with the workspace the library asks for and with the least it accepts, and the merge over
+more tasks than its threads hold at a time.  Tolerances: the bounds of test_gpu_attend.py."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_03884_amd as qkv
+from oracle import attend_ref
+from test_gpu_attend import bounds, build_card
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def least_workspace(L, H, T, rep, D):
+    """Bytes for tasks of as many tokens as the scores' LDS holds (192 where those would leave wave slots empty)."""
+    room = 1536 // ((rep + 3) // 4 * 4)
+    c = room // 192 * 192 if room >= 192 else 64
+    while c > 192 and L * H * ((T + c - 1) // c + 2) < 4096:
+        c -= 192
+    return (L * H * ((T + c - 1) // c + 3) * rep * (D + 2) + 4) * 4
+
+
+@pytest.mark.parametrize("T", [1, 16, 17, 48, 65, 193, 500, 1537])
+@pytest.mark.parametrize("mix", ["even", "low", "2", "4", "8", "16"])
+def test_short_cards(T, mix):
+    L, H, rep, D, G = 1, 2, 4, 128, 32
+    print("[case] T=%d widths %s" % (T, mix), flush=True)
+    rng = np.random.default_rng(T)
+    if mix in ("even", "low"):
+        bits = rng.choice(np.array([2, 4, 8, 16], np.uint8), size=T, p=[0.25] * 4 if mix == "even" else [0.8, 0.1, 0.08, 0.02])
+    else:
+        bits = np.full(T, int(mix), np.uint8)
+    rd, card = build_card(L, H, T, D, G, bits, T)
+    q = rng.standard_normal((L, H * rep, D)).astype(np.float16)
+    want_o, want_lse = attend_ref.card_attend(card, rd, q, D ** -0.5)
+    tol_o, tol_lse = bounds(card, rd, q, D ** -0.5)
+    desc = qkv.Desc.make(L, H, T, D, G)
+    card_dev, q_dev = torch.from_numpy(card).to(DEV), torch.from_numpy(q).to(DEV)
+    best, least = qkv.card_attend_workspace(desc, H * rep), least_workspace(L, H, T, rep, D)
+    assert best >= least
+    for size in (best, least, (best + least) // 2):
+        ws = torch.full((size + 256,), 0x7F, dtype=torch.uint8, device=DEV)
+        out = torch.full((L, H * rep, D), float("nan"), device=DEV)
+        lse = torch.full((L, H * rep), float("nan"), device=DEV)
+        qkv.card_attend(card_dev, desc, q_dev, D ** -0.5, out, lse=lse, workspace=ws[:size])
+        torch.cuda.synchronize()
+        assert float(np.abs(out.cpu().numpy() - want_o).max()) <= tol_o
+        assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
+        assert (ws[size:] == 0x7F).all()
+    with pytest.raises(qkv.QkvError):
+        qkv.card_attend(card_dev, desc, q_dev, D ** -0.5, out, lse=lse, workspace=ws[:least - 4])
+
+
+@pytest.mark.parametrize("D,rep,T", [(64, 1, 20000), (128, 3, 14000), (256, 2, 13000), (128, 16, 20000)])
+def test_merge_over_many_tasks(D, rep, T):
+    print("[case] D=%d rep=%d T=%d" % (D, rep, T), flush=True)
+    rng = np.random.default_rng(D + rep)
+    bits = rng.choice(np.array([2, 4, 8, 16], np.uint8), size=T, p=[0.5, 0.3, 0.15, 0.05])
+    rd, card = build_card(1, 1, T, D, 32, bits, T)
+    q = rng.standard_normal((1, rep, D)).astype(np.float16)
+    want_o, want_lse = attend_ref.card_attend(card, rd, q, D ** -0.5)
+    tol_o, tol_lse = bounds(card, rd, q, D ** -0.5)
+    out = torch.empty((1, rep, D), device=DEV)
+    lse = torch.empty((1, rep), device=DEV)
+    qkv.card_attend(torch.from_numpy(card).to(DEV), qkv.Desc.make(1, 1, T, D, 32), torch.from_numpy(q).to(DEV), D ** -0.5, out, lse=lse)
+    torch.cuda.synchronize()
+    assert float(np.abs(out.cpu().numpy() - want_o).max()) <= tol_o
+    assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
