@@ -83,8 +83,10 @@ __device__ inline bool kc_shape(const CardGeom& g) {
 // order[] disagrees with the other two tables - the same entries the tiles meet and skip, each looked at once
 // instead of once per plane.  A kernel of its own in front of the grid cost 1.8 us on an idle GPU and 4.7 us
 // behind another kernel (of 75 us for a handoff of 1K tokens); here the check runs beside the tiles.  Four
-// entries per thread and load, two loads in flight: about 2 us per 2048 tokens.
-__device__ inline void report_status(const uint8_t* card, const CardGeom& g, bool header_ok, bool check, uint32_t* status) {
+// entries per thread and load, two loads in flight: about 2 us per 2048 tokens.  `flags` is LDS the tiles would use (with
+// LDS of its own the workgroups of a compute unit went from five to four).
+__device__ inline void report_status(const uint8_t* card, const CardGeom& g, bool header_ok, bool check, uint32_t* status,
+                                     uint32_t* flags) {
   uint32_t bad = 0;
   if (header_ok && check) {
     const u32x4* order = reinterpret_cast<const u32x4*>(card + g.off_order);       // the section is padded to 256 bytes
@@ -103,8 +105,15 @@ __device__ inline void report_status(const uint8_t* card, const CardGeom& g, boo
       }
     }
   }
-  const int any = __syncthreads_or((int)bad);
-  if (threadIdx.x == 0) *status = (header_ok ? 0u : QKV_STATUS_BAD_HEADER) | (any ? QKV_STATUS_BAD_ORDER : 0u);
+  const bool in_wave = __builtin_amdgcn_ballot_w64(bad != 0u) != 0ull;
+  if ((threadIdx.x & 63u) == 0u) flags[threadIdx.x >> 6] = in_wave ? 1u : 0u;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t any = 0;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) any |= flags[w];
+    *status = (header_ok ? 0u : QKV_STATUS_BAD_HEADER) | (any ? QKV_STATUS_BAD_ORDER : 0u);
+  }
 }
 
 // Address of the output row that row `lane` of the tile starting at segment row r0 goes to;
@@ -167,10 +176,13 @@ __device__ inline void store_tile(uint64_t my_row_addr, uint32_t lane, uint32_t 
 }
 
 // Decodes the tile of class c that starts at segment row r0 (rows at or past n_rows are skipped) and stores
-// it to the row addresses in my_row (lane i: row r0 + i).  ROPE: rotate every row with `rope`.
-template <int W, int G, bool KEEP, bool ROPE>
+// it to the row addresses that row_address() gives (lane i: row r0 + i).  ROPE: rotate every row with `rope`.
+// The addresses take two dependent trips to the tables, so the tile's own loads are issued before them (one layer
+// of 3877 tokens, keys realigned: 10.1 us with the addresses first, 8.4 us; all tiles' rows of 8K tokens injected without
+// realignment: 281 and 269 us).
+template <int W, int G, bool KEEP, bool ROPE, typename ROWS>
 __device__ inline void unpack_tile(const uint8_t* card, const CardGeom& g, int c, uint32_t r0, uint32_t n_rows,
-                                   uint64_t my_row, uint32_t lane, u32x4* lds, const RopeLane& rope) {
+                                   const ROWS& row_address, uint32_t lane, u32x4* lds, const RopeLane& rope) {
   constexpr int GS = G / 32;                     // spans (lanes) per group
   const uint32_t lpr_shift = g.lpr_shift;
   const uint32_t spr_shift = lpr_shift - 2;      // log2(spans per row)
@@ -204,6 +216,7 @@ __device__ inline void unpack_tile(const uint8_t* card, const CardGeom& g, int c
       pair[round] = card_load<KEEP>(meta_seg + gsp / GS);
     }
   }
+  const uint64_t my_row = row_address();
 
   const uint32_t x = (lane >> 1) & 3u;           // swizzle term of this lane's spans
 #pragma unroll
@@ -234,9 +247,9 @@ __device__ inline void unpack_tile(const uint8_t* card, const CardGeom& g, int c
 // "two tokens of one channel" into "two channels of one token" and drops the tile into LDS row by row:
 // each of its 32 stores covers a whole row of the tile across the wave.  The tile then leaves like any
 // other.  Mirror image of the packing kernel's pack_tile_kc.
-template <int W, bool KEEP, bool ROPE>
+template <int W, bool KEEP, bool ROPE, typename ROWS>
 __device__ inline void unpack_tile_kc(const uint8_t* card, const CardGeom& g, int c, uint32_t r0, uint32_t key_rows,
-                                      uint64_t my_row, uint32_t lane, u32x4* lds, const RopeLane& rope) {
+                                      const ROWS& row_address, uint32_t lane, u32x4* lds, const RopeLane& rope) {
   const uint32_t lpr_shift = g.lpr_shift;
   const uint32_t D = g.head_dim;
   const uint32_t cp = lane & ((D >> 1) - 1u);               // channel pair: channels 2 cp, 2 cp + 1
@@ -259,6 +272,7 @@ __device__ inline void unpack_tile_kc(const uint8_t* card, const CardGeom& g, in
     for (int i = 0; i < W; ++i) { cw[0][i] = flat[i]; cw[1][i] = flat[W + i]; }
     pairs = card_load<KEEP>(reinterpret_cast<const u32x2*>(card + g.off_meta[c]) + (grp >> 1));
   }
+  const uint64_t my_row = row_address();
   uint32_t xa[16], xb[16];                                  // x[j] = tokens 2j, 2j+1 of the block, channel 2 cp / 2 cp + 1
   decode_span<W>(cw[0], half_bits_to_float(pairs.x & 0xFFFFu), half_bits_to_float(pairs.x >> 16), xa);
   decode_span<W>(cw[1], half_bits_to_float(pairs.y & 0xFFFFu), half_bits_to_float(pairs.y >> 16), xb);
@@ -282,8 +296,8 @@ __device__ inline void unpack_tile_kc(const uint8_t* card, const CardGeom& g, in
   store_tile(my_row, lane, lpr_shift, data);
 }
 
-template <bool KEEP, bool ROPE>
-__device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_t r0, uint32_t n_rows, uint64_t my_row,
+template <bool KEEP, bool ROPE, typename ROWS>
+__device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_t r0, uint32_t n_rows, const ROWS& row_address,
                                  uint32_t lane, const RopeLane& rope) {
   const uint32_t lpr_shift = g.lpr_shift;
   const uint32_t row_bytes = g.head_dim * 2u;
@@ -296,6 +310,7 @@ __device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_
     data[k] = (u32x4)(0u);
     if (off < seg_left) data[k] = card_load<KEEP>(reinterpret_cast<const u32x4*>(src + off));
   }
+  const uint64_t my_row = row_address();
   if (ROPE) {
 #pragma unroll
     for (int k = 0; k < kTileIters; ++k) {
@@ -329,7 +344,7 @@ __device__ inline void unpack_class(const UnpackArgs& a, const CardGeom& g, uint
   const RopeLane no_rope = {};
   for (uint32_t i = first; i < tiles; i += n_waves) {
     const uint32_t r0 = (tiles - 1 - i) * tile_rows;
-    const uint64_t my_row = tile_row_address(a, g, C, r0, n_rows, lane, tile_rows, bad);
+    const auto my_row = [&] { return tile_row_address(a, g, C, r0, n_rows, lane, tile_rows, bad); };
     if constexpr (C == 3) {
       copy_tile<KEEP, false>(a.card, g, r0, n_rows, my_row, lane, no_rope);
     } else {
@@ -351,7 +366,7 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
   bool shape_ok = header_ok;
   if (KC) shape_ok = header_ok && kc_shape(g);
   if (blockIdx.x < a.check_blocks) {
-    report_status(a.card, g, header_ok, shape_ok, a.status);
+    report_status(a.card, g, header_ok, shape_ok, a.status, reinterpret_cast<uint32_t*>(lds));
     return;
   }
   if (!shape_ok) return;                         // uniform over the grid: every wave leaves
@@ -384,20 +399,20 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
     const RopeLane no_rope = {};
     if (k < tp3) {
       const uint32_t r0 = p * g.n[3] + (tp3 - 1u - k) * tile_rows, end = (p + 1u) * g.n[3];
-      const uint64_t my_row = tile_row_address(a, g, 3, r0, end, lane, tile_rows, bad);
+      const auto my_row = [&] { return tile_row_address(a, g, 3, r0, end, lane, tile_rows, bad); };
       copy_tile<KEEP, false>(a.card, g, r0, end, my_row, lane, no_rope);
     } else if ((k -= tp3) < tp2) {
       const uint32_t r0 = p * g.n[2] + (tp2 - 1u - k) * tile_rows, end = (p + 1u) * g.n[2];
-      const uint64_t my_row = tile_row_address(a, g, 2, r0, end, lane, tile_rows, bad);
+      const auto my_row = [&] { return tile_row_address(a, g, 2, r0, end, lane, tile_rows, bad); };
       unpack_tile<8, G, KEEP, false>(a.card, g, 2, r0, end, my_row, lane, my_lds, no_rope);
     } else if ((k -= tp2) < tp1) {
       const uint32_t r0 = p * g.n[1] + (tp1 - 1u - k) * tile_rows, end = (p + 1u) * g.n[1];
-      const uint64_t my_row = tile_row_address(a, g, 1, r0, end, lane, tile_rows, bad);
+      const auto my_row = [&] { return tile_row_address(a, g, 1, r0, end, lane, tile_rows, bad); };
       unpack_tile<4, G, KEEP, false>(a.card, g, 1, r0, end, my_row, lane, my_lds, no_rope);
     } else {
       k -= tp1;
       const uint32_t r0 = p * g.n[0] + (tp0 - 1u - k) * tile_rows, end = (p + 1u) * g.n[0];
-      const uint64_t my_row = tile_row_address(a, g, 0, r0, end, lane, tile_rows, bad);
+      const auto my_row = [&] { return tile_row_address(a, g, 0, r0, end, lane, tile_rows, bad); };
       unpack_tile<2, G, KEEP, false>(a.card, g, 0, r0, end, my_row, lane, my_lds, no_rope);
     }
     if (bad && a.status && a.check_blocks == 0u) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
@@ -455,7 +470,7 @@ __device__ inline void inject_range(const InjectArgs& a, const CardGeom& g, cons
   const uint32_t first = (gw + n_waves - cum) % n_waves;
   for (uint32_t i = first; i < tiles; i += n_waves) {
     const uint32_t r0 = seg_lo + (tiles - 1 - i) * tile_rows;
-    const uint64_t my_row = inject_row_address(a, g, C, (uint32_t)KV, r0, seg_hi, lane, tile_rows, bad);
+    const auto my_row = [&] { return inject_row_address(a, g, C, (uint32_t)KV, r0, seg_hi, lane, tile_rows, bad); };
     if (C == 3) {
       copy_tile<KEEP, rot>(a.card, g, r0, seg_hi, my_row, lane, rope);
     } else {
@@ -468,7 +483,7 @@ __device__ inline void inject_range(const InjectArgs& a, const CardGeom& g, cons
 }
 
 template <int G, bool KEEP, bool ROPE, bool KC>
-__global__ __launch_bounds__(kBlockThreads) void inject_kernel(InjectArgs a) {
+__global__ __launch_bounds__(kBlockThreads, ROPE && !KC ? 4 : 1) void inject_kernel(InjectArgs a) {
   __shared__ u32x4 lds[kWavesPerBlock][kTileChunks];
   CardGeom g;
   const bool header_ok = card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, g,
@@ -476,7 +491,7 @@ __global__ __launch_bounds__(kBlockThreads) void inject_kernel(InjectArgs a) {
   bool shape_ok = header_ok;
   if (KC) shape_ok = header_ok && kc_shape(g);
   if (blockIdx.x < a.check_blocks) {
-    report_status(a.card, g, header_ok, shape_ok, a.status);
+    report_status(a.card, g, header_ok, shape_ok, a.status, reinterpret_cast<uint32_t*>(lds));
     return;
   }
   if (!shape_ok) return;
