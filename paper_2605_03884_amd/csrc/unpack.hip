@@ -34,19 +34,25 @@ struct UnpackArgs {
 // Injection into per-layer caches: the same tiles, but only the planes of a layer range,
 // rows addressed through per-layer base pointers and strides, and - optionally - every key
 // row rotated to a shifted position on its way out (rotary embedding, half-split pairing).
+// The pointer and rotation tables travel as kernel arguments, and a launch costs about 1 us per KiB of them on the
+// host: a call for up to kFewLayers layers, as a receiver makes that fills its caches layer by layer, takes a
+// struct of 0.7 KiB (0.2 without rotation) instead of 2.2 (1.2).
+constexpr uint32_t kFewLayers = 4, kFewPairs = 64;
+template <bool ROPE, bool FEW>
 struct InjectArgs {
+  static constexpr uint32_t kLayers = FEW ? kFewLayers : (uint32_t)QKV_INJECT_MAX_LAYERS;
+  static constexpr uint32_t kRotations = !ROPE ? 1u : FEW ? kFewPairs : 128u;
   const uint8_t* card;
   uint64_t card_bytes;
   uint32_t layers, kv_heads, head_dim, group_size;
   uint64_t tokens;
   uint32_t layer_begin, layer_count;
   uint64_t head_stride, token_stride;                // bytes
-  uint32_t rope;                                     // 1: rotate the keys with cs[]
   uint32_t* status;                                  // may be null
   uint32_t check_blocks;                             // as in UnpackArgs
-  uint64_t k_layer[QKV_INJECT_MAX_LAYERS];           // where token 0 of head 0 of layer layer_begin + i goes
-  uint64_t v_layer[QKV_INJECT_MAX_LAYERS];
-  float cs[128][2];                                  // (cos, sin) of the shift for pair index i < head_dim / 2
+  uint64_t k_layer[kLayers];                         // where token 0 of head 0 of layer layer_begin + i goes
+  uint64_t v_layer[kLayers];
+  float cs[kRotations][2];                           // (cos, sin) of the shift for pair index i < head_dim / 2
 };
 
 // What a lane needs to rotate its 16-byte chunk of a key row: the (cos, sin) of its 8 elements,
@@ -431,7 +437,8 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
 
 // Row address for injection: plane p of the card -> (K or V, layer, head) -> the caller's
 // per-layer tensor.  Only planes of the layer range are ever asked for.
-__device__ inline uint64_t inject_row_address(const InjectArgs& a, const CardGeom& g, int c, uint32_t kv, uint32_t r0,
+template <typename ARGS>
+__device__ inline uint64_t inject_row_address(const ARGS& a, const CardGeom& g, int c, uint32_t kv, uint32_t r0,
                                               uint32_t seg_hi, uint32_t lane, uint32_t tile_rows, uint32_t& bad) {
   uint64_t addr = 0;
   const uint32_t r = r0 + lane;
@@ -456,8 +463,8 @@ __device__ inline uint64_t inject_row_address(const InjectArgs& a, const CardGeo
 // One (class, K or V) range of the card's rows for the layer range: its tiles are dealt to the
 // waves round-robin, continuing where the previous range stopped.  (K and V as separate
 // instances of this code measure faster than one instance looping over both.)
-template <int C, int KV, int G, bool KEEP, bool ROPE, bool KC>
-__device__ inline void inject_range(const InjectArgs& a, const CardGeom& g, const RopeLane& rope, uint32_t gw,
+template <int C, int KV, int G, bool KEEP, bool ROPE, bool KC, typename ARGS>
+__device__ inline void inject_range(const ARGS& a, const CardGeom& g, const RopeLane& rope, uint32_t gw,
                                     uint32_t n_waves, uint32_t lane, u32x4* lds, uint32_t& cum, uint32_t& bad) {
   const uint32_t n = g.n[C];
   if (n == 0) return;
@@ -482,8 +489,8 @@ __device__ inline void inject_range(const InjectArgs& a, const CardGeom& g, cons
   cum = (cum + tiles) % n_waves;
 }
 
-template <int G, bool KEEP, bool ROPE, bool KC>
-__global__ __launch_bounds__(kBlockThreads, ROPE && !KC ? 4 : 1) void inject_kernel(InjectArgs a) {
+template <int G, bool KEEP, bool ROPE, bool KC, bool FEW>
+__global__ __launch_bounds__(kBlockThreads, ROPE && !KC ? 4 : 1) void inject_kernel(InjectArgs<ROPE, FEW> a) {
   __shared__ u32x4 lds[kWavesPerBlock][kTileChunks];
   CardGeom g;
   const bool header_ok = card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, g,
@@ -575,32 +582,71 @@ hipError_t launch_unpack(const uint8_t* card, uint64_t card_bytes, const CardGeo
   return hipGetLastError();
 }
 
+namespace {
+
+struct InjectCall {
+  const uint8_t* card;
+  uint64_t card_bytes;
+  uint32_t layer_begin, layer_count;
+  void* const* k_layers;
+  void* const* v_layers;
+  uint64_t head_stride, token_stride;
+  const float (*cos_sin)[2];
+  uint32_t* status;
+  uint32_t check_blocks;
+};
+
+template <int G, bool KEEP, bool ROPE, bool KC, bool FEW>
+void launch_inject_kernel(const CardGeom& expect, const InjectCall& call, const dim3& grid, hipStream_t stream) {
+  InjectArgs<ROPE, FEW> a;
+  a.card = call.card;
+  a.card_bytes = call.card_bytes;
+  a.layers = expect.layers; a.kv_heads = expect.kv_heads; a.head_dim = expect.head_dim; a.group_size = expect.group_size;
+  a.tokens = expect.tokens;
+  a.layer_begin = call.layer_begin;
+  a.layer_count = call.layer_count;
+  a.head_stride = call.head_stride;
+  a.token_stride = call.token_stride;
+  a.status = call.status;
+  a.check_blocks = call.check_blocks;
+  for (uint32_t i = 0; i < a.kLayers; ++i) {
+    a.k_layer[i] = i < call.layer_count ? reinterpret_cast<uint64_t>(call.k_layers[i]) : 0;
+    a.v_layer[i] = i < call.layer_count ? reinterpret_cast<uint64_t>(call.v_layers[i]) : 0;
+  }
+  for (uint32_t i = 0; i < a.kRotations; ++i) {
+    const bool used = ROPE && i < expect.head_dim / 2;
+    a.cs[i][0] = used ? call.cos_sin[i][0] : 1.0f;
+    a.cs[i][1] = used ? call.cos_sin[i][1] : 0.0f;
+  }
+  hipLaunchKernelGGL((inject_kernel<G, KEEP, ROPE, KC, FEW>), grid, dim3(kBlockThreads), 0, stream, a);
+}
+
+template <int G, bool KC>
+void launch_inject_group(const CardGeom& expect, const InjectCall& call, const dim3& grid, hipStream_t stream) {
+  const bool keep = call.card_bytes <= kCacheResidentCardBytes;
+  const bool few = call.layer_count <= kFewLayers && expect.head_dim <= 2u * kFewPairs;
+  switch ((keep ? 4 : 0) + (call.cos_sin ? 2 : 0) + (few ? 1 : 0)) {
+    case 7: launch_inject_kernel<G, true, true, KC, true>(expect, call, grid, stream); break;
+    case 6: launch_inject_kernel<G, true, true, KC, false>(expect, call, grid, stream); break;
+    case 5: launch_inject_kernel<G, true, false, KC, true>(expect, call, grid, stream); break;
+    case 4: launch_inject_kernel<G, true, false, KC, false>(expect, call, grid, stream); break;
+    case 3: launch_inject_kernel<G, false, true, KC, true>(expect, call, grid, stream); break;
+    case 2: launch_inject_kernel<G, false, true, KC, false>(expect, call, grid, stream); break;
+    case 1: launch_inject_kernel<G, false, false, KC, true>(expect, call, grid, stream); break;
+    default: launch_inject_kernel<G, false, false, KC, false>(expect, call, grid, stream); break;
+  }
+}
+
+}  // namespace
+
 hipError_t launch_inject(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, uint32_t layer_begin,
                          uint32_t layer_count, void* const* k_layers, void* const* v_layers, uint64_t head_stride_bytes,
                          uint64_t token_stride_bytes, const float (*cos_sin)[2], bool keys_per_channel, uint32_t* status,
                          hipStream_t stream) {
-  InjectArgs a;
-  a.card = card;
-  a.card_bytes = card_bytes;
-  a.layers = expect.layers; a.kv_heads = expect.kv_heads; a.head_dim = expect.head_dim; a.group_size = expect.group_size;
-  a.tokens = expect.tokens;
-  a.layer_begin = layer_begin;
-  a.layer_count = layer_count;
-  a.head_stride = head_stride_bytes;
-  a.token_stride = token_stride_bytes;
-  a.rope = cos_sin != nullptr;
-  a.status = status;
-  for (uint32_t i = 0; i < QKV_INJECT_MAX_LAYERS; ++i) {
-    a.k_layer[i] = i < layer_count ? reinterpret_cast<uint64_t>(k_layers[i]) : 0;
-    a.v_layer[i] = i < layer_count ? reinterpret_cast<uint64_t>(v_layers[i]) : 0;
-  }
-  for (uint32_t i = 0; i < 128; ++i) {
-    const bool used = cos_sin != nullptr && i < expect.head_dim / 2;
-    a.cs[i][0] = used ? cos_sin[i][0] : 1.0f;
-    a.cs[i][1] = used ? cos_sin[i][1] : 0.0f;
-  }
-  a.check_blocks = status && grid_reports(2ull * layer_count * expect.kv_heads, expect.head_dim, expect.tokens) ? 1u : 0u;
-  if (status && a.check_blocks == 0u) {
+  InjectCall call = {card, card_bytes, layer_begin, layer_count, k_layers, v_layers, head_stride_bytes, token_stride_bytes, cos_sin,
+                     status, 0u};
+  call.check_blocks = status && grid_reports(2ull * layer_count * expect.kv_heads, expect.head_dim, expect.tokens) ? 1u : 0u;
+  if (status && call.check_blocks == 0u) {
     UnpackArgs u;
     u.card = card; u.card_bytes = card_bytes; u.flags = keys_per_channel ? QKV_FLAG_KEYS_PER_CHANNEL : 0u;
     u.layers = expect.layers; u.kv_heads = expect.kv_heads; u.head_dim = expect.head_dim; u.group_size = expect.group_size;
@@ -614,32 +660,11 @@ hipError_t launch_inject(const uint8_t* card, uint64_t card_bytes, const CardGeo
   const uint32_t tile_rows = kTileChunks >> expect.lpr_shift;
   const uint64_t rows = 2ull * layer_count * expect.kv_heads * expect.tokens;
   const uint64_t tiles = (rows + tile_rows - 1) / tile_rows + 8;
-  const dim3 grid(grid_blocks(tiles) + a.check_blocks), block(kBlockThreads);
-  const bool keep = card_bytes <= kCacheResidentCardBytes;
-  if (keys_per_channel) {                        // group size 32 only (checked by the caller)
-    switch ((keep ? 2 : 0) + (a.rope ? 1 : 0)) {
-      case 3: hipLaunchKernelGGL((inject_kernel<32, true, true, true>), grid, block, 0, stream, a); break;
-      case 2: hipLaunchKernelGGL((inject_kernel<32, true, false, true>), grid, block, 0, stream, a); break;
-      case 1: hipLaunchKernelGGL((inject_kernel<32, false, true, true>), grid, block, 0, stream, a); break;
-      default: hipLaunchKernelGGL((inject_kernel<32, false, false, true>), grid, block, 0, stream, a); break;
-    }
-    return hipGetLastError();
-  }
-  const int variant = (int)expect.group_size * 4 + (keep ? 2 : 0) + (a.rope ? 1 : 0);
-  switch (variant) {
-    case 131: hipLaunchKernelGGL((inject_kernel<32, true, true, false>), grid, block, 0, stream, a); break;
-    case 130: hipLaunchKernelGGL((inject_kernel<32, true, false, false>), grid, block, 0, stream, a); break;
-    case 129: hipLaunchKernelGGL((inject_kernel<32, false, true, false>), grid, block, 0, stream, a); break;
-    case 128: hipLaunchKernelGGL((inject_kernel<32, false, false, false>), grid, block, 0, stream, a); break;
-    case 259: hipLaunchKernelGGL((inject_kernel<64, true, true, false>), grid, block, 0, stream, a); break;
-    case 258: hipLaunchKernelGGL((inject_kernel<64, true, false, false>), grid, block, 0, stream, a); break;
-    case 257: hipLaunchKernelGGL((inject_kernel<64, false, true, false>), grid, block, 0, stream, a); break;
-    case 256: hipLaunchKernelGGL((inject_kernel<64, false, false, false>), grid, block, 0, stream, a); break;
-    case 515: hipLaunchKernelGGL((inject_kernel<128, true, true, false>), grid, block, 0, stream, a); break;
-    case 514: hipLaunchKernelGGL((inject_kernel<128, true, false, false>), grid, block, 0, stream, a); break;
-    case 513: hipLaunchKernelGGL((inject_kernel<128, false, true, false>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((inject_kernel<128, false, false, false>), grid, block, 0, stream, a); break;
-  }
+  const dim3 grid(grid_blocks(tiles) + call.check_blocks);
+  if (keys_per_channel) launch_inject_group<32, true>(expect, call, grid, stream);        // group size 32 only (checked by the caller)
+  else if (expect.group_size == 32u) launch_inject_group<32, false>(expect, call, grid, stream);
+  else if (expect.group_size == 64u) launch_inject_group<64, false>(expect, call, grid, stream);
+  else launch_inject_group<128, false>(expect, call, grid, stream);
   return hipGetLastError();
 }
 
