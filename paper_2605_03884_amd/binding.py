@@ -151,15 +151,19 @@ def _check(rc, where):
         raise QkvError(rc, where)
 
 
+_Counts = ctypes.c_int64 * 4
+
+
 def _counts(counts):
-    arr = (ctypes.c_int64 * 4)(*[int(c) for c in counts])
-    return arr
+    return _Counts(*map(int, counts))
 
 
 def _stream(stream):
+    """The stream's handle.  Without one: the current stream of the current device, asked for without building the object
+    torch.cuda.current_stream() returns (2.9 us of a call's 8)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _dev_ptr(t, dtype=None, name="tensor"):
@@ -169,7 +173,11 @@ def _dev_ptr(t, dtype=None, name="tensor"):
         raise ValueError("%s must be contiguous" % name)
     if dtype is not None and t.dtype != dtype:
         raise ValueError("%s must be %s" % (name, dtype))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _optional_ptr(t, dtype=None, name="tensor"):
+    return None if t is None else _dev_ptr(t, dtype, name)
 
 
 def version():
@@ -187,7 +195,7 @@ def card_bytes(desc, counts):
 
 
 def budget_counts(tokens, avg_bits_budget):
-    out = (ctypes.c_int64 * 4)()
+    out = _Counts()
     _check(lib().qkv_budget_counts(int(tokens), float(avg_bits_budget), out), "qkv_budget_counts")
     return list(out)
 
@@ -197,7 +205,7 @@ def assign_bits(scores, avg_bits_budget, bits=None, stream=None):
     T = scores.numel()
     if bits is None:
         bits = torch.empty(T, dtype=torch.uint8, device=scores.device)
-    out = (ctypes.c_int64 * 4)()
+    out = _Counts()
     _check(lib().qkv_assign_bits(_dev_ptr(scores, torch.float32, "scores"), T, float(avg_bits_budget),
                                  _dev_ptr(bits, torch.uint8, "bits"), out, _stream(stream)), "qkv_assign_bits")
     return bits, list(out)
@@ -206,8 +214,8 @@ def assign_bits(scores, avg_bits_budget, bits=None, stream=None):
 def assign_plan(desc, scores, avg_bits_budget, card, bits=None, stream=None):
     """scores: device float32[T]; card: device uint8 buffer (header, tables and pads are written); bits: device
     uint8[T] or None.  Returns the class counts (list)."""
-    out = (ctypes.c_int64 * 4)()
-    bp = ctypes.c_void_p(0) if bits is None else _dev_ptr(bits, torch.uint8, "bits")
+    out = _Counts()
+    bp = _optional_ptr(bits, torch.uint8, "bits")
     _check(lib().qkv_assign_plan(ctypes.byref(desc), _dev_ptr(scores, torch.float32, "scores"), float(avg_bits_budget), bp,
                                  out, _dev_ptr(card, torch.uint8, "card"), card.numel(), _stream(stream)),
            "qkv_assign_plan")
@@ -216,8 +224,8 @@ def assign_plan(desc, scores, avg_bits_budget, card, bits=None, stream=None):
 
 def assign_quantize_pack(desc, k, v, scores, avg_bits_budget, card, bits=None, stream=None):
     """Scores, budget and K/V in; widths (if bits is given) and the whole card out.  Returns the class counts."""
-    out = (ctypes.c_int64 * 4)()
-    bp = ctypes.c_void_p(0) if bits is None else _dev_ptr(bits, torch.uint8, "bits")
+    out = _Counts()
+    bp = _optional_ptr(bits, torch.uint8, "bits")
     _check(lib().qkv_assign_quantize_pack(ctypes.byref(desc), _dev_ptr(k, torch.float16, "k"), _dev_ptr(v, torch.float16, "v"),
                                           _dev_ptr(scores, torch.float32, "scores"), float(avg_bits_budget), bp, out,
                                           _dev_ptr(card, torch.uint8, "card"), card.numel(), _stream(stream)),
@@ -252,7 +260,7 @@ def assign_bits_greedy(scores, avg_bits_budget, bits=None, counts=None, stream=N
 
 
 def count_bits(bits, stream=None):
-    out = (ctypes.c_int64 * 4)()
+    out = _Counts()
     _check(lib().qkv_count_bits(_dev_ptr(bits, torch.uint8, "bits"), bits.numel(), out, _stream(stream)),
            "qkv_count_bits")
     return list(out)
@@ -279,7 +287,7 @@ def quantize_pack_kc(desc, k, v, bits, counts, card, stream=None):
 def requantize(card_in, desc, bits, counts, card_out, status=None, card_in_nbytes=None, stream=None):
     """The card that quantize_pack would build from unpack_dequant(card_in), at the new widths, card to card."""
     n = card_in.numel() if card_in_nbytes is None else int(card_in_nbytes)
-    sp = ctypes.c_void_p(0) if status is None else _dev_ptr(status, None, "status")
+    sp = _optional_ptr(status, None, "status")
     _check(lib().qkv_requantize(_dev_ptr(card_in, torch.uint8, "card_in"), n, ctypes.byref(desc),
                                 _dev_ptr(bits, torch.uint8, "bits"), _counts(counts),
                                 _dev_ptr(card_out, torch.uint8, "card_out"), card_out.numel(), sp, _stream(stream)),
@@ -305,7 +313,7 @@ def card_fill(desc, k, v, counts, card, stream=None):
 def unpack_dequant(card, expect, k_out, v_out, status=None, card_nbytes=None, stream=None):
     """card: device uint8; k_out, v_out: device float16 [L, H, T, D]; status: device int32[1] or None."""
     n = card.numel() if card_nbytes is None else int(card_nbytes)
-    sp = ctypes.c_void_p(0) if status is None else _dev_ptr(status, None, "status")
+    sp = _optional_ptr(status, None, "status")
     _check(lib().qkv_unpack_dequant(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect),
                                     _dev_ptr(k_out, torch.float16, "k_out"), _dev_ptr(v_out, torch.float16, "v_out"),
                                     sp, _stream(stream)), "qkv_unpack_dequant")
@@ -315,7 +323,7 @@ def unpack_dequant(card, expect, k_out, v_out, status=None, card_nbytes=None, st
 def unpack_dequant_kc(card, expect, k_out, v_out, status=None, card_nbytes=None, stream=None):
     """unpack_dequant for a uniform card with the keys grouped per channel."""
     n = card.numel() if card_nbytes is None else int(card_nbytes)
-    sp = ctypes.c_void_p(0) if status is None else _dev_ptr(status, None, "status")
+    sp = _optional_ptr(status, None, "status")
     _check(lib().qkv_unpack_dequant_kc(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect),
                                        _dev_ptr(k_out, torch.float16, "k_out"), _dev_ptr(v_out, torch.float16, "v_out"),
                                        sp, _stream(stream)), "qkv_unpack_dequant_kc")
@@ -334,18 +342,22 @@ def inject_layers(card, expect, k_layers, v_layers, layer_begin=0, rope_base=0.0
     if count != len(v_layers) or count < 1:
         raise ValueError("k_layers and v_layers must be lists of the same, non-zero length")
     ref_strides = k_layers[0].stride()
-    for t in list(k_layers) + list(v_layers):
-        if not t.is_cuda or t.dtype != torch.float16 or t.dim() != 3:
-            raise ValueError("layer tensors must be device float16 [kv_heads, tokens, head_dim]")
-        if t.shape[0] != expect.kv_heads or t.shape[1] < expect.tokens or t.shape[2] != expect.head_dim:
-            raise ValueError("layer tensor shape %s does not hold the card's tokens" % (tuple(t.shape),))
-        if t.stride() != ref_strides or t.stride(2) != 1:
-            raise ValueError("layer tensors must share their strides and have contiguous rows")
-    kp = (ctypes.c_void_p * count)(*[t.data_ptr() for t in k_layers])
-    vp_ = (ctypes.c_void_p * count)(*[t.data_ptr() for t in v_layers])
-    where = Inject(int(layer_begin), count, kp, vp_, ref_strides[0], ref_strides[1], float(rope_base), int(rope_delta),
-                   1 if keys_per_channel else 0, 0)
-    sp = ctypes.c_void_p(0) if status is None else _dev_ptr(status, None, "status")
+    heads, tokens, dim = expect.kv_heads, expect.tokens, expect.head_dim
+    pointers = []
+    for tensors in (k_layers, v_layers):
+        for t in tensors:
+            shape = t.shape
+            if not t.is_cuda or t.dtype != torch.float16 or len(shape) != 3:
+                raise ValueError("layer tensors must be device float16 [kv_heads, tokens, head_dim]")
+            if shape[0] != heads or shape[1] < tokens or shape[2] != dim:
+                raise ValueError("layer tensor shape %s does not hold the card's tokens" % (tuple(shape),))
+            if t.stride() != ref_strides or ref_strides[2] != 1:
+                raise ValueError("layer tensors must share their strides and have contiguous rows")
+            pointers.append(t.data_ptr())
+    table = ctypes.c_void_p * count
+    where = Inject(int(layer_begin), count, table(*pointers[:count]), table(*pointers[count:]),
+                   ref_strides[0], ref_strides[1], float(rope_base), int(rope_delta), 1 if keys_per_channel else 0, 0)
+    sp = _optional_ptr(status, None, "status")
     _check(lib().qkv_inject_layers(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect), ctypes.byref(where),
                                    sp, _stream(stream)), "qkv_inject_layers")
 
@@ -364,8 +376,8 @@ def card_attend(card, expect, q, softmax_scale, out, lse=None, workspace=None, s
     q_heads = q.shape[1]
     if workspace is None:
         workspace = torch.empty(card_attend_workspace(expect, q_heads), dtype=torch.uint8, device=card.device)
-    lp = ctypes.c_void_p(0) if lse is None else _dev_ptr(lse, torch.float32, "lse")
-    sp = ctypes.c_void_p(0) if status is None else _dev_ptr(status, None, "status")
+    lp = _optional_ptr(lse, torch.float32, "lse")
+    sp = _optional_ptr(status, None, "status")
     _check(lib().qkv_card_attend(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect),
                                  _dev_ptr(q, torch.float16, "q"), int(q_heads), float(softmax_scale),
                                  _dev_ptr(out, torch.float32, "out"), lp, _dev_ptr(workspace, torch.uint8, "workspace"),
@@ -380,8 +392,8 @@ def card_attend_kc(card, expect, q, softmax_scale, out, lse=None, workspace=None
     q_heads = q.shape[1]
     if workspace is None:
         workspace = torch.empty(card_attend_workspace(expect, q_heads), dtype=torch.uint8, device=card.device)
-    lp = ctypes.c_void_p(0) if lse is None else _dev_ptr(lse, torch.float32, "lse")
-    sp = ctypes.c_void_p(0) if status is None else _dev_ptr(status, None, "status")
+    lp = _optional_ptr(lse, torch.float32, "lse")
+    sp = _optional_ptr(status, None, "status")
     _check(lib().qkv_card_attend_kc(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect),
                                     _dev_ptr(q, torch.float16, "q"), int(q_heads), float(softmax_scale),
                                     _dev_ptr(out, torch.float32, "out"), lp, _dev_ptr(workspace, torch.uint8, "workspace"),
@@ -392,8 +404,8 @@ def card_attend_kc(card, expect, q, softmax_scale, out, lse=None, workspace=None
 def card_attend_static(card, expect, q, softmax_scale, out, lse=None, status=None, card_nbytes=None, stream=None):
     """card_attend without a workspace: the partials live in the library's fixed scratch array (no allocation)."""
     n = card.numel() if card_nbytes is None else int(card_nbytes)
-    lp = ctypes.c_void_p(0) if lse is None else _dev_ptr(lse, torch.float32, "lse")
-    sp = ctypes.c_void_p(0) if status is None else _dev_ptr(status, None, "status")
+    lp = _optional_ptr(lse, torch.float32, "lse")
+    sp = _optional_ptr(status, None, "status")
     _check(lib().qkv_card_attend_static(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect),
                                         _dev_ptr(q, torch.float16, "q"), int(q.shape[1]), float(softmax_scale),
                                         _dev_ptr(out, torch.float32, "out"), lp, sp, _stream(stream)), "qkv_card_attend_static")
@@ -413,7 +425,7 @@ def card_peek(card, card_nbytes=None, stream=None):
     """Returns (Desc, counts, avg_bits, status).  Synchronises the stream."""
     n = card.numel() if card_nbytes is None else int(card_nbytes)
     d = Desc()
-    counts = (ctypes.c_int64 * 4)()
+    counts = _Counts()
     avg = ctypes.c_float(0)
     st = ctypes.c_uint32(0)
     _check(lib().qkv_card_peek(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(d), counts, ctypes.byref(avg),
