@@ -16,10 +16,12 @@
 // over the 32-bit gain keys, with histograms weighted by cost, finds the key at which the
 // budget runs out and what is left of the budget there; the upgrades with exactly that key
 // are then admitted level by level, by increasing token index, until one does not fit.
-#include "qkv_common.h"
+#include "qkv_select.h"
 
 namespace qkv {
 namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFeatures = 6, kHidden = 64;
 
@@ -42,168 +44,425 @@ __global__ __launch_bounds__(256) void controller_kernel(const float* __restrict
   scores[t] = s;
 }
 
-// ---------------------------------------------------------------------------------------------
+// ---- the greedy allocator -----------------------------------------------------------------------
+//
+// Up to 32768 tokens one workgroup does it in one launch, thread i owning KPT consecutive tokens whose scores stay in
+// registers (KPT = 2, 8, 16, 32: a short sequence runs short code).  Three passes over the keys: 12, 10 and 10 bits; every
+// thread holds its buckets' sums and a workgroup-wide prefix finds the bucket, and the last pass counts the levels
+// apart, so that the sweep that ranks equal keys by token is only made when a level is admitted in part.  Bound by
+// instruction issue and barriers on one compute unit: 8192 tokens took 15.5 us with four passes of 8 bits, one wave
+// searching each histogram, and an unconditional ranking sweep; 12.0 now (16384 tokens 33 and
+// 19 us, 32768 50 and 35, by events).
 
-constexpr int kThreads = 1024;
-constexpr int kWaves = kThreads / kWaveSize;
-constexpr int kCopies = 32;
+constexpr int kThreads = kSelectThreads;
+constexpr uint32_t kTop = 4096, kSub = 1024;             // buckets of the first pass, and of the two later ones
+constexpr uint32_t kLongFrom = 32768;                    // tokens beyond which several workgroups share the work
+
+__device__ constexpr float kPerBit[3] = {(float)(2.0 / 15.0), (float)(4.0 / 255.0), (float)(32.0 / 65535.0)};
 
 // Key of an upgrade: grows as the gain per bit falls.  The gain is +0 or positive, so its bit
 // pattern orders like its value.
-__device__ inline uint32_t gain_key(float score, float per_bit) {
+__device__ inline uint32_t gain_key(float score, int level) {
   const float s = score > 0.0f ? score : 0.0f;     // negative and NaN scores count as 0
-  return ~__float_as_uint(s * per_bit);
+  return ~__float_as_uint(s * kPerBit[level]);
 }
 
-// KPT > 0: each thread keeps the scores of its KPT consecutive tokens in registers (needs T <= KPT * kThreads);
-// KPT == 0: any T, scores re-read on every sweep.
-template <int KPT>
-__global__ __launch_bounds__(kThreads) void greedy_kernel(const float* __restrict__ scores, uint32_t T,
-                                                          uint32_t spare, uint8_t* __restrict__ bits,
-                                                          unsigned long long* __restrict__ counts4) {
-  __shared__ uint32_t wide[256 * kCopies];   // first pass: bucket d, copy c at [d * 32 + c]
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t sel_prefix, sel_left;
-  __shared__ uint32_t wave_tot[3][kWaves];
-  __shared__ uint32_t class_tot[4];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t lane = tid & 63u, wave = tid >> 6;
-  const float per_bit[3] = {(float)(2.0 / 15.0), (float)(4.0 / 255.0), (float)(32.0 / 65535.0)};
+// How many of the upgrades with exactly the last key are admitted: level by level until one does not fit; nothing
+// after it is taken.  left: units (of 2 bits) still free; the levels cost 1, 2, 4.
+__device__ inline void split_last_key(uint32_t left, const uint32_t (&n)[3], uint32_t (&quota)[3], bool& tied) {
+  quota[0] = min(n[0], left);
+  bool full = quota[0] == n[0];
+  left -= quota[0];
+  quota[1] = full ? min(n[1], left / 2u) : 0u;
+  full = full && quota[1] == n[1];
+  left -= 2u * quota[1];
+  quota[2] = full ? min(n[2], left / 4u) : 0u;
+  tied = false;
+#pragma unroll
+  for (int l = 0; l < 3; ++l) tied = tied || (quota[l] != 0u && quota[l] != n[l]);
+}
 
-  const uint32_t per = KPT > 0 ? (uint32_t)KPT : (T + kThreads - 1) / kThreads;   // thread tid owns the tokens [t0, t1)
-  const uint32_t t0 = min(tid * per, T);
-  const uint32_t t1 = min(t0 + per, T);
-  float mine[KPT > 0 ? KPT : 1];
-  if (KPT > 0) {
+// Class of a token, and its share of the equal keys seen so far (run).
+__device__ inline uint32_t greedy_class(float score, uint32_t kstar, const uint32_t (&quota)[3], bool tied, uint32_t (&run)[3]) {
+  bool taken[3];
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) mine[i] = (t0 + i < t1) ? scores[t0 + i] : 0.0f;
+  for (int l = 0; l < 3; ++l) {
+    const uint32_t key = gain_key(score, l);
+    const bool is_eq = key == kstar;
+    taken[l] = key < kstar || (is_eq && (tied ? run[l] < quota[l] : quota[l] != 0u));
+    run[l] += is_eq;
   }
-  // visits every owned token's score
-  auto for_each_score = [&](auto&& f) {
-    if (KPT > 0) {
+  return taken[0] ? (taken[1] ? (taken[2] ? 3u : 2u) : 1u) : 0u;
+}
+
+template <int KPT>
+__global__ __launch_bounds__(kThreads) void greedy_kernel(const float* __restrict__ scores, uint32_t T, uint32_t spare,
+                                                          uint8_t* __restrict__ bits, unsigned long long* __restrict__ counts4,
+                                                          bool aligned) {
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kTop * 2u];   // first pass: bucket d, copy c at [2 d + c]
+  __shared__ uint32_t tot[3][kSelectWaves];
+  __shared__ uint32_t sel_digit, sel_left, sel_same[3];
+  __shared__ uint32_t class_tot[4];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t t0 = min(tid * (uint32_t)KPT, T), n_own = min(t0 + (uint32_t)KPT, T) - t0;
+  float mine[KPT];
+  if (KPT % 4 == 0 && aligned && n_own == (uint32_t)KPT) {
 #pragma unroll
-      for (int i = 0; i < KPT; ++i) if (t0 + i < t1) f(mine[i], t0 + i);
-    } else {
-      for (uint32_t t = t0; t < t1; ++t) f(scores[t], t);
+    for (int i = 0; i < KPT; i += 4) {
+      const float4 f = *reinterpret_cast<const float4*>(scores + t0 + i);
+      mine[i] = f.x; mine[i + 1] = f.y; mine[i + 2] = f.z; mine[i + 3] = f.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) mine[i] = (uint32_t)i < n_own ? scores[t0 + i] : 0.0f;
+  }
+  // f(key, level) for every upgrade of the owned tokens
+  const auto for_each_key = [&](auto&& f) {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      if ((uint32_t)i >= n_own) continue;
+#pragma unroll
+      for (int l = 0; l < 3; ++l) f(gain_key(mine[i], l), l);
     }
   };
+  if (tid < 4u) class_tot[tid] = 0;
   // `spare` counts units of 2 bits; the upgrades weigh 1, 2, 4.  If all 7T fit, nothing is selected.
   const bool everything = spare >= 7u * T;
-
-  uint32_t kstar = 0, left = 0;
+  uint32_t kstar = 0, quota[3] = {0, 0, 0}, run[3] = {0, 0, 0};
+  bool tied = false;
   if (!everything) {
-    // ---- pass 0: weighted histogram of the top key byte over all upgrades
-    for (uint32_t i = tid; i < 256 * kCopies; i += kThreads) wide[i] = 0;
-    if (tid < 4) class_tot[tid] = 0;
+    for (uint32_t i = tid; i < kTop / 2u; i += kThreads) reinterpret_cast<u32x4*>(hist)[i] = (u32x4)(0u);
     __syncthreads();
-    for_each_score([&](float s, uint32_t) {
+    for_each_key([&](uint32_t key, int l) { atomicAdd(&hist[(key >> 20) * 2u + (lane & 1u)], 1u << l); });
+    __syncthreads();
+    uint32_t c[4];
+    {
+      const u32x4 h0 = reinterpret_cast<const u32x4*>(hist)[2u * tid], h1 = reinterpret_cast<const u32x4*>(hist)[2u * tid + 1u];
+      c[0] = h0.x + h0.y; c[1] = h0.z + h0.w; c[2] = h1.x + h1.y; c[3] = h1.z + h1.w;
+    }
+    uint32_t own[1] = {c[0] + c[1] + c[2] + c[3]}, inc[1], all[1];
+    block_scan<1>(own, inc, all, tot, lane, wave);             // every bucket has been read behind its barrier
 #pragma unroll
-      for (int l = 0; l < 3; ++l) atomicAdd(&wide[(gain_key(s, per_bit[l]) >> 24) * kCopies + (lane & 31u)], 1u << l);
-    });
-    __syncthreads();
-    if (tid < 256) {
-      uint32_t sum = 0;
-#pragma unroll 8
-      for (int i = 0; i < kCopies; ++i) sum += wide[tid * kCopies + ((i + tid) & 31u)];
-      hist[tid] = sum;
+    for (uint32_t i = 0; i < 4u; ++i) hist[i * kSub + tid] = 0u;
+    if (inc[0] > spare && inc[0] - own[0] <= spare) {           // exactly one thread: the total, 7T, exceeds spare
+      uint32_t left = spare - (inc[0] - own[0]), d = 0;
+      if (left >= c[0]) { left -= c[0]; d = 1; if (left >= c[1]) { left -= c[1]; d = 2; if (left >= c[2]) { left -= c[2]; d = 3; } } }
+      sel_digit = 4u * tid + d;
+      sel_left = left;
     }
     __syncthreads();
-    if (wave == 0) {      // the histogram's total, 7T, exceeds spare
-      uint32_t l = spare;
-      const uint32_t d = find_bucket(hist, lane, l);
-      if (lane == 0) { sel_prefix = d << 24; sel_left = l; }
+    const uint32_t top = uniform(sel_digit), want1 = uniform(sel_left);
+    for_each_key([&](uint32_t key, int l) { if ((key >> 20) == top) atomicAdd(&hist[(key >> 10) & (kSub - 1u)], 1u << l); });
+    __syncthreads();
+    own[0] = hist[tid];
+    block_scan<1>(own, inc, all, tot, lane, wave);
+    if (inc[0] > want1 && inc[0] - own[0] <= want1) { sel_digit = tid; sel_left = want1 - (inc[0] - own[0]); }
+    __syncthreads();
+    const uint32_t high = (top << 10) | uniform(sel_digit), want2 = uniform(sel_left);
+    for_each_key([&](uint32_t key, int l) { if ((key >> 10) == high) atomicAdd(&hist[(1u + l) * kSub + (key & (kSub - 1u))], 1u); });
+    __syncthreads();
+    const uint32_t n0 = hist[kSub + tid], n1 = hist[2u * kSub + tid], n2 = hist[3u * kSub + tid];
+    own[0] = n0 + 2u * n1 + 4u * n2;
+    block_scan<1>(own, inc, all, tot, lane, wave);
+    if (inc[0] > want2 && inc[0] - own[0] <= want2) {
+      sel_digit = tid; sel_left = want2 - (inc[0] - own[0]);
+      sel_same[0] = n0; sel_same[1] = n1; sel_same[2] = n2;
     }
     __syncthreads();
-    // ---- passes 1..3: only the upgrades inside the bucket chosen so far
-    for (int pass = 1; pass < 4; ++pass) {
-      const int shift = 24 - 8 * pass;
-      const uint32_t pre = sel_prefix;
-      if (tid < 256) hist[tid] = 0;
-      __syncthreads();
-      const uint32_t high_mask = 0xFFFFFFFFu << (shift + 8);
-      for_each_score([&](float s, uint32_t) {
+    kstar = (high << 10) | uniform(sel_digit);                  // the key at which the budget runs out
+    const uint32_t n[3] = {uniform(sel_same[0]), uniform(sel_same[1]), uniform(sel_same[2])};
+    split_last_key(uniform(sel_left), n, quota, tied);
+    if (tied) {                                                 // per level, how many of those keys lie at lower token indices
+      uint32_t eq[3] = {0, 0, 0}, inc3[3], all3[3];
+      for_each_key([&](uint32_t key, int l) { eq[l] += (uint32_t)(key == kstar); });
+      block_scan<3>(eq, inc3, all3, tot, lane, wave);
 #pragma unroll
-        for (int l = 0; l < 3; ++l) {
-          const uint32_t key = gain_key(s, per_bit[l]);
-          if (((key ^ pre) & high_mask) == 0) atomicAdd(&hist[(key >> shift) & 255u], 1u << l);
-        }
-      });
-      __syncthreads();
-      if (wave == 0) {
-        uint32_t l = sel_left;
-        const uint32_t d = find_bucket(hist, lane, l);
-        if (lane == 0) { sel_prefix = pre | (d << shift); sel_left = l; }
-      }
-      __syncthreads();
+      for (int l = 0; l < 3; ++l) run[l] = inc3[l] - eq[l];
     }
-    kstar = sel_prefix;     // the key at which the budget runs out
-    left = sel_left;        // units still free for the upgrades with exactly that key
   } else {
-    if (tid < 4) class_tot[tid] = 0;
     __syncthreads();
   }
 
-  // ---- upgrades with key == kstar: per level, how many lie at lower token indices
-  uint32_t run[3] = {0, 0, 0}, quota[3] = {0, 0, 0};
-  if (!everything) {
-    uint32_t eq[3] = {0, 0, 0};
-    for_each_score([&](float s, uint32_t) {
+  uint32_t cls[KPT], cnt[4] = {0, 0, 0, 0};
 #pragma unroll
-      for (int l = 0; l < 3; ++l) eq[l] += (gain_key(s, per_bit[l]) == kstar);
-    });
-#pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      const uint32_t inc = wave_inclusive_scan(eq[l]);
-      run[l] = inc - eq[l];
-      if (lane == 63) wave_tot[l][wave] = inc;
-    }
-    __syncthreads();
-    uint32_t n[3];
-#pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      uint32_t before = 0, all = 0;
-      for (uint32_t w = 0; w < (uint32_t)kWaves; ++w) {
-        const uint32_t x = wave_tot[l][w];
-        before += (w < wave) ? x : 0u;
-        all += x;
-      }
-      run[l] += before;
-      n[l] = all;
-    }
-    // admitted level by level until one upgrade does not fit; nothing after it is taken
-    uint32_t free_units = left;
-    quota[0] = min(n[0], free_units);
-    bool full = quota[0] == n[0];
-    free_units -= quota[0];
-    quota[1] = full ? min(n[1], free_units / 2u) : 0u;
-    full = full && quota[1] == n[1];
-    free_units -= 2u * quota[1];
-    quota[2] = full ? min(n[2], free_units / 4u) : 0u;
+  for (int i = 0; i < KPT; ++i) {
+    cls[i] = everything ? 3u : greedy_class(mine[i], kstar, quota, tied, run);
+    const bool real = (uint32_t)i < n_own;
+    cnt[0] += (uint32_t)(real && cls[i] == 0u); cnt[1] += (uint32_t)(real && cls[i] == 1u);
+    cnt[2] += (uint32_t)(real && cls[i] == 2u); cnt[3] += (uint32_t)(real && cls[i] == 3u);
   }
-
-  uint32_t cnt[4] = {0, 0, 0, 0};
-  for_each_score([&](float s, uint32_t t) {
-    bool taken[3];
+  if (KPT % 4 == 0 && n_own == (uint32_t)KPT && (reinterpret_cast<uintptr_t>(bits) & 3u) == 0u) {
 #pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      const uint32_t key = gain_key(s, per_bit[l]);
-      const bool is_eq = key == kstar;
-      taken[l] = everything || key < kstar || (is_eq && run[l] < quota[l]);
-      run[l] += is_eq;
-    }
-    const uint32_t c = taken[0] ? (taken[1] ? (taken[2] ? 3u : 2u) : 1u) : 0u;
-    bits[t] = (uint8_t)(2u << c);
-    cnt[0] += (c == 0); cnt[1] += (c == 1); cnt[2] += (c == 2); cnt[3] += (c == 3);
-  });
+    for (int i = 0; i < KPT; i += 4)
+      *reinterpret_cast<uint32_t*>(bits + t0 + i) = (2u << cls[i]) | ((2u << cls[i + 1]) << 8) | ((2u << cls[i + 2]) << 16) | ((2u << cls[i + 3]) << 24);
+  } else {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) if ((uint32_t)i < n_own) bits[t0 + i] = (uint8_t)(2u << cls[i]);
+  }
   if (counts4 != nullptr) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint32_t inc = wave_inclusive_scan(cnt[c]);
-      if (lane == 63 && inc) atomicAdd(&class_tot[c], inc);
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t inc = wave_inclusive_scan(cnt[k]);
+      if (lane == 63 && inc) atomicAdd(&class_tot[k], inc);
     }
     __syncthreads();
     if (tid < 4) counts4[tid] = class_tot[tid];
   }
+}
+
+// ---- longer sequences ------------------------------------------------------------------------------
+//
+// The same three passes as launches, up to 64 workgroups sharing the tokens, then one workgroup that settles the last key
+// and one launch that writes the widths.  As in assign_long.hip a pass leaves one histogram per workgroup, the next
+// pass's workgroups each add them up, and the histograms live in the bits array, which nothing final is written to
+// before the last launch; what that launch's workgroups need is left at the start of their own part of it.  One
+// workgroup re-reading every score in six sweeps took 450 us for 128K tokens; the chain takes 35.
+
+constexpr uint32_t kMaxParts = 64;
+
+struct GreedyTail {
+  uint32_t prefix[2], left[2];               // after the first and the second pass
+  uint32_t below[kMaxParts][3];              // a workgroup's keys in front of the second prefix, by level
+};
+
+struct GreedyPart {
+  uint32_t kstar, tied, quota[3], same[3];   // same: keys of earlier workgroups that equal kstar
+};
+
+struct GreedyArgs {
+  const float* scores;
+  uint32_t tokens, per, parts, spare, aligned;
+  uint8_t* bits;
+  uint8_t* hist;                             // `parts` times kPartWords words, then the tail
+  unsigned long long* counts4;
+};
+
+constexpr uint32_t kPartWords = kTop + kSub;               // the third pass's 3 x 1024 counts take the place of the first one's
+
+__device__ inline uint32_t* part_hist(const GreedyArgs& a, uint32_t b) { return reinterpret_cast<uint32_t*>(a.hist) + (uint64_t)b * kPartWords; }
+__device__ inline GreedyTail* tail_of(const GreedyArgs& a) { return reinterpret_cast<GreedyTail*>(part_hist(a, a.parts)); }
+__device__ inline GreedyPart* part_of(const GreedyArgs& a, uint32_t b) {
+  return reinterpret_cast<GreedyPart*>((reinterpret_cast<uint64_t>(a.bits) + (uint64_t)b * a.per + 15u) & ~(uint64_t)15u);
+}
+
+template <int PASS>
+__global__ __launch_bounds__(kThreads) void greedy_pass_kernel(GreedyArgs a) {
+  constexpr uint32_t kWords = PASS == 0 ? kTop * 2u : PASS == 1 ? kSub : 3u * kSub;
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kWords];
+  __shared__ uint32_t tot[3][kSelectWaves];
+  __shared__ uint32_t sel_prefix, sel_left;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, b = blockIdx.x;
+  const uint32_t t0 = b * a.per, t1 = min(t0 + a.per, a.tokens);
+  GreedyTail* tail = tail_of(a);
+  for (uint32_t i = tid; i < kWords / 4u; i += kThreads) reinterpret_cast<u32x4*>(hist)[i] = (u32x4)(0u);
+  uint32_t prefix = 0;
+  if constexpr (PASS > 0) {                                  // the bucket of the pass before, from everybody's histograms
+    uint32_t c[4] = {0, 0, 0, 0};
+    if constexpr (PASS == 1) {
+#pragma unroll 4
+      for (uint32_t p = 0; p < a.parts; ++p) {
+        const u32x4 h = reinterpret_cast<const u32x4*>(part_hist(a, p))[tid];
+        c[0] += h.x; c[1] += h.y; c[2] += h.z; c[3] += h.w;
+      }
+    } else {
+#pragma unroll 4
+      for (uint32_t p = 0; p < a.parts; ++p) c[0] += part_hist(a, p)[kTop + tid];
+    }
+    const uint32_t own[1] = {c[0] + c[1] + c[2] + c[3]};
+    uint32_t inc[1], all[1];
+    block_scan<1>(own, inc, all, tot, lane, wave);
+    const uint32_t want = PASS == 1 ? a.spare : tail->left[0];
+    if (inc[0] > want && inc[0] - own[0] <= want) {
+      uint32_t left = want - (inc[0] - own[0]), d = 0;
+      if (PASS == 1) {
+        if (left >= c[0]) { left -= c[0]; d = 1; if (left >= c[1]) { left -= c[1]; d = 2; if (left >= c[2]) { left -= c[2]; d = 3; } } }
+        sel_prefix = 4u * tid + d;
+      } else {
+        sel_prefix = (tail->prefix[0] << 10) | tid;
+      }
+      sel_left = left;
+    }
+    __syncthreads();
+    prefix = uniform(sel_prefix);
+    if (b == 0 && tid == 0) { tail->prefix[PASS - 1] = prefix; tail->left[PASS - 1] = sel_left; }
+  } else {
+    __syncthreads();
+  }
+  uint32_t below[3] = {0, 0, 0};
+  const auto visit = [&](float score) {
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+      const uint32_t key = gain_key(score, l);
+      if constexpr (PASS == 0) {
+        atomicAdd(&hist[(key >> 20) * 2u + (lane & 1u)], 1u << l);
+      } else if constexpr (PASS == 1) {
+        if ((key >> 20) == prefix) atomicAdd(&hist[(key >> 10) & (kSub - 1u)], 1u << l);
+      } else {
+        if ((key >> 10) == prefix) atomicAdd(&hist[l * kSub + (key & (kSub - 1u))], 1u);
+        below[l] += (uint32_t)((key >> 10) < prefix);
+      }
+    }
+  };
+  if (a.aligned) {
+    for (uint32_t t = t0 + 4u * tid; t < t1; t += 4u * kThreads) {
+      if (t + 4u <= t1) {
+        const float4 s = *reinterpret_cast<const float4*>(a.scores + t);
+        visit(s.x); visit(s.y); visit(s.z); visit(s.w);
+      } else {
+        for (uint32_t i = t; i < t1; ++i) visit(a.scores[i]);
+      }
+    }
+  } else {
+#pragma unroll 4
+    for (uint32_t t = t0 + tid; t < t1; t += kThreads) visit(a.scores[t]);
+  }
+  __syncthreads();
+  uint32_t* mine = part_hist(a, b);
+  if constexpr (PASS == 0) {
+    const u32x4 h0 = reinterpret_cast<const u32x4*>(hist)[2u * tid], h1 = reinterpret_cast<const u32x4*>(hist)[2u * tid + 1u];
+    reinterpret_cast<u32x4*>(mine)[tid] = (u32x4){h0.x + h0.y, h0.z + h0.w, h1.x + h1.y, h1.z + h1.w};
+  } else if constexpr (PASS == 1) {
+    mine[kTop + tid] = hist[tid];
+  } else {
+#pragma unroll
+    for (uint32_t l = 0; l < 3u; ++l) mine[l * kSub + tid] = hist[l * kSub + tid];
+    uint32_t inc[3], all[3];
+    block_scan<3>(below, inc, all, tot, lane, wave);
+    if (tid < 3) tail->below[b][tid] = tid == 0 ? all[0] : tid == 1 ? all[1] : all[2];
+  }
+}
+
+// The last key, what of it is admitted, and the class counts.  One workgroup.
+__global__ __launch_bounds__(kThreads) void greedy_settle_kernel(GreedyArgs a) {
+  __shared__ uint32_t tot[3][kSelectWaves];
+  __shared__ uint32_t sel_digit, sel_left, sel_same[3];
+  __shared__ uint32_t in_front[3];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const GreedyTail* tail = tail_of(a);
+  if (tid < 3u) in_front[tid] = 0u;
+  uint32_t n[3] = {0, 0, 0};
+#pragma unroll 4
+  for (uint32_t p = 0; p < a.parts; ++p) {
+#pragma unroll
+    for (int l = 0; l < 3; ++l) n[l] += part_hist(a, p)[l * kSub + tid];
+  }
+  const uint32_t want = tail->left[1], high = tail->prefix[1];
+  uint32_t own[1] = {n[0] + 2u * n[1] + 4u * n[2]}, inc[1], all[1];
+  block_scan<1>(own, inc, all, tot, lane, wave);
+  if (inc[0] > want && inc[0] - own[0] <= want) {
+    sel_digit = tid; sel_left = want - (inc[0] - own[0]);
+    sel_same[0] = n[0]; sel_same[1] = n[1]; sel_same[2] = n[2];
+  }
+  __syncthreads();
+  const uint32_t digit = uniform(sel_digit), kstar = (high << 10) | digit;
+  const uint32_t same[3] = {uniform(sel_same[0]), uniform(sel_same[1]), uniform(sel_same[2])};
+  uint32_t quota[3];
+  bool tied;
+  split_last_key(uniform(sel_left), same, quota, tied);
+  // upgrades of every level in front of the last key
+#pragma unroll
+  for (int l = 0; l < 3; ++l) {
+    uint32_t v = tid < digit ? n[l] : 0u;
+    if (tid < a.parts) v += tail->below[tid][l];
+    const uint32_t sum = wave_inclusive_scan(v);
+    if (lane == 63 && sum) atomicAdd(&in_front[l], sum);
+  }
+  uint32_t before = 0;                                        // wave = level, lane = workgroup
+  if (wave < 3) {
+    const uint32_t mine = lane < a.parts ? part_hist(a, lane)[wave * kSub + digit] : 0u;
+    before = wave_inclusive_scan(mine) - mine;
+  }
+  __syncthreads();                                            // everything has been read: the results may go over it
+  if (wave < 3 && lane < a.parts) {
+    GreedyPart* p = part_of(a, lane);
+    p->same[wave] = before;
+    p->quota[wave] = wave == 0 ? quota[0] : wave == 1 ? quota[1] : quota[2];
+    if (wave == 0) { p->kstar = kstar; p->tied = tied ? 1u : 0u; }
+  }
+  if (a.counts4 != nullptr && tid == 0) {                     // an upgrade is only taken with those below it
+    const uint32_t t4 = in_front[0] + quota[0], t8 = in_front[1] + quota[1], t16 = in_front[2] + quota[2];
+    a.counts4[0] = a.tokens - t4; a.counts4[1] = t4 - t8; a.counts4[2] = t8 - t16; a.counts4[3] = t16;
+  }
+}
+
+// EVERYTHING: the budget covers 16 bits for every token; no launch has gone before.
+template <bool EVERYTHING>
+__global__ __launch_bounds__(kThreads) void greedy_write_kernel(GreedyArgs a) {
+  __shared__ uint32_t tot[3][kSelectWaves];
+  __shared__ GreedyPart part;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, b = blockIdx.x;
+  const uint32_t t0 = b * a.per, t1 = min(t0 + a.per, a.tokens);
+  uint32_t kstar = 0, quota[3] = {0, 0, 0}, same[3] = {0, 0, 0};
+  bool tied = false;
+  if constexpr (!EVERYTHING) {
+    if (tid < sizeof(GreedyPart) / 4u) reinterpret_cast<uint32_t*>(&part)[tid] = reinterpret_cast<const uint32_t*>(part_of(a, b))[tid];
+    __syncthreads();                                          // read by now: the stores below may go over it
+    kstar = uniform(part.kstar);
+    tied = uniform(part.tied) != 0u;
+#pragma unroll
+    for (int l = 0; l < 3; ++l) { quota[l] = uniform(part.quota[l]); same[l] = uniform(part.same[l]); }
+  } else if (b == 0 && tid < 4u && a.counts4 != nullptr) {
+    a.counts4[tid] = tid == 3u ? a.tokens : 0u;
+  }
+  for (uint32_t base = t0; base < t1; base += 4u * kThreads) {
+    const uint32_t t = base + 4u * tid;
+    const uint32_t n = t < t1 ? min(t1 - t, 4u) : 0u;
+    float s[4];
+    if (!EVERYTHING && a.aligned && n == 4u) {
+      const float4 f = *reinterpret_cast<const float4*>(a.scores + t);
+      s[0] = f.x; s[1] = f.y; s[2] = f.z; s[3] = f.w;
+    } else {
+#pragma unroll
+      for (uint32_t i = 0; i < 4u; ++i) s[i] = !EVERYTHING && i < n ? a.scores[t + i] : 0.0f;
+    }
+    uint32_t run[3] = {0, 0, 0};
+    if (tied) {
+      uint32_t eq[3] = {0, 0, 0}, inc[3], all[3];
+#pragma unroll
+      for (uint32_t i = 0; i < 4u; ++i)
+#pragma unroll
+        for (int l = 0; l < 3; ++l) eq[l] += (uint32_t)(i < n && gain_key(s[i], l) == kstar);
+      block_scan<3>(eq, inc, all, tot, lane, wave);
+#pragma unroll
+      for (int l = 0; l < 3; ++l) { run[l] = same[l] + inc[l] - eq[l]; same[l] += all[l]; }
+      __syncthreads();                                        // the wave totals are written again
+    }
+    uint32_t widths = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 4u; ++i)
+      widths |= (2u << (EVERYTHING ? 3u : greedy_class(s[i], kstar, quota, tied, run))) << (8u * i);
+    if (n == 4u && (reinterpret_cast<uintptr_t>(a.bits) & 3u) == 0u) *reinterpret_cast<uint32_t*>(a.bits + t) = widths;
+    else for (uint32_t i = 0; i < n; ++i) a.bits[t + i] = (uint8_t)(widths >> (8u * i));
+  }
+}
+
+hipError_t launch_greedy_long(const float* scores, uint32_t tokens, uint32_t spare_units, uint8_t* bits,
+                              unsigned long long* counts4, hipStream_t stream) {
+  GreedyArgs a;
+  a.scores = scores;
+  a.tokens = tokens;
+  a.spare = spare_units;
+  a.aligned = reinterpret_cast<uintptr_t>(scores) % 16 == 0;
+  a.bits = bits;
+  a.counts4 = counts4;
+  // the bits array is all the scratch there is: as many workgroups as their histograms fit into it
+  const uint64_t room = (uint64_t)tokens - 15u - sizeof(GreedyTail);
+  uint64_t parts = room / (kPartWords * sizeof(uint32_t));
+  if (parts > kMaxParts) parts = kMaxParts;
+  a.per = (uint32_t)((tokens + parts - 1u) / parts + 3u) & ~3u;
+  a.parts = (tokens + a.per - 1u) / a.per;
+  a.hist = reinterpret_cast<uint8_t*>((reinterpret_cast<uint64_t>(bits) + 15u) & ~(uint64_t)15u);
+  const dim3 grid(a.parts), block(kThreads);
+  if (spare_units >= 7ull * tokens) {
+    hipLaunchKernelGGL(greedy_write_kernel<true>, grid, block, 0, stream, a);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(greedy_pass_kernel<0>, grid, block, 0, stream, a);
+  hipLaunchKernelGGL(greedy_pass_kernel<1>, grid, block, 0, stream, a);
+  hipLaunchKernelGGL(greedy_pass_kernel<2>, grid, block, 0, stream, a);
+  hipLaunchKernelGGL(greedy_settle_kernel, dim3(1), block, 0, stream, a);
+  hipLaunchKernelGGL(greedy_write_kernel<false>, grid, block, 0, stream, a);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -217,12 +476,17 @@ hipError_t launch_controller(const float* features, uint32_t tokens, const qkv_c
 
 hipError_t launch_greedy(const float* scores, uint32_t tokens, uint32_t spare_units, uint8_t* bits,
                          unsigned long long* counts4, hipStream_t stream) {
-  if (tokens <= 8u * kThreads)
-    hipLaunchKernelGGL(greedy_kernel<8>, dim3(1), dim3(kThreads), 0, stream, scores, tokens, spare_units, bits, counts4);
-  else if (tokens <= 32u * kThreads)
-    hipLaunchKernelGGL(greedy_kernel<32>, dim3(1), dim3(kThreads), 0, stream, scores, tokens, spare_units, bits, counts4);
+  if (tokens > kLongFrom) return launch_greedy_long(scores, tokens, spare_units, bits, counts4, stream);
+  const bool aligned = reinterpret_cast<uintptr_t>(scores) % 16 == 0;
+  const dim3 grid(1), block(kThreads);
+  if (tokens <= 2u * kThreads)
+    hipLaunchKernelGGL(greedy_kernel<2>, grid, block, 0, stream, scores, tokens, spare_units, bits, counts4, aligned);
+  else if (tokens <= 8u * kThreads)
+    hipLaunchKernelGGL(greedy_kernel<8>, grid, block, 0, stream, scores, tokens, spare_units, bits, counts4, aligned);
+  else if (tokens <= 16u * kThreads)
+    hipLaunchKernelGGL(greedy_kernel<16>, grid, block, 0, stream, scores, tokens, spare_units, bits, counts4, aligned);
   else
-    hipLaunchKernelGGL(greedy_kernel<0>, dim3(1), dim3(kThreads), 0, stream, scores, tokens, spare_units, bits, counts4);
+    hipLaunchKernelGGL(greedy_kernel<32>, grid, block, 0, stream, scores, tokens, spare_units, bits, counts4, aligned);
   return hipGetLastError();
 }
 
