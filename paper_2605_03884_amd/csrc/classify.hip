@@ -2,10 +2,11 @@
 // paper Sec. 4.2.1: the card carries the token-level bit-width vector; tokens are bucketed
 // by width so that every width owns one contiguous segment of the card).
 //
-// Workgroup b of 256 threads owns the 2048 tokens [2048 b, 2048 b + 2048), 8 consecutive
-// tokens (one 64-bit word of widths) per thread.  No workgroup talks to another: each one
-// first counts the classes over the whole bits vector by itself (a few words per thread,
-// byte-parallel arithmetic), which yields both the class totals - where each class starts
+// Workgroup b of 1024 threads owns the 2048 tokens [2048 b, 2048 b + 2048), 8 consecutive
+// tokens (one 64-bit word of widths) for each of its first 256 threads.  No workgroup talks to
+// another: each one first counts the classes over the whole bits vector by itself (all threads,
+// byte-parallel arithmetic; 256 threads took 12.4 us for 32K and 30 us for 128K tokens,
+// 1024 take 8.9 and 13), which yields both the class totals - where each class starts
 // inside order[] - and the counts in front of its own tokens.  A packed DPP scan over the
 // per-thread counters then gives every token its slot, so the bucketing is stable
 // (increasing token index inside a class).  The work is bound by instruction issue, not by
@@ -17,14 +18,16 @@
 #include "qkv_common.h"
 #include "qkv_decode.h"
 #include "qkv_plan.h"
+#include "qkv_select.h"
 
 namespace qkv {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / kWaveSize;
+constexpr int kThreads = kSelectThreads;
+constexpr uint32_t kOwners = 256;            // threads that own tokens
+constexpr int kOwnerWaves = (int)kOwners / kWaveSize;
 constexpr uint32_t kPerThread = 8;
-constexpr uint32_t kPerBlock = kThreads * kPerThread;
+constexpr uint32_t kPerBlock = kOwners * kPerThread;
 
 // Number of bytes of w equal to the byte replicated in `pattern` (exact, no carries between bytes).
 __device__ inline uint32_t count_bytes_equal(uint64_t w, uint64_t pattern) {
@@ -46,43 +49,24 @@ __device__ inline uint64_t load_widths(const uint8_t* __restrict__ bits, uint32_
   return w;
 }
 
-// Sums of N values over the workgroup with one barrier.  `slots` is LDS scratch.
-template <int N>
-__device__ inline void block_sums(uint32_t (&v)[N], uint32_t lane, uint32_t wave, uint32_t (*slots)[kWaves]) {
-#pragma unroll
-  for (int n = 0; n < N; ++n) {
-    const uint32_t inc = wave_inclusive_scan(v[n]);
-    if (lane == 63) slots[n][wave] = inc;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int n = 0; n < N; ++n) {
-    uint32_t s = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) s += slots[n][w];
-    v[n] = s;
-  }
-}
-
 __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __restrict__ bits, CardGeom g,
                                                            qkv_card_header_t header, PadTable pads,
                                                            uint8_t* __restrict__ card, bool aligned,
                                                            const uint8_t* card_in, uint64_t card_in_bytes,
                                                            uint32_t* status_in) {
-  __shared__ uint32_t sum_slots[7][kWaves];
-  __shared__ uint32_t slots[kWaves];
+  __shared__ uint32_t sum_slots[7][kSelectWaves];
+  __shared__ uint32_t slots[kOwnerWaves];
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u, wave = tid >> 6;
   const uint32_t T = g.tokens;
   const uint32_t block_t0 = blockIdx.x * kPerBlock;       // < T for every launched workgroup
   const uint32_t t0 = block_t0 + tid * kPerThread;
 
-  // ---- counts over the whole vector: totals, and what lies in front of this workgroup.
-  // Thread tid visits the words tid, tid + 256, ...: its own word is one of them.
+  // ---- counts over the whole vector: totals, and what lies in front of this workgroup
   const uint64_t p2 = 0x0202020202020202ull, p4 = p2 << 1, p8 = p2 << 2, p16 = p2 << 3;
   uint32_t tot1 = 0, tot2 = 0, tot3 = 0, valid = 0;       // classes 1..3, and all four valid widths
   uint32_t pre1 = 0, pre2 = 0, pre3 = 0;                  // classes 1..3 among the tokens below block_t0
-  uint64_t mine = 0;
+  const uint64_t mine = tid < kOwners ? load_widths(bits, t0, T, aligned) : 0ull;
   const uint32_t n_words = (T + kPerThread - 1) / kPerThread;
   for (uint32_t i = tid; i < n_words; i += kThreads) {
     const uint64_t w = load_widths(bits, i * kPerThread, T, aligned);
@@ -91,11 +75,11 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
     valid += c1 + c2 + c3 + count_bytes_equal(w, p2);
     const bool before = i * kPerThread < block_t0;
     pre1 += before ? c1 : 0u; pre2 += before ? c2 : 0u; pre3 += before ? c3 : 0u;
-    if (i * kPerThread == t0) mine = w;
   }
   {
-    uint32_t v[7] = {tot1, tot2, tot3, valid, pre1, pre2, pre3};
-    block_sums<7>(v, lane, wave, sum_slots);
+    const uint32_t own[7] = {tot1, tot2, tot3, valid, pre1, pre2, pre3};
+    uint32_t inc[7], v[7];
+    block_scan<7>(own, inc, v, sum_slots, lane, wave);
     tot1 = v[0]; tot2 = v[1]; tot3 = v[2]; valid = v[3]; pre1 = v[4]; pre2 = v[5]; pre3 = v[6];
   }
   const uint32_t tot0 = T - tot1 - tot2 - tot3;
@@ -112,47 +96,49 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
 #pragma unroll
   for (uint32_t i = 0; i < kPerThread; ++i) {
     cls[i] = class_of((uint32_t)(mine >> (8 * i)) & 0xFFu);
-    if (t0 + i < T) {
+    if (tid < kOwners && t0 + i < T) {
       ++n_mine;
       packed += (cls[i] == 1) ? 1u : (cls[i] == 2) ? (1u << 10) : (cls[i] == 3) ? (1u << 20) : 0u;
     }
   }
   const uint32_t inc = wave_inclusive_scan(packed);
   const uint32_t inc_n = wave_inclusive_scan(n_mine);
-  if (lane == 63) slots[wave] = inc;
+  if (lane == 63 && wave < (uint32_t)kOwnerWaves) slots[wave] = inc;
   __syncthreads();
-  uint32_t w1 = 0, w2 = 0, w3 = 0;                        // classes 1..3 in the lower waves of this workgroup
+  if (tid < kOwners) {
+    uint32_t w1 = 0, w2 = 0, w3 = 0;                        // classes 1..3 in the lower waves of this workgroup
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const uint32_t x = ((uint32_t)w < wave) ? slots[w] : 0u;
-    w1 += x & 1023u; w2 += (x >> 10) & 1023u; w3 += x >> 20;
-  }
-  const uint32_t ex = inc - packed;                       // lower lanes of this wave
-  const uint32_t e1 = ex & 1023u, e2 = (ex >> 10) & 1023u, e3 = ex >> 20;
-  const uint32_t tokens_below = wave * (kWaveSize * kPerThread) + (inc_n - n_mine);   // inside the workgroup
-  uint32_t run1 = pre1 + w1 + e1, run2 = pre2 + w2 + e2, run3 = pre3 + w3 + e3;
-  uint32_t run0 = pre0 + tokens_below - (w1 + e1) - (w2 + e2) - (w3 + e3);
+    for (int w = 0; w < kOwnerWaves; ++w) {
+      const uint32_t x = ((uint32_t)w < wave) ? slots[w] : 0u;
+      w1 += x & 1023u; w2 += (x >> 10) & 1023u; w3 += x >> 20;
+    }
+    const uint32_t ex = inc - packed;                       // lower lanes of this wave
+    const uint32_t e1 = ex & 1023u, e2 = (ex >> 10) & 1023u, e3 = ex >> 20;
+    const uint32_t tokens_below = wave * (kWaveSize * kPerThread) + (inc_n - n_mine);   // inside the workgroup
+    uint32_t run1 = pre1 + w1 + e1, run2 = pre2 + w2 + e2, run3 = pre3 + w3 + e3;
+    uint32_t run0 = pre0 + tokens_below - (w1 + e1) - (w2 + e2) - (w3 + e3);
 
-  uint8_t* bits_out = card + g.off_bits;
-  uint32_t* slot_out = reinterpret_cast<uint32_t*>(card + g.off_slot);
-  uint32_t* order_out = reinterpret_cast<uint32_t*>(card + g.off_order);
-  uint32_t slot[kPerThread];
-#pragma unroll
-  for (uint32_t i = 0; i < kPerThread; ++i) {
-    const uint32_t c = cls[i];
-    const uint32_t s = (c == 0) ? run0 : (c == 1) ? run1 : (c == 2) ? run2 : run3;
-    run0 += (c == 0); run1 += (c == 1); run2 += (c == 2); run3 += (c == 3);
-    slot[i] = s;
-    if (t0 + i < T) order_out[((c == 0) ? 0u : (c == 1) ? base1 : (c == 2) ? base2 : base3) + s] = t0 + i;
-  }
-  if (t0 + kPerThread <= T) {
-    *reinterpret_cast<u32x4*>(slot_out + t0) = (u32x4){slot[0], slot[1], slot[2], slot[3]};
-    *reinterpret_cast<u32x4*>(slot_out + t0 + 4) = (u32x4){slot[4], slot[5], slot[6], slot[7]};
-    *reinterpret_cast<uint64_t*>(bits_out + t0) = mine;
-  } else {
+    uint8_t* bits_out = card + g.off_bits;
+    uint32_t* slot_out = reinterpret_cast<uint32_t*>(card + g.off_slot);
+    uint32_t* order_out = reinterpret_cast<uint32_t*>(card + g.off_order);
+    uint32_t slot[kPerThread];
 #pragma unroll
     for (uint32_t i = 0; i < kPerThread; ++i) {
-      if (t0 + i < T) { slot_out[t0 + i] = slot[i]; bits_out[t0 + i] = (uint8_t)(mine >> (8 * i)); }
+      const uint32_t c = cls[i];
+      const uint32_t s = (c == 0) ? run0 : (c == 1) ? run1 : (c == 2) ? run2 : run3;
+      run0 += (c == 0); run1 += (c == 1); run2 += (c == 2); run3 += (c == 3);
+      slot[i] = s;
+      if (t0 + i < T) order_out[((c == 0) ? 0u : (c == 1) ? base1 : (c == 2) ? base2 : base3) + s] = t0 + i;
+    }
+    if (t0 + kPerThread <= T) {
+      *reinterpret_cast<u32x4*>(slot_out + t0) = (u32x4){slot[0], slot[1], slot[2], slot[3]};
+      *reinterpret_cast<u32x4*>(slot_out + t0 + 4) = (u32x4){slot[4], slot[5], slot[6], slot[7]};
+      *reinterpret_cast<uint64_t*>(bits_out + t0) = mine;
+    } else {
+#pragma unroll
+      for (uint32_t i = 0; i < kPerThread; ++i) {
+        if (t0 + i < T) { slot_out[t0 + i] = slot[i]; bits_out[t0 + i] = (uint8_t)(mine >> (8 * i)); }
+      }
     }
   }
 
