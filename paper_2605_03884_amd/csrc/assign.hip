@@ -4,8 +4,8 @@
 //
 // Ranking rule: tokens ordered by (score descending, index ascending), scores compared in
 // the IEEE total order.  The first cut[0] tokens get 16 bits, up to cut[1] 8 bits, up to
-// cut[2] 4 bits, the rest 2.  No sort is needed: for each cut a 4-pass radix select over the
-// 32-bit order keys finds the key of the token at that rank and how many tokens lie strictly
+// cut[2] 4 bits, the rest 2.  No sort is needed: for each cut a radix select over the 32-bit
+// order keys finds the key of the token at that rank and how many tokens lie strictly
 // before it; tokens whose key equals the cut key are then admitted by increasing index until
 // the cut is full (a stable block-wide prefix count).  One workgroup of 1024 threads does the
 // selection; thread i owns the consecutive tokens [i * per, (i + 1) * per).
@@ -14,11 +14,9 @@
 // so every line of its code is fetched cold, and its sixteen waves share the issue slots of one
 // compute unit.  Hence: a thread keeps its keys in registers, and the kernel is instantiated per
 // number of keys per thread (1, 2, 4, ... 32, chosen from the token count), so that a launch
-// touches only the code of its own size; the passes after the first are one rolled loop; the
-// first pass's histogram is kept in 16 copies against same-word atomics (real scores share sign
-// and exponent); later passes test a key against all three cut prefixes and skip the counting
-// code for waves that hold no match; cuts whose prefixes still coincide share one histogram; a
-// wave without ties needs three comparisons per key for the widths.  Longer sequences
+// touches only the code of its own size; the passes after the first are one rolled loop; later
+// passes test a key against all three cut prefixes and skip the counting code for waves that hold no
+// match; a wave without ties needs three comparisons per key for the widths.  Longer sequences
 // (kRankedMax, kPlanMax): assign_long.hip.
 //
 // Planning variant (PLAN): once the cut keys are known every thread knows the widths of its own
@@ -40,10 +38,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = kSelectThreads;
 constexpr int kWaves = kSelectWaves;
-constexpr int kCopies = 16;                  // of the first pass's histogram
+constexpr uint32_t kTop = 4096, kSub = 1024; // buckets of the first pass, and of the two later ones for each cut
+constexpr uint32_t kTopCopies = 2;           // of the first pass's histogram, against same-word atomics: real scores share sign and exponent
+constexpr uint32_t kByteCopies = 16;         // the same for a first pass of 8 bits
 // Longest sequences one workgroup's registers take; assign_long.hip goes on.  With planning the line lies lower, because
 // the chain of launches there also spreads the tables' writing (measured, one workgroup against the chain: widths alone
-// 13 / 24 us at 16384 tokens, 26 / 27 at 32768; with planning 17 / 24 us at 16384, 28 / 25 at 20000, 33 / 26 at 32768).
+// 12 / 24 us at 16384 tokens, 21 / 27 at 32768; with planning 15 / 24 us at 16384, 28 / 25 at 20000, 33 / 26 at 32768).
 constexpr uint32_t kRankedMax = 32768;
 constexpr uint32_t kPlanMax = 16384;
 constexpr uint32_t kShareTokens = 2048;      // tokens whose tables one workgroup writes
@@ -53,14 +53,19 @@ constexpr uint32_t kShareTokens = 2048;      // tokens whose tables one workgrou
 template <int KPT, bool PLAN>
 __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, uint32_t T, uint32_t cut0, uint32_t cut1,
                                             uint32_t cut2, uint8_t* __restrict__ bits, bool aligned, const PlanArgs* plan) {
-  __shared__ u32x4 wide4[256 * kCopies / 4];            // first pass: bucket d, copy c at word [d * 16 + c]; later the stage
-  __shared__ uint32_t hist2[2][3][256];                 // two sets, so that one is cleared while the other is searched; later the stage of the widths
+  // Up to 2 keys per thread four passes of 8 bits, more keys 12, 10 and 10 bits: a pass less to make over the keys, but
+  // more buckets to clear and add up (widths alone, us: 1024 tokens 4.4 / 4.7, 2048 5.1 / 5.3, 4096 6.1 / 6.1, 8192 8.1 / 7.7,
+  // 16384 13.3 / 11.5, 32768 25.9 / 20.6).
+  constexpr bool kBytes = KPT <= 2;
+  // first pass: bucket d, copy c at word [d * copies + c]; later the other passes' histograms; then the stage
+  __shared__ u32x4 wide4[(kBytes ? 256u * kByteCopies + 6u * 256u : kTop * kTopCopies) / 4u];
   __shared__ uint32_t sel_prefix[3];                    // key bits fixed so far
   __shared__ uint32_t sel_left[3];                      // rank still to descend inside the current bucket
   __shared__ uint32_t sel_same[3];                      // keys equal to the cut key
   __shared__ __attribute__((aligned(16))) uint32_t wave_tot[3][kWaves];
   __shared__ __attribute__((aligned(16))) uint32_t wave_cls[3][kWaves];
   uint32_t* wide = reinterpret_cast<uint32_t*>(wide4);
+  uint32_t* hist2 = wide + 256u * kByteCopies;          // 8-bit passes: two sets of [cut][256], one cleared while the other is searched
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u, wave = tid >> 6;
   const uint32_t cut[3] = {cut0, cut1, cut2};
@@ -82,67 +87,136 @@ __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, ui
     for (int i = 0; i < KPT; ++i) keys[i] = ((uint32_t)i < n_own) ? rank_key(scores[t0 + i]) : 0u;
   }
 
-  // ---- pass 0: one histogram of the top byte, shared by the three cuts
-  wide4[tid] = (u32x4)(0u);                             // 256 * 16 words = 1024 x 16 bytes
-  __syncthreads();
+  if constexpr (kBytes) {
+    // ---- pass 0: one histogram of the top byte, shared by the three cuts
+    wide4[tid] = (u32x4)(0u);                             // 256 * 16 words = 1024 x 16 bytes
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < KPT; ++i)
-    if ((uint32_t)i < n_own) atomicAdd(&wide[(keys[i] >> 24) * kCopies + (lane & (kCopies - 1u))], 1u);
-  __syncthreads();
-  if (tid < 256) {
-    uint32_t s = 0;
+    for (int i = 0; i < KPT; ++i)
+      if ((uint32_t)i < n_own) atomicAdd(&wide[(keys[i] >> 24) * kByteCopies + (lane & (kByteCopies - 1u))], 1u);
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t s = 0;
 #pragma unroll
-    for (int i = 0; i < kCopies; ++i) s += wide[tid * kCopies + ((i + tid) & (kCopies - 1u))];
-    hist2[0][0][tid] = s;
-  } else if (tid < 4 * 256) {
-    hist2[1][(tid >> 8) - 1u][tid & 255u] = 0;          // the set the next pass counts into
-  }
-  __syncthreads();
-  if (wave < 3 && live[wave]) {
-    uint32_t left = cut[wave], same;
-    const uint32_t d = find_bucket(hist2[0][0], lane, left, same);
-    if (lane == 0) { sel_prefix[wave] = d << 24; sel_left[wave] = left; }
-  }
-  __syncthreads();
+      for (int i = 0; i < kByteCopies; ++i) s += wide[tid * kByteCopies + ((i + tid) & (kByteCopies - 1u))];
+      hist2[tid] = s;
+    } else if (tid < 4 * 256) {
+      hist2[768u + tid - 256u] = 0;          // the set the next pass counts into
+    }
+    __syncthreads();
+    if (wave < 3 && live[wave]) {
+      uint32_t left = cut[wave], same;
+      const uint32_t d = find_bucket(hist2, lane, left, same);
+      if (lane == 0) { sel_prefix[wave] = d << 24; sel_left[wave] = left; }
+    }
+    __syncthreads();
 
-  // ---- passes 1..3: per cut, only the keys inside its bucket so far.  Cuts whose prefixes are still the
-  // same count the same keys: they share the histogram of the first of them (rep).
+    // ---- passes 1..3: per cut, only the keys inside its bucket so far.  Cuts whose prefixes are still the
+    // same count the same keys: they share the histogram of the first of them (rep).
 #pragma unroll 1
-  for (int pass = 1; pass < 4; ++pass) {
-    const uint32_t shift = 24u - 8u * (uint32_t)pass;
-    const uint32_t pre0 = uniform(sel_prefix[0]), pre1 = uniform(sel_prefix[1]), pre2 = uniform(sel_prefix[2]);
-    const uint32_t rep1 = (live[0] && pre1 == pre0) ? 0u : 1u;
-    const uint32_t rep2 = (live[0] && pre2 == pre0) ? 0u : (live[1] && pre2 == pre1) ? 1u : 2u;
-    const bool count0 = live[0], count1 = live[1] && rep1 == 1u, count2 = live[2] && rep2 == 2u;
-    uint32_t (*hist)[256] = hist2[pass & 1];            // cleared during the previous search
-    const uint32_t high_mask = 0xFFFFFFFFu << (shift + 8u);
+    for (int pass = 1; pass < 4; ++pass) {
+      const uint32_t shift = 24u - 8u * (uint32_t)pass;
+      const uint32_t pre0 = uniform(sel_prefix[0]), pre1 = uniform(sel_prefix[1]), pre2 = uniform(sel_prefix[2]);
+      const uint32_t rep1 = (live[0] && pre1 == pre0) ? 0u : 1u;
+      const uint32_t rep2 = (live[0] && pre2 == pre0) ? 0u : (live[1] && pre2 == pre1) ? 1u : 2u;
+      const bool count0 = live[0], count1 = live[1] && rep1 == 1u, count2 = live[2] && rep2 == 2u;
+      uint32_t* hist = hist2 + 768u * (pass & 1);         // cleared during the previous search
+      const uint32_t high_mask = 0xFFFFFFFFu << (shift + 8u);
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      const uint32_t key = keys[i];
-      const bool own = (uint32_t)i < n_own;
-      const bool h0 = own && count0 && ((key ^ pre0) & high_mask) == 0u;
-      const bool h1 = own && count1 && ((key ^ pre1) & high_mask) == 0u;
-      const bool h2 = own && count2 && ((key ^ pre2) & high_mask) == 0u;
-      if (__builtin_amdgcn_ballot_w64(h0 || h1 || h2) != 0ull) {       // many waves hold no key of any bucket
-        const uint32_t d = (key >> shift) & 255u;
-        if (h0) atomicAdd(&hist[0][d], 1u);
-        if (h1) atomicAdd(&hist[1][d], 1u);
-        if (h2) atomicAdd(&hist[2][d], 1u);
+      for (int i = 0; i < KPT; ++i) {
+        const uint32_t key = keys[i];
+        const bool own = (uint32_t)i < n_own;
+        const bool h0 = own && count0 && ((key ^ pre0) & high_mask) == 0u;
+        const bool h1 = own && count1 && ((key ^ pre1) & high_mask) == 0u;
+        const bool h2 = own && count2 && ((key ^ pre2) & high_mask) == 0u;
+        if (__builtin_amdgcn_ballot_w64(h0 || h1 || h2) != 0ull) {       // many waves hold no key of any bucket
+          const uint32_t d = (key >> shift) & 255u;
+          if (h0) atomicAdd(&hist[d], 1u);
+          if (h1) atomicAdd(&hist[256u + d], 1u);
+          if (h2) atomicAdd(&hist[512u + d], 1u);
+        }
+      }
+      __syncthreads();
+      if (wave < 3) {
+        if (live[wave]) {
+          const uint32_t from = wave == 0 ? 0u : wave == 1 ? rep1 : rep2;
+          uint32_t left = sel_left[wave], same;
+          const uint32_t d = find_bucket(hist + 256u * from, lane, left, same);
+          if (lane == 0) { sel_prefix[wave] |= d << shift; sel_left[wave] = left; sel_same[wave] = same; }
+        }
+      } else if (wave < 15) {                             // meanwhile the other set is cleared for the next pass
+        const uint32_t i = tid - 3u * kWaveSize;          // 0 .. 767
+        hist2[768u * ((pass & 1) ^ 1) + i] = 0;
+      }
+      __syncthreads();
+    }
+  } else {
+    // ---- pass 0: one histogram of the top 12 bits, shared by the three cuts; thread tid sums buckets 4 tid .. + 3
+#pragma unroll
+    for (uint32_t i = 0; i < kTop * kTopCopies / 4u / kThreads; ++i) wide4[i * kThreads + tid] = (u32x4)(0u);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < KPT; ++i)
+      if ((uint32_t)i < n_own) atomicAdd(&wide[(keys[i] >> 20) * kTopCopies + (lane & (kTopCopies - 1u))], 1u);
+    __syncthreads();
+    {
+      const u32x4 h0 = wide4[2u * tid], h1 = wide4[2u * tid + 1u];
+      const uint32_t c[4] = {h0.x + h0.y, h0.z + h0.w, h1.x + h1.y, h1.z + h1.w};
+      const uint32_t own[1] = {c[0] + c[1] + c[2] + c[3]};
+      uint32_t inc[1], all[1];
+      block_scan<1>(own, inc, all, wave_tot, lane, wave);         // every bucket has been read behind its barrier
+#pragma unroll
+      for (uint32_t i = 0; i < 2u * 3u; ++i) wide[i * kSub + tid] = 0u;      // the histograms of both later passes
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        uint32_t left = cut[k] - (inc[0] - own[0]);
+        if (live[k] && inc[0] > cut[k] && inc[0] - own[0] <= cut[k]) {        // exactly one thread
+          uint32_t d = 0;
+          if (left >= c[0]) { left -= c[0]; d = 1; if (left >= c[1]) { left -= c[1]; d = 2; if (left >= c[2]) { left -= c[2]; d = 3; } } }
+          sel_prefix[k] = 4u * tid + d;
+          sel_left[k] = left;
+        }
       }
     }
     __syncthreads();
-    if (wave < 3) {
-      if (live[wave]) {
-        const uint32_t from = wave == 0 ? 0u : wave == 1 ? rep1 : rep2;
-        uint32_t left = sel_left[wave], same;
-        const uint32_t d = find_bucket(hist[from], lane, left, same);
-        if (lane == 0) { sel_prefix[wave] |= d << shift; sel_left[wave] = left; sel_same[wave] = same; }
+
+    // ---- passes 1 and 2, 10 bits each: per cut, only the keys inside its bucket so far
+#pragma unroll 1
+    for (uint32_t pass = 0; pass < 2u; ++pass) {
+      uint32_t pre[3], want[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        pre[k] = live[k] ? uniform(sel_prefix[k]) : 0xFFFFFFFFu;              // no key has that prefix
+        want[k] = uniform(sel_left[k]);
       }
-    } else if (wave < 15) {                             // meanwhile the other set is cleared for the next pass
-      const uint32_t i = tid - 3u * kWaveSize;          // 0 .. 767
-      hist2[(pass & 1) ^ 1][i >> 8][i & 255u] = 0;
+      const uint32_t shift = pass == 0u ? 20u : 10u;
+      uint32_t* hist = wide + pass * 3u * kSub;
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        const uint32_t key = keys[i], high = key >> shift;
+        const bool own = (uint32_t)i < n_own;
+        const bool h0 = own && high == pre[0], h1 = own && high == pre[1], h2 = own && high == pre[2];
+        if (__builtin_amdgcn_ballot_w64(h0 || h1 || h2) != 0ull) {           // many waves hold no key of any bucket
+          const uint32_t d = (key >> (shift - 10u)) & (kSub - 1u);
+          if (h0) atomicAdd(&hist[d], 1u);
+          if (h1) atomicAdd(&hist[kSub + d], 1u);
+          if (h2) atomicAdd(&hist[2u * kSub + d], 1u);
+        }
+      }
+      __syncthreads();
+      const uint32_t own[3] = {hist[tid], hist[kSub + tid], hist[2u * kSub + tid]};
+      uint32_t inc[3], all[3];
+      block_scan<3>(own, inc, all, wave_tot, lane, wave);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        if (live[k] && inc[k] > want[k] && inc[k] - own[k] <= want[k]) {
+          sel_prefix[k] = (pre[k] << 10) | tid;
+          sel_left[k] = want[k] - (inc[k] - own[k]);
+          sel_same[k] = own[k];
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 
   // Now sel_prefix[c] is the key at rank cut[c], sel_same[c] the number of tokens with exactly that key and
@@ -254,7 +328,7 @@ __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, ui
     const uint32_t at[4] = {0u, len[0], len[0] + len[1], len[0] + len[1] + len[2]};      // run starts inside the stage
     uint32_t* stage_order = wide;                         // kShareTokens entries each
     uint32_t* stage_slot = wide + kShareTokens;
-    uint8_t* stage_bits = reinterpret_cast<uint8_t*>(&hist2[0][0][0]);
+    uint8_t* stage_bits = reinterpret_cast<uint8_t*>(wide + 2u * kShareTokens);
     if (mine) {
       // next free slot of every class for this thread's tokens; class 0 is what remains of the t0 tokens before
       uint32_t next[4] = {t0 - before[0] - before[1] - before[2], before[0], before[1], before[2]};
