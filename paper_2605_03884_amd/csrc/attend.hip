@@ -827,7 +827,7 @@ __global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(AttendArgs 
     const float rescale = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
     M = Mb;
     const float w = lt > 0.f ? __builtin_amdgcn_exp2f(m - M) : 0.f;
-    weight[tid] = w;
+    weight[tid] = lt > 0.f ? w : -1.f;                 // an empty task's sums are anything: not to be touched
     float wl = row_sum16(w * lt);
     wl += __shfl_xor(wl, 16, kWaveSize);
     wl += __shfl_xor(wl, 32, kWaveSize);
@@ -840,7 +840,7 @@ __global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(AttendArgs 
 #pragma unroll 4
     for (uint32_t t = mine; t < nb; t += split) {
       const float wt = weight[t];
-      if (wt != 0.f) num += wt * *reinterpret_cast<const f32x4*>(a.part_o + ((part0 + t0 + t) * a.rep + r) * D + 4u * d4);
+      if (!(wt < 0.f)) num += wt * *reinterpret_cast<const f32x4*>(a.part_o + ((part0 + t0 + t) * a.rep + r) * D + 4u * d4);
     }
     if (t0 + kMergeBatch < a.max_tasks) __syncthreads();        // the weights are written again
   }
