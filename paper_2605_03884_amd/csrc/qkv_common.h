@@ -133,10 +133,6 @@ __device__ inline uint32_t find_bucket(const uint32_t* hist, uint32_t lane, uint
   left = rest;
   return d;
 }
-__device__ inline uint32_t find_bucket(const uint32_t* hist, uint32_t lane, uint32_t& left) {
-  uint32_t in_bucket;
-  return find_bucket(hist, lane, left, in_bucket);
-}
 
 // Number of workgroups for a streaming kernel with `tiles` wave-tiles of work.
 int grid_blocks(uint64_t tiles);

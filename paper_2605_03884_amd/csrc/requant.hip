@@ -23,7 +23,7 @@
 //
 // What bounds it: vector instruction issue (about 70 % busy at 8K tokens), then requests for parts of lines.
 // Whole call, 8K tokens, budget 3 to 2.5, with the new widths' assignment: 199 us before (64 rows of one plane
-// sorted per wave, every span expanded to 32 values), 162 us now; 32K tokens, 6 to 4: 1162 and 853 us.
+// sorted per wave, every span expanded to 32 values), 160 us now; 32K tokens, 6 to 4: 1162 and 840 us.
 // Windows of 512 rows: 171 and 936 us; without the next round's loads in flight: 172 and 877 us; a window
 // of 256 tokens over all widths at once, four waves dealing 16 width pairs: 221 and 1137 us.
 //
