@@ -8,8 +8,9 @@
 // dense values only ever exist in registers.  The result is, byte for byte, the card that creation
 // would build from the injected cache.
 //
-// Work decomposition: a workgroup takes a window of 256 consecutive rows of one outgoing segment and does
-// it for one or more planes.  It looks the window's tokens up once (token through the outgoing card's
+// Work decomposition: a workgroup takes a window of up to 256 consecutive rows of one outgoing segment: of one
+// plane, done for one or two planes, or, in short cards, of the segment as it lies, across planes (a rule in
+// launch_requant).  It looks the window's tokens up once (token through the outgoing card's
 // order[], written by the classification kernel just before, old width and slot through the incoming
 // card's tables), sorts them by old width into a list in LDS and cuts the list into rounds of at most 64
 // spans of one old width; the four waves deal the rounds of all planes among themselves, each with the
@@ -40,6 +41,7 @@ constexpr uint32_t kWindow = 256;             // rows of an outgoing segment tha
 constexpr uint32_t kMaxPlanes = 2;            // planes it does them for, at most
 constexpr uint32_t kOld = 5;                  // old classes 0 .. 3, and 4: not placed by the incoming tables
 constexpr uint32_t kMaxRounds = kWindow * 8u / kWaveSize + kOld;
+constexpr uint32_t kMaxGridX = 65536;         // workgroups side by side: a grid's width in threads stays below 2^32 (2^21 layers times heads: 65536 and more)
 
 struct RequantArgs {
   const uint8_t* card_in;
@@ -49,7 +51,10 @@ struct RequantArgs {
   CardGeom out;                 // the outgoing card's geometry (host-known counts)
   uint8_t* card_out;
   uint32_t* status;             // may be null; holds the verdict on the incoming header already (classify_kernel)
-  uint32_t group_planes;        // planes per workgroup
+  uint32_t windows[4];          // of every outgoing class: of one plane, or of all planes where the windows run across them
+  uint32_t blocks;              // workgroups asked for (the grid may hold a few more)
+  uint32_t window;              // rows of a window
+  uint32_t group_planes;        // planes a workgroup does with one window; 0: the windows run across planes
 };
 
 // Bits chosen from a where mask is 1, from b where it is 0: one instruction.
@@ -202,15 +207,15 @@ struct Round {
 };
 
 struct Shared {
-  u32x2 list[kWindow];                         // (slot in the incoming segment, row of the window), sorted by old class
+  u32x2 list[kWindow];                         // (slot in the incoming segment - across planes: row -, row of the window), sorted by old class
   uint32_t counts[kWindow / kWaveSize][8];
   uint32_t round_list[kMaxRounds];             // co | rows << 8 | first << 16
   uint32_t n_rounds;
 };
 
-// The rows [j0, j0 + kWindow) of outgoing class C in the planes [p0, p1).
+// Window k of outgoing class C in the planes [p0, p1); across: window k of the class's rows of all planes.
 template <int C, int G>
-__device__ __forceinline__ void requant_window(const RequantArgs& a, const CardGeom& in, uint32_t j0, uint32_t p0, uint32_t p1,
+__device__ __forceinline__ void requant_window(const RequantArgs& a, const CardGeom& in, uint32_t k, bool across, uint32_t p0, uint32_t p1,
                                                Shared& sh) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
@@ -218,6 +223,8 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
   const uint32_t spr_shift = out.lpr_shift - 2u;                       // log2(spans per row)
   const uint32_t n_new = out.n[C];
   constexpr uint32_t kPer = kWindow / kBlockThreads;
+  const uint32_t r0 = k * a.window;                                    // first row: of a plane, across planes of the segment
+  const uint32_t rows = min(a.window, (across ? out.planes * n_new : n_new) - r0);
 
   // ---- look the rows up and sort them by old class
   uint32_t cls[kPer], slot[kPer], rank[kPer];                          // class 7: no row
@@ -226,17 +233,18 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
     const uint32_t* order = reinterpret_cast<const uint32_t*>(a.card_out + out.off_order) + out.base[C];
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) {
-      const uint32_t j = j0 + i * kBlockThreads + tid;
+      const uint32_t x = i * kBlockThreads + tid;
       cls[i] = 7u; slot[i] = 0u;
-      if (j < n_new) {
+      if (x < rows) {
         cls[i] = 4u;
+        uint32_t plane = 0, j = r0 + x;
+        if (across) { plane = j / n_new; j -= plane * n_new; }
         const uint32_t t = order[j];
         if (t < out.tokens) {
           const uint32_t width = a.card_in[in.off_bits + t];
           const uint32_t sl = reinterpret_cast<const uint32_t*>(a.card_in + in.off_slot)[t];
-          const bool ok = (width == 2 && sl < in.n[0]) || (width == 4 && sl < in.n[1]) || (width == 8 && sl < in.n[2]) ||
-                          (width == 16 && sl < in.n[3]);
-          if (ok) { cls[i] = class_of(width); slot[i] = sl; }
+          const uint32_t n_old = width == 2 ? in.n[0] : width == 4 ? in.n[1] : width == 8 ? in.n[2] : width == 16 ? in.n[3] : 0u;
+          if (sl < n_old) { cls[i] = class_of(width); slot[i] = plane * n_old + sl; }
         }
         bad |= cls[i] == 4u;
       }
@@ -291,12 +299,12 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
     const Round d = {x & 255u, x >> 16, (x >> 8) & 255u};
     return d;
   };
-  const auto fetch = [&](const Round& d, uint32_t p, uint32_t in_slot) {
+  const auto fetch = [&](const Round& d, uint32_t p, uint32_t in_row) {
     OldSpan o;
-    if (d.co == 0u) o = fetch_old<0, G>(a.card_in, in, ((uint64_t)(p * in.n[0] + in_slot) << spr_shift) + q);
-    else if (d.co == 1u) o = fetch_old<1, G>(a.card_in, in, ((uint64_t)(p * in.n[1] + in_slot) << spr_shift) + q);
-    else if (d.co == 2u) o = fetch_old<2, G>(a.card_in, in, ((uint64_t)(p * in.n[2] + in_slot) << spr_shift) + q);
-    else if (d.co == 3u) o = fetch_old<3, G>(a.card_in, in, ((uint64_t)(p * in.n[3] + in_slot) << spr_shift) + q);
+    if (d.co == 0u) o = fetch_old<0, G>(a.card_in, in, ((uint64_t)(p * in.n[0] + in_row) << spr_shift) + q);
+    else if (d.co == 1u) o = fetch_old<1, G>(a.card_in, in, ((uint64_t)(p * in.n[1] + in_row) << spr_shift) + q);
+    else if (d.co == 2u) o = fetch_old<2, G>(a.card_in, in, ((uint64_t)(p * in.n[2] + in_row) << spr_shift) + q);
+    else if (d.co == 3u) o = fetch_old<3, G>(a.card_in, in, ((uint64_t)(p * in.n[3] + in_row) << spr_shift) + q);
     return o;
   };
   uint32_t p = p0, r = wave;
@@ -319,7 +327,7 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
       next_o = fetch(next, p, next_e.x);
     }
     const bool live = row_of_lane < d.rows;
-    const uint64_t gsp = ((uint64_t)(plane * n_new + j0 + e.y) << spr_shift) + q;
+    const uint64_t gsp = ((uint64_t)(plane * n_new + r0 + e.y) << spr_shift) + q;
     bool done = false;
     if constexpr (C < 3) {
       if (d.co == 0u && can_relabel(o.pair)) {
@@ -348,23 +356,26 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
   }
 }
 
-__host__ __device__ inline uint32_t windows_of(uint32_t n) { return (uint32_t)(((uint64_t)n + kWindow - 1u) / kWindow); }
-
 template <int G>
 __global__ __launch_bounds__(kBlockThreads) void requant_kernel(RequantArgs a) {
   __shared__ Shared sh;
   CardGeom in;
   if (!card_geometry_from_header(a.card_in, a.card_in_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, in))
     return;                                   // uniform over the grid
-  const uint32_t w0 = windows_of(a.out.n[0]), w1 = windows_of(a.out.n[1]), w2 = windows_of(a.out.n[2]), w3 = windows_of(a.out.n[3]);
-  const uint32_t per_group = w0 + w1 + w2 + w3;
-  const uint32_t group = blockIdx.x / per_group;
-  uint32_t k = blockIdx.x - group * per_group;
-  const uint32_t p0 = group * a.group_planes, p1 = min(p0 + a.group_planes, a.out.planes);
-  if (k < w0) requant_window<0, G>(a, in, k * kWindow, p0, p1, sh);
-  else if ((k -= w0) < w1) requant_window<1, G>(a, in, k * kWindow, p0, p1, sh);
-  else if ((k -= w1) < w2) requant_window<2, G>(a, in, k * kWindow, p0, p1, sh);
-  else requant_window<3, G>(a, in, (k - w2) * kWindow, p0, p1, sh);
+  uint32_t k = blockIdx.y * gridDim.x + blockIdx.x;
+  if (k >= a.blocks) return;
+  const bool across = a.group_planes == 0u;
+  uint32_t p0 = 0, p1 = 1u;
+  if (!across) {
+    const uint32_t per_group = a.windows[0] + a.windows[1] + a.windows[2] + a.windows[3], group = k / per_group;
+    k -= group * per_group;
+    p0 = group * a.group_planes;
+    p1 = min(p0 + a.group_planes, a.out.planes);
+  }
+  if (k < a.windows[0]) requant_window<0, G>(a, in, k, across, p0, p1, sh);
+  else if ((k -= a.windows[0]) < a.windows[1]) requant_window<1, G>(a, in, k, across, p0, p1, sh);
+  else if ((k -= a.windows[1]) < a.windows[2]) requant_window<2, G>(a, in, k, across, p0, p1, sh);
+  else requant_window<3, G>(a, in, k - a.windows[2], across, p0, p1, sh);
 }
 
 }  // namespace
@@ -379,17 +390,39 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
   a.out = out;
   a.card_out = card_out;
   a.status = status;
-  uint64_t windows = 0;
-  for (int c = 0; c < 4; ++c) windows += windows_of(out.n[c]);
-  // A workgroup's look-ups are worth sharing between planes while the chip stays full several times over and both cards
-  // sit in the memory-side cache (8K tokens, budget 3 to 2.5: 161.7 us with two planes, 165.4 with one); larger cards
-  // want a plane's windows, which share lines of the incoming card, to run at the same time (32K, 6 to 4: 853 us with
-  // one plane, 951 with four).
-  const bool resident = out.total <= kCacheResidentCardBytes && card_in_bytes <= kCacheResidentCardBytes;
-  uint32_t group = resident ? kMaxPlanes : 1u;
-  while (group > 1u && windows * ((out.planes + group - 1u) / group) < 8192u) group /= 2u;
-  a.group_planes = group;
-  const dim3 grid((uint32_t)(windows * ((out.planes + group - 1u) / group))), block(kBlockThreads);
+  // Windows of a plane end where its rows of the width end, and each is sorted and cut into rounds by itself: with a few
+  // hundred tokens most rounds are then partly empty.  Short cards' windows run across planes instead, every one
+  // full, at the price of a division per row and of a plane's widths being read at different times, which costs more
+  // the less of the cards the 256 MB memory-side cache holds.  Where windows of a plane would be fewer than fill the
+  // chip, longer cards' run across planes too.  Kernel alone, us, with windows of a plane and across planes: 512 planes of
+  // 128 values, 200 tokens, budget 3 to 2.5, 17.0 and 9.0; 500 20.0 and 14.2; 1000 25.5 and 21.5; 1500, 6 to 4, 45.6
+  // and 36.4; 2000, 6 to 4, 45.3 and 47.4.  2048 planes, 850 tokens, 6 to 4 (310 MB) 85.9 and 86.5, 1400 143 and 155; of 256
+  // values 700 tokens 122 and 131.  64 planes of 6000 tokens 23.1 and 21.0, 16 of 32768 27.0 and 27.1.  Smaller windows
+  // while there are few: 200 tokens, 6 to 4, 11.6 with 128 rows and 12.1 with 256, 64 tokens 7.4 with 64 rows and 8.0 with 128.
+  const uint64_t rows = (uint64_t)out.planes * out.tokens;
+  const bool cached = card_in_bytes + out.total <= (192ull << 20);
+  const bool across = rows < 1536u * kWindow || (cached ? out.tokens < 1536u : (uint64_t)out.tokens * out.head_dim < 900u * 128u);
+  a.window = !across || rows > 512u * kWindow ? kWindow : rows > 128u * kWindow ? kWindow / 2u : kWindow / 4u;
+  uint64_t blocks = 0;
+  for (int c = 0; c < 4; ++c) {
+    a.windows[c] = (uint32_t)(((across ? (uint64_t)out.planes : 1ull) * out.n[c] + a.window - 1u) / a.window);
+    blocks += a.windows[c];
+  }
+  a.group_planes = 0u;
+  if (!across) {
+    // A workgroup's look-ups are worth sharing between planes while the chip stays full several times over and both cards
+    // sit in the memory-side cache (8K tokens, budget 3 to 2.5: 161.7 us with two planes, 165.4 with one); larger cards
+    // want a plane's windows, which share lines of the incoming card, to run at the same time (32K, 6 to 4: 853 us with
+    // one plane, 951 with four).
+    const bool resident = out.total <= kCacheResidentCardBytes && card_in_bytes <= kCacheResidentCardBytes;
+    uint32_t group = resident ? kMaxPlanes : 1u;
+    while (group > 1u && blocks * ((out.planes + group - 1u) / group) < 8192u) group /= 2u;
+    a.group_planes = group;
+    blocks *= (out.planes + group - 1u) / group;
+  }
+  a.blocks = (uint32_t)blocks;
+  const uint32_t grid_y = (a.blocks + kMaxGridX - 1u) / kMaxGridX, grid_x = (a.blocks + grid_y - 1u) / grid_y;
+  const dim3 grid(grid_x, grid_y), block(kBlockThreads);
   switch (out.group_size) {
     case 32: hipLaunchKernelGGL(requant_kernel<32>, grid, block, 0, stream, a); break;
     case 64: hipLaunchKernelGGL(requant_kernel<64>, grid, block, 0, stream, a); break;

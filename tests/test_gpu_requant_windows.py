@@ -45,6 +45,46 @@ def test_window_edges(T, D, G):
             hop(card, rd, draw_bits(T, rng, b), "T=%d D=%d G=%d %s to %s" % (T, D, G, na, nb))
 
 
+@pytest.mark.parametrize("T,D,G", [(250, 64, 64), (300, 64, 32), (1030, 64, 64), (1535, 128, 128), (3100, 64, 32)])
+def test_windows_across_planes_and_inside_them(T, D, G):
+    """128 planes: windows of 64, 128 and 256 rows that run across planes up to 393215 rows, then windows of a plane."""
+    rng = np.random.default_rng(T)
+    K, V = qkv_synth.make_kv(8, 8, T, D, T, "llama")
+    rd = ref.make_desc(8, 8, T, D, G)
+    a, b = draw_bits(T, rng, [0.4, 0.3, 0.2, 0.1]), draw_bits(T, rng, [0.62, 0.26, 0.08, 0.04])
+    card = ref.quantize_pack(rd, K.numpy().view(np.uint16), V.numpy().view(np.uint16), a, ref.count_bits(a).tolist())
+    hop(card, rd, b, "128 planes, T=%d D=%d G=%d" % (T, D, G))
+
+
+def chain_on_the_gpu(L, H, T, a, b, group_size=64):
+    """Cards too large for the oracle: the call's card against injection and creation on the GPU, byte for byte."""
+    ca, cb = ref.count_bits(a).tolist(), ref.count_bits(b).tolist()
+    a, b = torch.from_numpy(a).to(DEV), torch.from_numpy(b).to(DEV)
+    desc = qkv.Desc.make(L, H, T, 64, group_size)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T)
+    k = torch.randn((L, H, T, 64), dtype=torch.float16, device=DEV, generator=g)
+    v = torch.randn((L, H, T, 64), dtype=torch.float16, device=DEV, generator=g)
+    card = torch.empty(qkv.card_bytes(desc, ca), dtype=torch.uint8, device=DEV)
+    qkv.quantize_pack(desc, k, v, a, ca, card)
+    qkv.unpack_dequant(card, desc, k, v)
+    want = torch.empty(qkv.card_bytes(desc, cb), dtype=torch.uint8, device=DEV)
+    qkv.quantize_pack(desc, k, v, b, cb, want)
+    del k, v
+    out = torch.full((want.numel(),), 0xA5, dtype=torch.uint8, device=DEV)
+    status = torch.full((1,), 0x7777, dtype=torch.int32, device=DEV)
+    qkv.requantize(card, desc, b, cb, out, status=status)
+    assert int(status.item()) == 0
+    assert torch.equal(out, want)
+
+
+def test_more_planes_than_a_grid_is_wide():
+    """2^21 layers times heads of five tokens: a workgroup per plane and width would be a launch of more than 2^32 threads, and windows across
+    planes are more workgroups than stand side by side."""
+    print("[case] requant L=2048 H=1024 T=5", flush=True)
+    chain_on_the_gpu(2048, 1024, 5, np.array([16, 2, 8, 4, 2], np.uint8), np.array([2, 8, 16, 2, 4], np.uint8))
+
+
 @pytest.mark.parametrize("G", [32, 64, 128])
 @pytest.mark.parametrize("kind", ["normal", "subnormal scale", "zero scale", "negative scale", "one code", "two codes", "mixed"])
 def test_two_bit_groups_of_any_content(kind, G):
