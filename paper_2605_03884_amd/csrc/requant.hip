@@ -356,6 +356,11 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
   }
 }
 
+// Workgroups from one plane's first window to the next plane's.  Workgroups go to the eight XCDs in turn: with a multiple
+// of eight a class's windows of all planes would meet on the same ones (1500 tokens, 8 windows a plane: 45.6 us, with
+// a ninth workgroup that leaves at once 37.1).
+__host__ __device__ inline uint32_t odd_stride(uint32_t per_group) { return per_group | 1u; }
+
 template <int G>
 __global__ __launch_bounds__(kBlockThreads) void requant_kernel(RequantArgs a) {
   __shared__ Shared sh;
@@ -367,8 +372,10 @@ __global__ __launch_bounds__(kBlockThreads) void requant_kernel(RequantArgs a) {
   const bool across = a.group_planes == 0u;
   uint32_t p0 = 0, p1 = 1u;
   if (!across) {
-    const uint32_t per_group = a.windows[0] + a.windows[1] + a.windows[2] + a.windows[3], group = k / per_group;
-    k -= group * per_group;
+    const uint32_t per_group = a.windows[0] + a.windows[1] + a.windows[2] + a.windows[3], stride = odd_stride(per_group);
+    const uint32_t group = k / stride;
+    k -= group * stride;
+    if (k >= per_group) return;
     p0 = group * a.group_planes;
     p1 = min(p0 + a.group_planes, a.out.planes);
   }
@@ -395,7 +402,7 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
   // full, at the price of a division per row and of a plane's widths being read at different times, which costs more
   // the less of the cards the 256 MB memory-side cache holds.  Where windows of a plane would be fewer than fill the
   // chip, longer cards' run across planes too.  Kernel alone, us, with windows of a plane and across planes: 512 planes of
-  // 128 values, 200 tokens, budget 3 to 2.5, 17.0 and 9.0; 500 20.0 and 14.2; 1000 25.5 and 21.5; 1500, 6 to 4, 45.6
+  // 128 values, 200 tokens, budget 3 to 2.5, 17.0 and 9.0; 500 20.0 and 14.2; 1000 25.5 and 21.5; 1500, 6 to 4, 37.1
   // and 36.4; 2000, 6 to 4, 45.3 and 47.4.  2048 planes, 850 tokens, 6 to 4 (310 MB) 85.9 and 86.5, 1400 143 and 155; of 256
   // values 700 tokens 122 and 131.  64 planes of 6000 tokens 23.1 and 21.0, 16 of 32768 27.0 and 27.1.  Smaller windows
   // while there are few: 200 tokens, 6 to 4, 11.6 with 128 rows and 12.1 with 256, 64 tokens 7.4 with 64 rows and 8.0 with 128.
@@ -418,7 +425,7 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
     uint32_t group = resident ? kMaxPlanes : 1u;
     while (group > 1u && blocks * ((out.planes + group - 1u) / group) < 8192u) group /= 2u;
     a.group_planes = group;
-    blocks *= (out.planes + group - 1u) / group;
+    blocks = (uint64_t)odd_stride((uint32_t)blocks) * ((out.planes + group - 1u) / group);
   }
   a.blocks = (uint32_t)blocks;
   const uint32_t grid_y = (a.blocks + kMaxGridX - 1u) / kMaxGridX, grid_x = (a.blocks + grid_y - 1u) / grid_y;

@@ -45,13 +45,16 @@ def test_window_edges(T, D, G):
             hop(card, rd, draw_bits(T, rng, b), "T=%d D=%d G=%d %s to %s" % (T, D, G, na, nb))
 
 
-@pytest.mark.parametrize("T,D,G", [(250, 64, 64), (300, 64, 32), (1030, 64, 64), (1535, 128, 128), (3100, 64, 32)])
+@pytest.mark.parametrize("T,D,G", [(250, 64, 64), (300, 64, 32), (1030, 64, 64), (1535, 128, 128), (3100, 64, 32), (3200, 64, 64)])
 def test_windows_across_planes_and_inside_them(T, D, G):
-    """128 planes: windows of 64, 128 and 256 rows that run across planes up to 393215 rows, then windows of a plane."""
+    """128 planes: windows of 64, 128 and 256 rows that run across planes up to 393215 rows, then windows of a plane (3100 and
+    3200 tokens: an even and an odd number of them)."""
     rng = np.random.default_rng(T)
     K, V = qkv_synth.make_kv(8, 8, T, D, T, "llama")
     rd = ref.make_desc(8, 8, T, D, G)
     a, b = draw_bits(T, rng, [0.4, 0.3, 0.2, 0.1]), draw_bits(T, rng, [0.62, 0.26, 0.08, 0.04])
+    if T > 3000:
+        assert sum((n + 255) // 256 for n in ref.count_bits(b).tolist()) % 2 == (T == 3200)
     card = ref.quantize_pack(rd, K.numpy().view(np.uint16), V.numpy().view(np.uint16), a, ref.count_bits(a).tolist())
     hop(card, rd, b, "128 planes, T=%d D=%d G=%d" % (T, D, G))
 
