@@ -81,6 +81,18 @@ def chain_on_the_gpu(L, H, T, a, b, group_size=64):
     assert torch.equal(out, want)
 
 
+def test_two_planes_per_workgroup():
+    """2176 planes in pairs that share their look-ups: at least 8192 workgroups, both cards below 512 MiB."""
+    L, H, T = 64, 17, 1600
+    print("[case] requant L=%d H=%d T=%d, two planes a workgroup" % (L, H, T), flush=True)
+    rng = np.random.default_rng(1)
+    a, b = draw_bits(T, rng, [0.4, 0.3, 0.2, 0.1]), draw_bits(T, rng, [0.5, 0.3, 0.15, 0.05])
+    windows = sum((n + 255) // 256 for n in ref.count_bits(b).tolist())
+    assert windows * L * H >= 8192 and 2 * L * H * T >= 1536 * 256
+    assert max(qkv.card_bytes(qkv.Desc.make(L, H, T, 64, 64), ref.count_bits(x).tolist()) for x in (a, b)) <= 512 << 20
+    chain_on_the_gpu(L, H, T, a, b)
+
+
 def test_more_planes_than_a_grid_is_wide():
     """2^21 layers times heads of five tokens: a workgroup per plane and width would be a launch of more than 2^32 threads, and windows across
     planes are more workgroups than stand side by side."""
