@@ -876,8 +876,13 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
 // The number of tasks that short sequences are better cut into, where the workspace has room for their partials: one
 // per wave slot of the chip, but no more than there are units of work at a middling mix of widths (an empty task still
 // costs its dispatch).  Up to 4 query heads per kv head and head_dim 128: beyond, a task's fixed part is heavier, and the
-// call got slower (3877 tokens with 8 heads 29.6 -> 31.9 us, 6000 tokens at head_dim 256 61.4 -> 62.4).  Not beyond the fixed scratch array, so that the call that uses it cuts
-// its tasks - and rounds its sums - like the one with a workspace.
+// call got slower where it was tried (3877 tokens with 8 heads 29.6 -> 31.9 us, 6000 tokens at head_dim 256 61.4 -> 62.4).
+// Never a multiple of four: tasks go to the eight XCDs in turn, and the same task of all pairs - an empty one above all -
+// would land on the same one or two of them (attention kernel alone, 256 pairs, 2000 tokens at budget 4: 28.9 us with 14
+// tasks a pair, 37.7 with 16, 23.7 with 15; 1024 tokens of uniform 8 bits, keys per channel, 28.0 with 9, 31.4 with 16, 23.4
+// with 15; 384 pairs, 500 tokens: 16.4 with 10, 17.6 with 9).
+// Not beyond the fixed scratch array, so that the call that uses it cuts its tasks - and rounds its sums - like the
+// one with a workspace.
 uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t head_dim, uint32_t max_tasks) {
   if (rep > 4u || head_dim > 128u) return max_tasks;
   const uint64_t slots = 256u * 4u * 4u;
@@ -886,6 +891,7 @@ uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32
   if (want > useful) want = useful;
   const uint64_t fits = (QKV_ATTEND_STATIC_SCRATCH_BYTES / sizeof(float) - 4u) / (pairs * rep * (head_dim + 2u));
   if (want > fits) want = fits;
+  if (want % 4u == 0u && want != 0u) --want;
   return want > max_tasks ? (uint32_t)want : max_tasks;
 }
 
