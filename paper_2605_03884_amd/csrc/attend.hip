@@ -47,6 +47,7 @@ constexpr int kAttendWaves = 1;              // waves per workgroup (they would 
 // Rounds whose loads are in flight ahead of the arithmetic: as many as the registers allow
 // (a fetched span is 3 / 5 / 9 / 16 registers at 2 / 4 / 8 / 16 bits).
 template <int W> struct Prefetch { static constexpr int kRounds = (W == 2) ? 4 : (W == 4) ? 3 : (W == 8) ? 2 : 1; };
+constexpr uint32_t kUnit[4] = {64u, 48u, 32u, 16u};      // tokens of such a group of rounds, by class
 constexpr int kLdsFloatsPerWave = 1536;      // scores of one task: chunk tokens x padded query heads (6 KiB)
 
 struct AttendArgs {
@@ -62,7 +63,9 @@ struct AttendArgs {
   float* part_ml;          // [L*H][max_tasks][R][2]  (m in log2 units, l); l = 0 marks an empty task
   uint32_t max_tasks;      // tasks per (layer, kv head) the workspace was sized for
   uint32_t chunk;          // tokens per task at most
-  uint32_t unit[4];        // tokens of a class that make up one unit of work, see task_rows
+  uint32_t even_limit;     // units of work per (layer, kv head) up to which tasks are cut evenly, see find_task; 0: never
+  uint32_t unit[4];        // tokens of a class that make up one unit (read where keys are grouped per channel, kUnit otherwise)
+  uint32_t fit[4];         // chunk / unit
   float* out;              // fp32 [L][Hq][D]
   float* lse;              // fp32 [L][Hq] or null
   uint32_t* status;        // or null
@@ -696,26 +699,60 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
   }
 }
 
-// Rows a task of every class takes.  Long sequences: `chunk` of any class, the most LDS allows.  Where there are more
-// tasks than that needs, all of them get the same number of units: a unit is one group of rounds whose loads
-// are in flight together - fewer tokens at larger widths - so a task lasts about as long whatever its width,
-// and the longest one decides how long a short card takes (whole call, 1K tokens at budget 5, 256 pairs: 27.7 us with
-// 192 rows of any width a task, 23.9 us; 300 tokens: 18.3 and 15.2 us).
-// With s units a task there are at most sum (u_c + s - 1) / s tasks over the k classes present, so
+// Which class and which of its rows [j0, j1) task `tau` of a (layer, kv head) covers; -1: a spare task.
+//
+// Usually a task takes `chunk` rows of any class, the most LDS allows.  Where a pair has few rows (even_limit), all
+// tasks get the same number of units: a unit is one group of rounds whose loads are in flight together - fewer tokens
+// at larger widths - so a task lasts about as long whatever its width, and the longest one decides how long a short card
+// takes (whole call, 1K tokens at budget 5, 256 pairs: 27.7 us with 192 rows of any width a task, 23.9 us; 300 tokens: 18.3 and
+// 15.2 us).  With s units a task there are at most sum (u_c + s - 1) / s tasks over the k classes present, so
 // s >= (sum u_c - k) / (max_tasks - k) keeps them within max_tasks.
-__device__ inline void task_rows(const AttendArgs& a, const CardGeom& g, uint32_t (&rows)[4]) {
-  uint32_t sum = 0, present = 0, most = ~0u;             // most: units that fit a task of every class present
+//
+// Every wave goes through this between the header and its first load, so it has as few divisions in a row as can be: the
+// classes share one divisor, the units are constants (keys per channel apart, where one class has rows).  With a division
+// by a different number for every class the kernel lost 0.4 to 0.8 us on any card, more with more waves: 8000 tokens of 256
+// pairs at head_dim 64 70.0 -> 75.2 us, 3000 tokens of 384 pairs at 16 heads 65.7 -> 72.0; now 69.4 and 65.3.
+template <bool KC>
+__device__ inline int find_task(const AttendArgs& a, const CardGeom& g, uint32_t tau, uint32_t& j0, uint32_t& j1) {
+  int cls = -1;
+  // one divisor for all classes: its reciprocal is worked out once, ahead of the header's arrival where it is `chunk`
+  const auto walk = [&](const uint32_t (&count)[4], const uint32_t (&step)[4], uint32_t per) {
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    if (g.n[c] == 0u) continue;
-    sum += (g.n[c] + a.unit[c] - 1u) / a.unit[c];
-    ++present;
-    most = min(most, a.chunk / a.unit[c]);
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t tasks = (count[c] + per - 1u) / per;
+      if (cls < 0) {
+        if (tau < tasks) {
+          cls = c;
+          j0 = tau * per * step[c];
+          j1 = min(g.n[c], j0 + per * step[c]);
+        } else {
+          tau -= tasks;
+        }
+      }
+    }
+  };
+  if (a.even_limit != 0u) {
+    uint32_t unit[4], units[4], sum = 0, present = 0, most = ~0u;      // most: units that fit a task of every class present
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      unit[c] = KC ? a.unit[c] : kUnit[c];
+      units[c] = g.n[c] == 0u ? 0u : (g.n[c] + unit[c] - 1u) / unit[c];
+      sum += units[c];
+      present += (uint32_t)(g.n[c] != 0u);
+      most = g.n[c] == 0u ? most : min(most, a.fit[c]);
+    }
+    if (sum <= a.even_limit) {
+      const uint32_t room = a.max_tasks - present;         // max_tasks is at least 4
+      const uint32_t share = room == 0u ? ~0u : max(1u, (sum - present + room - 1u) / room);
+      if (share <= most) {
+        walk(units, unit, share);
+        return cls;
+      }
+    }
   }
-  const uint32_t room = a.max_tasks - present;           // max_tasks is at least 4
-  const uint32_t share = room == 0u ? ~0u : max(1u, (sum - present + room - 1u) / room);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) rows[c] = share <= most ? share * a.unit[c] : a.chunk;
+  const uint32_t rows[4] = {1u, 1u, 1u, 1u};
+  walk(g.n, rows, a.chunk);
+  return cls;
 }
 
 // KC: the card's key planes are grouped per channel (a uniform card at 2, 4 or 8 bits, group size 32).
@@ -745,27 +782,11 @@ void attend_kernel(AttendArgs a) {
   const uint32_t pairs = g.planes >> 1;
   const uint32_t pair = gw / a.max_tasks;
   if (pair >= pairs) return;
-  uint32_t tau = gw - pair * a.max_tasks;
+  const uint32_t tau = gw - pair * a.max_tasks;
   const uint64_t part = (uint64_t)pair * a.max_tasks + tau;
 
-  // which class and which rows this task covers
-  int cls = -1;
   uint32_t j0 = 0, j1 = 0;
-  uint32_t rows[4];
-  task_rows(a, g, rows);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const uint32_t chunks = (g.n[c] + rows[c] - 1) / rows[c];
-    if (cls < 0) {
-      if (tau < chunks) {
-        cls = c;
-        j0 = tau * rows[c];
-        j1 = min(g.n[c], j0 + rows[c]);
-      } else {
-        tau -= chunks;
-      }
-    }
-  }
+  const int cls = find_task<KC>(a, g, tau, j0, j1);
   if (cls < 0) {                               // spare task: an empty partial
     for (uint32_t r = lane; r < a.rep; r += kWaveSize) {
       a.part_ml[(part * a.rep + r) * 2] = -INFINITY;
@@ -855,6 +876,8 @@ __global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(AttendArgs 
 
 }  // namespace
 
+constexpr uint64_t kWaveSlots = 256u * 4u * 4u;        // four waves on each of the four SIMDs of 256 compute units
+
 // Tokens per task and tasks per (layer, kv head) for a given shape.  The scores of one task (tokens x
 // query heads padded to a multiple of 4) must fit the wave's 6 KiB of LDS.  Tasks are processed in groups
 // of 4, 3, 2 or 1 rounds of 16 tokens, depending on the width, and a task size that all of these divide
@@ -866,9 +889,8 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
   const uint32_t r4 = (rep + 3u) & ~3u;
   const uint32_t room = kLdsFloatsPerWave / r4;                 // tokens whose scores fit, 96 at least
   const uint32_t limit = room >= 192u ? room / 192u * 192u : 64u;
-  const uint64_t slots = 256u * 4u * 4u;
   uint32_t c = limit;
-  while (c > 192u && pairs * ((tokens + c - 1) / c + 2u) < slots) c -= 192u;
+  while (c > 192u && pairs * ((tokens + c - 1) / c + 2u) < kWaveSlots) c -= 192u;
   *chunk = c;
   *max_tasks = (uint32_t)((tokens + *chunk - 1) / *chunk) + 3u;   // every class may end with a partly filled task
 }
@@ -885,8 +907,7 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
 // one with a workspace.
 uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t head_dim, uint32_t max_tasks) {
   if (rep > 4u || head_dim > 128u) return max_tasks;
-  const uint64_t slots = 256u * 4u * 4u;
-  uint64_t want = slots / pairs;
+  uint64_t want = kWaveSlots / pairs;
   const uint64_t useful = tokens / 48u + 3u;
   if (want > useful) want = useful;
   const uint64_t fits = (QKV_ATTEND_STATIC_SCRATCH_BYTES / sizeof(float) - 4u) / (pairs * rep * (head_dim + 2u));
@@ -948,10 +969,15 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
   // a group of rounds whose loads are in flight together: 4, 3, 2 or 1 rounds of 16 tokens; keys grouped per channel are
   // scored up to 128 tokens at a time, in whole blocks of 32
   const bool wide_units = keys_per_channel && a.chunk >= 128u;
-  a.unit[0] = wide_units ? 128u : 64u;
-  a.unit[1] = keys_per_channel ? (a.chunk >= 96u ? 96u : 64u) : 48u;
-  a.unit[2] = wide_units ? 128u : 32u;
-  a.unit[3] = 16u;
+  a.unit[0] = wide_units ? 128u : kUnit[0];
+  a.unit[1] = keys_per_channel ? (a.chunk >= 96u ? 96u : 64u) : kUnit[1];
+  a.unit[2] = wide_units ? 128u : kUnit[2];
+  a.unit[3] = kUnit[3];
+  for (int c = 0; c < 4; ++c) a.fit[c] = a.chunk / a.unit[c];
+  // Up to two units per wave slot: beyond, the call is bound by its bytes, and more tasks only add their fixed parts (uniform
+  // 16 bits, attention kernel alone, evenly cut and by `chunk`: 200 tokens 9.2 and 14.8 us, 500 15.4 and 17.7, 1000 23.6 and 24.0,
+  // 3000 78.5 and 75.6; 384 pairs of head_dim 64, 1000 tokens at budget 4, 2.15 units per slot: 22.1 and 21.2).
+  a.even_limit = (uint32_t)(2u * kWaveSlots / pairs);
   a.part_o = workspace;
   a.part_ml = workspace + pairs * a.max_tasks * a.rep * D;
   a.valid = reinterpret_cast<uint32_t*>(workspace + pairs * a.max_tasks * a.rep * (D + 2u));

@@ -68,3 +68,23 @@ def test_merge_over_many_tasks(D, rep, T):
     torch.cuda.synchronize()
     assert float(np.abs(out.cpu().numpy() - want_o).max()) <= tol_o
     assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
+
+
+@pytest.mark.parametrize("T,rep", [(512, 4), (513, 4), (512, 16), (513, 16)])
+@pytest.mark.parametrize("mix", ["16", "low"])
+def test_around_the_limit_of_the_even_cut(T, rep, mix):
+    """256 pairs: tasks of equal length up to 32 units a pair (512 tokens of 16 bits), tasks of equal size beyond."""
+    L, H, D = 32, 8, 64
+    print("[case] T=%d rep=%d widths %s" % (T, rep, mix), flush=True)
+    rng = np.random.default_rng(T + rep)
+    bits = np.full(T, 16, np.uint8) if mix == "16" else rng.choice(np.array([2, 4, 8, 16], np.uint8), size=T, p=[0.2, 0.1, 0.1, 0.6])
+    rd, card = build_card(L, H, T, D, 64, bits, T)
+    q = rng.standard_normal((L, H * rep, D)).astype(np.float16)
+    want_o, want_lse = attend_ref.card_attend(card, rd, q, D ** -0.5)
+    tol_o, tol_lse = bounds(card, rd, q, D ** -0.5)
+    out = torch.empty((L, H * rep, D), device=DEV)
+    lse = torch.empty((L, H * rep), device=DEV)
+    qkv.card_attend(torch.from_numpy(card).to(DEV), qkv.Desc.make(L, H, T, D, 64), torch.from_numpy(q).to(DEV), D ** -0.5, out, lse=lse)
+    torch.cuda.synchronize()
+    assert float(np.abs(out.cpu().numpy() - want_o).max()) <= tol_o
+    assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
