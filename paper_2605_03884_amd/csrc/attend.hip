@@ -812,11 +812,10 @@ void attend_kernel(AttendArgs a) {
 // a thread per task; then every group of head_dim / 4 threads adds up its share of the tasks, four output
 // dimensions per thread, and the groups' sums are added in order.  Bound by the latency of one trip to the partials:
 // one thread per dimension walking over all tasks, with the weights' exponentials in the loop, took 7.6 us at 8K tokens
-// (25 tasks); this takes 6.4.
-constexpr int kMergeBatch = 256;             // tasks whose weights are held in LDS at a time
-constexpr int kMergeThreads = 256;
-
+// (25 tasks); this takes 5.8.  How many threads: merge_threads.
+template <int kMergeThreads>
 __global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(AttendArgs a) {
+  constexpr int kMergeBatch = kMergeThreads;           // tasks whose weights are held in LDS at a time
   __shared__ float weight[kMergeBatch];
   __shared__ float part_max[kMergeThreads / kWaveSize], part_den[kMergeThreads / kWaveSize];
   __shared__ f32x4 sums[kMergeThreads];
@@ -947,6 +946,16 @@ hipError_t attend_static_scratch(float** ptr) {
   return hipSuccess;
 }
 
+// Threads of a merging workgroup.  Few workgroups: 256, the partials of many tasks are under way at once.  More of them
+// than 256 threads each find room for: fewer, and one wave, which waits for no other, where that reads the partials in a
+// few trips.  Merge alone, us, with 256 / 128 / 64 threads (and with one thread per dimension): 1024 workgroups, head_dim
+// 128, 25 tasks 5.8 / 6.2 / 8.6 (7.6); 2048, 128, 5 tasks 4.9 / 4.0 / 4.2 (4.4); 3072, 64, 9 tasks 7.3 / 5.0 / 4.8 (4.9);
+// 4096, 64, 7 tasks 8.2 / 5.0 / 4.5 (5.0), 128, 128 tasks 60 / 53 / 66 (77); 6144, 64, 7 tasks 11.1 / 7.8 / 5.6 (5.7).
+static uint32_t merge_threads(uint32_t workgroups, uint32_t tasks, uint32_t head_dim) {
+  if (workgroups <= 1024u) return 256u;
+  return workgroups <= 2048u || tasks * head_dim / 4u > 256u ? 128u : 64u;
+}
+
 hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, const void* q,
                          uint32_t q_heads, float softmax_scale, float* out, float* lse, float* workspace,
                          uint64_t workspace_bytes, uint32_t* status, bool keys_per_channel, hipStream_t stream) {
@@ -1011,7 +1020,11 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
 #undef QKV_LAUNCH_ATTEND
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attend_merge_kernel, dim3(expect.layers * q_heads), dim3(kMergeThreads), 0, stream, a);
+  const dim3 merge_grid(expect.layers * q_heads);
+  const uint32_t threads = merge_threads(merge_grid.x, a.max_tasks, D);
+  if (threads == 64u) hipLaunchKernelGGL(attend_merge_kernel<64>, merge_grid, dim3(64), 0, stream, a);
+  else if (threads == 128u) hipLaunchKernelGGL(attend_merge_kernel<128>, merge_grid, dim3(128), 0, stream, a);
+  else hipLaunchKernelGGL(attend_merge_kernel<256>, merge_grid, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

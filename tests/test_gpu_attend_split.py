@@ -88,3 +88,25 @@ def test_around_the_limit_of_the_even_cut(T, rep, mix):
     torch.cuda.synchronize()
     assert float(np.abs(out.cpu().numpy() - want_o).max()) <= tol_o
     assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
+
+
+@pytest.mark.parametrize("L,H,T,D,rep,tasks", [(8, 16, 300, 64, 16, 8), (8, 16, 300, 256, 16, 8), (17, 8, 300, 128, 9, 8), (5, 26, 8300, 64, 16, 133),
+                                               (30, 16, 130, 64, 5, 4), (16, 16, 70, 128, 16, 5), (16, 16, 60, 256, 16, 4)])
+def test_merge_with_fewer_threads(L, H, T, D, rep, tasks):
+    """More than 1024 and 2048 workgroups of the merge: 128 threads (also with more tasks than that), and 64 where a task's rows are few."""
+    print("[case] L=%d H=%d T=%d D=%d rep=%d" % (L, H, T, D, rep), flush=True)
+    assert L * H * rep > 1024
+    desc = qkv.Desc.make(L, H, T, D, 64)
+    assert (qkv.card_attend_workspace(desc, H * rep) // 4 - 4) // (L * H * rep * (D + 2)) == tasks
+    rng = np.random.default_rng(D + rep)
+    bits = rng.choice(np.array([2, 4, 8, 16], np.uint8), size=T, p=[0.5, 0.3, 0.15, 0.05])
+    rd, card = build_card(L, H, T, D, 64, bits, T)
+    q = rng.standard_normal((L, H * rep, D)).astype(np.float16)
+    want_o, want_lse = attend_ref.card_attend(card, rd, q, D ** -0.5)
+    tol_o, tol_lse = bounds(card, rd, q, D ** -0.5)
+    out = torch.empty((L, H * rep, D), device=DEV)
+    lse = torch.empty((L, H * rep), device=DEV)
+    qkv.card_attend(torch.from_numpy(card).to(DEV), desc, torch.from_numpy(q).to(DEV), D ** -0.5, out, lse=lse)
+    torch.cuda.synchronize()
+    assert float(np.abs(out.cpu().numpy() - want_o).max()) <= tol_o
+    assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
