@@ -27,37 +27,49 @@ constexpr int kFeatures = 6, kHidden = 64;
 
 // The parameters go through LDS, a hidden unit's eight side by side: read straight from the arguments they are 35
 // scalar loads that each wait for the one before (registers hold only four of them at a time), which made
-// 8192 tokens take 9.2 us; 5.0 now.
+// 8192 tokens take 9.2 us; 5.0 now.  TOKENS per thread: launch_controller.
+template <int TOKENS>
 __global__ __launch_bounds__(256) void controller_kernel(const float* __restrict__ features, uint32_t T,
                                                          qkv_controller_t p, float* __restrict__ scores) {
   __shared__ __attribute__((aligned(16))) float unit[kHidden][8];       // six weights, bias, output weight
-  const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-  float x[kFeatures] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (t < T) {
-    const float2* row = reinterpret_cast<const float2*>(features + (uint64_t)t * kFeatures);   // 24-byte rows
-    const float2 x01 = row[0], x23 = row[1], x45 = row[2];
-    x[0] = x01.x; x[1] = x01.y; x[2] = x23.x; x[3] = x23.y; x[4] = x45.x; x[5] = x45.y;
+  const uint32_t t0 = blockIdx.x * (256u * TOKENS) + threadIdx.x;
+  float x[TOKENS][kFeatures], s[TOKENS];
+#pragma unroll
+  for (int k = 0; k < TOKENS; ++k) {
+    const uint32_t t = t0 + 256u * k;
+    s[k] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kFeatures; ++i) x[k][i] = 0.0f;
+    if (t < T) {
+      const float2* row = reinterpret_cast<const float2*>(features + (uint64_t)t * kFeatures);   // 24-byte rows
+      const float2 x01 = row[0], x23 = row[1], x45 = row[2];
+      x[k][0] = x01.x; x[k][1] = x01.y; x[k][2] = x23.x; x[k][3] = x23.y; x[k][4] = x45.x; x[k][5] = x45.y;
+    }
   }
   const float* w1 = &p.w1[0][0];
   for (uint32_t i = threadIdx.x; i < kHidden * kFeatures; i += 256u) unit[i / kFeatures][i % kFeatures] = w1[i];
   if (threadIdx.x < kHidden) unit[threadIdx.x][6] = p.b1[threadIdx.x];
   else if (threadIdx.x < 2u * kHidden) unit[threadIdx.x - kHidden][7] = p.w2[threadIdx.x - kHidden];
   __syncthreads();
-  float s = 0.0f;
-#pragma unroll 16
+#pragma unroll 16 / TOKENS
   for (int j = 0; j < kHidden; ++j) {
     const float4 u0 = *reinterpret_cast<const float4*>(&unit[j][0]), u1 = *reinterpret_cast<const float4*>(&unit[j][4]);
-    float a = u1.z;
-    a = __builtin_fmaf(x[0], u0.x, a);
-    a = __builtin_fmaf(x[1], u0.y, a);
-    a = __builtin_fmaf(x[2], u0.z, a);
-    a = __builtin_fmaf(x[3], u0.w, a);
-    a = __builtin_fmaf(x[4], u1.x, a);
-    a = __builtin_fmaf(x[5], u1.y, a);
-    const float h = a > 0.0f ? a : 0.0f;       // NaN -> 0
-    s = __builtin_fmaf(h, u1.w, s);
+#pragma unroll
+    for (int k = 0; k < TOKENS; ++k) {
+      float a = u1.z;
+      a = __builtin_fmaf(x[k][0], u0.x, a);
+      a = __builtin_fmaf(x[k][1], u0.y, a);
+      a = __builtin_fmaf(x[k][2], u0.z, a);
+      a = __builtin_fmaf(x[k][3], u0.w, a);
+      a = __builtin_fmaf(x[k][4], u1.x, a);
+      a = __builtin_fmaf(x[k][5], u1.y, a);
+      const float h = a > 0.0f ? a : 0.0f;       // NaN -> 0
+      s[k] = __builtin_fmaf(h, u1.w, s[k]);
+    }
   }
-  if (t < T) scores[t] = s;
+#pragma unroll
+  for (int k = 0; k < TOKENS; ++k)
+    if (t0 + 256u * k < T) scores[t0 + 256u * k] = s[k];
 }
 
 // ---- the greedy allocator -----------------------------------------------------------------------
@@ -485,8 +497,12 @@ hipError_t launch_greedy_long(const float* scores, uint32_t tokens, uint32_t spa
 
 hipError_t launch_controller(const float* features, uint32_t tokens, const qkv_controller_t& params, float* scores,
                              hipStream_t stream) {
-  hipLaunchKernelGGL(controller_kernel, dim3((tokens + 255u) / 256u), dim3(256), 0, stream, features, tokens, params,
-                     scores);
+  // Beyond 128K tokens the parameters' trips through LDS are what bounds it: two tokens then share one (1, 2 and 4 tokens a
+  // thread: 131072 tokens 5.5 / 5.8 / 7.7 us, 200000 7.1 / 6.5 / 7.9, 1M 19.0 / 14.6 / 14.2; without LDS 5.5, 6.4 and 17.9).
+  if (tokens <= 131072u)
+    hipLaunchKernelGGL(controller_kernel<1>, dim3((tokens + 255u) / 256u), dim3(256), 0, stream, features, tokens, params, scores);
+  else
+    hipLaunchKernelGGL(controller_kernel<2>, dim3((tokens + 511u) / 512u), dim3(256), 0, stream, features, tokens, params, scores);
   return hipGetLastError();
 }
 

@@ -33,6 +33,18 @@ def test_scores_match_oracle_bit_for_bit(T):
     assert np.array_equal(got.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("T", [131072, 131073, 131328, 131329, 200000])
+def test_scores_of_long_sequences(T):
+    """Two tokens a thread beyond 131072: remainders of the first and the second half of a workgroup's tokens."""
+    say("controller_scores T=%d" % T)
+    w1, b1, w2, params = net(T)
+    x = qkv_synth.make_features(T, T).numpy()
+    got = qkv.controller_scores(torch.from_numpy(x).to(DEV), params)
+    torch.cuda.synchronize()
+    want = ref.controller_scores(x, w1, b1, w2)
+    assert np.array_equal(got.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 def test_scores_special_values():
     say("controller_scores special values")
     rng = np.random.default_rng(7)
