@@ -164,7 +164,9 @@ int qkv_budget_counts(int64_t tokens, double avg_bits_budget, int64_t counts_out
  * index ascending), scores compared in the IEEE total order (-0 < +0; NaN is a
  * precondition violation); the first n16 get 16, the next n8 get 8, the next n4
  * get 4, the rest 2, with the counts of qkv_budget_counts.
- *   scores_dev: device, float[T].   bits_dev: device, uint8_t[T], written.
+ *   scores_dev: device, float[T].   bits_dev: device, uint8_t[T], written.  Beyond 32768 tokens it
+ *   holds intermediate counts until the call's last kernel: its bytes are widths only once all of the call's
+ *   work has run.
  *   counts_out: host, int64_t[4], filled before return without a device sync.
  * Asynchronous on `stream`.
  */
@@ -216,7 +218,8 @@ int qkv_controller_scores(const float* features_dev, int64_t tokens, const qkv_c
  * descending, level ascending, token index ascending) and the longest prefix whose cost fits
  * floor(budget * T) - 2T bits is taken; the budget is read as in qkv_assign_bits (rounded to
  * 1/1000 bit).  The class counts depend on the scores, so they are produced on the device:
- *   scores_dev: device, float[T], 4-byte aligned.   bits_dev: device, uint8_t[T], written.
+ *   scores_dev: device, float[T], 4-byte aligned.   bits_dev: device, uint8_t[T], written (beyond
+ *   32768 tokens intermediate counts first, as in qkv_assign_bits).
  *   counts_dev: device, uint64_t[4] for widths 2,4,8,16, 8-byte aligned, written; may be NULL.
  * Asynchronous on `stream`; allocates nothing.
  * Errors: QKV_ERR_NULL, QKV_ERR_SHAPE (T < 1 or T >= 2^28), QKV_ERR_BUDGET, QKV_ERR_ALIGN, QKV_ERR_HIP.
@@ -275,7 +278,8 @@ int qkv_card_fill(const qkv_desc_t* desc, const void* k_dev, const void* v_dev, 
  *   bits_dev:   device, uint8_t[T], written; may be NULL (the widths are in the card anyway).
  *   counts_out: host, int64_t[4]: the budget's class counts (= qkv_budget_counts), filled before
  *               return without a device sync; pass them on to qkv_card_fill.
- *   card_dev:   device, 256-byte aligned, card_capacity >= qkv_card_bytes(desc, counts_out).
+ *   card_dev:   device, 256-byte aligned, card_capacity >= qkv_card_bytes(desc, counts_out).  Beyond
+ *               16384 tokens its slot and order tables hold intermediate counts until the call's last kernel.
  * qkv_card_fill on the same stream completes the card.  qkv_assign_quantize_pack is the two in
  * one call: scores, budget and K/V in, widths and the whole card out (k_dev, v_dev as for
  * qkv_quantize_pack).  Asynchronous on `stream`; allocate nothing.
@@ -421,8 +425,14 @@ int qkv_requantize(const void* card_in_dev, uint64_t card_in_bytes, const qkv_de
  *   out_dev:  device, float [layers][q_heads][head_dim], 16-byte aligned, written in full.
  *   lse_dev:  device, float [layers][q_heads], may be NULL.  With (out, lse) the caller can
  *             merge this result with attention over its own tokens.
- *   workspace_dev: device scratch of at least qkv_card_attend_workspace() bytes, 16-byte
- *             aligned; contents on entry and exit are unspecified.
+ *   workspace_dev: device scratch of qkv_card_attend_workspace() bytes or more, 16-byte
+ *             aligned; contents on entry and exit are unspecified.  workspace_bytes beyond that
+ *             change nothing.  Short cards (up to 4 query heads per kv head, head_dim up to 128) are cut
+ *             into more tasks than the call needs at least, and that size has room for them; a
+ *             smaller workspace is accepted down to the one for the least number of tasks
+ *             (QKV_ERR_CAPACITY below it).  With less than the full size the sums are taken in another
+ *             order: out and lse then differ in their last bits, within the bound above, and the
+ *             call takes longer.
  * When the header does not match, out / lse are left untouched (status_dev says so).
  * Asynchronous on `stream`.
  *
@@ -455,7 +465,8 @@ int qkv_card_attend_kc(const void* card_dev, uint64_t card_bytes, const qkv_desc
 /*
  * qkv_card_attend for callers that cannot allocate device memory - code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc: the same kernels, the same results bit for
- * bit, with the partials kept in a fixed array inside the library instead of a caller's workspace.
+ * bit as with a workspace of at least qkv_card_attend_workspace() bytes, with the partials kept in a
+ * fixed array inside the library instead of a caller's workspace.
  * Arguments as for qkv_card_attend, without the workspace.  The call allocates and frees nothing.
  *   - The array holds QKV_ATTEND_STATIC_SCRATCH_BYTES per GPU the library runs on, from the first
  *     call on that GPU until the process ends.  A shape whose qkv_card_attend_workspace() exceeds it

@@ -53,8 +53,40 @@ def test_short_cards(T, mix):
         qkv.card_attend(card_dev, desc, q_dev, D ** -0.5, out, lse=lse, workspace=ws[:least - 4])
 
 
-@pytest.mark.parametrize("D,rep,T", [(64, 1, 20000), (128, 3, 14000), (256, 2, 13000), (128, 16, 20000)])
+@pytest.mark.parametrize("L,H,T,D,rep", [(32, 8, 300, 128, 4), (32, 8, 1000, 64, 2), (1, 8, 2000, 128, 4)])
+def test_results_depend_on_the_workspace_size_only_below_the_queried_one(L, H, T, D, rep):
+    """A finer cut than the least: the queried workspace, a larger one and the library's own scratch give the same bits, the
+    smallest workspace accepted gives them to the bound."""
+    print("[case] L=%d H=%d T=%d D=%d rep=%d" % (L, H, T, D, rep), flush=True)
+    rng = np.random.default_rng(T)
+    bits = rng.choice(np.array([2, 4, 8, 16], np.uint8), size=T, p=[0.5, 0.3, 0.15, 0.05])
+    rd, card = build_card(L, H, T, D, 32, bits, T)
+    q = rng.standard_normal((L, H * rep, D)).astype(np.float16)
+    want_o, want_lse = attend_ref.card_attend(card, rd, q, D ** -0.5)
+    tol_o, tol_lse = bounds(card, rd, q, D ** -0.5)
+    desc = qkv.Desc.make(L, H, T, D, 32)
+    card_dev, q_dev = torch.from_numpy(card).to(DEV), torch.from_numpy(q).to(DEV)
+    best, least = qkv.card_attend_workspace(desc, H * rep), least_workspace(L, H, T, rep, D)
+    assert best > least
+    results = []
+    for size in (best, best + 4096, least, None):
+        out = torch.full((L, H * rep, D), float("nan"), device=DEV)
+        lse = torch.full((L, H * rep), float("nan"), device=DEV)
+        if size is None:
+            qkv.card_attend_static(card_dev, desc, q_dev, D ** -0.5, out, lse=lse)
+        else:
+            qkv.card_attend(card_dev, desc, q_dev, D ** -0.5, out, lse=lse, workspace=torch.empty(size, dtype=torch.uint8, device=DEV))
+        torch.cuda.synchronize()
+        assert float(np.abs(out.cpu().numpy() - want_o).max()) <= tol_o
+        assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
+        results.append((out, lse))
+    for out, lse in (results[1], results[3]):
+        assert torch.equal(out, results[0][0]) and torch.equal(lse, results[0][1])
+
+
+@pytest.mark.parametrize("D,rep,T", [(64, 1, 20000), (128, 3, 14000), (256, 16, 17000), (128, 16, 20000)])
 def test_merge_over_many_tasks(D, rep, T):
+    assert (qkv.card_attend_workspace(qkv.Desc.make(1, 1, T, D, 32), rep) // 4 - 4) // (rep * (D + 2)) > 256
     print("[case] D=%d rep=%d T=%d" % (D, rep, T), flush=True)
     rng = np.random.default_rng(D + rep)
     bits = rng.choice(np.array([2, 4, 8, 16], np.uint8), size=T, p=[0.5, 0.3, 0.15, 0.05])
