@@ -41,9 +41,11 @@ constexpr int kWaves = kSelectWaves;
 constexpr uint32_t kTop = 4096, kSub = 1024; // buckets of the first pass, and of the two later ones for each cut
 constexpr uint32_t kTopCopies = 2;           // of the first pass's histogram, against same-word atomics: real scores share sign and exponent
 constexpr uint32_t kByteCopies = 16;         // the same for a first pass of 8 bits
-// Longest sequences one workgroup's registers take; assign_long.hip goes on.  With planning the line lies lower, because
-// the chain of launches there also spreads the tables' writing (measured, one workgroup against the chain: widths alone
-// 12 / 24 us at 16384 tokens, 21 / 27 at 32768; with planning 15 / 24 us at 16384, 28 / 25 at 20000, 33 / 26 at 32768).
+// Longest sequences one workgroup's registers take; assign_long.hip goes on.  Widths alone, one workgroup against the chain
+// of launches there: 12 / 24 us at 16384 tokens, 21 / 27 at 32768.  With planning the line lies at the last size of 16
+// keys per thread: with 32 one workgroup is little faster without ties and much slower with (scores without ties: 16385 tokens
+// 21.5 / 24.4 us, 20000 23.0 / 24.6, 24000 23.4 / 24.7, 28000 25.0 / 25.3, 32768 26.1 / 25.3; fifty different scores: 28.2 / 26.5,
+// 30.8 / 26.4, 31.3 / 26.7, 34.5 / 26.9, 35.6 / 26.8).
 constexpr uint32_t kRankedMax = 32768;
 constexpr uint32_t kPlanMax = 16384;
 constexpr uint32_t kShareTokens = 2048;      // tokens whose tables one workgroup writes

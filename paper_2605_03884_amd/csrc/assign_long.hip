@@ -2,14 +2,17 @@
 // (Sec. 4.2.1), for sequences longer than one workgroup's registers hold.  Same rule and same results as assign.hip.
 //
 // Five launches on the caller's stream: three histogram passes over the 32-bit order keys (12, 10 and 10 bits), one
-// workgroup that settles the cuts, and the pass that writes widths (and tables).  Up to 64 workgroups share the
-// tokens, each a run of `per` consecutive ones.  A pass leaves one histogram per workgroup; the next pass's
+// workgroup that settles the cuts, and the pass that writes widths (and tables).  Several workgroups share the
+// tokens, each a run of `per` consecutive ones: widths alone one per 14 KiB of tokens, which is what a workgroup's histograms
+// take of the bits array (2 at 32769 tokens, 9 at 128K, 64 - the most - from 0.9 M on), with planning one per 8192 (3 at 16385,
+// 16 at 128K, 64 from 512K on).  A pass leaves one histogram per workgroup; the next pass's
 // workgroups each add all of them up again and find the buckets of the three cuts by themselves, so nothing is
 // zeroed beforehand, there are no atomics on global memory and no workgroup waits for another.
 //
 // What bounds it: five launches' latencies and the few microseconds each needs for its loads to come back.  The
 // single workgroup that did this before re-read every score from cache in six sweeps: 446 us for 128K tokens, and 30 us
-// for the classification behind it; the chain takes 39 us (5 + 7 + 8 + 9 + 10, kernel trace).
+// for the classification behind it; the chain takes 39 us (5 + 7 + 8 + 9 + 10, kernel trace).  Widths alone: 32769 tokens
+// 106 -> 28 us, 62000 204 -> 28, 128K 449 -> 30, 1M 3624 -> 65.
 //
 // Scratch without a workspace argument: the histograms live where the results go - in the bits array, or, when a
 // card is planned, in its slot and order tables - because nothing is final there before the last launch.  The last

@@ -29,7 +29,8 @@
 // four codes drives v_perm_b32 to pick them.  Rounds are taken in whole groups of 4 / 3 / 2 /
 // 1 (at 2 / 4 / 8 / 16 bits) without a branch in between; rounds past a task's end see zeros and
 // count as -inf.  About 106 registers (head_dim 256: up to 128) and 10 KiB of LDS per wave: four
-// waves per SIMD.
+// waves per SIMD.  Keys grouped per channel take 125 registers at head_dim 64 and up to 4 heads, else 130 to
+// 140: three waves.
 
 #include <atomic>
 
@@ -896,8 +897,10 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
 
 // The number of tasks that short sequences are better cut into, where the workspace has room for their partials: one
 // per wave slot of the chip, but no more than there are units of work at a middling mix of widths (an empty task still
-// costs its dispatch).  Up to 4 query heads per kv head and head_dim 128: beyond, a task's fixed part is heavier, and the
-// call got slower where it was tried (3877 tokens with 8 heads 29.6 -> 31.9 us, 6000 tokens at head_dim 256 61.4 -> 62.4).
+// costs its dispatch).  Only up to 4 query heads per kv head and head_dim 128: beyond, a task's fixed part and the merge are
+// heavier, and the rule would need a line of its own.  Attention and merge, us, with the least number of tasks and cut like
+// this: 256 pairs, 8 heads, 300 tokens 20.2 and 18.8, 1000 29.6 and 25.0, 4000 55.2 and 55.4; 16 heads, 2000 tokens 51.5 and 53.8;
+// 32 pairs, 8 heads, 1000 tokens 18.6 and 15.3, 4000 20.9 and 23.8; head_dim 256, 4 heads, 1000 23.7 and 19.2, 4000 29.9 and 35.5.
 // Never a multiple of four: tasks go to the eight XCDs in turn, and the same task of all pairs - an empty one above all -
 // would land on the same one or two of them (attention kernel alone, 256 pairs, 2000 tokens at budget 4: 28.9 us with 14
 // tasks a pair, 37.7 with 16, 23.7 with 15; 1024 tokens of uniform 8 bits, keys per channel, 28.0 with 9, 31.4 with 16, 23.4

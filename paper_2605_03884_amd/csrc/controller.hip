@@ -240,11 +240,13 @@ __global__ __launch_bounds__(kThreads) void greedy_kernel(const float* __restric
 
 // ---- longer sequences ------------------------------------------------------------------------------
 //
-// The same three passes as launches, up to 64 workgroups sharing the tokens, then one workgroup that settles the last key
+// The same three passes as launches with several workgroups sharing the tokens, then one workgroup that settles the last key
 // and one launch that writes the widths.  As in assign_long.hip a pass leaves one histogram per workgroup, the next
 // pass's workgroups each add them up, and the histograms live in the bits array, which nothing final is written to
-// before the last launch; what that launch's workgroups need is left at the start of their own part of it.  One
-// workgroup re-reading every score in six sweeps took 450 us for 128K tokens; the chain takes 35.
+// before the last launch; what that launch's workgroups need is left at the start of their own part of it.  A workgroup's
+// histograms take 20 KiB, so there is one workgroup per 20 KiB of tokens: a single one up to 41758 tokens, 6 at 128K, 64 - the
+// most - from 1.3 M on.  One workgroup re-reading every score in six sweeps, and the chain: 32769 tokens 106 and 40 us, 41000
+// 130 and 48, 42000 (two workgroups) 133 and 32, 62000 201 and 40, 128K 452 and 35, 1M 3619 and 58.
 
 constexpr uint32_t kMaxParts = 64;
 

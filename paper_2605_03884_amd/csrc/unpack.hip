@@ -28,7 +28,7 @@ struct UnpackArgs {
   uint8_t* k_out;
   uint8_t* v_out;
   uint32_t* status;                                  // may be null
-  uint32_t check_blocks;                             // 1: workgroup 0 reports for all (verdict_in_grid), the others are silent
+  uint32_t check_blocks;                             // 1: workgroup 0 reports for all (see grid_reports), the others are silent
 };
 
 // Injection into per-layer caches: the same tiles, but only the planes of a layer range,
