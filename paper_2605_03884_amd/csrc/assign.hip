@@ -39,7 +39,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = kSelectThreads;
 constexpr int kWaves = kSelectWaves;
 constexpr uint32_t kTop = 4096, kSub = 1024; // buckets of the first pass, and of the two later ones for each cut
-constexpr uint32_t kTopCopies = 2;           // of the first pass's histogram, against same-word atomics: real scores share sign and exponent
+constexpr uint32_t kTopCopies = 4;           // of the first pass's histogram, against same-word atomics: real scores share sign and exponent
 constexpr uint32_t kByteCopies = 16;         // the same for a first pass of 8 bits
 // Longest sequences one workgroup's registers take; assign_long.hip goes on.  Widths alone, one workgroup against the chain
 // of launches there: 12 / 24 us at 16384 tokens, 21 / 27 at 32768.  With planning the line lies at the last size of 16
@@ -55,10 +55,12 @@ constexpr uint32_t kShareTokens = 2048;      // tokens whose tables one workgrou
 template <int KPT, bool PLAN>
 __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, uint32_t T, uint32_t cut0, uint32_t cut1,
                                             uint32_t cut2, uint8_t* __restrict__ bits, bool aligned, const PlanArgs* plan) {
-  // Up to 2 keys per thread four passes of 8 bits, more keys 12, 10 and 10 bits: a pass less to make over the keys, but
-  // more buckets to clear and add up (widths alone, us: 1024 tokens 4.4 / 4.7, 2048 5.1 / 5.3, 4096 6.1 / 6.1, 8192 8.1 / 7.7,
-  // 16384 13.3 / 11.5, 32768 25.9 / 20.6).
-  constexpr bool kBytes = KPT <= 2;
+  // Up to 8 keys per thread four passes of 8 bits, more keys 12, 10 and 10 bits: a pass less to make over the keys, but
+  // more buckets to clear and add up, and fewer copies of them, which scores that crowd together feel (see lanes_crowd).
+  // Widths alone, us, four passes and three, for uniform scores / a constant / half of them zero: 4096 tokens 6.4 / 16.5 / 6.3
+  // and 6.8 / 14.3 / 7.0, 8192 8.4 / 28.7 / 8.3 and 8.3 / 23.2 / 9.5, 16384 13.6 / 54.0 / 13.3 and 12.4 / 42.2 / 14.2, 32768
+  // 26.3 / 108 / 25.8 and 22.3 / 82.2 / 25.8.
+  constexpr bool kBytes = KPT <= 8;
   // first pass: bucket d, copy c at word [d * copies + c]; later the other passes' histograms; then the stage
   __shared__ u32x4 wide4[(kBytes ? 256u * kByteCopies + 6u * 256u : kTop * kTopCopies) / 4u];
   __shared__ uint32_t sel_prefix[3];                    // key bits fixed so far
@@ -157,13 +159,19 @@ __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, ui
 #pragma unroll
     for (uint32_t i = 0; i < kTop * kTopCopies / 4u / kThreads; ++i) wide4[i * kThreads + tid] = (u32x4)(0u);
     __syncthreads();
+    if (lanes_crowd(keys[0] >> 20, n_own != 0u)) {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i)
-      if ((uint32_t)i < n_own) atomicAdd(&wide[(keys[i] >> 20) * kTopCopies + (lane & (kTopCopies - 1u))], 1u);
+      for (int i = 0; i < KPT; ++i) add_crowded(wide, (keys[i] >> 20) * kTopCopies, (uint32_t)i < n_own, lane);
+    } else {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i)
+        if ((uint32_t)i < n_own) atomicAdd(&wide[(keys[i] >> 20) * kTopCopies + (lane & (kTopCopies - 1u))], 1u);
+    }
     __syncthreads();
     {
-      const u32x4 h0 = wide4[2u * tid], h1 = wide4[2u * tid + 1u];
-      const uint32_t c[4] = {h0.x + h0.y, h0.z + h0.w, h1.x + h1.y, h1.z + h1.w};
+      uint32_t c[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { const u32x4 h = wide4[4u * tid + i]; c[i] = h.x + h.y + h.z + h.w; }
       const uint32_t own[1] = {c[0] + c[1] + c[2] + c[3]};
       uint32_t inc[1], all[1];
       block_scan<1>(own, inc, all, wave_tot, lane, wave);         // every bucket has been read behind its barrier
@@ -182,7 +190,8 @@ __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, ui
     }
     __syncthreads();
 
-    // ---- passes 1 and 2, 10 bits each: per cut, only the keys inside its bucket so far
+    // ---- passes 1 and 2, 10 bits each: per cut, only the keys inside its bucket so far.  Cuts whose prefixes are still the
+    // same share the histogram of the first of them (rep).
 #pragma unroll 1
     for (uint32_t pass = 0; pass < 2u; ++pass) {
       uint32_t pre[3], want[3];
@@ -192,21 +201,32 @@ __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, ui
         want[k] = uniform(sel_left[k]);
       }
       const uint32_t shift = pass == 0u ? 20u : 10u;
+      const uint32_t rep1 = pre[1] == pre[0] ? 0u : 1u, rep2 = pre[2] == pre[0] ? 0u : pre[2] == pre[1] ? 1u : 2u;
       uint32_t* hist = wide + pass * 3u * kSub;
+      if (rep1 == 1u && rep2 == 2u) {
 #pragma unroll
-      for (int i = 0; i < KPT; ++i) {
-        const uint32_t key = keys[i], high = key >> shift;
-        const bool own = (uint32_t)i < n_own;
-        const bool h0 = own && high == pre[0], h1 = own && high == pre[1], h2 = own && high == pre[2];
-        if (__builtin_amdgcn_ballot_w64(h0 || h1 || h2) != 0ull) {           // many waves hold no key of any bucket
-          const uint32_t d = (key >> (shift - 10u)) & (kSub - 1u);
-          if (h0) atomicAdd(&hist[d], 1u);
-          if (h1) atomicAdd(&hist[kSub + d], 1u);
-          if (h2) atomicAdd(&hist[2u * kSub + d], 1u);
+        for (int i = 0; i < KPT; ++i) {
+          const uint32_t key = keys[i], high = key >> shift;
+          const bool own = (uint32_t)i < n_own;
+          const bool h0 = own && high == pre[0], h1 = own && high == pre[1], h2 = own && high == pre[2];
+          if (__builtin_amdgcn_ballot_w64(h0 || h1 || h2) != 0ull) {           // many waves hold no key of any bucket
+            const uint32_t d = (key >> (shift - 10u)) & (kSub - 1u);
+            if (h0) atomicAdd(&hist[d], 1u);
+            if (h1) atomicAdd(&hist[kSub + d], 1u);
+            if (h2) atomicAdd(&hist[2u * kSub + d], 1u);
+          }
+        }
+      } else {
+        const uint32_t only1 = rep1 == 1u ? pre[1] : 0xFFFFFFFFu, only2 = rep2 == 2u ? pre[2] : 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) {
+          const uint32_t key = keys[i], high = key >> shift, d = (key >> (shift - 10u)) & (kSub - 1u);
+          const bool h0 = high == pre[0], h1 = high == only1, h2 = high == only2;      // one of them at most
+          if ((uint32_t)i < n_own && (h0 || h1 || h2)) atomicAdd(&hist[d + (h1 ? kSub : h2 ? 2u * kSub : 0u)], 1u);
         }
       }
       __syncthreads();
-      const uint32_t own[3] = {hist[tid], hist[kSub + tid], hist[2u * kSub + tid]};
+      const uint32_t own[3] = {hist[tid], hist[rep1 * kSub + tid], hist[rep2 * kSub + tid]};
       uint32_t inc[3], all[3];
       block_scan<3>(own, inc, all, wave_tot, lane, wave);
 #pragma unroll

@@ -18,6 +18,29 @@ __device__ inline uint32_t rank_key(float score) {
 
 __device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
+// Histograms in LDS: additions of several lanes to one word are made one after the other, so scores that crowd together (one
+// value, a few, a narrow range) slow a sweep down.  Where the lanes of a wave crowd, those that share the first
+// one's bucket are counted and added at once (16384 tokens of one value, first sweep of assign.hip with two copies: 52 -> 42 us
+// in all; asked once per wave and not per key, which cost 1 us of 8 where they do not crowd).
+//
+// Whether they do: at least half of the lanes with a key (on) are in the bucket d of the first of them.
+__device__ inline bool lanes_crowd(uint32_t d, bool on) {
+  const uint64_t all = __builtin_amdgcn_ballot_w64(on);
+  if (all == 0ull) return false;
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(all));
+  return 2 * __builtin_popcountll(__builtin_amdgcn_ballot_w64(on && d == first)) >= __builtin_popcountll(all);
+}
+// hist[d] += weight for every lane with on.
+__device__ inline void add_crowded(uint32_t* hist, uint32_t d, bool on, uint32_t lane, uint32_t weight = 1u) {
+  const uint64_t all = __builtin_amdgcn_ballot_w64(on);
+  if (all == 0ull) return;
+  const uint32_t leader = (uint32_t)__builtin_ctzll(all);
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)d, (int)leader);
+  const uint64_t same = __builtin_amdgcn_ballot_w64(on && d == first);
+  if (lane == leader) atomicAdd(&hist[first], weight * (uint32_t)__builtin_popcountll(same));
+  if (on && d != first) atomicAdd(&hist[d], weight);
+}
+
 // Prefix over the waves of a workgroup.  tot[0 .. kSelectWaves) are wave totals in LDS (written before the last
 // barrier); the result holds, in lanes 0 .. 15 of every wave, the inclusive running sum.  One LDS read and
 // four DPP steps: a loop of dependent LDS reads would cost a full LDS latency per wave.
