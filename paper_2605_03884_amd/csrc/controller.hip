@@ -81,6 +81,9 @@ __global__ __launch_bounds__(256) void controller_kernel(const float* __restrict
 // instruction issue and barriers on one compute unit: 8192 tokens took 15.5 us with four passes of 8 bits, one wave
 // searching each histogram, and an unconditional ranking sweep; 12.0 now (16384 tokens 33 and
 // 19 us, 32768 50 and 35, by events).
+// The first pass's histogram has four copies: with two, scores that crowd together took longer than before (two copies, four, and
+// before, us: a narrow range of 32768 tokens 64 / 47 / 52, normally distributed 52 / 43 / 50, one range of 4096 13.3 / 11.5 /
+// 11.5; uniform 8192 11.4 / 11.7 / 16.0); eight cost more to clear and add up (uniform 8192 12.9).  Up to 2048 tokens two do.
 
 constexpr int kThreads = kSelectThreads;
 constexpr uint32_t kTop = 4096, kSub = 1024;             // buckets of the first pass, and of the two later ones
@@ -127,7 +130,8 @@ template <int KPT>
 __global__ __launch_bounds__(kThreads) void greedy_kernel(const float* __restrict__ scores, uint32_t T, uint32_t spare,
                                                           uint8_t* __restrict__ bits, unsigned long long* __restrict__ counts4,
                                                           bool aligned) {
-  __shared__ __attribute__((aligned(16))) uint32_t hist[kTop * 2u];   // first pass: bucket d, copy c at [2 d + c]
+  constexpr uint32_t kCopies = KPT <= 2 ? 2u : 4u;          // of the first pass's histogram, see above
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kTop * kCopies];    // first pass: bucket d, copy c at [kCopies d + c]
   __shared__ uint32_t tot[3][kSelectWaves];
   __shared__ uint32_t sel_digit, sel_left, sel_same[3];
   __shared__ uint32_t class_tot[4];
@@ -159,14 +163,20 @@ __global__ __launch_bounds__(kThreads) void greedy_kernel(const float* __restric
   uint32_t kstar = 0, quota[3] = {0, 0, 0}, run[3] = {0, 0, 0};
   bool tied = false;
   if (!everything) {
-    for (uint32_t i = tid; i < kTop / 2u; i += kThreads) reinterpret_cast<u32x4*>(hist)[i] = (u32x4)(0u);
+    for (uint32_t i = tid; i < kTop * kCopies / 4u; i += kThreads) reinterpret_cast<u32x4*>(hist)[i] = (u32x4)(0u);
     __syncthreads();
-    for_each_key([&](uint32_t key, int l) { atomicAdd(&hist[(key >> 20) * 2u + (lane & 1u)], 1u << l); });
+    for_each_key([&](uint32_t key, int l) { atomicAdd(&hist[(key >> 20) * kCopies + (lane & (kCopies - 1u))], 1u << l); });
     __syncthreads();
     uint32_t c[4];
-    {
+    if constexpr (kCopies == 2u) {
       const u32x4 h0 = reinterpret_cast<const u32x4*>(hist)[2u * tid], h1 = reinterpret_cast<const u32x4*>(hist)[2u * tid + 1u];
       c[0] = h0.x + h0.y; c[1] = h0.z + h0.w; c[2] = h1.x + h1.y; c[3] = h1.z + h1.w;
+    } else {
+#pragma unroll
+      for (uint32_t i = 0; i < 4u; ++i) {
+        const u32x4 h = reinterpret_cast<const u32x4*>(hist)[4u * tid + i];
+        c[i] = h.x + h.y + h.z + h.w;
+      }
     }
     uint32_t own[1] = {c[0] + c[1] + c[2] + c[3]}, inc[1], all[1];
     block_scan<1>(own, inc, all, tot, lane, wave);             // every bucket has been read behind its barrier
