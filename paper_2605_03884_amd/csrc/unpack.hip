@@ -29,6 +29,7 @@ struct UnpackArgs {
   uint8_t* v_out;
   uint32_t* status;                                  // may be null
   uint32_t check_blocks;                             // 1: workgroup 0 reports for all (see grid_reports), the others are silent
+  uint32_t rows_first;                               // keys per channel: see unpack_tile
 };
 
 // Injection into per-layer caches: the same tiles, but only the planes of a layer range,
@@ -185,10 +186,15 @@ __device__ inline void store_tile(uint64_t my_row_addr, uint32_t lane, uint32_t 
 // it to the row addresses that row_address() gives (lane i: row r0 + i).  ROPE: rotate every row with `rope`.
 // The addresses take two dependent trips to the tables, so the tile's own loads are issued before them (one layer
 // of 3877 tokens, keys realigned: 10.1 us with the addresses first, 8.4 us; all tiles' rows of 8K tokens injected without
-// realignment: 281 and 269 us).
+// realignment: 281 and 269 us) - except with rows_first, where the card streams and the wider loads in flight only crowd the
+// writes out: raw rows of a uniform card too large to stay in cache (8K tokens of 16 bits: 378 us with the addresses first,
+// 386), uniform cards injected into more layers than a call for few takes (8K of 8 bits 285 and 301, of 4 bits 235 and 249; 32K of
+// 4 bits 985 and 1045), and cards of 4 and 8 bits with keys per channel from 512 MB of cache on
+// (32K tokens of 4 bits, 941 and 1026; below, 64 planes of 8K tokens of 8 bits, 66.9 and 63.6), key tiles that are rotated
+// apart (32K of 4 bits 1164 and 1077).
 template <int W, int G, bool KEEP, bool ROPE, typename ROWS>
 __device__ inline void unpack_tile(const uint8_t* card, const CardGeom& g, int c, uint32_t r0, uint32_t n_rows,
-                                   const ROWS& row_address, uint32_t lane, u32x4* lds, const RopeLane& rope) {
+                                   const ROWS& row_address, bool rows_first, uint32_t lane, u32x4* lds, const RopeLane& rope) {
   constexpr int GS = G / 32;                     // spans (lanes) per group
   const uint32_t lpr_shift = g.lpr_shift;
   const uint32_t spr_shift = lpr_shift - 2;      // log2(spans per row)
@@ -198,7 +204,9 @@ __device__ inline void unpack_tile(const uint8_t* card, const CardGeom& g, int c
   const uint64_t span0 = (uint64_t)r0 << spr_shift;
   const uint64_t seg_spans = (uint64_t)n_rows << spr_shift;
 
-  // both rounds' codes and pairs first, so the loads overlap
+  uint64_t my_row = 0;
+  if (rows_first) my_row = row_address();
+  // both rounds' codes and pairs at once, so the loads overlap
   uint32_t cw[kTileRounds][W];
   uint32_t pair[kTileRounds];
 #pragma unroll
@@ -222,7 +230,7 @@ __device__ inline void unpack_tile(const uint8_t* card, const CardGeom& g, int c
       pair[round] = card_load<KEEP>(meta_seg + gsp / GS);
     }
   }
-  const uint64_t my_row = row_address();
+  if (!rows_first) my_row = row_address();
 
   const uint32_t x = (lane >> 1) & 3u;           // swizzle term of this lane's spans
 #pragma unroll
@@ -255,12 +263,14 @@ __device__ inline void unpack_tile(const uint8_t* card, const CardGeom& g, int c
 // other.  Mirror image of the packing kernel's pack_tile_kc.
 template <int W, bool KEEP, bool ROPE, typename ROWS>
 __device__ inline void unpack_tile_kc(const uint8_t* card, const CardGeom& g, int c, uint32_t r0, uint32_t key_rows,
-                                      const ROWS& row_address, uint32_t lane, u32x4* lds, const RopeLane& rope) {
+                                      const ROWS& row_address, bool rows_first, uint32_t lane, u32x4* lds, const RopeLane& rope) {
   const uint32_t lpr_shift = g.lpr_shift;
   const uint32_t D = g.head_dim;
   const uint32_t cp = lane & ((D >> 1) - 1u);               // channel pair: channels 2 cp, 2 cp + 1
   const uint32_t tbl = lane >> (lpr_shift + 2u);            // token block inside the tile (head_dim 64: two)
   const uint32_t blk = r0 / 32u + tbl;
+  uint64_t my_row = 0;
+  if (rows_first) my_row = row_address();
   uint32_t cw[2][W];
   u32x2 pairs = (u32x2)(0u);
 #pragma unroll
@@ -278,7 +288,7 @@ __device__ inline void unpack_tile_kc(const uint8_t* card, const CardGeom& g, in
     for (int i = 0; i < W; ++i) { cw[0][i] = flat[i]; cw[1][i] = flat[W + i]; }
     pairs = card_load<KEEP>(reinterpret_cast<const u32x2*>(card + g.off_meta[c]) + (grp >> 1));
   }
-  const uint64_t my_row = row_address();
+  if (!rows_first) my_row = row_address();
   uint32_t xa[16], xb[16];                                  // x[j] = tokens 2j, 2j+1 of the block, channel 2 cp / 2 cp + 1
   decode_span<W>(cw[0], half_bits_to_float(pairs.x & 0xFFFFu), half_bits_to_float(pairs.x >> 16), xa);
   decode_span<W>(cw[1], half_bits_to_float(pairs.y & 0xFFFFu), half_bits_to_float(pairs.y >> 16), xb);
@@ -304,11 +314,13 @@ __device__ inline void unpack_tile_kc(const uint8_t* card, const CardGeom& g, in
 
 template <bool KEEP, bool ROPE, typename ROWS>
 __device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_t r0, uint32_t n_rows, const ROWS& row_address,
-                                 uint32_t lane, const RopeLane& rope) {
+                                 bool rows_first, uint32_t lane, const RopeLane& rope) {
   const uint32_t lpr_shift = g.lpr_shift;
   const uint32_t row_bytes = g.head_dim * 2u;
   const uint8_t* src = card + g.off_fp16 + (uint64_t)r0 * row_bytes;
   const uint64_t seg_left = ((uint64_t)n_rows - r0) * row_bytes;   // bytes from the tile start to the segment end
+  uint64_t my_row = 0;
+  if (rows_first) my_row = row_address();
   u32x4 data[kTileIters];
 #pragma unroll
   for (int k = 0; k < kTileIters; ++k) {
@@ -316,7 +328,7 @@ __device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_
     data[k] = (u32x4)(0u);
     if (off < seg_left) data[k] = card_load<KEEP>(reinterpret_cast<const u32x4*>(src + off));
   }
-  const uint64_t my_row = row_address();
+  if (!rows_first) my_row = row_address();
   if (ROPE) {
 #pragma unroll
     for (int k = 0; k < kTileIters; ++k) {
@@ -352,11 +364,12 @@ __device__ inline void unpack_class(const UnpackArgs& a, const CardGeom& g, uint
     const uint32_t r0 = (tiles - 1 - i) * tile_rows;
     const auto my_row = [&] { return tile_row_address(a, g, C, r0, n_rows, lane, tile_rows, bad); };
     if constexpr (C == 3) {
-      copy_tile<KEEP, false>(a.card, g, r0, n_rows, my_row, lane, no_rope);
+      copy_tile<KEEP, false>(a.card, g, r0, n_rows, my_row, true, lane, no_rope);
     } else {
       constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
-      if (KC && r0 < (n_rows >> 1)) unpack_tile_kc<W, KEEP, false>(a.card, g, C, r0, n_rows >> 1, my_row, lane, lds, no_rope);   // key rows
-      else unpack_tile<W, G, KEEP, false>(a.card, g, C, r0, n_rows, my_row, lane, lds, no_rope);
+      const bool rows_first = KC && C >= 1 && a.rows_first != 0u;
+      if (KC && r0 < (n_rows >> 1)) unpack_tile_kc<W, KEEP, false>(a.card, g, C, r0, n_rows >> 1, my_row, rows_first, lane, lds, no_rope);   // key rows
+      else unpack_tile<W, G, KEEP, false>(a.card, g, C, r0, n_rows, my_row, rows_first, lane, lds, no_rope);
     }
   }
   cum = (cum + tiles) % n_waves;
@@ -406,20 +419,20 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
     if (k < tp3) {
       const uint32_t r0 = p * g.n[3] + (tp3 - 1u - k) * tile_rows, end = (p + 1u) * g.n[3];
       const auto my_row = [&] { return tile_row_address(a, g, 3, r0, end, lane, tile_rows, bad); };
-      copy_tile<KEEP, false>(a.card, g, r0, end, my_row, lane, no_rope);
+      copy_tile<KEEP, false>(a.card, g, r0, end, my_row, !KEEP && g.n[3] == g.tokens, lane, no_rope);
     } else if ((k -= tp3) < tp2) {
       const uint32_t r0 = p * g.n[2] + (tp2 - 1u - k) * tile_rows, end = (p + 1u) * g.n[2];
       const auto my_row = [&] { return tile_row_address(a, g, 2, r0, end, lane, tile_rows, bad); };
-      unpack_tile<8, G, KEEP, false>(a.card, g, 2, r0, end, my_row, lane, my_lds, no_rope);
+      unpack_tile<8, G, KEEP, false>(a.card, g, 2, r0, end, my_row, false, lane, my_lds, no_rope);
     } else if ((k -= tp2) < tp1) {
       const uint32_t r0 = p * g.n[1] + (tp1 - 1u - k) * tile_rows, end = (p + 1u) * g.n[1];
       const auto my_row = [&] { return tile_row_address(a, g, 1, r0, end, lane, tile_rows, bad); };
-      unpack_tile<4, G, KEEP, false>(a.card, g, 1, r0, end, my_row, lane, my_lds, no_rope);
+      unpack_tile<4, G, KEEP, false>(a.card, g, 1, r0, end, my_row, false, lane, my_lds, no_rope);
     } else {
       k -= tp1;
       const uint32_t r0 = p * g.n[0] + (tp0 - 1u - k) * tile_rows, end = (p + 1u) * g.n[0];
       const auto my_row = [&] { return tile_row_address(a, g, 0, r0, end, lane, tile_rows, bad); };
-      unpack_tile<2, G, KEEP, false>(a.card, g, 0, r0, end, my_row, lane, my_lds, no_rope);
+      unpack_tile<2, G, KEEP, false>(a.card, g, 0, r0, end, my_row, false, lane, my_lds, no_rope);
     }
     if (bad && a.status && a.check_blocks == 0u) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
     return;
@@ -474,16 +487,17 @@ __device__ inline void inject_range(const ARGS& a, const CardGeom& g, const Rope
   const uint32_t seg_hi = seg_lo + seg_rows;
   const uint32_t tiles = (seg_rows + tile_rows - 1) / tile_rows;
   constexpr bool rot = KV == 0 && ROPE;            // only keys depend on the position
+  constexpr bool many = ARGS::kLayers > kFewLayers;
   const uint32_t first = (gw + n_waves - cum) % n_waves;
   for (uint32_t i = first; i < tiles; i += n_waves) {
     const uint32_t r0 = seg_lo + (tiles - 1 - i) * tile_rows;
     const auto my_row = [&] { return inject_row_address(a, g, C, (uint32_t)KV, r0, seg_hi, lane, tile_rows, bad); };
     if (C == 3) {
-      copy_tile<KEEP, rot>(a.card, g, r0, seg_hi, my_row, lane, rope);
+      copy_tile<KEEP, rot>(a.card, g, r0, seg_hi, my_row, !KEEP && n == g.tokens, lane, rope);
     } else {
       constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
-      if (KC && KV == 0) unpack_tile_kc<W, KEEP, rot>(a.card, g, C, r0, (g.planes >> 1) * n, my_row, lane, lds, rope);
-      else unpack_tile<W, G, KEEP, rot>(a.card, g, C, r0, seg_hi, my_row, lane, lds, rope);
+      if (KC && KV == 0) unpack_tile_kc<W, KEEP, rot>(a.card, g, C, r0, (g.planes >> 1) * n, my_row, many && C >= 1 && !rot, lane, lds, rope);
+      else unpack_tile<W, G, KEEP, rot>(a.card, g, C, r0, seg_hi, my_row, many && n == g.tokens, lane, lds, rope);
     }
   }
   cum = (cum + tiles) % n_waves;
@@ -554,6 +568,7 @@ hipError_t launch_unpack(const uint8_t* card, uint64_t card_bytes, const CardGeo
   a.v_out = static_cast<uint8_t*>(v_out);
   a.status = status;
   a.check_blocks = status && grid_reports(expect.planes, expect.head_dim, expect.tokens) ? 1u : 0u;
+  a.rows_first = (uint64_t)expect.planes * expect.tokens * expect.head_dim >= (256ull << 20) ? 1u : 0u;
   if (status && a.check_blocks == 0u) {
     hipLaunchKernelGGL(unpack_status_kernel, dim3(1), dim3(kWaveSize), 0, stream, a);
     const hipError_t e = hipGetLastError();
@@ -651,7 +666,7 @@ hipError_t launch_inject(const uint8_t* card, uint64_t card_bytes, const CardGeo
     u.card = card; u.card_bytes = card_bytes; u.flags = keys_per_channel ? QKV_FLAG_KEYS_PER_CHANNEL : 0u;
     u.layers = expect.layers; u.kv_heads = expect.kv_heads; u.head_dim = expect.head_dim; u.group_size = expect.group_size;
     u.tokens = expect.tokens;
-    u.k_out = nullptr; u.v_out = nullptr; u.status = status; u.check_blocks = 0u;
+    u.k_out = nullptr; u.v_out = nullptr; u.status = status; u.check_blocks = 0u; u.rows_first = 0u;
     hipLaunchKernelGGL(unpack_status_kernel, dim3(1), dim3(kWaveSize), 0, stream, u);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
