@@ -55,6 +55,7 @@ struct RequantArgs {
   uint32_t blocks;              // workgroups asked for (the grid may hold a few more)
   uint32_t window;              // rows of a window
   uint32_t group_planes;        // planes a workgroup does with one window; 0: the windows run across planes
+  uint32_t stride;              // workgroups from those planes' first window to the next planes'
 };
 
 // Bits chosen from a where mask is 1, from b where it is 0: one instruction.
@@ -356,11 +357,6 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
   }
 }
 
-// Workgroups from one plane's first window to the next plane's.  Workgroups go to the eight XCDs in turn: with a multiple
-// of eight a class's windows of all planes would meet on the same ones (1500 tokens, 8 windows a plane: 45.6 us, with
-// a ninth workgroup that leaves at once 37.1).
-__host__ __device__ inline uint32_t odd_stride(uint32_t per_group) { return per_group | 1u; }
-
 template <int G>
 __global__ __launch_bounds__(kBlockThreads) void requant_kernel(RequantArgs a) {
   __shared__ Shared sh;
@@ -372,10 +368,9 @@ __global__ __launch_bounds__(kBlockThreads) void requant_kernel(RequantArgs a) {
   const bool across = a.group_planes == 0u;
   uint32_t p0 = 0, p1 = 1u;
   if (!across) {
-    const uint32_t per_group = a.windows[0] + a.windows[1] + a.windows[2] + a.windows[3], stride = odd_stride(per_group);
-    const uint32_t group = k / stride;
-    k -= group * stride;
-    if (k >= per_group) return;
+    const uint32_t group = k / a.stride;
+    k -= group * a.stride;
+    if (k >= a.windows[0] + a.windows[1] + a.windows[2] + a.windows[3]) return;
     p0 = group * a.group_planes;
     p1 = min(p0 + a.group_planes, a.out.planes);
   }
@@ -416,6 +411,7 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
     blocks += a.windows[c];
   }
   a.group_planes = 0u;
+  a.stride = 1u;
   if (!across) {
     // A workgroup's look-ups are worth sharing between planes while the chip stays full several times over and both cards
     // sit in the memory-side cache (8K tokens, budget 3 to 2.5: 161.7 us with two planes, 165.4 with one); larger cards
@@ -425,7 +421,12 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
     uint32_t group = resident ? kMaxPlanes : 1u;
     while (group > 1u && blocks * ((out.planes + group - 1u) / group) < 8192u) group /= 2u;
     a.group_planes = group;
-    blocks = (uint64_t)odd_stride((uint32_t)blocks) * ((out.planes + group - 1u) / group);
+    // Workgroups go to the eight XCDs in turn: with eight windows a plane, or a multiple, a width's windows of all planes would
+    // meet on the same ones (1500 tokens, 8 windows: 45.6 us, with a ninth workgroup that leaves at once 37.1).  Windows of
+    // one width are all alike and need none (2000 tokens, 8 bits to 2: 44.6 us without, 46.1 with).
+    const bool one_width = blocks == a.windows[0] || blocks == a.windows[1] || blocks == a.windows[2] || blocks == a.windows[3];
+    a.stride = (uint32_t)blocks | (one_width ? 0u : 1u);
+    blocks = (uint64_t)a.stride * ((out.planes + group - 1u) / group);
   }
   a.blocks = (uint32_t)blocks;
   const uint32_t grid_y = (a.blocks + kMaxGridX - 1u) / kMaxGridX, grid_x = (a.blocks + grid_y - 1u) / grid_y;
