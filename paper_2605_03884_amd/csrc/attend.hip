@@ -32,6 +32,7 @@
 // waves per SIMD.  Keys grouped per channel take 125 registers at head_dim 64 and up to 4 heads, else 130 to
 // 140: three waves.
 
+#include <algorithm>
 #include <atomic>
 
 #include "qkv_common.h"
@@ -64,7 +65,9 @@ struct AttendArgs {
   float* part_ml;          // [L*H][max_tasks][R][2]  (m in log2 units, l); l = 0 marks an empty task
   uint32_t max_tasks;      // tasks per (layer, kv head) the workspace was sized for
   uint32_t chunk;          // tokens per task at most
-  uint32_t even_limit;     // units of work per (layer, kv head) up to which tasks are cut evenly, see find_task; 0: never
+  uint32_t even_tasks;     // how many of them an even cut may use, see find_task
+  uint32_t task_major;     // waves go through the pairs first, then through the tasks; else the other way round, see order_waves
+  uint32_t wave_step;      // what splits a wave's number: the pairs, or the waves per pair (one of them idle where max_tasks is even)
   uint32_t unit[4];        // tokens of a class that make up one unit (read where keys are grouped per channel, kUnit otherwise)
   uint32_t fit[4];         // chunk / unit
   float* out;              // fp32 [L][Hq][D]
@@ -702,12 +705,12 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
 
 // Which class and which of its rows [j0, j1) task `tau` of a (layer, kv head) covers; -1: a spare task.
 //
-// Usually a task takes `chunk` rows of any class, the most LDS allows.  Where a pair has few rows (even_limit), all
-// tasks get the same number of units: a unit is one group of rounds whose loads are in flight together - fewer tokens
-// at larger widths - so a task lasts about as long whatever its width, and the longest one decides how long a short card
-// takes (whole call, 1K tokens at budget 5, 256 pairs: 27.7 us with 192 rows of any width a task, 23.9 us; 300 tokens: 18.3 and
-// 15.2 us).  With s units a task there are at most sum (u_c + s - 1) / s tasks over the k classes present, so
-// s >= (sum u_c - k) / (max_tasks - k) keeps them within max_tasks.
+// Where the tasks at hand allow it, all get the same number of units: a unit is one group of rounds whose loads are in flight
+// together - fewer tokens at larger widths - so a task lasts about as long whatever its width, and the longest one decides how
+// long a short card takes (whole call, 1K tokens at budget 5, 256 pairs: 27.7 us with 192 rows of any width a task, 23.9 us; 300
+// tokens: 18.3 and 15.2 us).  Otherwise a task takes `chunk` rows of any class, the most LDS allows.
+// s units a task make at most k - 1 + (sum u_c - (k - 1)) / s tasks (rounded up) of the k classes present, so
+// s >= (sum u_c - (k - 1)) / (even_tasks - (k - 1)) keeps them within even_tasks.
 //
 // Every wave goes through this between the header and its first load, so it has as few divisions in a row as can be: the
 // classes share one divisor, the units are constants (keys per channel apart, where one class has rows).  With a division
@@ -732,24 +735,21 @@ __device__ inline int find_task(const AttendArgs& a, const CardGeom& g, uint32_t
       }
     }
   };
-  if (a.even_limit != 0u) {
-    uint32_t unit[4], units[4], sum = 0, present = 0, most = ~0u;      // most: units that fit a task of every class present
+  uint32_t unit[4], units[4], sum = 0, present = 0, most = ~0u;        // most: units that fit a task of every class present
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      unit[c] = KC ? a.unit[c] : kUnit[c];
-      units[c] = g.n[c] == 0u ? 0u : (g.n[c] + unit[c] - 1u) / unit[c];
-      sum += units[c];
-      present += (uint32_t)(g.n[c] != 0u);
-      most = g.n[c] == 0u ? most : min(most, a.fit[c]);
-    }
-    if (sum <= a.even_limit) {
-      const uint32_t room = a.max_tasks - present;         // max_tasks is at least 4
-      const uint32_t share = room == 0u ? ~0u : max(1u, (sum - present + room - 1u) / room);
-      if (share <= most) {
-        walk(units, unit, share);
-        return cls;
-      }
-    }
+  for (int c = 0; c < 4; ++c) {
+    unit[c] = KC ? a.unit[c] : kUnit[c];
+    units[c] = g.n[c] == 0u ? 0u : (g.n[c] + unit[c] - 1u) / unit[c];
+    sum += units[c];
+    present += (uint32_t)(g.n[c] != 0u);
+    most = g.n[c] == 0u ? most : min(most, a.fit[c]);
+  }
+  const uint32_t spare = present - 1u;                   // every class but one may end with a partly filled task
+  const uint32_t room = a.even_tasks - spare;
+  const uint32_t share = a.even_tasks <= spare ? ~0u : max(1u, (sum - spare + room - 1u) / room);
+  if (share <= most) {
+    walk(units, unit, share);
+    return cls;
   }
   const uint32_t rows[4] = {1u, 1u, 1u, 1u};
   walk(g.n, rows, a.chunk);
@@ -781,9 +781,9 @@ void attend_kernel(AttendArgs a) {
   const uint32_t wave = (kAttendWaves == 1) ? 0u : threadIdx.x >> 6;     // a constant keeps every LDS address an immediate
   const uint32_t gw = blockIdx.x * kAttendWaves + wave;
   const uint32_t pairs = g.planes >> 1;
-  const uint32_t pair = gw / a.max_tasks;
-  if (pair >= pairs) return;
-  const uint32_t tau = gw - pair * a.max_tasks;
+  const uint32_t outer = gw / a.wave_step, inner = gw - outer * a.wave_step;
+  const uint32_t pair = a.task_major ? inner : outer, tau = a.task_major ? outer : inner;
+  if (pair >= pairs || tau >= a.max_tasks) return;
   const uint64_t part = (uint64_t)pair * a.max_tasks + tau;
 
   uint32_t j0 = 0, j1 = 0;
@@ -901,10 +901,6 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
 // heavier, and the rule would need a line of its own.  Attention and merge, us, with the least number of tasks and cut like
 // this: 256 pairs, 8 heads, 300 tokens 20.2 and 18.8, 1000 29.6 and 25.0, 4000 55.2 and 55.4; 16 heads, 2000 tokens 51.5 and 53.8;
 // 32 pairs, 8 heads, 1000 tokens 18.6 and 15.3, 4000 20.9 and 23.8; head_dim 256, 4 heads, 1000 23.7 and 19.2, 4000 29.9 and 35.5.
-// Never a multiple of four: tasks go to the eight XCDs in turn, and the same task of all pairs - an empty one above all -
-// would land on the same one or two of them (attention kernel alone, 256 pairs, 2000 tokens at budget 4: 28.9 us with 14
-// tasks a pair, 37.7 with 16, 23.7 with 15; 1024 tokens of uniform 8 bits, keys per channel, 28.0 with 9, 31.4 with 16, 23.4
-// with 15; 384 pairs, 500 tokens: 16.4 with 10, 17.6 with 9).
 // Not beyond the fixed scratch array, so that the call that uses it cuts its tasks - and rounds its sums - like the
 // one with a workspace.
 uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t head_dim, uint32_t max_tasks) {
@@ -914,7 +910,6 @@ uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32
   if (want > useful) want = useful;
   const uint64_t fits = (QKV_ATTEND_STATIC_SCRATCH_BYTES / sizeof(float) - 4u) / (pairs * rep * (head_dim + 2u));
   if (want > fits) want = fits;
-  if (want % 4u == 0u && want != 0u) --want;
   return want > max_tasks ? (uint32_t)want : max_tasks;
 }
 
@@ -959,6 +954,25 @@ static uint32_t merge_threads(uint32_t workgroups, uint32_t tasks, uint32_t head
   return workgroups <= 2048u || tasks * head_dim / 4u > 256u ? 128u : 64u;
 }
 
+// The order of the waves, and how many there are.  Every pair has the same spare tasks (its classes' rows may leave them
+// empty), and an empty wave is gone at once: one after the tasks of each pair, they leave holes in the round-robin that deals waves
+// to XCDs and compute units, and where the tasks of a pair are a multiple of a power of two the same units get the holes each
+// time.  So up to 1.75 waves per slot (1.33 at head_dim 256) the pairs go first, all first tasks, then all second ones: the holes
+// are one piece at the end.  Whole call, us, tasks first and pairs first: 256 pairs, 2000 tokens at budget 4 41.4 and 26.8, 6000
+// 67.5 and 57.1, 1660 of head_dim 64 at budget 7.3 45.6 and 23.9; 128 pairs, 3000 tokens 29.7 and 23.7; 48 pairs, 9196 33.2 and
+// 28.2; 184 pairs of head_dim 256, 8298 tokens at budget 2.9 126.7 and 105.0.
+// Beyond that there are waves enough for the holes not to matter, and tasks of one pair that run together read neighbouring
+// rows: 1.8 waves per slot 109.2 and 112.7, 2.8 104.3 and 111.2, 4.1 102.0 and 111.7, 12 325.8 and 359.3; head_dim 256 at 1.4,
+// 8000 tokens of 16 bits 220.2 and 226.6, at 1.3 145.0 and 133.5.  There one idle wave makes the waves of a pair odd
+// (512 pairs of 16 tasks, 4896 tokens at budget 6.5: 210.6 -> 139.7).
+static uint64_t order_waves(uint64_t pairs, uint32_t head_dim, AttendArgs& a) {
+  const uint64_t waves = pairs * a.max_tasks;
+  a.task_major = head_dim > 128u ? 3u * waves <= 4u * kWaveSlots : 4u * waves <= 7u * kWaveSlots;
+  const uint32_t idle = waves < 1u << 24 ? 1u : 0u;      // no more waves than a grid may have
+  a.wave_step = a.task_major ? (uint32_t)pairs : a.max_tasks | idle;
+  return a.task_major ? waves : pairs * a.wave_step;
+}
+
 hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, const void* q,
                          uint32_t q_heads, float softmax_scale, float* out, float* lse, float* workspace,
                          uint64_t workspace_bytes, uint32_t* status, bool keys_per_channel, hipStream_t stream) {
@@ -986,17 +1000,18 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
   a.unit[2] = wide_units ? 128u : kUnit[2];
   a.unit[3] = kUnit[3];
   for (int c = 0; c < 4; ++c) a.fit[c] = a.chunk / a.unit[c];
-  // Up to two units per wave slot: beyond, the call is bound by its bytes, and more tasks only add their fixed parts (uniform
-  // 16 bits, attention kernel alone, evenly cut and by `chunk`: 200 tokens 9.2 and 14.8 us, 500 15.4 and 17.7, 1000 23.6 and 24.0,
-  // 3000 78.5 and 75.6; 384 pairs of head_dim 64, 1000 tokens at budget 4, 2.15 units per slot: 22.1 and 21.2).
-  a.even_limit = (uint32_t)(2u * kWaveSlots / pairs);
+  // Where full tasks fit the wave slots, even ones have to as well: a few waves more than slots would run after all others
+  // (whole call, us, with every task in use and like this: 256 pairs, 6000 tokens of 8 bits 102.1 and 96.0, 3000 of 16 bits
+  // 85.0 and 81.7; 128 pairs, 6000 of 16 bits 85.2 and 80.6).
+  const uint64_t full = (expect.tokens + a.chunk - 1u) / a.chunk;
+  a.even_tasks = pairs * full <= kWaveSlots ? (uint32_t)std::min<uint64_t>(a.max_tasks, kWaveSlots / pairs) : a.max_tasks;
+  const uint64_t waves = order_waves(pairs, D, a);
   a.part_o = workspace;
   a.part_ml = workspace + pairs * a.max_tasks * a.rep * D;
   a.valid = reinterpret_cast<uint32_t*>(workspace + pairs * a.max_tasks * a.rep * (D + 2u));
   a.out = out;
   a.lse = lse;
   a.status = status;
-  const uint64_t waves = pairs * a.max_tasks;
   const dim3 grid((uint32_t)((waves + kAttendWaves - 1) / kAttendWaves)), block(kAttendWaves * kWaveSize);
   const bool narrow = a.rep <= 4u;             // grouped-query shapes: the 4 x 4 x 4 contraction
   const uint32_t G = expect.group_size;

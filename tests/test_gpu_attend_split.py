@@ -102,10 +102,10 @@ def test_merge_over_many_tasks(D, rep, T):
     assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
 
 
-@pytest.mark.parametrize("T,rep", [(512, 4), (513, 4), (512, 16), (513, 16)])
+@pytest.mark.parametrize("T,rep", [(512, 4), (513, 4), (512, 16), (513, 16), (1023, 16), (1025, 16)])
 @pytest.mark.parametrize("mix", ["16", "low"])
 def test_around_the_limit_of_the_even_cut(T, rep, mix):
-    """256 pairs: tasks of equal length up to 32 units a pair (512 tokens of 16 bits), tasks of equal size beyond."""
+    """256 pairs: full tasks that fit the wave slots (1024 tokens at 16 heads), where even ones may not be more than the slots."""
     L, H, D = 32, 8, 64
     print("[case] T=%d rep=%d widths %s" % (T, rep, mix), flush=True)
     rng = np.random.default_rng(T + rep)
@@ -142,3 +142,38 @@ def test_merge_with_fewer_threads(L, H, T, D, rep, tasks):
     torch.cuda.synchronize()
     assert float(np.abs(out.cpu().numpy() - want_o).max()) <= tol_o
     assert float(np.abs(lse.cpu().numpy() - want_lse).max()) <= tol_lse
+
+
+@pytest.mark.parametrize("L,H,T,D,rep,tasks", [(5, 26, 3328, 64, 16, 55), (5, 26, 3392, 64, 16, 56), (5, 26, 8350, 64, 16, 134),
+                                               (5, 26, 2496, 256, 16, 42), (5, 26, 2560, 256, 16, 43)])
+@pytest.mark.parametrize("mix", ["low", "4"])
+def test_order_of_waves(L, H, T, D, rep, tasks, mix):
+    """Pairs first up to 1.75 waves per slot of 4096 (1.33 at head_dim 256), tasks first beyond, an idle wave a pair where the tasks
+    are even: every (layer, kv head) has its own query, so a wave at another place shows."""
+    print("[case] L=%d H=%d T=%d D=%d rep=%d widths %s" % (L, H, T, D, rep, mix), flush=True)
+    desc = qkv.Desc.make(L, H, T, D, 64)
+    size = qkv.card_attend_workspace(desc, H * rep)
+    assert (size // 4 - 4) // (L * H * rep * (D + 2)) == tasks
+    bits, counts = torch.full((T,), 4, dtype=torch.uint8, device=DEV), [0, T, 0, 0]
+    if mix == "low":
+        bits, counts = qkv.assign_bits(torch.rand((T,), device=DEV), 3.0)
+    gen = torch.Generator(device=DEV).manual_seed(T)
+    k, v = (torch.randn((L, H, T, D), dtype=torch.float16, device=DEV, generator=gen) for _ in range(2))
+    card = torch.empty(qkv.card_bytes(desc, counts), dtype=torch.uint8, device=DEV)
+    qkv.quantize_pack(desc, k, v, bits, counts, card)
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    qkv.unpack_dequant(card, desc, k, v, status=status)
+    q = torch.randn((L, H * rep, D), dtype=torch.float16, device=DEV, generator=gen)
+    ws = torch.full((size + 256,), 0x7F, dtype=torch.uint8, device=DEV)
+    out, lse = torch.full((L, H * rep, D), float("nan"), device=DEV), torch.full((L, H * rep), float("nan"), device=DEV)
+    qkv.card_attend(card, desc, q, D ** -0.5, out, lse=lse, workspace=ws[:size])
+    torch.cuda.synchronize()
+    assert (ws[size:] == 0x7F).all()
+    for l in range(L):                           # float64 on the dequantized values, a layer at a time
+        s = (q[l].double().view(H, rep, D) @ k[l].double().transpose(1, 2).contiguous()) * D ** -0.5
+        want_lse = torch.logsumexp(s, dim=-1)
+        want = torch.softmax(s, dim=-1) @ v[l].double()
+        # a score is off by at most D 2^-24 scale sum |q k|, and out by twice that times max |v| (and its own fp32 sums)
+        e = D * 2.0 ** -24 * D ** -0.5 * float((q[l].double().abs().view(H, rep, D) @ k[l].double().abs().transpose(1, 2).contiguous()).max())
+        assert float((out[l].view(H, rep, D).double() - want).abs().max()) <= (2 * e + 1e-5) * float(v[l].abs().max())
+        assert float((lse[l].view(H, rep).double() - want_lse).abs().max()) <= e + 1e-5
