@@ -944,13 +944,14 @@ hipError_t attend_static_scratch(float** ptr) {
   return hipSuccess;
 }
 
-// Threads of a merging workgroup.  Few workgroups: 256, the partials of many tasks are under way at once.  More of them
-// than 256 threads each find room for: fewer, and one wave, which waits for no other, where that reads the partials in a
-// few trips.  Merge alone, us, with 256 / 128 / 64 threads (and with one thread per dimension): 1024 workgroups, head_dim
-// 128, 25 tasks 5.8 / 6.2 / 8.6 (7.6); 2048, 128, 5 tasks 4.9 / 4.0 / 4.2 (4.4); 3072, 64, 9 tasks 7.3 / 5.0 / 4.8 (4.9);
-// 4096, 64, 7 tasks 8.2 / 5.0 / 4.5 (5.0), 128, 128 tasks 60 / 53 / 66 (77); 6144, 64, 7 tasks 11.1 / 7.8 / 5.6 (5.7).
+// Threads of a merging workgroup.  Few workgroups, or many partials each: 256, many partials are under way at once.  Else, with
+// more workgroups than 256 threads each find room for: fewer, and one wave, which waits for no other, where that reads the
+// partials in a few trips.  Merge alone, us, with 256 / 128 / 64 threads: head_dim 128, 1024 workgroups, 25 tasks 5.8 / 6.2 /
+// 8.6; 1280, 17 tasks 5.9 / 5.4 / 6.5, 33 tasks 6.5 / 7.0 / 9.8; 1792, 400 tasks 75 / 97 / 146; 3072, 9 tasks 6.8 / 5.5 / 5.5, 65
+// tasks 20.2 / 18.4 / 20.4, 129 tasks 41 / 48 / 61; 6144, 5 tasks 10.5 / 7.4 / 5.4; head_dim 64, 4096 workgroups, 9 tasks 8.8 / 5.9
+// / 4.9, 65 tasks 14.5 / 14.5 / 15.6, 400 tasks 107 / 103 / 110; head_dim 256, 4096, 33 tasks 22.0 / 20.9 / 21.6, 129 140 / 145 / 150.
 static uint32_t merge_threads(uint32_t workgroups, uint32_t tasks, uint32_t head_dim) {
-  if (workgroups <= 1024u) return 256u;
+  if (workgroups <= 1024u || tasks * head_dim > (workgroups <= 2048u ? 4096u : 9216u)) return 256u;
   return workgroups <= 2048u || tasks * head_dim / 4u > 256u ? 128u : 64u;
 }
 
