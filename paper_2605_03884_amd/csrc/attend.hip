@@ -901,6 +901,9 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
 // heavier, and the rule would need a line of its own.  Attention and merge, us, with the least number of tasks and cut like
 // this: 256 pairs, 8 heads, 300 tokens 20.2 and 18.8, 1000 29.6 and 25.0, 4000 55.2 and 55.4; 16 heads, 2000 tokens 51.5 and 53.8;
 // 32 pairs, 8 heads, 1000 tokens 18.6 and 15.3, 4000 20.9 and 23.8; head_dim 256, 4 heads, 1000 23.7 and 19.2, 4000 29.9 and 35.5.
+// And no more than 96: with few pairs the merge, a few workgroups that go through all partials, takes longer than what shorter
+// tasks save.  Whole call, 4 heads and a mean over widths, us, with at most 1368 / 192 / 96 / 64: 1 pair, 8192 tokens 16 / 16 / 15 / 15,
+// 32768 40 / 22 / 23 / 22, 65536 73 / 32 / 33 / 32; 8 pairs, 8192 19 / 19 / 17 / 17, 24000 39 / 26 / 23 / 23; 16 pairs, 12000 24 / 22 / 20 / 19.
 // Not beyond the fixed scratch array, so that the call that uses it cuts its tasks - and rounds its sums - like the
 // one with a workspace.
 uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t head_dim, uint32_t max_tasks) {
@@ -908,6 +911,7 @@ uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32
   uint64_t want = kWaveSlots / pairs;
   const uint64_t useful = tokens / 48u + 3u;
   if (want > useful) want = useful;
+  if (want > 96u) want = 96u;
   const uint64_t fits = (QKV_ATTEND_STATIC_SCRATCH_BYTES / sizeof(float) - 4u) / (pairs * rep * (head_dim + 2u));
   if (want > fits) want = fits;
   return want > max_tasks ? (uint32_t)want : max_tasks;

@@ -23,7 +23,8 @@ def base_tasks(L, H, T, rep):
 @pytest.mark.parametrize("L,H", [(32, 8), (48, 8), (64, 8), (32, 1), (1, 8), (1, 1)])
 @pytest.mark.parametrize("D", [64, 128, 256])
 def test_a_finer_cut_fits_the_wave_slots_and_the_fixed_scratch(L, H, D):
-    """A cut beyond the least number of tasks fills the chip's 4096 wave slots once at most, and qkv_card_attend_static has the room for it (16 MiB), so that it cuts - and rounds - like the call with a workspace."""
+    """A cut beyond the least number of tasks fills the chip's 4096 wave slots once at most, leaves the merge no more than 96 partials
+    a head, and qkv_card_attend_static has the room for it (16 MiB), so that it cuts - and rounds - like the call with a workspace."""
     finer = 0
     for rep in (1, 2, 3, 4, 5, 16):
         for T in list(range(1, 4000, 37)) + [5000, 8192, 20000, 32768]:
@@ -31,7 +32,7 @@ def test_a_finer_cut_fits_the_wave_slots_and_the_fixed_scratch(L, H, D):
             assert n >= base
             if n > base:
                 finer += 1
-                assert L * H * n <= 4096 and n <= T // 48 + 3, (L, H, T, D, rep, n)
+                assert L * H * n <= 4096 and n <= min(96, T // 48 + 3), (L, H, T, D, rep, n)
                 assert qkv.card_attend_workspace(qkv.Desc.make(L, H, T, D, 32), H * rep) <= 16 << 20
                 assert rep <= 4 and D <= 128
     assert (finer > 0) == (D <= 128)
