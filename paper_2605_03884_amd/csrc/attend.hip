@@ -708,7 +708,7 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
 // Where the tasks at hand allow it, all get the same number of units: a unit is one group of rounds whose loads are in flight
 // together - fewer tokens at larger widths - so a task lasts about as long whatever its width, and the longest one decides how
 // long a short card takes (whole call, 1K tokens at budget 5, 256 pairs: 27.7 us with 192 rows of any width a task, 23.9 us; 300
-// tokens: 18.3 and 15.2 us).  Otherwise a task takes `chunk` rows of any class, the most LDS allows.
+// tokens: 18.3 and 15.2 us; with the present order of the waves 1K tokens take 19.7).  Otherwise a task takes `chunk` rows of any class, the most LDS allows.
 // s units a task make at most k - 1 + (sum u_c - (k - 1)) / s tasks (rounded up) of the k classes present, so
 // s >= (sum u_c - (k - 1)) / (even_tasks - (k - 1)) keeps them within even_tasks.
 //
@@ -899,8 +899,9 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
 // per wave slot of the chip, but no more than there are units of work at a middling mix of widths (an empty task still
 // costs its dispatch).  Only up to 4 query heads per kv head and head_dim 128: beyond, a task's fixed part and the merge are
 // heavier, and the rule would need a line of its own.  Attention and merge, us, with the least number of tasks and cut like
-// this: 256 pairs, 8 heads, 300 tokens 20.2 and 18.8, 1000 29.6 and 25.0, 4000 55.2 and 55.4; 16 heads, 2000 tokens 51.5 and 53.8;
-// 32 pairs, 8 heads, 1000 tokens 18.6 and 15.3, 4000 20.9 and 23.8; head_dim 256, 4 heads, 1000 23.7 and 19.2, 4000 29.9 and 35.5.
+// this (a pair's waves one after the other, see order_waves): 256 pairs, 8 heads, 300 tokens 20.2 and 18.8, 1000 29.6 and 25.0,
+// 4000 55.2 and 55.4; 16 heads, 2000 tokens 51.5 and 53.8; 32 pairs, 8 heads, 1000 tokens 18.6 and 15.3, 4000 20.9 and 23.8;
+// head_dim 256, 4 heads, 1000 23.7 and 19.2, 4000 29.9 and 35.5.
 // And no more than 96: with few pairs the merge, a few workgroups that go through all partials, takes longer than what shorter
 // tasks save.  Whole call, 4 heads and a mean over widths, us, with at most 1368 / 192 / 96 / 64: 1 pair, 8192 tokens 16 / 16 / 15 / 15,
 // 32768 40 / 22 / 23 / 22, 65536 73 / 32 / 33 / 32; 8 pairs, 8192 19 / 19 / 17 / 17, 24000 39 / 26 / 23 / 23; 16 pairs, 12000 24 / 22 / 20 / 19.
