@@ -11,29 +11,33 @@
 // Work decomposition.  A wave takes one task: up to `chunk` consecutive rows of one width's
 // segment for one (layer, kv head), for all R query heads, and leaves an unnormalised
 // partial (running maximum m, sum l, sum of p.V^) in a workspace; a second kernel merges the
-// partials of each (layer, query head).  Inside a task, in rounds of 16 tokens:
-//   scores   lane (n, kq) = (token n of the round, quarter kq of a slab of 128 dimensions) reads
-//            its span of 32 codes and its pair, decodes it to 8 MFMA operands of 4 dimensions,
-//            and eight MFMAs accumulate q.K^ for the round's tokens and the kv head's query
+// partials of each (layer, query head).  Inside a task, in rounds of 2048 values (16 tokens of 128 dimensions, 32 of 64):
+//   scores   a lane reads a span of 32 codes and its pair, decodes it to four MFMA operands of 8 dimensions,
+//            and four MFMAs accumulate q.K^ for the round's tokens and the kv head's query
 //            heads (the k index of the MFMA is a fixed permutation of the head dimension,
 //            applied to q and K^ alike).  Scores go to LDS.
-//   softmax  one maximum per head over the task's tokens, p = exp2(s - m) back into LDS.
-//   values   the round's packed V rows are regrouped through LDS (still packed) so that a lane
-//            holds 4 consecutive tokens x 8 dimensions, decodes them into 8 MFMA operands,
-//            and 2 x 8 MFMAs (softmax weights as an fp16 high part and the fp16 remainder, into
-//            the same accumulators) add p.V^.
-// Which MFMA: v_mfma_f32_4x4x4_16b_f16 for up to 4 query heads per kv head, the 16 x 16 x 16
-// form for 5 .. 16 (see attend_task).  head_dim 256 is two slabs, head_dim 64 half a one.
+//   softmax  one maximum per head over the task's tokens, p = exp2(s - m) back into LDS, as an fp16 high part and
+//            the fp16 remainder.
+//   values   the round's packed V rows are regrouped through LDS (still packed; raw rows are read as they are wanted) so
+//            that a lane holds 4 tokens x 8 dimensions (64 dimensions: 8 x 4), decodes them into MFMA operands of 4 tokens
+//            x 2 dimensions, and MFMAs add p.V^.
+// Both products are v_mfma_f32_16x16x32_f16 (see attend_task).  head_dim 256 is two slabs of 128.
 // 2-bit spans, most of a card at low budgets, are not decoded by arithmetic: a group has only
-// four decoded values, which are computed once, and a selector table in LDS indexed by a byte of
-// four codes drives v_perm_b32 to pick them.  Rounds are taken in whole groups of 4 / 3 / 2 /
-// 1 (at 2 / 4 / 8 / 16 bits) without a branch in between; rounds past a task's end see zeros and
-// count as -inf.  About 106 registers (head_dim 256: up to 128) and 10 KiB of LDS per wave: four
-// waves per SIMD.  Keys grouped per channel take 125 registers at head_dim 64 and up to 4 heads, else 130 to
-// 140: three waves.
+// four decoded values, which are computed once and picked by v_perm_b32.  Rounds are taken in whole groups of 4 / 3 / 2 /
+// 1 (at 2 / 4 / 8 / 16 bits; 64 dimensions: 2 / 2 / 1 / 1) without a branch in between; rounds past a task's end see zeros and
+// count as -inf.  88 .. 128 registers and 9.5 KiB of LDS per wave: four waves per SIMD.
+//
+// Vector instructions of a round of 16 tokens x 128 dimensions with up to 4 query heads, at 2 / 4 / 8 bits: scores 61 / 85 / 80, softmax 9,
+// values 38 / 91 / 88, and 8 MFMAs of 16 cycles.  With v_mfma_f32_4x4x4_16b_f16, whose operands are four tokens of one dimension,
+// values had to be turned from pairs of dimensions into pairs of tokens, sums added up across lanes, high and low parts of
+// the weights took an MFMA each: 84, 18 and 112 at 2 bits, 24 MFMAs of 8 cycles.  Whole call, 32 query heads on 8 kv heads, 32
+// layers, us, then and now: 8192 tokens at budget 3 73.0 and 63.6, all 2 bits 60.0 and 51.7, 4 bits 85.4 and 78.5, 8 bits 124.6 and
+// 123.0; 1024 tokens at budget 5 20.6 and 18.5.  64 dimensions had left half the lanes idle, and more than 4 heads took the 16 x 16 x 16
+// product: 8 heads, 3877 tokens of 128 pairs 30.0 and 21.0; 16 heads of 128 dimensions, 3622 tokens of 256 pairs 75.2 and 73.3.
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 
 #include "qkv_common.h"
 #include "qkv_decode.h"
@@ -41,15 +45,13 @@
 namespace qkv {
 namespace {
 
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRoundTokens = 16;
 constexpr int kAttendWaves = 1;              // waves per workgroup (they would not interact): one keeps every LDS address an immediate
-// Rounds whose loads are in flight ahead of the arithmetic: as many as the registers allow
-// (a fetched span is 3 / 5 / 9 / 16 registers at 2 / 4 / 8 / 16 bits).
-template <int W> struct Prefetch { static constexpr int kRounds = (W == 2) ? 4 : (W == 4) ? 3 : (W == 8) ? 2 : 1; };
-constexpr uint32_t kUnit[4] = {64u, 48u, 32u, 16u};      // tokens of such a group of rounds, by class
+// Tokens of a group of rounds whose loads are in flight together (Prefetch), by class; 64 dimensions.
+constexpr uint32_t kUnit[2][4] = {{64u, 48u, 32u, 16u}, {64u, 64u, 32u, 32u}};
 constexpr int kLdsFloatsPerWave = 1536;      // scores of one task: chunk tokens x padded query heads (6 KiB)
 
 struct AttendArgs {
@@ -60,7 +62,8 @@ struct AttendArgs {
   const uint16_t* q;       // fp16 [L][Hq][D]
   uint32_t q_heads;        // Hq
   uint32_t rep;            // R = Hq / H, 1 .. 16
-  float scale_log2;        // softmax scale times log2(e)
+  float scale_log2;        // softmax scale times log2(e); its absolute value where keys are not grouped per channel, and then
+  uint32_t q_flip;         // the sign bits to turn in q for the scale's own: the largest score is the one of the largest product
   float* part_o;           // [L*H][max_tasks][R][D] unnormalised sums of p.V^
   float* part_ml;          // [L*H][max_tasks][R][2]  (m in log2 units, l); l = 0 marks an empty task
   uint32_t max_tasks;      // tasks per (layer, kv head) the workspace was sized for
@@ -76,174 +79,225 @@ struct AttendArgs {
   uint32_t* valid;         // one word of the workspace: 1 when the header was accepted
 };
 
+// What a lane holds of one round's rows before it is decoded: the codes of a span of 32 values (or raw values) and its pair.
 template <int W, int G>
 struct SpanData {
   uint32_t cw[W == 16 ? 16 : W];
   uint32_t pair;
 };
 
-// Where lane (n, kq) finds its span in round 0 of a task; every round is 16 rows further.
-struct LanePtrs {
-  const uint8_t* codes;    // packed codes (or the raw fp16 span)
-  const uint8_t* pair;     // the group's (scale, zero)
+// A task's rows of one plane as two buffers that end with the task's last row: what is read past them is zero, in
+// hardware, so no round needs a test, a mask or zeros of its own.  `codes_at` and `pairs_at` are the lane's own
+// offsets in round 0; every round is a fixed number of bytes further.
+struct RowStream {
+  __amdgpu_buffer_rsrc_t codes, pairs;
+  uint32_t codes_at, pairs_at;
 };
 
-// DS = spans of 32 values per token (head_dim / 32); sq = which of them, 0 .. DS - 1.
-template <int W, int G, int DS>
-__device__ inline LanePtrs lane_pointers(const uint8_t* card, const CardGeom& g, int c, uint64_t row0, uint32_t n,
-                                         uint32_t sq) {
-  constexpr int GS = G / 32;
-  const uint64_t gsp = (row0 + n) * DS + sq;
-  LanePtrs p;
-  if (W == 16) {
-    p.codes = card + g.off_fp16 + gsp * 64u;
-    p.pair = nullptr;
-  } else {
-    p.codes = card + g.off_codes[c] + gsp * (4u * W);
-    p.pair = card + g.off_meta[c] + (gsp / GS) * 4u;
-  }
-  return p;
+__device__ inline uint64_t uniform64(uint64_t x) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+  return ((uint64_t)hi << 32) | lo;
 }
 
-// Issues the loads of the lane's span in round rd; nothing is decoded yet.  Zeros when !valid.
+// The untyped buffer [at, at + bytes): a load that would reach past its end gives zero.
+__device__ inline __amdgpu_buffer_rsrc_t bounded(const uint8_t* at, uint32_t bytes) {
+  const uint64_t p = uniform64(reinterpret_cast<uint64_t>(at));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(p), 0, (int)(uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00027000);
+}
+
+// Rows of a round, and how lane (n, kq) = (lane % 16, lane / 16) sits in it.  A round is 2048 values of a slab of up to 128
+// dimensions: 16 tokens, or 32 where a token has 64 dimensions.
+template <int DS> struct RoundGeo {
+  static constexpr uint32_t kTokens = DS == 2 ? 32u : 16u;
+  static constexpr uint32_t kSpans = DS == 2 ? 2u : 4u;                // spans of a token in the slab
+  // loader side: the lane's row of the round and its span of that row
+  static __device__ inline uint32_t row(uint32_t n, uint32_t kq) { return DS == 2 ? n + 16u * (kq >> 1) : n; }
+  static __device__ inline uint32_t span(uint32_t kq) { return DS == 2 ? (kq & 1u) : kq; }
+};
+
+template <int W, int DS> struct RowBytes {
+  static constexpr uint32_t kCodes = (uint32_t)DS * 4u * W;            // of a row; raw rows: 64 bytes per span
+};
+
+// The rows [row0, row0 + cnt) of class c, read from span `span` of row `row` of every round.
 template <int W, int G, int DS>
-__device__ inline SpanData<W, G> fetch_span(const LanePtrs& p, uint32_t rd, bool valid) {
-  constexpr int GS = G / 32;
-  constexpr int NW = (W == 16) ? 16 : W;
-  SpanData<W, G> d;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) d.cw[i] = 0;
-  d.pair = 0;
-  if (valid) {
-    const uint8_t* src = p.codes + (uint64_t)rd * (kRoundTokens * DS * 4u * W);    // 16 rows of DS spans of 4 W bytes
-    if (W == 2) {
-      const u32x2 t = *reinterpret_cast<const u32x2*>(src);
-      d.cw[0] = t.x; d.cw[1] = t.y;
-    } else {
-#pragma unroll
-      for (int h = 0; h < NW / 4; ++h) {
-        const u32x4 t = *reinterpret_cast<const u32x4*>(src + 16 * h);
-        d.cw[4 * h] = t.x; d.cw[4 * h + 1] = t.y; d.cw[4 * h + 2] = t.z; d.cw[4 * h + 3] = t.w;
-      }
-    }
-    if (W != 16) d.pair = *reinterpret_cast<const uint32_t*>(p.pair + (uint64_t)rd * (kRoundTokens * DS * 4u / GS));
+__device__ inline RowStream row_stream(const uint8_t* card, const CardGeom& g, int c, uint64_t row0, uint32_t cnt, uint32_t row, uint32_t span) {
+  constexpr uint32_t kPairBytes = (uint32_t)DS * 32u / G * 4u;
+  RowStream s;
+  const uint64_t off = W == 16 ? g.off_fp16 : g.off_codes[c];
+  s.codes = bounded(card + off + row0 * RowBytes<W, DS>::kCodes, cnt * RowBytes<W, DS>::kCodes);
+  s.codes_at = row * RowBytes<W, DS>::kCodes + span * (4u * W);
+  if constexpr (W != 16) {
+    s.pairs = bounded(card + g.off_meta[c] + row0 * kPairBytes, cnt * kPairBytes);
+    s.pairs_at = row * kPairBytes + span / (G / 32u) * 4u;
+  } else {
+    s.pairs = s.codes;
+    s.pairs_at = 0u;
   }
+  return s;
+}
+
+__device__ inline u32x4 buffer_load4(__amdgpu_buffer_rsrc_t r, uint32_t at) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, 0, 0));
+}
+__device__ inline u32x2 buffer_load2(__amdgpu_buffer_rsrc_t r, uint32_t at) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)at, 0, 0));
+}
+
+// Issues the loads of the lane's span in round rd; nothing is decoded yet.  Zeros past the task's last row.
+template <int W, int G, int DS>
+__device__ inline SpanData<W, G> fetch_span(const RowStream& s, uint32_t rd) {
+  constexpr uint32_t kRows = RoundGeo<DS>::kTokens;
+  SpanData<W, G> d;
+  const uint32_t at = s.codes_at + rd * (kRows * RowBytes<W, DS>::kCodes);
+  if constexpr (W == 2) {
+    const u32x2 t = buffer_load2(s.codes, at);
+    d.cw[0] = t.x; d.cw[1] = t.y;
+  } else {
+#pragma unroll
+    for (int h = 0; h < W / 4; ++h) {
+      const u32x4 t = buffer_load4(s.codes, at + 16u * h);
+      d.cw[4 * h] = t.x; d.cw[4 * h + 1] = t.y; d.cw[4 * h + 2] = t.z; d.cw[4 * h + 3] = t.w;
+    }
+  }
+  d.pair = 0u;
+  if constexpr (W != 16) d.pair = __builtin_amdgcn_raw_buffer_load_b32(s.pairs, (int)(s.pairs_at + rd * (kRows * ((uint32_t)DS * 32u / G * 4u))), 0, 0);
   return d;
 }
 
-// The 32 values of a fetched span as 16 packed fp16 pairs.
+// Codes that sit in the two halves of a word are fp16 numbers already, code * 2^-24: v_fma_mix_f32 reads either half and
+// rounds code * scale + zero to fp32 (scale24 = scale * 2^24), so a code costs no conversion of its own - 2.4 vector
+// instructions a value at 4 bits where picking bytes apart and converting them takes 2.9.
+__device__ inline float fma_low(uint32_t codes, float scale24, float zero) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(codes), "v"(scale24), "v"(zero));
+  return r;
+}
+__device__ inline float fma_high(uint32_t codes, float scale24, float zero) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(codes), "v"(scale24), "v"(zero));
+  return r;
+}
+__device__ inline uint32_t pack_halves(float a, float b) {
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+}
+
+// Decoded values come two to a word, and a word of codes is cheapest taken apart into two equal parts: pair m of a piece of 8
+// values is values piece_dim(m, 0) and piece_dim(m, 1).  Nothing that follows needs another order.
+template <int W> __device__ constexpr int piece_dim(int m, int h) {
+  return W == 4 ? m + 4 * h : W == 8 ? 4 * (m >> 1) + (m & 1) + 2 * h : 2 * m + h;
+}
+
+// 8 values at 4 bits (one word) or 4 at 8 bits (one word), in that order.
+template <int W>
+__device__ inline void decode_word(uint32_t w, float scale24, float zero, uint32_t* out) {
+  static_assert(W == 4 || W == 8, "");
+#pragma unroll
+  for (int i = 0; i < 16 / (int)sizeof(uint32_t) / (W == 4 ? 1 : 2); ++i) {
+    const uint32_t codes = (w >> (W * i)) & (W == 4 ? 0x000F000Fu : 0x00FF00FFu);
+    out[i] = pack_halves(fma_low(codes, scale24, zero), fma_high(codes, scale24, zero));
+  }
+}
+
+// The 32 values of a fetched span as 16 packed fp16 pairs, in the order of its pieces of 8 (2 bits: see decode_fetched_bytes).
 template <int W, int G>
 __device__ inline void decode_fetched(const SpanData<W, G>& d, uint32_t (&out)[16]) {
   if constexpr (W == 16) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) out[i] = d.cw[i];
   } else {
-    const float s = half_bits_to_float(d.pair & 0xFFFFu);
+    const float s = half_bits_to_float(d.pair & 0xFFFFu) * 16777216.0f;
     const float z = half_bits_to_float(d.pair >> 16);
-    decode_span<W>(d.cw, s, z, out);
+#pragma unroll
+    for (int i = 0; i < W; ++i) decode_word<W>(d.cw[i], s, z, out + 16 / W * i);
   }
 }
 
+// The 32 values of a 2-bit span by byte selection: the low bytes of the span's four values and their high bytes are picked
+// apart, four codes at a time, and put together: out[8 w + 2 k + h] = values 16 w + 8 h + k and 16 w + 8 h + 4 + k.
+// 1.8 vector instructions a value where the selector table in LDS takes 0.75 and a look-up for every four values, but the
+// look-ups' bank conflicts filled the LDS pipe while the vector units had room (8K tokens of 2 bits 56.6 -> 53.6 us).
 template <int G>
-__device__ inline void decode_fetched_select(const SpanData<2, G>& d, const uint8_t* table, uint32_t (&out)[16]) {
-  decode_span2_select(d.cw, half_bits_to_float(d.pair & 0xFFFFu), half_bits_to_float(d.pair >> 16), table, out);
-}
-
-// ---- value pass helpers -----------------------------------------------------------------------
-//
-// For the weighted sum the MFMA contracts over tokens, so a lane must hold, for one output
-// dimension, the values of four consecutive tokens.  The round's 16 rows are therefore loaded
-// as they lie (lane (n, kq) = token n, quarter kq), dropped into LDS still packed, and picked
-// up again by lane (a, kt) as the pieces "token 4 kt + i, dimensions 8 a .. 8 a + 7", i = 0..3.
-// Operand e of the round is then B_e[token][a] = V^[token][8 a + e], and eight MFMAs give
-// out[head][8 a + e] for 16 heads at once.  Only packed codes cross LDS, never decoded values.
-
-template <int W> struct Piece { uint32_t w[W == 16 ? 4 : (W == 8 ? 2 : 1)]; };
-
-// float values of the 8 codes of pieces i0 and i0+1 (W = 2: two 16-bit pieces share the masks)
-template <int W>
-__device__ inline void piece_codes(const Piece<W>& p0, const Piece<W>& p1, float (&c0)[8], float (&c1)[8]) {
-  if constexpr (W == 2) {
-    const uint32_t both = (p0.w[0] & 0xFFFFu) | (p1.w[0] << 16);
+__device__ inline void decode_fetched_bytes(const SpanData<2, G>& d, uint32_t (&out)[16]) {
+  const float s = half_bits_to_float(d.pair & 0xFFFFu), z = half_bits_to_float(d.pair >> 16);
+  const uint32_t x01 = decode_pair(0.0f, 1.0f, s, z), x23 = decode_pair(2.0f, 3.0f, s, z);
+  const uint32_t low = __builtin_amdgcn_perm(x23, x01, 0x06040200u), high = __builtin_amdgcn_perm(x23, x01, 0x07050301u);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {                       // byte layout of m: [p0 code k, p0 code 4+k, p1 code k, p1 code 4+k]
-      const uint32_t m = (both >> (2 * k)) & 0x03030303u;
-      c0[k] = byte_to_float(m, 0); c0[4 + k] = byte_to_float(m, 1);
-      c1[k] = byte_to_float(m, 2); c1[4 + k] = byte_to_float(m, 3);
-    }
-  } else if constexpr (W == 4) {
-    const uint32_t e0 = p0.w[0] & 0x0F0F0F0Fu, o0 = (p0.w[0] >> 4) & 0x0F0F0F0Fu;
-    const uint32_t e1 = p1.w[0] & 0x0F0F0F0Fu, o1 = (p1.w[0] >> 4) & 0x0F0F0F0Fu;
+  for (int w = 0; w < 2; ++w) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      c0[2 * j] = byte_to_float(e0, j); c0[2 * j + 1] = byte_to_float(o0, j);
-      c1[2 * j] = byte_to_float(e1, j); c1[2 * j + 1] = byte_to_float(o1, j);
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      c0[j] = byte_to_float(p0.w[0], j); c0[4 + j] = byte_to_float(p0.w[1], j);
-      c1[j] = byte_to_float(p1.w[0], j); c1[4 + j] = byte_to_float(p1.w[1], j);
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t code = (d.cw[w] >> (2 * k)) & 0x03030303u;            // codes k, 4 + k, 8 + k, 12 + k of the word
+      const uint32_t lo = __builtin_amdgcn_perm(low, low, code), hi = __builtin_amdgcn_perm(high, high, code);
+      out[8 * w + 2 * k] = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
+      out[8 * w + 2 * k + 1] = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
     }
   }
 }
 
-// fp16(fma(c0, s0, z0)) | fp16(fma(c1, s1, z1)) << 16: the two roundings of the decoder, two tokens at once
-__device__ inline uint32_t decode_two_tokens(float c0, float s0, float z0, float c1, float s1, float z1) {
-  float x = __builtin_fmaf(c0, s0, z0);
-  float y = __builtin_fmaf(c1, s1, z1);
-  asm("" : "+v"(x));
-  asm("" : "+v"(y));
-  const f32x2 v = {x, y};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+// The 32 values of q that meet such a span, in the same order.
+template <int W>
+__device__ inline void order_q(u32x4 (&raw)[4]) {
+  if constexpr (W != 16) {
+    uint32_t out[16];
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      // the two values of word x
+      const int a = W == 2 ? 16 * (x >> 3) + 8 * (x & 1) + ((x >> 1) & 3) : 8 * (x >> 2) + piece_dim<W>(x & 3, 0);
+      const int b = W == 2 ? a + 4 : 8 * (x >> 2) + piece_dim<W>(x & 3, 1);
+      out[x] = __builtin_amdgcn_perm(raw[b >> 3][(b >> 1) & 3], raw[a >> 3][(a >> 1) & 3], (a & 1) ? 0x07060302u : 0x05040100u);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) raw[j] = (u32x4){out[4 * j], out[4 * j + 1], out[4 * j + 2], out[4 * j + 3]};
+  }
 }
 
-// ---- the LDS tile of a round: 16 packed rows, regrouped ------------------------------------------
+// ---- the LDS tile of a round: packed rows, regrouped ---------------------------------------------
 //
-// Used for the value rows of every card and for the key rows of cards grouped per channel.  In both
-// cases the MFMA contracts over the tile's rows, so a lane must hold four consecutive rows of one
-// column; the loader lane (n, kq) holds row n, columns 32 kq .. 32 kq + 31.
+// Used for the value rows (2, 4 and 8 bits) of every card and for the key rows of cards grouped per channel.  In both
+// cases the MFMA contracts over the tile's rows, so a lane must hold several rows of the same columns; the loader lane holds
+// one span of one row.  The rows are dropped into LDS still packed and picked up again in pieces; only codes
+// cross LDS, never decoded values.
 
-// one row's pitch in the tile; rows of 32 / 64 bytes get a pitch of 40 / 80 so that the four rows a read
-// instruction touches (4 apart) fall on different banks.  Behind the rows, as [quarter][row]: the
-// 4 x 16 pairs (2-bit rows: 4 x 16 four-value tables), and at 2 bits the 2 KiB selector table.
-template <int W> struct TileGeo {
-  static constexpr uint32_t kRowBytes = (W == 2) ? 40u : (W == 4) ? 80u : 16u * W;
-  static constexpr uint32_t kPairsAt = (W == 16) ? 0u : 16u * kRowBytes;
+// Rows of 16 spans, or 32 of 8 bytes at head_dim 64.  The pitch keeps the rows that a read instruction touches (4 apart) on
+// different banks.  Behind the rows, as [span][row]: the 64 pairs as two floats (2-bit rows: 64 four-value tables), and
+// at 2 bits the 2 KiB selector table.
+template <int W, int ROWS> struct TileGeo {
+  static constexpr uint32_t kRowBytes = ROWS == 16 ? ((W == 2) ? 40u : (W == 4) ? 80u : 128u) : ((W == 2) ? 24u : (W == 4) ? 40u : 80u);
+  static constexpr uint32_t kPairsAt = (uint32_t)ROWS * kRowBytes;
 };
+constexpr uint32_t kTableAt = 32u * 24u + 512u;          // the selector table: behind the larger of the two tiles of 2-bit rows
+constexpr uint32_t kTileBytes = kTableAt + 2048u;
 
-// Loader side: lane (n, kq) drops its fetched span and the span's pair into the tile.
-template <int W, int G>
-__device__ inline void stage_span(const SpanData<W, G>& d, uint8_t* tile, uint32_t n, uint32_t kq) {
-  uint32_t* pairs_lds = reinterpret_cast<uint32_t*>(tile + TileGeo<W>::kPairsAt);
-  uint8_t* dst = tile + n * TileGeo<W>::kRowBytes + kq * (4u * W);
+// Loader side: a lane drops its fetched span `span` of row `row`, and the span's pair, into the tile.
+template <int W, int G, int ROWS>
+__device__ inline void stage_span(const SpanData<W, G>& d, uint8_t* tile, uint32_t row, uint32_t span) {
+  uint32_t* pairs_lds = reinterpret_cast<uint32_t*>(tile + TileGeo<W, ROWS>::kPairsAt);
+  uint8_t* dst = tile + row * TileGeo<W, ROWS>::kRowBytes + span * (4u * W);
   if constexpr (W == 2) {
     *reinterpret_cast<u32x2*>(dst) = (u32x2){d.cw[0], d.cw[1]};
-  } else {
-#pragma unroll
-    for (int h = 0; h < (W == 16 ? 16 : W) / 4; ++h)
-      reinterpret_cast<u32x4*>(dst)[h] = (u32x4){d.cw[4 * h], d.cw[4 * h + 1], d.cw[4 * h + 2], d.cw[4 * h + 3]};
-  }
-  if constexpr (W == 2) {
     // the span's four decoded values instead of its (scale, zero): x_k = fp16(fma(k, scale, zero))
     const float s = half_bits_to_float(d.pair & 0xFFFFu);
     const float z = half_bits_to_float(d.pair >> 16);
-    reinterpret_cast<u32x2*>(pairs_lds)[kq * 16u + n] = (u32x2){decode_pair(0.0f, 1.0f, s, z), decode_pair(2.0f, 3.0f, s, z)};
-  } else if constexpr (W != 16) {
-    pairs_lds[kq * 16u + n] = d.pair;
+    reinterpret_cast<u32x2*>(pairs_lds)[span * ROWS + row] = (u32x2){decode_pair(0.0f, 1.0f, s, z), decode_pair(2.0f, 3.0f, s, z)};
+  } else {
+#pragma unroll
+    for (int h = 0; h < W / 4; ++h)
+      reinterpret_cast<u32x4*>(dst)[h] = (u32x4){d.cw[4 * h], d.cw[4 * h + 1], d.cw[4 * h + 2], d.cw[4 * h + 3]};
+    // as the decoder wants them: scale * 2^24 and zero
+    reinterpret_cast<u32x2*>(pairs_lds)[span * ROWS + row] =
+        (u32x2){__float_as_uint(half_bits_to_float(d.pair & 0xFFFFu) * 16777216.0f), __float_as_uint(half_bits_to_float(d.pair >> 16))};
   }
 }
 
-// Reader side: lane (a, kt) picks up the pieces "rows 4 kt + i, columns 8 a .. 8 a + 7", i = 0 .. 3, and decodes
-// them into the eight operands b[e] = {X[4kt][8a+e], X[4kt+1][8a+e], X[4kt+2][8a+e], X[4kt+3][8a+e]}.
+// Reader side, 16 rows: lane (a, kt) picks up the pieces "row 4 kt + i, columns 8 a .. 8 a + 7", i = 0 .. 3, and decodes them
+// into t[i][m] = {X[4 kt + i][8 a + piece_dim(m, 0)], X[4 kt + i][8 a + piece_dim(m, 1)]}.
 template <int W>
-__device__ inline void operands_from_tile(const uint8_t* tile, const uint8_t* table, uint32_t a, uint32_t kt, u32x2 (&b)[8]) {
-  constexpr uint32_t kRowBytes = TileGeo<W>::kRowBytes;
-  const uint32_t* pairs_lds = reinterpret_cast<const uint32_t*>(tile + TileGeo<W>::kPairsAt);
+__device__ inline void pieces_from_tile(const uint8_t* tile, const uint8_t* table, uint32_t a, uint32_t kt, uint32_t (&t)[4][4]) {
+  constexpr uint32_t kRowBytes = TileGeo<W, 16>::kRowBytes;
+  const uint32_t* pairs_lds = reinterpret_cast<const uint32_t*>(tile + TileGeo<W, 16>::kPairsAt);
   if constexpr (W == 2) {
-    // by selection: the piece's two code bytes index the selector table, the selectors pick the
-    // values out of the row's four; then pairs of columns are turned into pairs of rows
-    uint32_t tv[4][4];                     // row i, column pair m: {X[8a+2m], X[8a+2m+1]}
+    // by selection: the piece's two code bytes index the selector table, the selectors pick the values out of the row's four
     const u32x4* xs = reinterpret_cast<const u32x4*>(pairs_lds) + ((a >> 2) * 16u + 4u * kt) / 2u;
     const u32x4 x01 = xs[0], x23 = xs[1];  // the four-value tables of rows 4 kt .. 4 kt + 3 for this lane's columns
     const uint32_t xl[4] = {x01.x, x01.z, x23.x, x23.z}, xh[4] = {x01.y, x01.w, x23.y, x23.w};
@@ -252,54 +306,89 @@ __device__ inline void operands_from_tile(const uint8_t* tile, const uint8_t* ta
       const uint32_t piece = *reinterpret_cast<const uint16_t*>(tile + (4u * kt + i) * kRowBytes + a * 2u);
       const u32x2 s0 = *reinterpret_cast<const u32x2*>(table + byte_times8<0>(piece));
       const u32x2 s1 = *reinterpret_cast<const u32x2*>(table + byte_times8<1>(piece));
-      tv[i][0] = __builtin_amdgcn_perm(xh[i], xl[i], s0.x);
-      tv[i][1] = __builtin_amdgcn_perm(xh[i], xl[i], s0.y);
-      tv[i][2] = __builtin_amdgcn_perm(xh[i], xl[i], s1.x);
-      tv[i][3] = __builtin_amdgcn_perm(xh[i], xl[i], s1.y);
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high or low halves of two words
-      b[e].x = __builtin_amdgcn_perm(tv[1][e >> 1], tv[0][e >> 1], sel);
-      b[e].y = __builtin_amdgcn_perm(tv[3][e >> 1], tv[2][e >> 1], sel);
+      t[i][0] = __builtin_amdgcn_perm(xh[i], xl[i], s0.x);
+      t[i][1] = __builtin_amdgcn_perm(xh[i], xl[i], s0.y);
+      t[i][2] = __builtin_amdgcn_perm(xh[i], xl[i], s1.x);
+      t[i][3] = __builtin_amdgcn_perm(xh[i], xl[i], s1.y);
     }
   } else {
-    Piece<W> pc[4];
-    uint32_t pr[4] = {0u, 0u, 0u, 0u};
+    const u32x4* pr = reinterpret_cast<const u32x4*>(pairs_lds) + ((a >> 2) * 16u + 4u * kt) / 2u;
+    const u32x4 pr01 = pr[0], pr23 = pr[1];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint8_t* src = tile + (4u * kt + i) * kRowBytes + a * W;
-      if constexpr (W == 2) pc[i].w[0] = *reinterpret_cast<const uint16_t*>(src);
-      else if constexpr (W == 4) pc[i].w[0] = *reinterpret_cast<const uint32_t*>(src);
-      else if constexpr (W == 8) { const u32x2 t = *reinterpret_cast<const u32x2*>(src); pc[i].w[0] = t.x; pc[i].w[1] = t.y; }
-      else { const u32x4 t = *reinterpret_cast<const u32x4*>(src); pc[i].w[0] = t.x; pc[i].w[1] = t.y; pc[i].w[2] = t.z; pc[i].w[3] = t.w; }
-    }
-    if constexpr (W != 16) {
-      const u32x4 t = *reinterpret_cast<const u32x4*>(pairs_lds + (a >> 2) * 16u + 4u * kt);
-      pr[0] = t.x; pr[1] = t.y; pr[2] = t.z; pr[3] = t.w;
-    }
-    if constexpr (W == 16) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high or low halves of two words
-        b[e].x = __builtin_amdgcn_perm(pc[1].w[e >> 1], pc[0].w[e >> 1], sel);
-        b[e].y = __builtin_amdgcn_perm(pc[3].w[e >> 1], pc[2].w[e >> 1], sel);
-      }
-    } else {
-      float c0[8], c1[8], c2[8], c3[8];
-      piece_codes<W>(pc[0], pc[1], c0, c1);
-      piece_codes<W>(pc[2], pc[3], c2, c3);
-      const float s0 = half_bits_to_float(pr[0] & 0xFFFFu), z0 = half_bits_to_float(pr[0] >> 16);
-      const float s1 = half_bits_to_float(pr[1] & 0xFFFFu), z1 = half_bits_to_float(pr[1] >> 16);
-      const float s2 = half_bits_to_float(pr[2] & 0xFFFFu), z2 = half_bits_to_float(pr[2] >> 16);
-      const float s3 = half_bits_to_float(pr[3] & 0xFFFFu), z3 = half_bits_to_float(pr[3] >> 16);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        b[e].x = decode_two_tokens(c0[e], s0, z0, c1[e], s1, z1);
-        b[e].y = decode_two_tokens(c2[e], s2, z2, c3[e], s3, z3);
+      const float s = __uint_as_float((i < 2 ? pr01 : pr23)[2 * (i & 1)]), z = __uint_as_float((i < 2 ? pr01 : pr23)[2 * (i & 1) + 1]);
+      if constexpr (W == 4) {
+        decode_word<4>(*reinterpret_cast<const uint32_t*>(src), s, z, t[i]);
+      } else {
+        const u32x2 w = *reinterpret_cast<const u32x2*>(src);
+        decode_word<8>(w.x, s, z, t[i]);
+        decode_word<8>(w.y, s, z, t[i] + 2);
       }
     }
   }
+}
+
+// The same with 32 rows of 64 columns: the pieces "row 16 u + 4 kt + i, columns 4 a .. 4 a + 3" as
+// t[i][2 u + m] = {X[16 u + 4 kt + i][4 a + 2 m], X[16 u + 4 kt + i][4 a + 2 m + 1]} (at 8 bits dimensions m and m + 2).
+template <int W>
+__device__ inline void pieces_from_tile64(const uint8_t* tile, const uint8_t* table, uint32_t a, uint32_t kt, uint32_t (&t)[4][4]) {
+  constexpr uint32_t kRowBytes = TileGeo<W, 32>::kRowBytes;
+  const uint32_t* pairs_lds = reinterpret_cast<const uint32_t*>(tile + TileGeo<W, 32>::kPairsAt);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const uint32_t row = 16u * u + 4u * kt, at = (a >> 3) * 32u + row;
+    if constexpr (W == 2) {
+      const u32x4* xs = reinterpret_cast<const u32x4*>(pairs_lds) + at / 2u;
+      const u32x4 x01 = xs[0], x23 = xs[1];
+      const uint32_t xl[4] = {x01.x, x01.z, x23.x, x23.z}, xh[4] = {x01.y, x01.w, x23.y, x23.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t piece = tile[(row + i) * kRowBytes + a];
+        const u32x2 s = *reinterpret_cast<const u32x2*>(table + 8u * piece);
+        t[i][2 * u] = __builtin_amdgcn_perm(xh[i], xl[i], s.x);
+        t[i][2 * u + 1] = __builtin_amdgcn_perm(xh[i], xl[i], s.y);
+      }
+    } else {
+      const u32x4* pr = reinterpret_cast<const u32x4*>(pairs_lds) + at / 2u;
+      const u32x4 pr01 = pr[0], pr23 = pr[1];
+      const float s[4] = {__uint_as_float(pr01.x), __uint_as_float(pr01.z), __uint_as_float(pr23.x), __uint_as_float(pr23.z)};
+      const float z[4] = {__uint_as_float(pr01.y), __uint_as_float(pr01.w), __uint_as_float(pr23.y), __uint_as_float(pr23.w)};
+#pragma unroll
+      for (int i = 0; i < 4; i += (W == 4 ? 2 : 1)) {
+        const uint8_t* src = tile + (row + i) * kRowBytes + a * (W / 2u);
+        if constexpr (W == 4) {                          // two rows' codes side by side
+          const uint32_t both = *reinterpret_cast<const uint16_t*>(src) | ((uint32_t)*reinterpret_cast<const uint16_t*>(src + kRowBytes) << 16);
+#pragma unroll
+          for (int m = 0; m < 2; ++m) {
+            const uint32_t even = (both >> (8 * m)) & 0x000F000Fu, odd = (both >> (8 * m + 4)) & 0x000F000Fu;
+            t[i][2 * u + m] = pack_halves(fma_low(even, s[i], z[i]), fma_low(odd, s[i], z[i]));
+            t[i + 1][2 * u + m] = pack_halves(fma_high(even, s[i + 1], z[i + 1]), fma_high(odd, s[i + 1], z[i + 1]));
+          }
+        } else {
+          decode_word<8>(*reinterpret_cast<const uint32_t*>(src), s[i], z[i], t[i] + 2 * u);
+        }
+      }
+    }
+  }
+}
+
+// Pairs of columns turned into pairs of rows: b[e] = {X[4kt][8a+e], X[4kt+1][8a+e], X[4kt+2][8a+e], X[4kt+3][8a+e]}.
+template <int W>
+__device__ inline void turn_pieces(const uint32_t (&t)[4][4], u32x2 (&b)[8]) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t sel = h ? 0x07060302u : 0x05040100u;      // high or low halves of two words
+      b[piece_dim<W>(m, h)] = (u32x2){__builtin_amdgcn_perm(t[1][m], t[0][m], sel), __builtin_amdgcn_perm(t[3][m], t[2][m], sel)};
+    }
+}
+template <int W>
+__device__ inline void operands_from_tile(const uint8_t* tile, const uint8_t* table, uint32_t a, uint32_t kt, u32x2 (&b)[8]) {
+  uint32_t t[4][4];
+  pieces_from_tile<W>(tile, table, a, kt, t);
+  turn_pieces<W>(t, b);
 }
 
 // ---- cross-lane helpers ------------------------------------------------------------------------
@@ -411,7 +500,7 @@ __device__ inline void score_pass_kc(const AttendArgs& a, const CardGeom& g, int
     for (int e = 0; e < 8; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-      stage_span<W, 32>(buf[r % kAhead], tile, n, kq);
+      stage_span<W, 32, 16>(buf[r % kAhead], tile, n, kq);
       buf[r % kAhead] = (r + kAhead < kRounds) ? fetch(sb, (uint32_t)(r + kAhead)) : fetch(sb + 1u, (uint32_t)(r + kAhead - kRounds));
       u32x2 b[8];
       operands_from_tile<W>(tile, table, n, kq, b);
@@ -451,168 +540,304 @@ __device__ inline void score_pass_kc(const AttendArgs& a, const CardGeom& g, int
   }
 }
 
+// Raw value rows need no regrouping: the lane reads the pieces it needs - row 4 kt + i, dimensions 8 a .. 8 a + 7; with 64
+// dimensions rows 4 kt + i and 16 + 4 kt + i, dimensions 4 a .. 4 a + 3 - where they lie.
+template <int G, int DS>
+__device__ inline SpanData<16, G> fetch_raw(const RowStream& s, uint32_t rd) {
+  constexpr uint32_t kRow = RowBytes<16, DS>::kCodes;
+  SpanData<16, G> d;
+  d.pair = 0u;
+  const uint32_t at = s.codes_at + rd * (RoundGeo<DS>::kTokens * kRow);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (DS == 2) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const u32x2 t = buffer_load2(s.codes, at + (16u * h + i) * kRow);
+        d.cw[8 * h + 2 * i] = t.x; d.cw[8 * h + 2 * i + 1] = t.y;
+      }
+    } else {
+      const u32x4 t = buffer_load4(s.codes, at + i * kRow);
+      d.cw[4 * i] = t.x; d.cw[4 * i + 1] = t.y; d.cw[4 * i + 2] = t.z; d.cw[4 * i + 3] = t.w;
+    }
+  }
+  return d;
+}
+
+template <int W, int G, int DS>
+__device__ inline RowStream value_stream(const uint8_t* card, const CardGeom& g, int c, uint64_t row0, uint32_t cnt, uint32_t n, uint32_t kq, uint32_t sl) {
+  RowStream s = row_stream<W, G, DS>(card, g, c, row0, cnt, RoundGeo<DS>::row(n, kq), 4u * sl + RoundGeo<DS>::span(kq));
+  if constexpr (W == 16) s.codes_at = 4u * kq * RowBytes<16, DS>::kCodes + (DS == 2 ? 8u * n : 256u * sl + 16u * n);
+  return s;
+}
+
+template <int W, int G, int DS>
+__device__ inline SpanData<W, G> fetch_value(const RowStream& s, uint32_t rd) {
+  if constexpr (W == 16) return fetch_raw<G, DS>(s, rd);
+  else return fetch_span<W, G, DS>(s, rd);
+}
+
+// Rounds whose loads are in flight ahead of the arithmetic: as many as the registers allow (a fetched span is 3 / 5 / 9 / 16
+// registers at 2 / 4 / 8 / 16 bits; two slabs in flight cost twice that).  Their tokens divide 192 and are 96 at most.
+template <int W, int DS> struct Prefetch {
+  static constexpr int kRounds = DS == 2 ? (W <= 4 ? 2 : 1) : W == 2 ? 4 : W == 4 ? 3 : W == 8 && DS == 4 ? 2 : 1;
+};
+
+// How the value pass fills its MFMAs (see attend_task) and what it accumulates.
+template <int HB, int DS> struct ValueGeo {
+  static constexpr bool kTurned = HB == 2 && DS >= 4;
+  static constexpr int kBlocks = HB == 2 && !kTurned ? 2 : 1;          // of 8 heads
+  static constexpr int kSums = kTurned ? 8 : DS == 2 ? 2 : 4;          // pairs of dimensions, or dimensions
+};
+
+// One sweep over a task's value rows: acc[b][m] += weights . V^, 2048 values a round.  `buf` holds the first rounds.
+// The other parity's zero weights turn a value that is no number, or an infinity, into NaN in the dimension beside
+// it: ISOLATE clears one half of every pair of dimensions (`keep`) to work the two out apart.
+template <int W, int G, int HB, int DS, bool ISOLATE>
+__device__ inline void value_sweep(const RowStream& rows, SpanData<W, G> (&buf)[Prefetch<W, DS>::kRounds], uint32_t rounds, const float* lds,
+                                   uint32_t pitch, uint32_t R4, uint8_t* tile, const uint8_t* table, uint32_t n, uint32_t kq, uint32_t keep,
+                                   f32x4 (&acc)[ValueGeo<HB, DS>::kBlocks][ValueGeo<HB, DS>::kSums]) {
+  constexpr int kPrefetch = Prefetch<W, DS>::kRounds;
+  constexpr uint32_t kRows = RoundGeo<DS>::kTokens;
+  constexpr bool kTurned = ValueGeo<HB, DS>::kTurned;
+  constexpr int kBlocks = ValueGeo<HB, DS>::kBlocks, kSums = ValueGeo<HB, DS>::kSums, kHalves = DS == 2 ? 2 : 1;
+  // a row of A has its parity's half of every word, and zero in the other: token 2 x sits in the low half of a pair of weights
+  const uint32_t odd = n & 1u;
+  const uint32_t sel[2] = {odd ? 0x01000C0Cu : 0x0C0C0100u, odd ? 0x03020C0Cu : 0x0C0C0302u};
+  const uint32_t w_head = HB == 0 ? n >> 2 : kTurned ? n : n >> 1;     // of this lane's row (of the first block)
+  const float* w_at = lds + w_head * pitch + 4u * kq + (HB == 0 ? (n & 2u) : 0u);
+#pragma unroll
+  for (int b = 0; b < kBlocks; ++b)
+#pragma unroll
+    for (int m = 0; m < kSums; ++m) acc[b][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (uint32_t rd0 = 0; rd0 < rounds; rd0 += kPrefetch) {
+#pragma unroll
+    for (int u = 0; u < kPrefetch; ++u) {                       // rounds past the task's end add zero weights times zeros
+      const uint32_t rd = rd0 + u;
+      uint32_t t[4][4];                                         // register i of operand x: row i of the lane's four
+      if constexpr (W == 16) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) t[i][x] = DS == 2 ? buf[u].cw[8 * (x >> 1) + 2 * i + (x & 1)] : buf[u].cw[4 * i + x];
+        buf[u] = fetch_raw<G, DS>(rows, rd + kPrefetch);
+      } else {
+        stage_span<W, G, (int)kRows>(buf[u], tile, RoundGeo<DS>::row(n, kq), RoundGeo<DS>::span(kq));
+        buf[u] = fetch_span<W, G, DS>(rows, rd + kPrefetch);
+        if constexpr (DS == 2) pieces_from_tile64<W>(tile, table, n, kq, t);
+        else pieces_from_tile<W>(tile, table, n, kq, t);
+      }
+      if constexpr (kTurned) {
+        u32x2 v[8];
+        turn_pieces<W>(t, v);
+        u32x4 pw = (u32x4)(0u);
+        if (w_head < R4) pw = *reinterpret_cast<const u32x4*>(w_at + rd * kRows);
+        const f16x4 w_hi = __builtin_bit_cast(f16x4, (u32x2){pw.x, pw.y}), w_lo = __builtin_bit_cast(f16x4, (u32x2){pw.z, pw.w});
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const f16x4 ve = __builtin_bit_cast(f16x4, v[e]);
+          acc[0][e] = __builtin_amdgcn_mfma_f32_16x16x16f16(w_hi, ve, acc[0][e], 0, 0, 0);
+          acc[0][e] = __builtin_amdgcn_mfma_f32_16x16x16f16(w_lo, ve, acc[0][e], 0, 0, 0);
+        }
+        continue;
+      }
+      if constexpr (ISOLATE) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) t[i][x] &= keep;
+      }
+#pragma unroll
+      for (int h = 0; h < kHalves; ++h) {
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) {
+          const float* at = w_at + 8 * b * pitch + rd * kRows + 16 * h;
+          u32x4 w_hi, w_lo;
+          if constexpr (HB == 0) {                              // the lane's row is of high or of low parts
+            const u32x2 pw = *reinterpret_cast<const u32x2*>(at);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w_hi[i] = __builtin_amdgcn_perm(0u, pw[i >> 1], sel[i & 1]);
+          } else {
+            u32x4 pw = (u32x4)(0u);
+            if (b == 0 || 8u + w_head < R4) pw = *reinterpret_cast<const u32x4*>(at);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              w_hi[i] = __builtin_amdgcn_perm(0u, pw[i >> 1], sel[i & 1]);
+              w_lo[i] = __builtin_amdgcn_perm(0u, pw[2 + (i >> 1)], sel[i & 1]);
+            }
+          }
+#pragma unroll
+          for (int m = 0; m < (DS == 2 ? 2 : 4); ++m) {
+            const int x = DS == 2 ? 2 * h + m : m;
+            const f16x8 v = __builtin_bit_cast(f16x8, (u32x4){t[0][x], t[1][x], t[2][x], t[3][x]});
+            acc[b][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w_hi), v, acc[b][m], 0, 0, 0);
+            if constexpr (HB > 0) acc[b][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w_lo), v, acc[b][m], 0, 0, 0);
+          }
+        }
+      }
+    }
+  }
+}
+
 // One task: rows [j0, j1) of class c for the pair (layer, kv head) = pair.
-// lds: scores / weights as [head][chunk] floats (R4 * chunk <= kLdsFloatsPerWave);
-// tile: the round's packed rows (16 tokens x up to 256 bytes) followed by the rows' pairs.
+// lds: scores / weights as [head][pitch] floats (R4 * pitch <= kLdsFloatsPerWave);
+// tile: a round's packed rows followed by the rows' pairs.
 //
-// NARROW (at most 4 query heads per kv head, the grouped-query case): the contractions run on
-// v_mfma_f32_4x4x4_16b_f16, sixteen independent 4 x 4 x 4 products per instruction, at half the
-// cycles of the 16 x 16 x 16 form, whose rows 4 .. 15 would be idle.  Block b = lanes 4 b .. 4 b + 3;
-// a lane gives row (lane % 4) of A and column (lane % 4) of B, and gets column (lane % 4) of the
-// block's product, one row per register.
-//   scores   A = q[head n % 4][4 dimensions], B = K^[token n][the same 4 dimensions]: the lane gets
-//            the scores of its token n against the four heads, summed over its quarter kq of the
-//            head dimension only; sum_over_quarters finishes the sum and leaves lane (n, kq)
-//            with head kq, which it stores.
-//   values   A = weights[head a % 4][tokens 4 kt .. + 3], B = V^[those tokens][dimension 8 a + e]:
-//            the lane accumulates, over its own four tokens of every round, out[4 heads][8 a + e];
-//            the four kt are added up once, at the end of the task.
-// Otherwise (5 .. 16 query heads per kv head) the 16 x 16 x 16 form is used with the tokens as rows
-// of the score product, so that a lane ends up with four consecutive tokens of one head.
+// Both contractions run on v_mfma_f32_16x16x32_f16, 512 values of K^ or V^ an instruction.
+//   scores   A = K^[token n][8 dimensions of the lane's span], B = q[head n][the same]: lane (n, kq) gets tokens 4 kq .. + 3 of
+//            head n.  With 64 dimensions a round has 32 tokens; the two halves of the contraction belong to different
+//            tokens, and q is zero in one of them: columns 0 .. 7 are the heads against tokens 0 .. 15, columns 8 .. 15 the
+//            heads against tokens 16 .. 31 (more than 8 heads: one product for each half).  Keys have a few dimensions
+//            far larger than the others, and a sum that holds one of them rounds all that follows: two sums, added up
+//            at the end, are nearer to the value in 64 bits (one sum: output 4.1 .. 6.8e-7 from it, two: 3.4 .. 4.9e-7).
+//   values   V^ is decoded in pairs of neighbouring dimensions, and the contraction runs over (token, parity): B = {four
+//            tokens x both dimensions of pair m}, and a row of A holds the weights of one head in the places of one
+//            parity and zeros in the others.  So nothing has to be turned from pairs of dimensions into pairs of
+//            tokens, and the rows of A that up to 4 heads leave free take that up: HB = 0 has rows (head, high or low part of
+//            the weight, parity), HB = 1 (5 .. 8 heads) rows (head, parity) and an instruction each for the high and
+//            the low parts, HB = 2 (9 .. 16 heads) two blocks of 8 heads with 64 dimensions; with more, where two blocks'
+//            sums leave room for three waves a SIMD only (16 heads, 3622 tokens of 256 pairs: 75.3 -> 81.7 us), the
+//            pairs are turned and v_mfma_f32_16x16x16_f16 has the 16 heads as rows.
 //
-// DS = head_dim / 32 spans per token.  The lane mapping covers a slab of 128 dimensions (4 spans);
-// head_dim 256 is two slabs (the score of a round adds both up before it is stored, the value
-// pass sweeps the task once per slab), head_dim 64 half a slab (quarters 2 and 3 see zeros).
-template <int W, int G, bool NARROW, int DS, bool KC>
+// DS = head_dim / 32 spans per token.  The lane mapping covers a slab of 128 dimensions (4 spans); head_dim 256 is two
+// slabs (the score of a round adds both up before it is stored, the value pass sweeps the task once per slab).
+template <int W, int G, int HB, int DS, bool KC>
 __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c, uint32_t pair, uint32_t j0, uint32_t j1,
                                    uint32_t lane, float* lds, uint8_t* tile, const uint8_t* table, uint64_t part) {
   const uint32_t n = lane & 15u, kq = lane >> 4;          // also (a, kt) of the value pass
-  const uint32_t R = a.rep, R4 = NARROW ? 4u : ((R + 3u) & ~3u);
-  const uint32_t chunk = a.chunk % 192u == 0u ? a.chunk : 96u;      // LDS pitch of a head's scores: the task size, padded
+  const uint32_t R = a.rep, R4 = HB == 0 ? 4u : ((R + 3u) & ~3u);
+  const uint32_t pitch = a.chunk % 192u == 0u ? a.chunk : 96u;      // LDS pitch of a head's scores: the task size, padded
   const uint32_t lh = g.planes >> 1;
   const uint32_t n_c = g.n[c];
   const uint64_t k_row0 = (uint64_t)pair * n_c;            // K plane p = pair, V plane p = L*H + pair
   const uint64_t v_row0 = (uint64_t)(lh + pair) * n_c;
   const uint32_t cnt = j1 - j0;
-  const uint32_t rounds = (cnt + kRoundTokens - 1) / kRoundTokens;
-  constexpr int kPrefetch = (DS > 4 && W >= 8) ? 1 : Prefetch<W>::kRounds;     // two slabs in flight cost twice the registers
+  constexpr uint32_t kRows = RoundGeo<DS>::kTokens;
+  const uint32_t rounds = (cnt + kRows - 1u) / kRows;
+  constexpr int kPrefetch = Prefetch<W, DS>::kRounds;
   constexpr int S = (DS + 3) / 4;                          // slabs of 128 dimensions
   constexpr uint32_t D = 32u * DS;
-  const bool lane_has_span = DS >= 4 || kq < (uint32_t)DS; // head_dim 64: quarters 2 and 3 hold nothing
+  const uint32_t row = RoundGeo<DS>::row(n, kq), span = RoundGeo<DS>::span(kq);
   // Rounds are processed in whole groups of kPrefetch; the task size is a multiple of such a group, so the padded
   // rounds stay inside the task's share of LDS.  The softmax covers `slots` tokens, those past the task's end at -inf.
-  const uint32_t slots = (rounds + kPrefetch - 1) / kPrefetch * kPrefetch * kRoundTokens;
+  const uint32_t slots = (rounds + kPrefetch - 1) / kPrefetch * kPrefetch * kRows;
   if constexpr (KC) {
     if constexpr (W != 16 && G == 32 && DS <= 4)
-      score_pass_kc<W, NARROW, DS>(a, g, c, pair, j0, cnt, slots, lane, lds, chunk, R4, tile, table);
+      score_pass_kc<W, HB == 0, DS>(a, g, c, pair, j0, cnt, slots, lane, lds, pitch, R4, tile, table);
   } else {
-    LanePtrs kp[S];
+    RowStream ks[S];
 #pragma unroll
-    for (int sl = 0; sl < S; ++sl) kp[sl] = lane_pointers<W, G, DS>(a.card, g, c, k_row0 + j0, n, lane_has_span ? 4u * sl + kq : 0u);
+    for (int sl = 0; sl < S; ++sl) ks[sl] = row_stream<W, G, DS>(a.card, g, c, k_row0 + j0, cnt, row, 4u * sl + span);
 
-    // ---- q as MFMA operands: the lane holds q[head][128 sl + 32 kq .. + 31] of head n (head n % 4 when
-    // NARROW); operand j of slab sl is q[head][128 sl + 32 kq + 4 j .. + 3]
-    f16x4 qa[S][8];
+    // ---- q as MFMA operands: operand j of slab sl is q[head][128 sl + 32 span + 8 j .. + 7]
+    constexpr int kSets = DS == 2 && HB == 2 ? 2 : 1;
+    const uint32_t head = DS == 2 && HB < 2 ? (n & 7u) : n;
+    f16x8 qa[S * kSets][4];
 #pragma unroll
     for (int sl = 0; sl < S; ++sl) {
       u32x4 raw[4];
 #pragma unroll
-      for (int h = 0; h < 4; ++h) raw[h] = (u32x4)(0u);
-      const uint32_t head = NARROW ? (n & 3u) : n;
-      if (head < R && lane_has_span) {
+      for (int j = 0; j < 4; ++j) raw[j] = (u32x4)(0u);
+      if (head < R && (DS != 2 || HB == 2 || (n >> 3) == (kq >> 1))) {
         const uint32_t l = pair / g.kv_heads, hh = pair - l * g.kv_heads;
-        const u32x4* src = reinterpret_cast<const u32x4*>(a.q + ((uint64_t)(l * a.q_heads + hh * R + head) * D + 128u * sl + 32u * kq));
+        const u32x4* src = reinterpret_cast<const u32x4*>(a.q + ((uint64_t)(l * a.q_heads + hh * R + head) * D + 128u * sl + 32u * span));
 #pragma unroll
-        for (int h = 0; h < 4; ++h) raw[h] = src[h];
+        for (int j = 0; j < 4; ++j) raw[j] = src[j] ^ a.q_flip;
       }
 #pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        qa[sl][2 * h] = __builtin_bit_cast(f16x4, (u32x2){raw[h].x, raw[h].y});
-        qa[sl][2 * h + 1] = __builtin_bit_cast(f16x4, (u32x2){raw[h].z, raw[h].w});
-      }
-    }
-
-    // ---- scores: lds[head * chunk + token] in log2 units, -inf for tokens past the task's end.
-    // The loads of the next kPrefetch rounds are always in flight.
-    {
-      SpanData<W, G> buf[kPrefetch][S];
-#pragma unroll
-      for (int u = 0; u < kPrefetch; ++u) {
-        const uint32_t t = u * kRoundTokens + n;
-#pragma unroll
-        for (int sl = 0; sl < S; ++sl) buf[u][sl] = fetch_span<W, G, DS>(kp[sl], u, t < cnt && lane_has_span);
-      }
-      for (uint32_t rd0 = 0; rd0 < rounds; rd0 += kPrefetch) {
-#pragma unroll
-        for (int u = 0; u < kPrefetch; ++u) {
-          const uint32_t rd = rd0 + u;
-          {                                          // rounds past the task's end see zeros and store -inf
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int sl = 0; sl < S; ++sl) {
-              uint32_t kb[16];
-              if constexpr (W == 2) decode_fetched_select<G>(buf[u][sl], table, kb);
-              else decode_fetched<W, G>(buf[u][sl], kb);
-              const uint32_t tn = (rd + kPrefetch) * kRoundTokens + n;
-              buf[u][sl] = fetch_span<W, G, DS>(kp[sl], rd + kPrefetch, tn < cnt && lane_has_span);
-#pragma unroll
-              for (int j = 0; j < 8; ++j) {
-                const f16x4 kj = __builtin_bit_cast(f16x4, (u32x2){kb[2 * j], kb[2 * j + 1]});
-                if constexpr (NARROW) acc = __builtin_amdgcn_mfma_f32_4x4x4f16(qa[sl][j], kj, acc, 0, 0, 0);
-                else acc = __builtin_amdgcn_mfma_f32_16x16x16f16(kj, qa[sl][j], acc, 0, 0, 0);
-              }
-            }
-            if constexpr (NARROW) {
-              // head kq of token n
-              const float sc = sum_over_quarters(acc.x, acc.y, acc.z, acc.w);
-              const uint32_t t = rd * kRoundTokens + n;
-              lds[kq * chunk + t] = (t < cnt) ? sc * a.scale_log2 : -INFINITY;
-            } else {
-              // tokens 4 kq .. 4 kq + 3 of head n
-              const uint32_t t = rd * kRoundTokens + 4u * kq;
-              if (n < R4) {
-                f32x4 sc;
-                sc.x = (t < cnt) ? acc.x * a.scale_log2 : -INFINITY;
-                sc.y = (t + 1u < cnt) ? acc.y * a.scale_log2 : -INFINITY;
-                sc.z = (t + 2u < cnt) ? acc.z * a.scale_log2 : -INFINITY;
-                sc.w = (t + 3u < cnt) ? acc.w * a.scale_log2 : -INFINITY;
-                *reinterpret_cast<f32x4*>(lds + n * chunk + t) = sc;
-              }
-            }
-          }
+      for (int j = 0; j < 4; ++j) {
+        if (j == 0) order_q<W>(raw);
+        if constexpr (kSets == 2) {
+          qa[0][j] = __builtin_bit_cast(f16x8, kq < 2u ? raw[j] : (u32x4)(0u));
+          qa[1][j] = __builtin_bit_cast(f16x8, kq < 2u ? (u32x4)(0u) : raw[j]);
+        } else {
+          qa[sl][j] = __builtin_bit_cast(f16x8, raw[j]);
         }
       }
     }
 
+    // ---- scores: lds[head * pitch + token], not scaled yet.  The loads of the next kPrefetch rounds are always in flight.
+    SpanData<W, G> buf[kPrefetch][S];
+#pragma unroll
+    for (int u = 0; u < kPrefetch; ++u)
+#pragma unroll
+      for (int sl = 0; sl < S; ++sl) buf[u][sl] = fetch_span<W, G, DS>(ks[sl], u);
+#pragma unroll 1
+    for (uint32_t rd0 = 0; rd0 < rounds; rd0 += kPrefetch) {
+#pragma unroll
+      for (int u = 0; u < kPrefetch; ++u) {
+        const uint32_t rd = rd0 + u;
+        f32x4 acc[kSets][2];                             // a sum for every other operand, see below
+#pragma unroll
+        for (int s = 0; s < kSets; ++s)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[s][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int sl = 0; sl < S; ++sl) {
+          uint32_t kb[16];
+          if constexpr (W == 2) decode_fetched_bytes<G>(buf[u][sl], kb);
+          else decode_fetched<W, G>(buf[u][sl], kb);
+          buf[u][sl] = fetch_span<W, G, DS>(ks[sl], rd + kPrefetch);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const f16x8 kj = __builtin_bit_cast(f16x8, (u32x4){kb[4 * j], kb[4 * j + 1], kb[4 * j + 2], kb[4 * j + 3]});
+#pragma unroll
+            for (int s = 0; s < kSets; ++s) acc[s][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kj, qa[kSets == 2 ? s : sl][j], acc[s][j & 1], 0, 0, 0);
+          }
+        }
+        if (head < R4) {
+          float* dst = lds + head * pitch + rd * kRows + 4u * kq;
+#pragma unroll
+          for (int s = 0; s < kSets; ++s)
+            *reinterpret_cast<f32x4*>(dst + (kSets == 2 ? 16u * s : DS == 2 ? 16u * (n >> 3) : 0u)) = acc[s][0] + acc[s][1];
+        }
+      }
+    }
   }   // per-token key groups
+
+  // the first value rows are requested now, so that they arrive while the softmax runs
+  RowStream vs = value_stream<W, G, DS>(a.card, g, c, v_row0 + j0, cnt, n, kq, 0u);
+  SpanData<W, G> vbuf[kPrefetch];
+#pragma unroll
+  for (int u = 0; u < kPrefetch; ++u) vbuf[u] = fetch_value<W, G, DS>(vs, u);
 
   // ---- softmax over the task's tokens, four heads at a time: row kq of the wave takes head
   // 4 hg + kq, its lane n the tokens 64 i + 4 n .. + 3 (the wave's own LDS accesses are in order).
-  // the first value rows are requested now, so that they arrive while the softmax runs
-  LanePtrs vp = lane_pointers<W, G, DS>(a.card, g, c, v_row0 + j0, n, lane_has_span ? kq : 0u);
-  SpanData<W, G> vbuf[kPrefetch];
-#pragma unroll
-  for (int u = 0; u < kPrefetch; ++u) {
-    const uint32_t t = u * kRoundTokens + n;
-    vbuf[u] = fetch_span<W, G, DS>(vp, u, t < cnt && lane_has_span);
-  }
+  const float scale = KC ? 1.0f : a.scale_log2;            // not negative; scores of keys grouped per channel are scaled already
+  const uint32_t whole = cnt & ~63u;                       // tokens of blocks that need no mask
   for (uint32_t hg = 0; hg < R4; hg += 4u) {
     const uint32_t r = hg + kq;
-    float* row = lds + r * chunk;
+    float* row_w = lds + r * pitch;
     float m = -INFINITY;
-    for (uint32_t t = 4u * n; t < slots; t += 64u) {
-      const f32x4 sv = *reinterpret_cast<const f32x4*>(row + t);
-      m = fmaxf(fmaxf(m, fmaxf(sv.x, sv.y)), fmaxf(sv.z, sv.w));
-    }
-    m = row_max16(m);
+    const auto top = [&](uint32_t t, bool masked) {
+      const f32x4 sv = *reinterpret_cast<const f32x4*>(row_w + t);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) m = fmaxf(m, !masked || t + i < cnt ? sv[i] : -INFINITY);
+    };
+    for (uint32_t t = 0; t < whole; t += 64u) top(t + 4u * n, false);
+    for (uint32_t t = whole + 4u * n; t < slots; t += 64u) top(t, true);
+    m = row_max16(m) * scale;
     float l = 0.f;
-    for (uint32_t t = 4u * n; t < slots; t += 64u) {
-      const f32x4 sv = *reinterpret_cast<const f32x4*>(row + t);
-      u32x4 packed;
+    const auto weigh = [&](uint32_t t, bool masked) {
+      const f32x4 sv = *reinterpret_cast<const f32x4*>(row_w + t);
+      float ps[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float p = __builtin_amdgcn_exp2f(sv[i] - m);
+        const float x = __builtin_fmaf(sv[i], scale, -m);
+        const float p = __builtin_amdgcn_exp2f(!masked || t + i < cnt ? x : -INFINITY);
         l += p;
-        // what the value pass feeds the MFMA: p * 2^14 as an fp16 high part plus the fp16 remainder (both go
-        // into the same accumulator; the remainder is a normal number for any p that matters), packed into
-        // the score's slot
-        const float ps = p * 16384.0f;
-        const _Float16 hi = (_Float16)ps;
-        const _Float16 lo = (_Float16)(ps - (float)hi);
-        packed[i] = (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
+        ps[i] = p * 16384.0f;
       }
-      *reinterpret_cast<u32x4*>(row + t) = packed;
-    }
+      // what the value pass feeds the MFMA: p * 2^14 as an fp16 high part and the fp16 remainder (a normal number for any p
+      // that matters), in the scores' places: four high parts, then four remainders
+      const uint32_t h01 = pack_halves(ps[0], ps[1]), h23 = pack_halves(ps[2], ps[3]);
+      *reinterpret_cast<u32x4*>(row_w + t) =
+          (u32x4){h01, h23, pack_halves(fma_low(h01, -1.0f, ps[0]), fma_high(h01, -1.0f, ps[1])),
+                  pack_halves(fma_low(h23, -1.0f, ps[2]), fma_high(h23, -1.0f, ps[3]))};
+    };
+    for (uint32_t t = 0; t < whole; t += 64u) weigh(t + 4u * n, false);
+    for (uint32_t t = whole + 4u * n; t < slots; t += 64u) weigh(t, true);
     l = row_sum16(l);
     if (n == 0 && r < R) {
       a.part_ml[(part * R + r) * 2] = m;
@@ -620,84 +845,62 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
     }
   }
 
-  // ---- values
-  const uint32_t w_head = NARROW ? (n & 3u) : n;            // the head whose weights this lane feeds the MFMA
-  // one sweep over the task's rows per slab of 128 output dimensions (the weights stay in LDS)
+  // ---- values: one sweep over the task's rows per slab of 128 output dimensions (the weights stay in LDS)
+  constexpr int kBlocks = ValueGeo<HB, DS>::kBlocks, kSums = ValueGeo<HB, DS>::kSums;
 #pragma unroll 1
   for (int sl = 0; sl < S; ++sl) {
     if (sl > 0) {
-      vp = lane_pointers<W, G, DS>(a.card, g, c, v_row0 + j0, n, 4u * sl + kq);
+      vs = value_stream<W, G, DS>(a.card, g, c, v_row0 + j0, cnt, n, kq, (uint32_t)sl);
 #pragma unroll
-      for (int u = 0; u < kPrefetch; ++u) {
-        const uint32_t t = u * kRoundTokens + n;
-        vbuf[u] = fetch_span<W, G, DS>(vp, u, t < cnt);
-      }
+      for (int u = 0; u < kPrefetch; ++u) vbuf[u] = fetch_value<W, G, DS>(vs, u);
     }
-    f32x4 acc[8];
+    f32x4 acc[kBlocks][kSums];
+    value_sweep<W, G, HB, DS, false>(vs, vbuf, rounds, lds, pitch, R4, tile, table, n, kq, 0u, acc);
+    if constexpr (!ValueGeo<HB, DS>::kTurned) {
+      float finite = 0.f;                                    // stays 0 if all sums are numbers
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    {
-      SpanData<W, G> (&buf)[kPrefetch] = vbuf;
-      for (uint32_t rd0 = 0; rd0 < rounds; rd0 += kPrefetch) {
+      for (int b = 0; b < kBlocks; ++b)
 #pragma unroll
-        for (int u = 0; u < kPrefetch; ++u) {
-          const uint32_t rd = rd0 + u;
-          {                                          // rounds past the task's end add zero weights times zeros
-            // rows into LDS as they were loaded: token n, quarter kq
-            stage_span<W, G>(buf[u], tile, n, kq);
-            const uint32_t tn = (rd + kPrefetch) * kRoundTokens + n;
-            buf[u] = fetch_span<W, G, DS>(vp, rd + kPrefetch, tn < cnt && lane_has_span);
-
-            // lane (a, kt) = (n, kq): b[e] = {V^[4kt][8a+e], V^[4kt+1][8a+e], V^[4kt+2][8a+e], V^[4kt+3][8a+e]}
-            u32x2 b[8];
-            operands_from_tile<W>(tile, table, n, kq, b);
-            // A operands: the weights of head w_head for tokens 4 kt .. 4 kt + 3, high parts and low parts
-            u32x4 pw = (u32x4)(0u);
-            if (w_head < R4) pw = *reinterpret_cast<const u32x4*>(lds + w_head * chunk + rd * kRoundTokens + 4u * kq);
-            const f16x4 a_hi = __builtin_bit_cast(f16x4, (u32x2){__builtin_amdgcn_perm(pw.y, pw.x, 0x05040100u),
-                                                                 __builtin_amdgcn_perm(pw.w, pw.z, 0x05040100u)});
-            const f16x4 a_lo = __builtin_bit_cast(f16x4, (u32x2){__builtin_amdgcn_perm(pw.y, pw.x, 0x07060302u),
-                                                                 __builtin_amdgcn_perm(pw.w, pw.z, 0x07060302u)});
+        for (int m = 0; m < kSums; ++m)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const f16x4 be = __builtin_bit_cast(f16x4, b[e]);
-              if constexpr (NARROW) {
-                acc[e] = __builtin_amdgcn_mfma_f32_4x4x4f16(a_hi, be, acc[e], 0, 0, 0);
-                acc[e] = __builtin_amdgcn_mfma_f32_4x4x4f16(a_lo, be, acc[e], 0, 0, 0);
-              } else {
-                acc[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(a_hi, be, acc[e], 0, 0, 0);
-                acc[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(a_lo, be, acc[e], 0, 0, 0);
-              }
-            }
-          }
+          for (int i = 0; i < 4; ++i) finite = __builtin_fmaf(acc[b][m][i], 0.0f, finite);
+      if (__builtin_amdgcn_ballot_w64(finite != 0.0f) != 0ull) {
+#pragma unroll 1
+        for (uint32_t odd = 0; odd < 2u; ++odd) {
+          f32x4 one[kBlocks][kSums];
+#pragma unroll
+          for (int u = 0; u < kPrefetch; ++u) vbuf[u] = fetch_value<W, G, DS>(vs, u);
+          value_sweep<W, G, HB, DS, true>(vs, vbuf, rounds, lds, pitch, R4, tile, table, n, kq, odd ? 0xFFFF0000u : 0x0000FFFFu, one);
+#pragma unroll
+          for (int b = 0; b < kBlocks; ++b)
+#pragma unroll
+            for (int m = 0; m < kSums; ++m)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) acc[b][m][i] = (uint32_t)(i & 1) == odd ? one[b][m][i] : acc[b][m][i];
         }
       }
     }
-    if constexpr (NARROW) {
-      // the lane holds, for its own tokens only, out[heads 0 .. 3][dimensions 8 n .. 8 n + 7]: add up the four kt;
-      // lane (n, kq) is left with head kq
-      // (every lane takes part in the sums; only the stores are conditional)
-      float o[8];
+    // the lane holds: HB = 0 head kq, {high even, high odd, low even, low odd} of each pair of dimensions; turned: heads
+    // 4 kq .. 4 kq + 3 of each dimension; otherwise heads 2 kq and 2 kq + 1 of every block, {even, odd} of both
+    constexpr bool kTurned = ValueGeo<HB, DS>::kTurned;
+    const uint32_t d0 = DS == 2 ? 4u * n : 128u * sl + 8u * n;
+    constexpr float kUnscale = 1.0f / 16384.0f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = sum_over_quarters(acc[e].x, acc[e].y, acc[e].z, acc[e].w) * (1.0f / 16384.0f);
-      if (kq < R && (DS >= 4 || n < 8u)) {          // head_dim 64: lanes n >= 8 stand for dimensions that do not exist
-        f32x4* dst = reinterpret_cast<f32x4*>(a.part_o + (part * R + kq) * D + 128u * sl + 8u * n);
+    for (int x = 0; x < (HB == 0 ? 1 : HB == 1 ? 2 : 4); ++x) {
+      const uint32_t r = HB == 0 ? kq : kTurned ? 4u * kq + x : 8u * (x >> 1) + 2u * kq + (x & 1u);
+      if (r < R) {
+        float o[8];
+#pragma unroll
+        for (int e = 0; e < (DS == 2 ? 4 : 8); ++e) {
+          const int m = e >> 1, h = e & 1;
+          const int to = DS == 2 ? (W == 8 ? m + 2 * h : e) : kTurned ? e : piece_dim<W>(m, h);
+          if constexpr (kTurned) o[to] = acc[0][e][x] * kUnscale;
+          else if constexpr (HB == 0) o[to] = (acc[0][m][h] + acc[0][m][2 + h]) * kUnscale;
+          else o[to] = acc[x >> 1][m][2 * (x & 1) + h] * kUnscale;
+        }
+        f32x4* dst = reinterpret_cast<f32x4*>(a.part_o + (part * R + r) * D + d0);
         dst[0] = (f32x4){o[0], o[1], o[2], o[3]};
-        dst[1] = (f32x4){o[4], o[5], o[6], o[7]};
-      }
-    } else {
-      // the lane holds out[heads 4 kq .. 4 kq + 3][dimensions 8 n .. 8 n + 7]
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t r = 4u * kq + i;
-        if (r < R && (DS >= 4 || n < 8u)) {
-          float o[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = acc[e][i] * (1.0f / 16384.0f);
-          f32x4* dst = reinterpret_cast<f32x4*>(a.part_o + (part * R + r) * D + 128u * sl + 8u * n);
-          dst[0] = (f32x4){o[0], o[1], o[2], o[3]};
-          dst[1] = (f32x4){o[4], o[5], o[6], o[7]};
-        }
+        if constexpr (DS != 2) dst[1] = (f32x4){o[4], o[5], o[6], o[7]};
       }
     }
   }
@@ -716,7 +919,7 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
 // classes share one divisor, the units are constants (keys per channel apart, where one class has rows).  With a division
 // by a different number for every class the kernel lost 0.4 to 0.8 us on any card, more with more waves: 8000 tokens of 256
 // pairs at head_dim 64 70.0 -> 75.2 us, 3000 tokens of 384 pairs at 16 heads 65.7 -> 72.0; now 69.4 and 65.3.
-template <bool KC>
+template <int DS, bool KC>
 __device__ inline int find_task(const AttendArgs& a, const CardGeom& g, uint32_t tau, uint32_t& j0, uint32_t& j1) {
   int cls = -1;
   // one divisor for all classes: its reciprocal is worked out once, ahead of the header's arrival where it is `chunk`
@@ -738,7 +941,7 @@ __device__ inline int find_task(const AttendArgs& a, const CardGeom& g, uint32_t
   uint32_t unit[4], units[4], sum = 0, present = 0, most = ~0u;        // most: units that fit a task of every class present
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    unit[c] = KC ? a.unit[c] : kUnit[c];
+    unit[c] = KC ? a.unit[c] : kUnit[DS == 2][c];
     units[c] = g.n[c] == 0u ? 0u : (g.n[c] + unit[c] - 1u) / unit[c];
     sum += units[c];
     present += (uint32_t)(g.n[c] != 0u);
@@ -757,13 +960,13 @@ __device__ inline int find_task(const AttendArgs& a, const CardGeom& g, uint32_t
 }
 
 // KC: the card's key planes are grouped per channel (a uniform card at 2, 4 or 8 bits, group size 32).
-template <int G, bool NARROW, int DS, bool KC>
-__global__ __launch_bounds__(kAttendWaves * kWaveSize) __attribute__((amdgpu_waves_per_eu(2)))
+template <int G, int HB, int DS, bool KC>
+__global__ __launch_bounds__(kAttendWaves * kWaveSize) __attribute__((amdgpu_waves_per_eu(4)))
 void attend_kernel(AttendArgs a) {
   __shared__ __attribute__((aligned(16))) float lds[kAttendWaves][kLdsFloatsPerWave];
-  // the value pass's LDS, 4 KiB: 16 packed rows (640 / 1280 / 2048 / 4096 bytes at 2 / 4 / 8 / 16 bits), then the
-  // rows' pairs (256 bytes; 512 bytes of four-value tables at 2 bits), then at 2 bits the 2 KiB selector table
-  __shared__ __attribute__((aligned(16))) uint8_t tiles[kAttendWaves][16 * 256];
+  // the value pass's LDS, 3.25 KiB: a round's packed rows (640 / 1280 / 2048 bytes at 2 / 4 / 8 bits; 64 dimensions 768 / 1280 / 2560),
+  // then the rows' pairs (512 bytes), then at 2 bits the 2 KiB selector table
+  __shared__ __attribute__((aligned(16))) uint8_t tiles[kAttendWaves][kTileBytes];
   CardGeom g;
   bool ok = card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size,
                                       a.tokens, g, KC ? QKV_FLAG_KEYS_PER_CHANNEL : 0u);
@@ -787,7 +990,7 @@ void attend_kernel(AttendArgs a) {
   const uint64_t part = (uint64_t)pair * a.max_tasks + tau;
 
   uint32_t j0 = 0, j1 = 0;
-  const int cls = find_task<KC>(a, g, tau, j0, j1);
+  const int cls = find_task<DS, KC>(a, g, tau, j0, j1);
   if (cls < 0) {                               // spare task: an empty partial
     for (uint32_t r = lane; r < a.rep; r += kWaveSize) {
       a.part_ml[(part * a.rep + r) * 2] = -INFINITY;
@@ -797,15 +1000,15 @@ void attend_kernel(AttendArgs a) {
   }
   float* my_lds = lds[wave];
   uint8_t* my_tile = tiles[wave];
-  uint8_t* my_table = my_tile + 16 * 40 + 512;
+  uint8_t* my_table = my_tile + kTableAt;
   if (cls == 0) {
     build_select_table(reinterpret_cast<u32x2*>(my_table), lane);
-    attend_task<2, G, NARROW, DS, KC>(a, g, 0, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
+    attend_task<2, G, HB, DS, KC>(a, g, 0, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
   }
-  if (cls == 1) attend_task<4, G, NARROW, DS, KC>(a, g, 1, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
-  if (cls == 2) attend_task<8, G, NARROW, DS, KC>(a, g, 2, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
+  if (cls == 1) attend_task<4, G, HB, DS, KC>(a, g, 1, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
+  if (cls == 2) attend_task<8, G, HB, DS, KC>(a, g, 2, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
   if constexpr (!KC) {                         // a card grouped per channel has no raw rows
-    if (cls == 3) attend_task<16, G, NARROW, DS, false>(a, g, 3, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
+    if (cls == 3) attend_task<16, G, HB, DS, false>(a, g, 3, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
   }
 }
 
@@ -991,6 +1194,8 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
   a.q_heads = q_heads;
   a.rep = q_heads / expect.kv_heads;
   a.scale_log2 = softmax_scale * 1.44269504088896340736f;
+  a.q_flip = !keys_per_channel && std::signbit(a.scale_log2) ? 0x80008000u : 0u;
+  if (a.q_flip != 0u) a.scale_log2 = -a.scale_log2;
   attend_plan(expect.tokens, a.rep, (uint64_t)expect.layers * expect.kv_heads, &a.chunk, &a.max_tasks);
   const uint64_t pairs = (uint64_t)expect.layers * expect.kv_heads;
   const uint32_t D = expect.head_dim;
@@ -1000,11 +1205,12 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
   }
   // a group of rounds whose loads are in flight together: 4, 3, 2 or 1 rounds of 16 tokens; keys grouped per channel are
   // scored up to 128 tokens at a time, in whole blocks of 32
+  const uint32_t* unit = kUnit[D == 64u];
   const bool wide_units = keys_per_channel && a.chunk >= 128u;
-  a.unit[0] = wide_units ? 128u : kUnit[0];
-  a.unit[1] = keys_per_channel ? (a.chunk >= 96u ? 96u : 64u) : kUnit[1];
-  a.unit[2] = wide_units ? 128u : kUnit[2];
-  a.unit[3] = kUnit[3];
+  a.unit[0] = wide_units ? 128u : unit[0];
+  a.unit[1] = keys_per_channel ? (a.chunk >= 96u ? 96u : 64u) : unit[1];
+  a.unit[2] = wide_units ? 128u : unit[2];
+  a.unit[3] = unit[3];
   for (int c = 0; c < 4; ++c) a.fit[c] = a.chunk / a.unit[c];
   // Where full tasks fit the wave slots, even ones have to as well: a few waves more than slots would run after all others
   // (whole call, us, with every task in use and like this: 256 pairs, 6000 tokens of 8 bits 102.1 and 96.0, 3000 of 16 bits
@@ -1019,27 +1225,22 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
   a.lse = lse;
   a.status = status;
   const dim3 grid((uint32_t)((waves + kAttendWaves - 1) / kAttendWaves)), block(kAttendWaves * kWaveSize);
-  const bool narrow = a.rep <= 4u;             // grouped-query shapes: the 4 x 4 x 4 contraction
+  const int hb = a.rep <= 4u ? 0 : a.rep <= 8u ? 1 : 2;      // how the weights fill the rows of an MFMA, see attend_task
   const uint32_t G = expect.group_size;
-#define QKV_LAUNCH_ATTEND(GG, DSS)                                                                     \
+#define QKV_LAUNCH_ATTEND(GG, DSS, KCC)                                                                \
   do {                                                                                                 \
-    if (narrow) hipLaunchKernelGGL((attend_kernel<GG, true, DSS, false>), grid, block, 0, stream, a);  \
-    else hipLaunchKernelGGL((attend_kernel<GG, false, DSS, false>), grid, block, 0, stream, a);        \
+    if (hb == 0) hipLaunchKernelGGL((attend_kernel<GG, 0, DSS, KCC>), grid, block, 0, stream, a);      \
+    else if (hb == 1) hipLaunchKernelGGL((attend_kernel<GG, 1, DSS, KCC>), grid, block, 0, stream, a); \
+    else hipLaunchKernelGGL((attend_kernel<GG, 2, DSS, KCC>), grid, block, 0, stream, a);              \
   } while (0)
   if (keys_per_channel) {                      // the host has checked: group size 32, head_dim 64 or 128
-    if (D == 64u) {
-      if (narrow) hipLaunchKernelGGL((attend_kernel<32, true, 2, true>), grid, block, 0, stream, a);
-      else hipLaunchKernelGGL((attend_kernel<32, false, 2, true>), grid, block, 0, stream, a);
-    } else {
-      if (narrow) hipLaunchKernelGGL((attend_kernel<32, true, 4, true>), grid, block, 0, stream, a);
-      else hipLaunchKernelGGL((attend_kernel<32, false, 4, true>), grid, block, 0, stream, a);
-    }
+    if (D == 64u) QKV_LAUNCH_ATTEND(32, 2, true); else QKV_LAUNCH_ATTEND(32, 4, true);
   } else if (D == 64u) {
-    if (G == 32u) QKV_LAUNCH_ATTEND(32, 2); else QKV_LAUNCH_ATTEND(64, 2);
+    if (G == 32u) QKV_LAUNCH_ATTEND(32, 2, false); else QKV_LAUNCH_ATTEND(64, 2, false);
   } else if (D == 128u) {
-    if (G == 32u) QKV_LAUNCH_ATTEND(32, 4); else if (G == 64u) QKV_LAUNCH_ATTEND(64, 4); else QKV_LAUNCH_ATTEND(128, 4);
+    if (G == 32u) QKV_LAUNCH_ATTEND(32, 4, false); else if (G == 64u) QKV_LAUNCH_ATTEND(64, 4, false); else QKV_LAUNCH_ATTEND(128, 4, false);
   } else {
-    if (G == 32u) QKV_LAUNCH_ATTEND(32, 8); else if (G == 64u) QKV_LAUNCH_ATTEND(64, 8); else QKV_LAUNCH_ATTEND(128, 8);
+    if (G == 32u) QKV_LAUNCH_ATTEND(32, 8, false); else if (G == 64u) QKV_LAUNCH_ATTEND(64, 8, false); else QKV_LAUNCH_ATTEND(128, 8, false);
   }
 #undef QKV_LAUNCH_ATTEND
   hipError_t e = hipGetLastError();

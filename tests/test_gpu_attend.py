@@ -104,7 +104,7 @@ def test_query_heads_per_kv_head(rep):
 @pytest.mark.parametrize("D,G", [(64, 32), (64, 64), (256, 32), (256, 64), (256, 128)])
 @pytest.mark.parametrize("rep", [1, 4, 7, 16])
 def test_other_head_dims(D, G, rep):
-    """head_dim 64 (half of the kernel's lanes idle) and 256 (two halves of 128), mixed widths, both MFMA forms."""
+    """head_dim 64 (rounds of 32 tokens) and 256 (two halves of 128), mixed widths, every layout of the heads."""
     T = 600
     bits = qkv_synth.make_bits_uniform_choice(T, 90 + D + rep).numpy()
     check(2, 2, rep, T, G, bits, 900 + D + G + rep, "attend head_dim=%d G=%d rep=%d" % (D, G, rep), D=D)
