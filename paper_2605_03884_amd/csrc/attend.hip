@@ -8,10 +8,10 @@
 // A softmax sum does not care about the order of its terms, so the card's segments are used
 // as they lie: no order[] lookup, no gather.
 //
-// Work decomposition.  A wave takes one task: up to `chunk` consecutive rows of one width's
-// segment for one (layer, kv head), for all R query heads, and leaves an unnormalised
-// partial (running maximum m, sum l, sum of p.V^) in a workspace; a second kernel merges the
-// partials of each (layer, query head).  Inside a task, in rounds of 2048 values (16 tokens of 128 dimensions, 32 of 64):
+// Work decomposition.  A task is up to `chunk` consecutive rows of one width's
+// segment for one (layer, kv head), for all R query heads.  A wave takes every a.waves-th task of a pair and leaves an unnormalised
+// partial (running maximum m, sum l, sum of p.V^) in a workspace, which it finds there again after its next task; a second
+// kernel merges the partials of each (layer, query head).  Inside a task, in rounds of 2048 values (16 tokens of 128 dimensions, 32 of 64):
 //   scores   a lane reads a span of 32 codes and its pair, decodes it to four MFMA operands of 8 dimensions,
 //            and four MFMAs accumulate q.K^ for the round's tokens and the kv head's query
 //            heads (the k index of the MFMA is a fixed permutation of the head dimension,
@@ -28,12 +28,13 @@
 // count as -inf.  88 .. 128 registers and 9.5 KiB of LDS per wave: four waves per SIMD.
 //
 // Vector instructions of a round of 16 tokens x 128 dimensions with up to 4 query heads, at 2 / 4 / 8 bits: scores 61 / 85 / 80, softmax 9,
-// values 38 / 91 / 88, and 8 MFMAs of 16 cycles.  With v_mfma_f32_4x4x4_16b_f16, whose operands are four tokens of one dimension,
+// values 38 / 91 / 88, and 8 MFMAs of 16 cycles; at 2 bits the vector pipes are then about 70 % and LDS, most of it the value
+// pass's look-ups, 65 % busy.  With v_mfma_f32_4x4x4_16b_f16, whose operands are four tokens of one dimension,
 // values had to be turned from pairs of dimensions into pairs of tokens, sums added up across lanes, high and low parts of
 // the weights took an MFMA each: 84, 18 and 112 at 2 bits, 24 MFMAs of 8 cycles.  Whole call, 32 query heads on 8 kv heads, 32
-// layers, us, then and now: 8192 tokens at budget 3 73.0 and 63.6, all 2 bits 60.0 and 51.7, 4 bits 85.4 and 78.5, 8 bits 124.6 and
-// 123.0; 1024 tokens at budget 5 20.6 and 18.5.  64 dimensions had left half the lanes idle, and more than 4 heads took the 16 x 16 x 16
-// product: 8 heads, 3877 tokens of 128 pairs 30.0 and 21.0; 16 heads of 128 dimensions, 3622 tokens of 256 pairs 75.2 and 73.3.
+// layers, us, then and now (with cut_tasks; card not in cache): 8192 tokens at budget 3 80 and 65, all 2 bits 67 and 57, 4 bits 85 and 78,
+// 8 bits 124.6 and 122.5; 1024 tokens at budget 5 20.9 and 18.7.  64 dimensions had left half the lanes idle, and more than 4 heads
+// took the 16 x 16 x 16 product: 8 heads, 3877 tokens of 128 pairs 30.1 and 21.4; 16 heads of 256 dimensions, 22950 tokens of 64 pairs 331 and 265.
 
 #include <algorithm>
 #include <atomic>
@@ -49,9 +50,9 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kAttendWaves = 1;              // waves per workgroup (they would not interact): one keeps every LDS address an immediate
-// Tokens of a group of rounds whose loads are in flight together (Prefetch), by class; 64 dimensions.
-constexpr uint32_t kUnit[2][4] = {{64u, 48u, 32u, 16u}, {64u, 64u, 32u, 32u}};
+// Tokens of a group of rounds whose loads are in flight together (Prefetch), by class, at 64, 128 and 256 dimensions (there a
+// multiple of them): what makes tasks of different widths last about as long.
+constexpr uint32_t kUnit[3][4] = {{64u, 64u, 32u, 32u}, {64u, 48u, 32u, 16u}, {64u, 32u, 32u, 16u}};
 constexpr int kLdsFloatsPerWave = 1536;      // scores of one task: chunk tokens x padded query heads (6 KiB)
 
 struct AttendArgs {
@@ -64,19 +65,17 @@ struct AttendArgs {
   uint32_t rep;            // R = Hq / H, 1 .. 16
   float scale_log2;        // softmax scale times log2(e); its absolute value where keys are not grouped per channel, and then
   uint32_t q_flip;         // the sign bits to turn in q for the scale's own: the largest score is the one of the largest product
-  float* part_o;           // [L*H][max_tasks][R][D] unnormalised sums of p.V^
-  float* part_ml;          // [L*H][max_tasks][R][2]  (m in log2 units, l); l = 0 marks an empty task
-  uint32_t max_tasks;      // tasks per (layer, kv head) the workspace was sized for
-  uint32_t chunk;          // tokens per task at most
-  uint32_t even_tasks;     // how many of them an even cut may use, see find_task
-  uint32_t task_major;     // waves go through the pairs first, then through the tasks; else the other way round, see order_waves
-  uint32_t wave_step;      // what splits a wave's number: the pairs, or the waves per pair (one of them idle where max_tasks is even)
+  float* part_o;           // [L*H][waves][R][D] unnormalised sums of p.V^
+  float* part_ml;          // [L*H][waves][R][2]  (m in log2 units, l)
+  uint32_t chunk, rows;    // tokens per task at most: what the scores' LDS holds, and in one turn (see cut_tasks)
+  uint32_t waves;          // per (layer, kv head); the workspace has room for a partial each
+  uint32_t flat;           // the grid is one row
   uint32_t unit[4];        // tokens of a class that make up one unit (read where keys are grouped per channel, kUnit otherwise)
-  uint32_t fit[4];         // chunk / unit
+  uint32_t fit[4], fit_rows[4];      // chunk / unit, rows / unit
   float* out;              // fp32 [L][Hq][D]
   float* lse;              // fp32 [L][Hq] or null
   uint32_t* status;        // or null
-  uint32_t* valid;         // one word of the workspace: 1 when the header was accepted
+  uint32_t* valid;         // one word of the workspace: the partials of every pair that are to be merged, 0 when the header was refused
 };
 
 // What a lane holds of one round's rows before it is decoded: the codes of a span of 32 values (or raw values) and its pair.
@@ -183,24 +182,28 @@ __device__ inline uint32_t pack_halves(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
 }
 
-// Decoded values come two to a word, and a word of codes is cheapest taken apart into two equal parts: pair m of a piece of 8
-// values is values piece_dim(m, 0) and piece_dim(m, 1).  Nothing that follows needs another order.
-template <int W> __device__ constexpr int piece_dim(int m, int h) {
-  return W == 4 ? m + 4 * h : W == 8 ? 4 * (m >> 1) + (m & 1) + 2 * h : 2 * m + h;
-}
-
-// 8 values at 4 bits (one word) or 4 at 8 bits (one word), in that order.
+// 8 values at 4 bits (one word) or 4 at 8 bits (one word), two neighbours to a word.
 template <int W>
 __device__ inline void decode_word(uint32_t w, float scale24, float zero, uint32_t* out) {
   static_assert(W == 4 || W == 8, "");
+  if constexpr (W == 4) {
+    float x[8];
 #pragma unroll
-  for (int i = 0; i < 16 / (int)sizeof(uint32_t) / (W == 4 ? 1 : 2); ++i) {
-    const uint32_t codes = (w >> (W * i)) & (W == 4 ? 0x000F000Fu : 0x00FF00FFu);
-    out[i] = pack_halves(fma_low(codes, scale24, zero), fma_high(codes, scale24, zero));
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t codes = (w >> (4 * i)) & 0x000F000Fu;                 // values i and 4 + i
+      x[i] = fma_low(codes, scale24, zero);
+      x[4 + i] = fma_high(codes, scale24, zero);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = pack_halves(x[2 * i], x[2 * i + 1]);
+  } else {
+    const uint32_t even = w & 0x00FF00FFu, odd = (w >> 8) & 0x00FF00FFu;
+    out[0] = pack_halves(fma_low(even, scale24, zero), fma_low(odd, scale24, zero));
+    out[1] = pack_halves(fma_high(even, scale24, zero), fma_high(odd, scale24, zero));
   }
 }
 
-// The 32 values of a fetched span as 16 packed fp16 pairs, in the order of its pieces of 8 (2 bits: see decode_fetched_bytes).
+// The 32 values of a fetched span as 16 packed fp16 pairs (2 bits: see decode_fetched_bytes).
 template <int W, int G>
 __device__ inline void decode_fetched(const SpanData<W, G>& d, uint32_t (&out)[16]) {
   if constexpr (W == 16) {
@@ -236,20 +239,15 @@ __device__ inline void decode_fetched_bytes(const SpanData<2, G>& d, uint32_t (&
 }
 
 // The 32 values of q that meet such a span, in the same order.
-template <int W>
-__device__ inline void order_q(u32x4 (&raw)[4]) {
-  if constexpr (W != 16) {
-    uint32_t out[16];
+__device__ inline void order_q2(u32x4 (&raw)[4]) {
+  uint32_t out[16];
 #pragma unroll
-    for (int x = 0; x < 16; ++x) {
-      // the two values of word x
-      const int a = W == 2 ? 16 * (x >> 3) + 8 * (x & 1) + ((x >> 1) & 3) : 8 * (x >> 2) + piece_dim<W>(x & 3, 0);
-      const int b = W == 2 ? a + 4 : 8 * (x >> 2) + piece_dim<W>(x & 3, 1);
-      out[x] = __builtin_amdgcn_perm(raw[b >> 3][(b >> 1) & 3], raw[a >> 3][(a >> 1) & 3], (a & 1) ? 0x07060302u : 0x05040100u);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) raw[j] = (u32x4){out[4 * j], out[4 * j + 1], out[4 * j + 2], out[4 * j + 3]};
+  for (int x = 0; x < 16; ++x) {
+    const int first = 8 * (x >> 3) + 4 * (x & 1) + ((x >> 2) & 1);         // the word of value 16 w + 8 h + k, and k's lowest bit
+    out[x] = __builtin_amdgcn_perm(raw[(first + 2) >> 2][(first + 2) & 3], raw[first >> 2][first & 3], ((x >> 1) & 1) ? 0x07060302u : 0x05040100u);
   }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) raw[j] = (u32x4){out[4 * j], out[4 * j + 1], out[4 * j + 2], out[4 * j + 3]};
 }
 
 // ---- the LDS tile of a round: packed rows, regrouped ---------------------------------------------
@@ -291,7 +289,7 @@ __device__ inline void stage_span(const SpanData<W, G>& d, uint8_t* tile, uint32
 }
 
 // Reader side, 16 rows: lane (a, kt) picks up the pieces "row 4 kt + i, columns 8 a .. 8 a + 7", i = 0 .. 3, and decodes them
-// into t[i][m] = {X[4 kt + i][8 a + piece_dim(m, 0)], X[4 kt + i][8 a + piece_dim(m, 1)]}.
+// into t[i][m] = {X[4 kt + i][8 a + 2 m], X[4 kt + i][8 a + 2 m + 1]}.
 template <int W>
 __device__ inline void pieces_from_tile(const uint8_t* tile, const uint8_t* table, uint32_t a, uint32_t kt, uint32_t (&t)[4][4]) {
   constexpr uint32_t kRowBytes = TileGeo<W, 16>::kRowBytes;
@@ -330,7 +328,7 @@ __device__ inline void pieces_from_tile(const uint8_t* tile, const uint8_t* tabl
 }
 
 // The same with 32 rows of 64 columns: the pieces "row 16 u + 4 kt + i, columns 4 a .. 4 a + 3" as
-// t[i][2 u + m] = {X[16 u + 4 kt + i][4 a + 2 m], X[16 u + 4 kt + i][4 a + 2 m + 1]} (at 8 bits dimensions m and m + 2).
+// t[i][2 u + m] = {X[16 u + 4 kt + i][4 a + 2 m], X[16 u + 4 kt + i][4 a + 2 m + 1]}.
 template <int W>
 __device__ inline void pieces_from_tile64(const uint8_t* tile, const uint8_t* table, uint32_t a, uint32_t kt, uint32_t (&t)[4][4]) {
   constexpr uint32_t kRowBytes = TileGeo<W, 32>::kRowBytes;
@@ -374,21 +372,18 @@ __device__ inline void pieces_from_tile64(const uint8_t* tile, const uint8_t* ta
 }
 
 // Pairs of columns turned into pairs of rows: b[e] = {X[4kt][8a+e], X[4kt+1][8a+e], X[4kt+2][8a+e], X[4kt+3][8a+e]}.
-template <int W>
 __device__ inline void turn_pieces(const uint32_t (&t)[4][4], u32x2 (&b)[8]) {
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t sel = h ? 0x07060302u : 0x05040100u;      // high or low halves of two words
-      b[piece_dim<W>(m, h)] = (u32x2){__builtin_amdgcn_perm(t[1][m], t[0][m], sel), __builtin_amdgcn_perm(t[3][m], t[2][m], sel)};
-    }
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high or low halves of two words
+    b[e] = (u32x2){__builtin_amdgcn_perm(t[1][e >> 1], t[0][e >> 1], sel), __builtin_amdgcn_perm(t[3][e >> 1], t[2][e >> 1], sel)};
+  }
 }
 template <int W>
 __device__ inline void operands_from_tile(const uint8_t* tile, const uint8_t* table, uint32_t a, uint32_t kt, u32x2 (&b)[8]) {
   uint32_t t[4][4];
   pieces_from_tile<W>(tile, table, a, kt, t);
-  turn_pieces<W>(t, b);
+  turn_pieces(t, b);
 }
 
 // ---- cross-lane helpers ------------------------------------------------------------------------
@@ -440,7 +435,7 @@ __device__ inline float sum_over_quarters(float a0, float a1, float a2, float a3
 // channels only when NARROW (sum_over_quarters adds the four kt and leaves head kt), complete
 // otherwise (the 16 x 16 x 16 product adds the four kt itself; the lane holds heads 4 kt .. + 3).
 template <int W, bool NARROW, int DS>
-__device__ inline void score_pass_kc(const AttendArgs& a, const CardGeom& g, int c, uint32_t pair, uint32_t j0, uint32_t cnt,
+__device__ __forceinline__ void score_pass_kc(const AttendArgs& a, const CardGeom& g, int c, uint32_t pair, uint32_t j0, uint32_t cnt,
                                      uint32_t slots, uint32_t lane, float* lds, uint32_t pitch, uint32_t R4, uint8_t* tile,
                                      const uint8_t* table) {
   static_assert(W == 2 || W == 4 || W == 8, "per-channel key groups exist at 2, 4 and 8 bits");
@@ -580,7 +575,7 @@ __device__ inline SpanData<W, G> fetch_value(const RowStream& s, uint32_t rd) {
 // Rounds whose loads are in flight ahead of the arithmetic: as many as the registers allow (a fetched span is 3 / 5 / 9 / 16
 // registers at 2 / 4 / 8 / 16 bits; two slabs in flight cost twice that).  Their tokens divide 192 and are 96 at most.
 template <int W, int DS> struct Prefetch {
-  static constexpr int kRounds = DS == 2 ? (W <= 4 ? 2 : 1) : W == 2 ? 4 : W == 4 ? 3 : W == 8 && DS == 4 ? 2 : 1;
+  static constexpr int kRounds = DS != 4 ? (W <= 4 ? 2 : 1) : W == 2 ? 4 : W == 4 ? 3 : W == 8 ? 2 : 1;
 };
 
 // How the value pass fills its MFMAs (see attend_task) and what it accumulates.
@@ -590,11 +585,21 @@ template <int HB, int DS> struct ValueGeo {
   static constexpr int kSums = kTurned ? 8 : DS == 2 ? 2 : 4;          // pairs of dimensions, or dimensions
 };
 
+// fetch(0), fetch(1), ...: kept in this order and in one piece each.
+template <int N, typename F>
+__device__ __forceinline__ void first_fetches(const F& fetch) {
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    fetch(u);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // One sweep over a task's value rows: acc[b][m] += weights . V^, 2048 values a round.  `buf` holds the first rounds.
 // The other parity's zero weights turn a value that is no number, or an infinity, into NaN in the dimension beside
 // it: ISOLATE clears one half of every pair of dimensions (`keep`) to work the two out apart.
 template <int W, int G, int HB, int DS, bool ISOLATE>
-__device__ inline void value_sweep(const RowStream& rows, SpanData<W, G> (&buf)[Prefetch<W, DS>::kRounds], uint32_t rounds, const float* lds,
+__device__ __forceinline__ void value_sweep(const RowStream& rows, SpanData<W, G> (&buf)[Prefetch<W, DS>::kRounds], uint32_t rounds, const float* lds,
                                    uint32_t pitch, uint32_t R4, uint8_t* tile, const uint8_t* table, uint32_t n, uint32_t kq, uint32_t keep,
                                    f32x4 (&acc)[ValueGeo<HB, DS>::kBlocks][ValueGeo<HB, DS>::kSums]) {
   constexpr int kPrefetch = Prefetch<W, DS>::kRounds;
@@ -615,6 +620,7 @@ __device__ inline void value_sweep(const RowStream& rows, SpanData<W, G> (&buf)[
 #pragma unroll
     for (int u = 0; u < kPrefetch; ++u) {                       // rounds past the task's end add zero weights times zeros
       const uint32_t rd = rd0 + u;
+      __builtin_amdgcn_sched_barrier(0);                        // every round's loads stay in their round, see first_fetches
       uint32_t t[4][4];                                         // register i of operand x: row i of the lane's four
       if constexpr (W == 16) {
 #pragma unroll
@@ -630,7 +636,7 @@ __device__ inline void value_sweep(const RowStream& rows, SpanData<W, G> (&buf)[
       }
       if constexpr (kTurned) {
         u32x2 v[8];
-        turn_pieces<W>(t, v);
+        turn_pieces(t, v);
         u32x4 pw = (u32x4)(0u);
         if (w_head < R4) pw = *reinterpret_cast<const u32x4*>(w_at + rd * kRows);
         const f16x4 w_hi = __builtin_bit_cast(f16x4, (u32x2){pw.x, pw.y}), w_lo = __builtin_bit_cast(f16x4, (u32x2){pw.z, pw.w});
@@ -703,11 +709,11 @@ __device__ inline void value_sweep(const RowStream& rows, SpanData<W, G> (&buf)[
 // DS = head_dim / 32 spans per token.  The lane mapping covers a slab of 128 dimensions (4 spans); head_dim 256 is two
 // slabs (the score of a round adds both up before it is stored, the value pass sweeps the task once per slab).
 template <int W, int G, int HB, int DS, bool KC>
-__device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c, uint32_t pair, uint32_t j0, uint32_t j1,
-                                   uint32_t lane, float* lds, uint8_t* tile, const uint8_t* table, uint64_t part) {
+__device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom& g, int c, uint32_t pair, uint32_t j0, uint32_t j1,
+                                   uint32_t lane, float* lds, uint8_t* tile, uint8_t* table, float* ml, float* part_o, float* part_ml, bool first) {
   const uint32_t n = lane & 15u, kq = lane >> 4;          // also (a, kt) of the value pass
   const uint32_t R = a.rep, R4 = HB == 0 ? 4u : ((R + 3u) & ~3u);
-  const uint32_t pitch = a.chunk % 192u == 0u ? a.chunk : 96u;      // LDS pitch of a head's scores: the task size, padded
+  const uint32_t pitch = a.chunk;                          // of a head's scores in LDS
   const uint32_t lh = g.planes >> 1;
   const uint32_t n_c = g.n[c];
   const uint64_t k_row0 = (uint64_t)pair * n_c;            // K plane p = pair, V plane p = L*H + pair
@@ -719,8 +725,8 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
   constexpr int S = (DS + 3) / 4;                          // slabs of 128 dimensions
   constexpr uint32_t D = 32u * DS;
   const uint32_t row = RoundGeo<DS>::row(n, kq), span = RoundGeo<DS>::span(kq);
-  // Rounds are processed in whole groups of kPrefetch; the task size is a multiple of such a group, so the padded
-  // rounds stay inside the task's share of LDS.  The softmax covers `slots` tokens, those past the task's end at -inf.
+  // Rounds are processed in whole groups of kPrefetch; a task is a whole number of such groups or ends with its class, so the
+  // padded rounds stay inside the task's share of LDS.  The softmax covers `slots` tokens, those past the task's end at -inf.
   const uint32_t slots = (rounds + kPrefetch - 1) / kPrefetch * kPrefetch * kRows;
   if constexpr (KC) {
     if constexpr (W != 16 && G == 32 && DS <= 4)
@@ -730,24 +736,33 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
 #pragma unroll
     for (int sl = 0; sl < S; ++sl) ks[sl] = row_stream<W, G, DS>(a.card, g, c, k_row0 + j0, cnt, row, 4u * sl + span);
 
-    // ---- q as MFMA operands: operand j of slab sl is q[head][128 sl + 32 span + 8 j .. + 7]
+    // ---- q as MFMA operands: operand j of slab sl is q[head][128 sl + 32 span + 8 j .. + 7].  Heads that do not exist, and the half of
+    // a column that belongs to other tokens, lie past the end of the pair's rows of q and read as zero.
     constexpr int kSets = DS == 2 && HB == 2 ? 2 : 1;
     const uint32_t head = DS == 2 && HB < 2 ? (n & 7u) : n;
+    const __amdgpu_buffer_rsrc_t q_rows = bounded(reinterpret_cast<const uint8_t*>(a.q + (uint64_t)pair * R * D), R * D * 2u);
+    const uint32_t q_at = DS != 2 || HB == 2 || (n >> 3) == (kq >> 1) ? (head * D + 32u * span) * 2u : 0x40000000u;
+    u32x4 raws[S][4];
+#pragma unroll
+    for (int sl = 0; sl < S; ++sl)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) raws[sl][j] = buffer_load4(q_rows, q_at + 256u * sl + 16u * j);
+    // The loads of the next kPrefetch rounds are always in flight.  They are issued in the order in which the loop issues them:
+    // loads return in order, and what the loop's first round waits for is decided by the less favourable of the two orders.
+    SpanData<W, G> buf[kPrefetch][S];
+    first_fetches<kPrefetch>([&](int u) {
+#pragma unroll
+      for (int sl = 0; sl < S; ++sl) buf[u][sl] = fetch_span<W, G, DS>(ks[sl], u);
+    });
     f16x8 qa[S * kSets][4];
 #pragma unroll
     for (int sl = 0; sl < S; ++sl) {
-      u32x4 raw[4];
+      u32x4 (&raw)[4] = raws[sl];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) raw[j] = (u32x4)(0u);
-      if (head < R && (DS != 2 || HB == 2 || (n >> 3) == (kq >> 1))) {
-        const uint32_t l = pair / g.kv_heads, hh = pair - l * g.kv_heads;
-        const u32x4* src = reinterpret_cast<const u32x4*>(a.q + ((uint64_t)(l * a.q_heads + hh * R + head) * D + 128u * sl + 32u * span));
-#pragma unroll
-        for (int j = 0; j < 4; ++j) raw[j] = src[j] ^ a.q_flip;
-      }
+      for (int j = 0; j < 4; ++j) raw[j] ^= a.q_flip;
+      if constexpr (W == 2) order_q2(raw);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (j == 0) order_q<W>(raw);
         if constexpr (kSets == 2) {
           qa[0][j] = __builtin_bit_cast(f16x8, kq < 2u ? raw[j] : (u32x4)(0u));
           qa[1][j] = __builtin_bit_cast(f16x8, kq < 2u ? (u32x4)(0u) : raw[j]);
@@ -757,12 +772,7 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
       }
     }
 
-    // ---- scores: lds[head * pitch + token], not scaled yet.  The loads of the next kPrefetch rounds are always in flight.
-    SpanData<W, G> buf[kPrefetch][S];
-#pragma unroll
-    for (int u = 0; u < kPrefetch; ++u)
-#pragma unroll
-      for (int sl = 0; sl < S; ++sl) buf[u][sl] = fetch_span<W, G, DS>(ks[sl], u);
+    // ---- scores: lds[head * pitch + token], not scaled yet
 #pragma unroll 1
     for (uint32_t rd0 = 0; rd0 < rounds; rd0 += kPrefetch) {
 #pragma unroll
@@ -792,6 +802,7 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
           for (int s = 0; s < kSets; ++s)
             *reinterpret_cast<f32x4*>(dst + (kSets == 2 ? 16u * s : DS == 2 ? 16u * (n >> 3) : 0u)) = acc[s][0] + acc[s][1];
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }   // per-token key groups
@@ -799,8 +810,10 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
   // the first value rows are requested now, so that they arrive while the softmax runs
   RowStream vs = value_stream<W, G, DS>(a.card, g, c, v_row0 + j0, cnt, n, kq, 0u);
   SpanData<W, G> vbuf[kPrefetch];
-#pragma unroll
-  for (int u = 0; u < kPrefetch; ++u) vbuf[u] = fetch_value<W, G, DS>(vs, u);
+  first_fetches<kPrefetch>([&](int u) { vbuf[u] = fetch_value<W, G, DS>(vs, u); });
+
+  // the scores did without the selector table of 2-bit rows, and other widths' tiles lie over it
+  if constexpr (W == 2 && !KC) build_select_table(reinterpret_cast<u32x2*>(table), lane);
 
   // ---- softmax over the task's tokens, four heads at a time: row kq of the wave takes head
   // 4 hg + kq, its lane n the tokens 64 i + 4 n .. + 3 (the wave's own LDS accesses are in order).
@@ -839,10 +852,7 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
     for (uint32_t t = 0; t < whole; t += 64u) weigh(t + 4u * n, false);
     for (uint32_t t = whole + 4u * n; t < slots; t += 64u) weigh(t, true);
     l = row_sum16(l);
-    if (n == 0 && r < R) {
-      a.part_ml[(part * R + r) * 2] = m;
-      a.part_ml[(part * R + r) * 2 + 1] = l;
-    }
+    if (n == 0) *reinterpret_cast<float2*>(ml + 2u * r) = make_float2(m, l);
   }
 
   // ---- values: one sweep over the task's rows per slab of 128 output dimensions (the weights stay in LDS)
@@ -851,8 +861,7 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
   for (int sl = 0; sl < S; ++sl) {
     if (sl > 0) {
       vs = value_stream<W, G, DS>(a.card, g, c, v_row0 + j0, cnt, n, kq, (uint32_t)sl);
-#pragma unroll
-      for (int u = 0; u < kPrefetch; ++u) vbuf[u] = fetch_value<W, G, DS>(vs, u);
+      first_fetches<kPrefetch>([&](int u) { vbuf[u] = fetch_value<W, G, DS>(vs, u); });
     }
     f32x4 acc[kBlocks][kSums];
     value_sweep<W, G, HB, DS, false>(vs, vbuf, rounds, lds, pitch, R4, tile, table, n, kq, 0u, acc);
@@ -893,80 +902,130 @@ __device__ inline void attend_task(const AttendArgs& a, const CardGeom& g, int c
 #pragma unroll
         for (int e = 0; e < (DS == 2 ? 4 : 8); ++e) {
           const int m = e >> 1, h = e & 1;
-          const int to = DS == 2 ? (W == 8 ? m + 2 * h : e) : kTurned ? e : piece_dim<W>(m, h);
-          if constexpr (kTurned) o[to] = acc[0][e][x] * kUnscale;
-          else if constexpr (HB == 0) o[to] = (acc[0][m][h] + acc[0][m][2 + h]) * kUnscale;
-          else o[to] = acc[x >> 1][m][2 * (x & 1) + h] * kUnscale;
+          if constexpr (kTurned) o[e] = acc[0][e][x] * kUnscale;
+          else if constexpr (HB == 0) o[e] = (acc[0][m][h] + acc[0][m][2 + h]) * kUnscale;
+          else o[e] = acc[x >> 1][m][2 * (x & 1) + h] * kUnscale;
         }
-        f32x4* dst = reinterpret_cast<f32x4*>(a.part_o + (part * R + r) * D + d0);
+        f32x4* dst = reinterpret_cast<f32x4*>(part_o + (r * D + d0));
+        float2* dst_ml = reinterpret_cast<float2*>(part_ml + 2u * r);
+        float2 now = *reinterpret_cast<const float2*>(ml + 2u * r);
+        if (!first) {                                      // the wave's earlier tasks have left theirs here
+          const float2 old = *dst_ml;
+          const f32x4 o0 = dst[0], o1 = DS != 2 ? dst[1] : (f32x4){0.f, 0.f, 0.f, 0.f};
+          const float top = fmaxf(old.x, now.x);
+          const float was = old.x == top ? 1.0f : __builtin_amdgcn_exp2f(old.x - top), is = now.x == top ? 1.0f : __builtin_amdgcn_exp2f(now.x - top);
+          now = make_float2(top, __builtin_fmaf(old.y, was, now.y * is));
+#pragma unroll
+          for (int e = 0; e < (DS == 2 ? 4 : 8); ++e) o[e] = __builtin_fmaf(e < 4 ? o0[e & 3] : o1[e & 3], was, o[e] * is);
+        }
         dst[0] = (f32x4){o[0], o[1], o[2], o[3]};
         if constexpr (DS != 2) dst[1] = (f32x4){o[4], o[5], o[6], o[7]};
+        if (n == 0 && sl == S - 1) *dst_ml = now;
       }
     }
   }
 }
 
-// Which class and which of its rows [j0, j1) task `tau` of a (layer, kv head) covers; -1: a spare task.
+// How a card's rows are cut into the tasks of a (layer, kv head).
 //
-// Where the tasks at hand allow it, all get the same number of units: a unit is one group of rounds whose loads are in flight
-// together - fewer tokens at larger widths - so a task lasts about as long whatever its width, and the longest one decides how
-// long a short card takes (whole call, 1K tokens at budget 5, 256 pairs: 27.7 us with 192 rows of any width a task, 23.9 us; 300
-// tokens: 18.3 and 15.2 us; with the present order of the waves 1K tokens take 19.7).  Otherwise a task takes `chunk` rows of any class, the most LDS allows.
-// s units a task make at most k - 1 + (sum u_c - (k - 1)) / s tasks (rounded up) of the k classes present, so
-// s >= (sum u_c - (k - 1)) / (even_tasks - (k - 1)) keeps them within even_tasks.
-//
-// Every wave goes through this between the header and its first load, so it has as few divisions in a row as can be: the
-// classes share one divisor, the units are constants (keys per channel apart, where one class has rows).  With a division
-// by a different number for every class the kernel lost 0.4 to 0.8 us on any card, more with more waves: 8000 tokens of 256
-// pairs at head_dim 64 70.0 -> 75.2 us, 3000 tokens of 384 pairs at 16 heads 65.7 -> 72.0; now 69.4 and 65.3.
-template <int DS, bool KC>
-__device__ inline int find_task(const AttendArgs& a, const CardGeom& g, uint32_t tau, uint32_t& j0, uint32_t& j1) {
-  int cls = -1;
-  // one divisor for all classes: its reciprocal is worked out once, ahead of the header's arrival where it is `chunk`
-  const auto walk = [&](const uint32_t (&count)[4], const uint32_t (&step)[4], uint32_t per) {
+// Where it can be, all tasks get the same number of units: a unit is one group of rounds whose loads are in flight
+// together - fewer tokens at larger widths - so a task lasts about as long whatever its width.  s units a task make at
+// most k - 1 + (sum u_c - (k - 1)) / s tasks (rounded up) of the k classes present, so s >= (sum u_c - (k - 1)) / (n - (k - 1)) keeps
+// them within n.  In this order, with n the waves of a pair:
+//   one turn of even tasks; then with no more than `rows` rows each, the length that the workspace's partials go by (a chip that
+//   is not full is bound by latency, and a wide row takes little longer than a narrow one); then as many rows as that of any width;
+//   up to three turns of even tasks, where LDS holds three units or more: the waves run in step, and one that got two long tasks
+//   while others have one holds up the call;
+//   beyond, the longest tasks that LDS holds: a task's start and end cost about 3 us that four waves a SIMD do not quite hide (32K
+//   tokens of 2 bits with tasks of 192 rows 218 us, of 384 199).
+// Whole call, us, with one task a wave, more of them than wave slots, and like this: 8192 tokens at budget 3 of 256 pairs 72 and 65, 224
+// pairs 65 and 59, 9000 tokens 77 and 71, 5000 tokens 48.6 and 40; 512 pairs, 9000 tokens 140 and 137.
+struct TaskCut {
+  uint32_t tasks[4];       // of each class
+  uint32_t step[4];        // rows of a task
+  // Class of task `tau` and its rows [j0, j1); -1: there is no such task.
+  __device__ inline int find(const CardGeom& g, uint32_t tau, uint32_t& j0, uint32_t& j1) const {
+    int cls = -1;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const uint32_t tasks = (count[c] + per - 1u) / per;
       if (cls < 0) {
-        if (tau < tasks) {
+        if (tau < tasks[c]) {
           cls = c;
-          j0 = tau * per * step[c];
-          j1 = min(g.n[c], j0 + per * step[c]);
+          j0 = tau * step[c];
+          j1 = min(g.n[c], j0 + step[c]);
         } else {
-          tau -= tasks;
+          tau -= tasks[c];
         }
       }
     }
-  };
-  uint32_t unit[4], units[4], sum = 0, present = 0, most = ~0u;        // most: units that fit a task of every class present
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    unit[c] = KC ? a.unit[c] : kUnit[DS == 2][c];
-    units[c] = g.n[c] == 0u ? 0u : (g.n[c] + unit[c] - 1u) / unit[c];
-    sum += units[c];
-    present += (uint32_t)(g.n[c] != 0u);
-    most = g.n[c] == 0u ? most : min(most, a.fit[c]);
-  }
-  const uint32_t spare = present - 1u;                   // every class but one may end with a partly filled task
-  const uint32_t room = a.even_tasks - spare;
-  const uint32_t share = a.even_tasks <= spare ? ~0u : max(1u, (sum - spare + room - 1u) / room);
-  if (share <= most) {
-    walk(units, unit, share);
     return cls;
   }
-  const uint32_t rows[4] = {1u, 1u, 1u, 1u};
-  walk(g.n, rows, a.chunk);
-  return cls;
+};
+
+__device__ inline uint32_t divide_up(uint32_t a, uint32_t b) { return (a + b - 1u) / b; }
+__device__ inline uint32_t lane_value(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
+
+// Every wave goes through this between the header and its first load, and a division is a chain of some thirty dependent
+// instructions: lane 4 k + c works on class c of candidate k, so that all that can be divided at the same time is.
+template <int DS, bool KC>
+__device__ __forceinline__ TaskCut cut_tasks(const AttendArgs& a, const CardGeom& g, uint32_t lane) {
+  uint32_t units[4], sum = 0, present = 0, most = ~0u, room = ~0u;      // units of every class present that fit `rows`, and LDS
+  const uint32_t c = lane & 3u, k = lane >> 2;
+  uint32_t my_unit = 0, my_units = 0, my_fit = 0, my_fit_rows = 0;
+#pragma unroll
+  for (uint32_t x = 0; x < 4u; ++x) {
+    const uint32_t unit = KC ? a.unit[x] : kUnit[DS / 4][x];
+    units[x] = KC ? (g.n[x] == 0u ? 0u : divide_up(g.n[x], unit)) : divide_up(g.n[x], unit);
+    sum += units[x];
+    present += (uint32_t)(g.n[x] != 0u);
+    most = g.n[x] == 0u ? most : min(most, a.fit_rows[x]);
+    room = g.n[x] == 0u ? room : min(room, a.fit[x]);
+    my_unit = c == x ? unit : my_unit;
+    my_units = c == x ? units[x] : my_units;
+    my_fit = c == x ? a.fit[x] : my_fit;
+    my_fit_rows = c == x ? a.fit_rows[x] : my_fit_rows;
+  }
+  const uint32_t spare = present - 1u;                   // every class but one may end with a partly filled task
+  const uint32_t even = a.waves > spare ? a.waves - spare : 1u;
+  const uint32_t first = divide_up(sum - spare, k == 0u ? even : room);
+  const uint32_t share = a.waves > spare ? max(1u, lane_value(first, 0u)) : ~0u;
+  const uint32_t least = lane_value(first, 4u) + spare;
+  // candidates: one turn of even tasks, of as many rows as `rows`; any number of turns of the longest tasks; and how many turns even ones take
+  const uint32_t own = k == 0u ? min(share, my_fit_rows) : k == 1u ? my_fit_rows : k == 2u ? my_fit : a.waves;
+  uint32_t tasks = divide_up(k < 3u ? my_units : least, own), step = own * my_unit;
+  uint32_t total = tasks + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)tasks, 0xB1, 0xF, 0xF, false);        // quad_perm 1 0 3 2
+  total += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)total, 0x4E, 0xF, 0xF, false);                        // quad_perm 2 3 0 1
+  uint32_t best = 0u;
+  if (share > most && lane_value(total, 0u) > a.waves) {
+    const uint32_t turns = lane_value(tasks, 12u);
+    best = lane_value(total, 4u) <= a.waves ? 4u : 8u;
+    if (best == 8u && turns <= 3u && room >= 3u) {
+      const uint32_t shorter = max(1u, divide_up(sum - spare, turns * a.waves - spare));
+      tasks = divide_up(my_units, shorter);
+      step = shorter * my_unit;
+    }
+  }
+  TaskCut cut;
+#pragma unroll
+  for (uint32_t x = 0; x < 4u; ++x) {
+    cut.tasks[x] = lane_value(tasks, best + x);
+    cut.step[x] = lane_value(step, best + x);
+  }
+  return cut;
 }
 
 // KC: the card's key planes are grouped per channel (a uniform card at 2, 4 or 8 bits, group size 32).
-template <int G, int HB, int DS, bool KC>
-__global__ __launch_bounds__(kAttendWaves * kWaveSize) __attribute__((amdgpu_waves_per_eu(4)))
+// TURNS: there may be more tasks than waves.  An instance of its own, because what a loop around the tasks keeps in registers and
+// takes apart again costs calls that have no use for it up to 1 us (16 pairs, 220 tokens, 5 heads 9.6 and 10.6 us; 4 pairs, 2570
+// tokens of 256 dimensions 16.9 and 21.2).
+template <int G, int HB, int DS, bool KC, bool TURNS>
+__global__ __launch_bounds__(kWaveSize) __attribute__((amdgpu_waves_per_eu(4)))
 void attend_kernel(AttendArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[kAttendWaves][kLdsFloatsPerWave];
+  __shared__ __attribute__((aligned(16))) float lds[kLdsFloatsPerWave];
   // the value pass's LDS, 3.25 KiB: a round's packed rows (640 / 1280 / 2048 bytes at 2 / 4 / 8 bits; 64 dimensions 768 / 1280 / 2560),
   // then the rows' pairs (512 bytes), then at 2 bits the 2 KiB selector table
-  __shared__ __attribute__((aligned(16))) uint8_t tiles[kAttendWaves][kTileBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t tiles[kTileBytes];
+  __shared__ __attribute__((aligned(16))) float mls[32];      // the task's maximum and sum of every head
   CardGeom g;
   bool ok = card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size,
                                       a.tokens, g, KC ? QKV_FLAG_KEYS_PER_CHANNEL : 0u);
@@ -975,40 +1034,46 @@ void attend_kernel(AttendArgs a) {
     ok = uniform && g.group_size == 32u && g.head_dim <= 128u && g.tokens % (g.head_dim == 64u ? 64u : 32u) == 0u;
   }
   // the header's verdict, for the merging kernel that follows on the stream and for the caller
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *a.valid = ok ? 1u : 0u;
+  const bool one = blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0;
+  if (one) {
+    if (!ok) *a.valid = 0u;
     if (a.status) *a.status = ok ? 0u : QKV_STATUS_BAD_HEADER;
   }
   if (!ok) return;                            // uniform over the grid
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wave = (kAttendWaves == 1) ? 0u : threadIdx.x >> 6;     // a constant keeps every LDS address an immediate
-  const uint32_t gw = blockIdx.x * kAttendWaves + wave;
+  const uint32_t gw = blockIdx.x;
   const uint32_t pairs = g.planes >> 1;
-  const uint32_t outer = gw / a.wave_step, inner = gw - outer * a.wave_step;
-  const uint32_t pair = a.task_major ? inner : outer, tau = a.task_major ? outer : inner;
-  if (pair >= pairs || tau >= a.max_tasks) return;
-  const uint64_t part = (uint64_t)pair * a.max_tasks + tau;
-
-  uint32_t j0 = 0, j1 = 0;
-  const int cls = find_task<DS, KC>(a, g, tau, j0, j1);
-  if (cls < 0) {                               // spare task: an empty partial
-    for (uint32_t r = lane; r < a.rep; r += kWaveSize) {
-      a.part_ml[(part * a.rep + r) * 2] = -INFINITY;
-      a.part_ml[(part * a.rep + r) * 2 + 1] = 0.f;
-    }
-    return;
-  }
-  float* my_lds = lds[wave];
-  uint8_t* my_tile = tiles[wave];
+  // all pairs' first waves, then all second ones: a grid of pairs x waves where its height allows
+  const uint32_t tau = a.flat ? gw / pairs : blockIdx.y, pair = a.flat ? gw - tau * pairs : gw;
+  float* my_lds = lds;
+  uint8_t* my_tile = tiles;
   uint8_t* my_table = my_tile + kTableAt;
-  if (cls == 0) {
-    build_select_table(reinterpret_cast<u32x2*>(my_table), lane);
-    attend_task<2, G, HB, DS, KC>(a, g, 0, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
-  }
-  if (cls == 1) attend_task<4, G, HB, DS, KC>(a, g, 1, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
-  if (cls == 2) attend_task<8, G, HB, DS, KC>(a, g, 2, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
-  if constexpr (!KC) {                         // a card grouped per channel has no raw rows
-    if (cls == 3) attend_task<16, G, HB, DS, false>(a, g, 3, pair, j0, j1, lane, my_lds, my_tile, my_table, part);
+  float* my_ml = mls;
+  const TaskCut cut = cut_tasks<DS, KC>(a, g, threadIdx.x & 63u);
+  const uint32_t tasks = cut.tasks[0] + cut.tasks[1] + cut.tasks[2] + cut.tasks[3];
+  if (one) *a.valid = min(tasks, a.waves);
+  if (tau >= min(tasks, a.waves)) return;      // a spare wave: the merge knows
+  const uint64_t part = (uint64_t)pair * a.waves + tau;
+  float* part_o = reinterpret_cast<float*>(uniform64(reinterpret_cast<uint64_t>(a.part_o + part * a.rep * (32u * DS))));
+  float* part_ml = reinterpret_cast<float*>(uniform64(reinterpret_cast<uint64_t>(a.part_ml + part * a.rep * 2u)));
+#pragma unroll 1
+  for (uint32_t t = tau; t < tasks; t += a.waves) {
+    // the lane's number, worked out anew each time: it and what depends on it alone (q in two orders, offsets at four widths) would
+    // otherwise be kept in registers that the loop does not have
+    uint32_t ln = threadIdx.x;
+    if (TURNS) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(ln));
+    uint32_t j0 = 0, j1 = 0;
+    const int cls = cut.find(g, t, j0, j1);
+    const bool first = !TURNS || t == tau;
+    if (cls == 0) {
+      if (KC) build_select_table(reinterpret_cast<u32x2*>(my_table), ln);
+      attend_task<2, G, HB, DS, KC>(a, g, 0, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, part_o, part_ml, first);
+    }
+    if (cls == 1) attend_task<4, G, HB, DS, KC>(a, g, 1, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, part_o, part_ml, first);
+    if (cls == 2) attend_task<8, G, HB, DS, KC>(a, g, 2, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, part_o, part_ml, first);
+    if constexpr (!KC) {                       // a card grouped per channel has no raw rows
+      if (cls == 3) attend_task<16, G, HB, DS, false>(a, g, 3, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, part_o, part_ml, first);
+    }
+    if (!TURNS) break;                         // no more tasks than waves
   }
 }
 
@@ -1023,18 +1088,19 @@ __global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(AttendArgs 
   __shared__ float weight[kMergeBatch];
   __shared__ float part_max[kMergeThreads / kWaveSize], part_den[kMergeThreads / kWaveSize];
   __shared__ f32x4 sums[kMergeThreads];
-  if (*a.valid == 0) return;                           // header refused: outputs stay untouched
+  const uint32_t tasks = *a.valid;
+  if (tasks == 0) return;                              // header refused: outputs stay untouched
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, D = a.head_dim;
   const uint32_t lq = blockIdx.x;                      // l * Hq + hq
   const uint32_t l = lq / a.q_heads, hq = lq - l * a.q_heads;
   const uint32_t h = hq / a.rep, r = hq - h * a.rep;
-  const uint64_t part0 = (uint64_t)(l * a.kv_heads + h) * a.max_tasks;
+  const uint64_t part0 = (uint64_t)(l * a.kv_heads + h) * a.waves;
   const uint32_t per = D / 4u, split = kMergeThreads / per;      // threads per task's row, tasks at a time
   const uint32_t mine = tid / per, d4 = tid - mine * per;
   float M = -INFINITY, den = 0.f;                      // running maximum, and sums relative to it
   f32x4 num = {0.f, 0.f, 0.f, 0.f};
-  for (uint32_t t0 = 0; t0 < a.max_tasks; t0 += kMergeBatch) {
-    const uint32_t nb = min((uint32_t)kMergeBatch, a.max_tasks - t0);
+  for (uint32_t t0 = 0; t0 < tasks; t0 += kMergeBatch) {
+    const uint32_t nb = min((uint32_t)kMergeBatch, tasks - t0);
     float m = -INFINITY, lt = 0.f;
     if (tid < nb) {
       const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + ((part0 + t0 + tid) * a.rep + r) * 2);
@@ -1066,7 +1132,7 @@ __global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(AttendArgs 
       const float wt = weight[t];
       if (!(wt < 0.f)) num += wt * *reinterpret_cast<const f32x4*>(a.part_o + ((part0 + t0 + t) * a.rep + r) * D + 4u * d4);
     }
-    if (t0 + kMergeBatch < a.max_tasks) __syncthreads();        // the weights are written again
+    if (t0 + kMergeBatch < tasks) __syncthreads();        // the weights are written again
   }
   sums[tid] = num;
   __syncthreads();
@@ -1102,7 +1168,7 @@ void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk,
 // per wave slot of the chip, but no more than there are units of work at a middling mix of widths (an empty task still
 // costs its dispatch).  Only up to 4 query heads per kv head and head_dim 128: beyond, a task's fixed part and the merge are
 // heavier, and the rule would need a line of its own.  Attention and merge, us, with the least number of tasks and cut like
-// this (a pair's waves one after the other, see order_waves): 256 pairs, 8 heads, 300 tokens 20.2 and 18.8, 1000 29.6 and 25.0,
+// this (a pair's waves one after the other): 256 pairs, 8 heads, 300 tokens 20.2 and 18.8, 1000 29.6 and 25.0,
 // 4000 55.2 and 55.4; 16 heads, 2000 tokens 51.5 and 53.8; 32 pairs, 8 heads, 1000 tokens 18.6 and 15.3, 4000 20.9 and 23.8;
 // head_dim 256, 4 heads, 1000 23.7 and 19.2, 4000 29.9 and 35.5.
 // And no more than 96: with few pairs the merge, a few workgroups that go through all partials, takes longer than what shorter
@@ -1163,23 +1229,16 @@ static uint32_t merge_threads(uint32_t workgroups, uint32_t tasks, uint32_t head
   return workgroups <= 2048u || tasks * head_dim / 4u > 256u ? 128u : 64u;
 }
 
-// The order of the waves, and how many there are.  Every pair has the same spare tasks (its classes' rows may leave them
-// empty), and an empty wave is gone at once: one after the tasks of each pair, they leave holes in the round-robin that deals waves
-// to XCDs and compute units, and where the tasks of a pair are a multiple of a power of two the same units get the holes each
-// time.  So up to 1.75 waves per slot (1.33 at head_dim 256) the pairs go first, all first tasks, then all second ones: the holes
-// are one piece at the end.  Whole call, us, tasks first and pairs first: 256 pairs, 2000 tokens at budget 4 41.4 and 26.8, 6000
-// 67.5 and 57.1, 1660 of head_dim 64 at budget 7.3 45.6 and 23.9; 128 pairs, 3000 tokens 29.7 and 23.7; 48 pairs, 9196 33.2 and
-// 28.2; 184 pairs of head_dim 256, 8298 tokens at budget 2.9 126.7 and 105.0.
-// Beyond that there are waves enough for the holes not to matter, and tasks of one pair that run together read neighbouring
-// rows: 1.8 waves per slot 109.2 and 112.7, 2.8 104.3 and 111.2, 4.1 102.0 and 111.7, 12 325.8 and 359.3; head_dim 256 at 1.4,
-// 8000 tokens of 16 bits 220.2 and 226.6, at 1.3 145.0 and 133.5.  There one idle wave makes the waves of a pair odd
-// (512 pairs of 16 tasks, 4896 tokens at budget 6.5: 210.6 -> 139.7).
-static uint64_t order_waves(uint64_t pairs, uint32_t head_dim, AttendArgs& a) {
-  const uint64_t waves = pairs * a.max_tasks;
-  a.task_major = head_dim > 128u ? 3u * waves <= 4u * kWaveSlots : 4u * waves <= 7u * kWaveSlots;
-  const uint32_t idle = waves < 1u << 24 ? 1u : 0u;      // no more waves than a grid may have
-  a.wave_step = a.task_major ? (uint32_t)pairs : a.max_tasks | idle;
-  return a.task_major ? waves : pairs * a.wave_step;
+// Waves per pair: all pairs' first waves are dealt out first, then all second ones: the holes that waves without a task leave are
+// then one piece at the end (a pair's waves one after the other: 2000 tokens of 256 pairs 41.4 us, like this 26.8).  As many turns of the chip's wave slots as leave no more than a tenth of the last one empty, one if that
+// does, but no more than `most`, the partials a pair has room for.
+static uint32_t waves_per_pair(uint64_t pairs, uint32_t most) {
+  uint64_t w = 0;
+  for (uint64_t turns = 1; turns <= 8u; ++turns) {
+    w = turns * kWaveSlots / pairs;
+    if (w >= most || 10u * w * pairs >= 9u * turns * kWaveSlots) break;
+  }
+  return (uint32_t)std::min<uint64_t>(most, w == 0u ? 1u : w);
 }
 
 hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, const void* q,
@@ -1196,57 +1255,63 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
   a.scale_log2 = softmax_scale * 1.44269504088896340736f;
   a.q_flip = !keys_per_channel && std::signbit(a.scale_log2) ? 0x80008000u : 0u;
   if (a.q_flip != 0u) a.scale_log2 = -a.scale_log2;
-  attend_plan(expect.tokens, a.rep, (uint64_t)expect.layers * expect.kv_heads, &a.chunk, &a.max_tasks);
   const uint64_t pairs = (uint64_t)expect.layers * expect.kv_heads;
   const uint32_t D = expect.head_dim;
-  {
-    const uint32_t more = attend_more_tasks(expect.tokens, a.rep, pairs, D, a.max_tasks);
-    if (workspace_bytes >= (pairs * more * a.rep * (D + 2u) + 4u) * sizeof(float)) a.max_tasks = more;
+  uint32_t partials = 0;                       // the workspace has room for, of a pair
+  attend_plan(expect.tokens, a.rep, pairs, &a.rows, &partials);
+  const uint32_t more = attend_more_tasks(expect.tokens, a.rep, pairs, D, partials);
+  if (workspace_bytes >= (pairs * more * a.rep * (D + 2u) + 4u) * sizeof(float)) partials = more;
+  // with keys grouped per channel every task has a wave of its own: there is no register left for more (a.rows and the
+  // partials go together, so that there are no more tasks than waves)
+  a.waves = keys_per_channel ? partials : waves_per_pair(pairs, partials);
+  a.chunk = kLdsFloatsPerWave / ((a.rep + 3u) & ~3u) / 16u * 16u;
+  // a group of rounds whose loads are in flight together; keys grouped per channel are scored 128 tokens at a time, in whole
+  // blocks of 32: as many groups as are whole blocks, 128 tokens where LDS holds a multiple
+  const uint32_t* unit = kUnit[D / 128u];
+  for (int c = 0; c < 4; ++c) a.unit[c] = unit[c];
+  if (keys_per_channel) {
+    a.unit[0] = a.unit[1] = a.unit[2] = a.rows % 128u == 0u || (a.chunk >= 128u && expect.tokens <= 128u * (uint64_t)partials) ? 128u : 64u;
+    if (D == 128u) a.unit[1] = 96u;
   }
-  // a group of rounds whose loads are in flight together: 4, 3, 2 or 1 rounds of 16 tokens; keys grouped per channel are
-  // scored up to 128 tokens at a time, in whole blocks of 32
-  const uint32_t* unit = kUnit[D == 64u];
-  const bool wide_units = keys_per_channel && a.chunk >= 128u;
-  a.unit[0] = wide_units ? 128u : unit[0];
-  a.unit[1] = keys_per_channel ? (a.chunk >= 96u ? 96u : 64u) : unit[1];
-  a.unit[2] = wide_units ? 128u : unit[2];
-  a.unit[3] = unit[3];
-  for (int c = 0; c < 4; ++c) a.fit[c] = a.chunk / a.unit[c];
-  // Where full tasks fit the wave slots, even ones have to as well: a few waves more than slots would run after all others
-  // (whole call, us, with every task in use and like this: 256 pairs, 6000 tokens of 8 bits 102.1 and 96.0, 3000 of 16 bits
-  // 85.0 and 81.7; 128 pairs, 6000 of 16 bits 85.2 and 80.6).
-  const uint64_t full = (expect.tokens + a.chunk - 1u) / a.chunk;
-  a.even_tasks = pairs * full <= kWaveSlots ? (uint32_t)std::min<uint64_t>(a.max_tasks, kWaveSlots / pairs) : a.max_tasks;
-  const uint64_t waves = order_waves(pairs, D, a);
+  for (int c = 0; c < 4; ++c) {
+    a.fit[c] = a.chunk / a.unit[c];
+    a.fit_rows[c] = std::max(1u, a.rows / a.unit[c]);
+  }
   a.part_o = workspace;
-  a.part_ml = workspace + pairs * a.max_tasks * a.rep * D;
-  a.valid = reinterpret_cast<uint32_t*>(workspace + pairs * a.max_tasks * a.rep * (D + 2u));
+  a.part_ml = workspace + pairs * a.waves * a.rep * D;
+  a.valid = reinterpret_cast<uint32_t*>(workspace + pairs * a.waves * a.rep * (D + 2u));
   a.out = out;
   a.lse = lse;
   a.status = status;
-  const dim3 grid((uint32_t)((waves + kAttendWaves - 1) / kAttendWaves)), block(kAttendWaves * kWaveSize);
+  a.flat = a.waves > 65535u ? 1u : 0u;
+  const dim3 grid(a.flat ? (uint32_t)(pairs * a.waves) : (uint32_t)pairs, a.flat ? 1u : a.waves), block(kWaveSize);
   const int hb = a.rep <= 4u ? 0 : a.rep <= 8u ? 1 : 2;      // how the weights fill the rows of an MFMA, see attend_task
   const uint32_t G = expect.group_size;
-#define QKV_LAUNCH_ATTEND(GG, DSS, KCC)                                                                \
-  do {                                                                                                 \
-    if (hb == 0) hipLaunchKernelGGL((attend_kernel<GG, 0, DSS, KCC>), grid, block, 0, stream, a);      \
-    else if (hb == 1) hipLaunchKernelGGL((attend_kernel<GG, 1, DSS, KCC>), grid, block, 0, stream, a); \
-    else hipLaunchKernelGGL((attend_kernel<GG, 2, DSS, KCC>), grid, block, 0, stream, a);              \
+#define QKV_LAUNCH_ATTEND_T(GG, DSS, KCC, TT)                                                                      \
+  do {                                                                                                             \
+    if (hb == 0) hipLaunchKernelGGL((attend_kernel<GG, 0, DSS, KCC, TT>), grid, block, 0, stream, a);              \
+    else if (hb == 1) hipLaunchKernelGGL((attend_kernel<GG, 1, DSS, KCC, TT>), grid, block, 0, stream, a);         \
+    else hipLaunchKernelGGL((attend_kernel<GG, 2, DSS, KCC, TT>), grid, block, 0, stream, a);                      \
+  } while (0)
+#define QKV_LAUNCH_ATTEND(GG, DSS)                                                                                 \
+  do {                                                                                                             \
+    if (a.waves < partials) QKV_LAUNCH_ATTEND_T(GG, DSS, false, true); else QKV_LAUNCH_ATTEND_T(GG, DSS, false, false); \
   } while (0)
   if (keys_per_channel) {                      // the host has checked: group size 32, head_dim 64 or 128
-    if (D == 64u) QKV_LAUNCH_ATTEND(32, 2, true); else QKV_LAUNCH_ATTEND(32, 4, true);
+    if (D == 64u) QKV_LAUNCH_ATTEND_T(32, 2, true, false); else QKV_LAUNCH_ATTEND_T(32, 4, true, false);
   } else if (D == 64u) {
-    if (G == 32u) QKV_LAUNCH_ATTEND(32, 2, false); else QKV_LAUNCH_ATTEND(64, 2, false);
+    if (G == 32u) QKV_LAUNCH_ATTEND(32, 2); else QKV_LAUNCH_ATTEND(64, 2);
   } else if (D == 128u) {
-    if (G == 32u) QKV_LAUNCH_ATTEND(32, 4, false); else if (G == 64u) QKV_LAUNCH_ATTEND(64, 4, false); else QKV_LAUNCH_ATTEND(128, 4, false);
+    if (G == 32u) QKV_LAUNCH_ATTEND(32, 4); else if (G == 64u) QKV_LAUNCH_ATTEND(64, 4); else QKV_LAUNCH_ATTEND(128, 4);
   } else {
-    if (G == 32u) QKV_LAUNCH_ATTEND(32, 8, false); else if (G == 64u) QKV_LAUNCH_ATTEND(64, 8, false); else QKV_LAUNCH_ATTEND(128, 8, false);
+    if (G == 32u) QKV_LAUNCH_ATTEND(32, 8); else if (G == 64u) QKV_LAUNCH_ATTEND(64, 8); else QKV_LAUNCH_ATTEND(128, 8);
   }
+#undef QKV_LAUNCH_ATTEND_T
 #undef QKV_LAUNCH_ATTEND
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 merge_grid(expect.layers * q_heads);
-  const uint32_t threads = merge_threads(merge_grid.x, a.max_tasks, D);
+  const uint32_t threads = merge_threads(merge_grid.x, a.waves, D);
   if (threads == 64u) hipLaunchKernelGGL(attend_merge_kernel<64>, merge_grid, dim3(64), 0, stream, a);
   else if (threads == 128u) hipLaunchKernelGGL(attend_merge_kernel<128>, merge_grid, dim3(128), 0, stream, a);
   else hipLaunchKernelGGL(attend_merge_kernel<256>, merge_grid, dim3(256), 0, stream, a);
