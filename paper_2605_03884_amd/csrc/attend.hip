@@ -24,7 +24,7 @@
 // Both products are v_mfma_f32_16x16x32_f16 (see attend_task).  head_dim 256 is two slabs of 128.
 // 2-bit spans, most of a card at low budgets, are not decoded by arithmetic: a group has only
 // four decoded values, which are computed once and picked by v_perm_b32.  Rounds are taken in whole groups of 4 / 3 / 2 /
-// 1 (at 2 / 4 / 8 / 16 bits; 64 dimensions: 2 / 2 / 1 / 1) without a branch in between; rounds past a task's end see zeros and
+// 1 (at 2 / 4 / 8 / 16 bits; 64 and 256 dimensions: 2 / 2 / 1 / 1) without a branch in between; rounds past a task's end see zeros and
 // count as -inf.  88 .. 128 registers and 9.5 KiB of LDS per wave: four waves per SIMD.
 //
 // Vector instructions of a round of 16 tokens x 128 dimensions with up to 4 query heads, at 2 / 4 / 8 bits: scores 61 / 85 / 80, softmax 9,
@@ -33,8 +33,8 @@
 // values had to be turned from pairs of dimensions into pairs of tokens, sums added up across lanes, high and low parts of
 // the weights took an MFMA each: 84, 18 and 112 at 2 bits, 24 MFMAs of 8 cycles.  Whole call, 32 query heads on 8 kv heads, 32
 // layers, us, then and now (with cut_tasks; card not in cache): 8192 tokens at budget 3 80 and 65, all 2 bits 67 and 57, 4 bits 85 and 78,
-// 8 bits 124.6 and 122.5; 1024 tokens at budget 5 20.9 and 18.7.  64 dimensions had left half the lanes idle, and more than 4 heads
-// took the 16 x 16 x 16 product: 8 heads, 3877 tokens of 128 pairs 30.1 and 21.4; 16 heads of 256 dimensions, 22950 tokens of 64 pairs 331 and 265.
+// 8 bits 124.6 and 122.5; 1024 tokens at budget 5 20.9 and 17.7.  64 dimensions had left half the lanes idle, and more than 4 heads
+// took the 16 x 16 x 16 product: 8 heads, 3877 tokens of 128 pairs 30.1 and 20.3; 16 heads of 256 dimensions, 22950 tokens of 64 pairs 331 and 265.
 
 #include <algorithm>
 #include <atomic>
