@@ -11,10 +11,10 @@
 // per-thread counters then gives every token its slot, so the bucketing is stable
 // (increasing token index inside a class).  The work is bound by instruction issue, not by
 // memory, which is why it is spread over several compute units instead of one.
-// One more workgroup, which owns no tokens, writes the header and zeroes the pad bytes of every section, and, where the card
-// is made from another one (requantization), the verdict on that card's header into the caller's
-// status word: the kernel that follows on the stream only adds to it (a launch of its own for the
-// verdict cost 4.6 us of 215).
+// Workgroup 0 also writes the header and zeroes the pad bytes of every section.  Where the card is made from
+// another one (requantization), one more workgroup does, together with the verdict on that card's header
+// into the caller's status word: the kernel that follows on the stream only adds to it (a launch of its
+// own for the verdict cost 4.6 us of 215).
 #include "qkv_common.h"
 #include "qkv_decode.h"
 #include "qkv_plan.h"
@@ -59,13 +59,14 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u, wave = tid >> 6;
   const uint32_t T = g.tokens;
-  // The last workgroup owns no tokens: it writes the header and the pad bytes, and the verdict on an incoming card, while the others
-  // write the tables (behind the first workgroup's own tables: requantization of 8K tokens 160.3 us, like this 159.4).
-  const bool head = blockIdx.x == gridDim.x - 1u;
+  // Where there is an incoming card to look at, a last workgroup, which owns no tokens, does that and writes the header and the pad
+  // bytes while the others write the tables (behind the first workgroup's own tables: requantization of 8K tokens 160.3 us,
+  // like this 159.4); otherwise the first one does, which has only the header to add.
+  const bool head = status_in != nullptr && blockIdx.x == gridDim.x - 1u;
   const uint32_t block_t0 = blockIdx.x * kPerBlock;       // < T for every workgroup but the last
   const uint32_t t0 = block_t0 + tid * kPerThread;
 
-  if (head && status_in) {
+  if (head) {
     CardGeom in;
     const bool ok = card_geometry_from_header(card_in, card_in_bytes, g.layers, g.kv_heads, g.head_dim, g.group_size, T, in);
     if (tid == 0) *status_in = ok ? 0u : QKV_STATUS_BAD_HEADER;
@@ -97,11 +98,14 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
   // whatever the host passed as counts
   const uint32_t base1 = tot0, base2 = base1 + tot1, base3 = base2 + tot2;
 
-  if (head) {
-    // header (the status word filled in from what the device saw) and the pad bytes behind every section
+  // header (the status word filled in from what the device saw) and the pad bytes behind every section
+  const auto write_head = [&] {
     uint32_t status = (valid != T) ? QKV_STATUS_BAD_BITS : 0u;
     if (tot0 != g.n[0] || tot1 != g.n[1] || tot2 != g.n[2] || tot3 != g.n[3]) status |= QKV_STATUS_BAD_COUNTS;
     write_header_and_pads(card, header, pads, status, tid);
+  };
+  if (head) {
+    write_head();
     return;
   }
 
@@ -158,6 +162,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
       }
     }
   }
+  if (status_in == nullptr && blockIdx.x == 0) write_head();
 }
 
 }  // namespace
@@ -167,7 +172,7 @@ hipError_t launch_classify(const uint8_t* bits, const CardGeom& geom, const qkv_
                            uint32_t* status_in) {
   const bool aligned = reinterpret_cast<uintptr_t>(bits) % 8 == 0;
   const uint32_t blocks = (geom.tokens + kPerBlock - 1) / kPerBlock;
-  hipLaunchKernelGGL(classify_kernel, dim3(blocks + 1u), dim3(kThreads), 0, stream, bits, geom, header, make_pad_table(geom), card, aligned,
+  hipLaunchKernelGGL(classify_kernel, dim3(blocks + (status_in ? 1u : 0u)), dim3(kThreads), 0, stream, bits, geom, header, make_pad_table(geom), card, aligned,
                      card_in, card_in_bytes, status_in);
   return hipGetLastError();
 }
