@@ -686,6 +686,79 @@ __device__ __forceinline__ void value_sweep(const RowStream& rows, SpanData<W, G
   }
 }
 
+// Softmax over a task's tokens, four heads at a time: row kq of the wave takes head 4 hg + kq, its lane n the tokens
+// 64 i + 4 n .. + 3 (the wave's own LDS accesses are in order).  Weights take the scores' places, `ml` the maximum and sum of every head.
+__device__ __forceinline__ void softmax_pass(float scale, uint32_t cnt, uint32_t slots, uint32_t n, uint32_t kq, float* lds, uint32_t pitch,
+                                             uint32_t R4, float* ml) {
+  const uint32_t whole = cnt & ~63u;                       // tokens of blocks that need no mask
+  for (uint32_t hg = 0; hg < R4; hg += 4u) {
+    const uint32_t r = hg + kq;
+    float* row_w = lds + r * pitch;
+    float m = -INFINITY;
+    const auto top = [&](uint32_t t, bool masked) {
+      const f32x4 sv = *reinterpret_cast<const f32x4*>(row_w + t);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) m = fmaxf(m, !masked || t + i < cnt ? sv[i] : -INFINITY);
+    };
+    for (uint32_t t = 0; t < whole; t += 64u) top(t + 4u * n, false);
+    for (uint32_t t = whole + 4u * n; t < slots; t += 64u) top(t, true);
+    m = row_max16(m) * scale;
+    float l = 0.f;
+    const auto weigh = [&](uint32_t t, bool masked) {
+      const f32x4 sv = *reinterpret_cast<const f32x4*>(row_w + t);
+      float ps[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float x = __builtin_fmaf(sv[i], scale, -m);
+        const float p = __builtin_amdgcn_exp2f(!masked || t + i < cnt ? x : -INFINITY);
+        l += p;
+        ps[i] = p * 16384.0f;
+      }
+      // what the value pass feeds the MFMA: p * 2^14 as an fp16 high part and the fp16 remainder (a normal number for any p
+      // that matters), in the scores' places: four high parts, then four remainders
+      const uint32_t h01 = pack_halves(ps[0], ps[1]), h23 = pack_halves(ps[2], ps[3]);
+      *reinterpret_cast<u32x4*>(row_w + t) =
+          (u32x4){h01, h23, pack_halves(fma_low(h01, -1.0f, ps[0]), fma_high(h01, -1.0f, ps[1])),
+                  pack_halves(fma_low(h23, -1.0f, ps[2]), fma_high(h23, -1.0f, ps[3]))};
+    };
+    for (uint32_t t = 0; t < whole; t += 64u) weigh(t + 4u * n, false);
+    for (uint32_t t = whole + 4u * n; t < slots; t += 64u) weigh(t, true);
+    l = row_sum16(l);
+    if (n == 0) *reinterpret_cast<float2*>(ml + 2u * r) = make_float2(m, l);
+  }
+}
+
+// Scores of 64 dimensions once more, where a head's weights do not add up to a number: a zero of q times an infinity or a NaN in
+// the key of the one token of a contraction is NaN in the other one's score.  Here each half of the contraction is
+// multiplied with the other half of the keys cleared, so that zeros only meet zeros; scores that are numbers come out as before,
+// to the bit.
+template <int W, int G, int HB>
+__device__ __forceinline__ void scores_apart(const RowStream& keys, __amdgpu_buffer_rsrc_t q_rows, uint32_t q_flip, uint32_t rounds, uint32_t n,
+                                             uint32_t kq, float* lds, uint32_t pitch, uint32_t R4) {
+  const uint32_t head = HB < 2 ? (n & 7u) : n;
+#pragma unroll 1
+  for (uint32_t half = 0; half < 2u; ++half) {              // tokens 0 .. 15 of every round, then tokens 16 .. 31
+    const bool mine = (kq >> 1) == half;
+    u32x4 q[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = buffer_load4(q_rows, mine ? head * 128u + 64u * (kq & 1u) + 16u * j : 0x40000000u) ^ q_flip;
+    if constexpr (W == 2) order_q2(q);
+#pragma unroll 1
+    for (uint32_t rd = 0; rd < rounds; ++rd) {
+      uint32_t kb[16];
+      if constexpr (W == 2) decode_fetched_bytes<G>(fetch_span<W, G, 2>(keys, rd), kb);
+      else decode_fetched<W, G>(fetch_span<W, G, 2>(keys, rd), kb);
+      f32x4 acc[2] = {(f32x4)(0.f), (f32x4)(0.f)};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const u32x4 k4 = {kb[4 * j], kb[4 * j + 1], kb[4 * j + 2], kb[4 * j + 3]};
+        acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, mine ? k4 : (u32x4)(0u)), __builtin_bit_cast(f16x8, q[j]), acc[j & 1], 0, 0, 0);
+      }
+      if (head < R4 && (HB == 2 || n < 8u)) *reinterpret_cast<f32x4*>(lds + head * pitch + rd * 32u + 16u * half + 4u * kq) = acc[0] + acc[1];
+    }
+  }
+}
+
 // One task: rows [j0, j1) of class c for the pair (layer, kv head) = pair.
 // lds: scores / weights as [head][pitch] floats (R4 * pitch <= kLdsFloatsPerWave);
 // tile: a round's packed rows followed by the rows' pairs.
@@ -694,7 +767,8 @@ __device__ __forceinline__ void value_sweep(const RowStream& rows, SpanData<W, G
 //   scores   A = K^[token n][8 dimensions of the lane's span], B = q[head n][the same]: lane (n, kq) gets tokens 4 kq .. + 3 of
 //            head n.  With 64 dimensions a round has 32 tokens; the two halves of the contraction belong to different
 //            tokens, and q is zero in one of them: columns 0 .. 7 are the heads against tokens 0 .. 15, columns 8 .. 15 the
-//            heads against tokens 16 .. 31 (more than 8 heads: one product for each half).  Keys have a few dimensions
+//            heads against tokens 16 .. 31 (more than 8 heads: one product for each half).  Zeros do not keep a key that is an
+//            infinity or no number from the other token's score: see scores_apart.  Keys have a few dimensions
 //            far larger than the others, and a sum that holds one of them rounds all that follows: two sums, added up
 //            at the end, are nearer to the value in 64 bits (one sum: output 4.1 .. 6.8e-7 from it, two: 3.4 .. 4.9e-7).
 //   values   V^ is decoded in pairs of neighbouring dimensions, and the contraction runs over (token, parity): B = {four
@@ -815,45 +889,8 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
   // the scores did without the selector table of 2-bit rows, and other widths' tiles lie over it
   if constexpr (W == 2 && !KC) build_select_table(reinterpret_cast<u32x2*>(table), lane);
 
-  // ---- softmax over the task's tokens, four heads at a time: row kq of the wave takes head
-  // 4 hg + kq, its lane n the tokens 64 i + 4 n .. + 3 (the wave's own LDS accesses are in order).
   const float scale = KC ? 1.0f : a.scale_log2;            // not negative; scores of keys grouped per channel are scaled already
-  const uint32_t whole = cnt & ~63u;                       // tokens of blocks that need no mask
-  for (uint32_t hg = 0; hg < R4; hg += 4u) {
-    const uint32_t r = hg + kq;
-    float* row_w = lds + r * pitch;
-    float m = -INFINITY;
-    const auto top = [&](uint32_t t, bool masked) {
-      const f32x4 sv = *reinterpret_cast<const f32x4*>(row_w + t);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) m = fmaxf(m, !masked || t + i < cnt ? sv[i] : -INFINITY);
-    };
-    for (uint32_t t = 0; t < whole; t += 64u) top(t + 4u * n, false);
-    for (uint32_t t = whole + 4u * n; t < slots; t += 64u) top(t, true);
-    m = row_max16(m) * scale;
-    float l = 0.f;
-    const auto weigh = [&](uint32_t t, bool masked) {
-      const f32x4 sv = *reinterpret_cast<const f32x4*>(row_w + t);
-      float ps[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float x = __builtin_fmaf(sv[i], scale, -m);
-        const float p = __builtin_amdgcn_exp2f(!masked || t + i < cnt ? x : -INFINITY);
-        l += p;
-        ps[i] = p * 16384.0f;
-      }
-      // what the value pass feeds the MFMA: p * 2^14 as an fp16 high part and the fp16 remainder (a normal number for any p
-      // that matters), in the scores' places: four high parts, then four remainders
-      const uint32_t h01 = pack_halves(ps[0], ps[1]), h23 = pack_halves(ps[2], ps[3]);
-      *reinterpret_cast<u32x4*>(row_w + t) =
-          (u32x4){h01, h23, pack_halves(fma_low(h01, -1.0f, ps[0]), fma_high(h01, -1.0f, ps[1])),
-                  pack_halves(fma_low(h23, -1.0f, ps[2]), fma_high(h23, -1.0f, ps[3]))};
-    };
-    for (uint32_t t = 0; t < whole; t += 64u) weigh(t + 4u * n, false);
-    for (uint32_t t = whole + 4u * n; t < slots; t += 64u) weigh(t, true);
-    l = row_sum16(l);
-    if (n == 0) *reinterpret_cast<float2*>(ml + 2u * r) = make_float2(m, l);
-  }
+  softmax_pass(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
 
   // ---- values: one sweep over the task's rows per slab of 128 output dimensions (the weights stay in LDS)
   constexpr int kBlocks = ValueGeo<HB, DS>::kBlocks, kSums = ValueGeo<HB, DS>::kSums;
@@ -874,6 +911,14 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
 #pragma unroll
           for (int i = 0; i < 4; ++i) finite = __builtin_fmaf(acc[b][m][i], 0.0f, finite);
       if (__builtin_amdgcn_ballot_w64(finite != 0.0f) != 0ull) {
+        if constexpr (DS == 2 && !KC) {                      // sums of a head that are no numbers may be a score's doing
+          const float l = ml[2u * min(n, R - 1u) + 1u];
+          if (__builtin_amdgcn_ballot_w64(!(l == l)) != 0ull) {
+            const RowStream keys = row_stream<W, G, DS>(a.card, g, c, k_row0 + j0, cnt, row, span);
+            scores_apart<W, G, HB>(keys, bounded(reinterpret_cast<const uint8_t*>(a.q + (uint64_t)pair * R * D), R * D * 2u), a.q_flip, rounds, n, kq, lds, pitch, R4);
+            softmax_pass(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
+          }
+        }
 #pragma unroll 1
         for (uint32_t odd = 0; odd < 2u; ++odd) {
           f32x4 one[kBlocks][kSums];

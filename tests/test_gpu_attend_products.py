@@ -1,5 +1,6 @@
 """The products of attention over a card where their packing could show: a value that is no number, or an infinity, reaches its own
-output dimension and no other (the value product pairs neighbouring dimensions), scales of either sign and zero (the sign is
+output dimension and no other (the value product pairs neighbouring dimensions), such a key its own token's score and no other (with 64
+dimensions the score product pairs tokens), scales of either sign and zero (the sign is
 taken into q), rows that end inside a round at every width, and head counts at the edges of the three row layouts.
 Tolerances: the bounds of test_gpu_attend.py."""
 import numpy as np
@@ -35,6 +36,64 @@ def test_no_number_stays_in_its_dimension(D, G, rep, value):
     assert not np.isfinite(out[0, rep:, d]).any()         # every head of the second kv head
     out[0, rep:, d] = want_o[0, rep:, d]
     assert float(np.abs(out - want_o).max()) <= tol_o and float(np.abs(lse - want_lse).max()) <= tol_lse
+
+
+def check_keys(card, rd, q, scale, exact):
+    """`exact`: the query heads whose result the definition gives, a weight of zero for a score of -inf."""
+    out, lse, st = run_gpu(card, rd.layers, rd.kv_heads, rd.tokens, rd.head_dim, rd.group_size, q, scale)
+    with np.errstate(invalid="ignore"):
+        want_o, want_lse = attend_ref.card_attend(card, rd, q, scale)
+    kq, vq = ref.unpack_dequant(card, rd)
+    k = np.abs(kq.view(np.float16).astype(np.float64))
+    k[~np.isfinite(k)] = 0.0                              # such a token's weight is exactly zero: it has no part in the error
+    ds = max(float((k[l, hq // (q.shape[1] // rd.kv_heads)] @ np.abs(q[l, hq].astype(np.float64))).max()) for l in range(rd.layers) for hq in exact)
+    ds *= rd.head_dim * 2.0 ** -24 * scale
+    base, vmax = (rd.tokens + 8) * 2.0 ** -24 + 2.0 ** -21, float(np.abs(vq.view(np.float16).astype(np.float64)).max())
+    assert st == 0 and np.isfinite(want_o[:, exact]).all()
+    assert float(np.abs(out[:, exact] - want_o[:, exact]).max()) <= (2 * ds + base) * vmax
+    assert float(np.abs(lse[:, exact] - want_lse[:, exact]).max()) <= ds + base
+
+
+@pytest.mark.parametrize("D,G", [(64, 32), (64, 64), (128, 32), (256, 64)])
+@pytest.mark.parametrize("rep", [1, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_no_number_in_a_key_stays_with_its_token(D, G, rep, value):
+    """Raw rows in either half of a round of 32 tokens, alone and several, at the ends of the card and of the segment."""
+    H, T, scale = 2, 301, D ** -0.5
+    for tokens in ([5], [21], [0, 31, 300], [96, 120, 150, 151]):
+        print("[case] D=%d G=%d rep=%d key %s at %s" % (D, G, rep, value, tokens), flush=True)
+        bits = np.full(T, 16, np.uint8)
+        bits[100:150] = qkv_synth.make_bits_uniform_choice(50, D + rep).numpy()
+        bits[tokens] = 16
+        K, V = qkv_synth.make_kv(1, H, T, D, 41 + rep, "llama")
+        q = np.random.default_rng(D + rep + tokens[0]).standard_normal((1, H * rep, D)).astype(np.float16)
+        exact = list(range(rep))                          # all of the first kv head, whose keys are numbers
+        for i, t in enumerate(tokens):
+            d = (17 * i + 3 + D // 2) % D
+            K[0, 1, t, d] = value
+            if not np.isnan(value):                       # every other head of the second: a score of -inf
+                q[0, rep::2, d] = -np.abs(q[0, rep::2, d]) * np.sign(value) - np.float16(0.01 * np.sign(value))
+        if not np.isnan(value):
+            exact += list(range(rep, 2 * rep, 2))
+        rd = ref.make_desc(1, H, T, D, G)
+        card = ref.quantize_pack(rd, K.numpy(), V.numpy(), bits, [int((bits == w).sum()) for w in (2, 4, 8, 16)])
+        check_keys(card, rd, q, scale, exact)
+
+
+@pytest.mark.parametrize("width", [2, 4, 8])
+@pytest.mark.parametrize("D,rep", [(64, 3), (64, 8), (64, 12), (128, 4), (256, 2)])
+def test_a_decoded_infinity_in_a_key_stays_with_its_token(width, D, rep):
+    """A group whose zero point is -inf, against heads that are positive there: scores of -inf at 2, 4 and 8 bits too."""
+    H, T, G, group = 2, 200, 32, 1
+    for t in (3, 19, 64 + 16, 199):
+        print("[case] D=%d rep=%d width %d token %d" % (D, rep, width, t), flush=True)
+        rd, card = build_card(1, H, T, D, G, np.full(T, width, np.uint8), 50 + rep + width)
+        card = card.copy()
+        at = int(card[128:152].view(np.uint64)[{2: 0, 4: 1, 8: 2}[width]]) + ((1 * T + t) * (D // G) + group) * 4
+        card[at:at + 4] = np.array([0x0000, 0xFC00], np.uint16).view(np.uint8)             # (scale, zero) = (0, -inf)
+        q = np.random.default_rng(D + rep + t).standard_normal((1, H * rep, D)).astype(np.float16)
+        q[..., group * G:(group + 1) * G] = np.abs(q[..., group * G:(group + 1) * G]) + np.float16(0.01)
+        check_keys(card, rd, q, D ** -0.5, list(range(H * rep)))
 
 
 @pytest.mark.parametrize("scale", [-0.09, 0.0, -0.0])
