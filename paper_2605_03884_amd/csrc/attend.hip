@@ -688,6 +688,8 @@ __device__ __forceinline__ void value_sweep(const RowStream& rows, SpanData<W, G
 
 // Softmax over a task's tokens, four heads at a time: row kq of the wave takes head 4 hg + kq, its lane n the tokens
 // 64 i + 4 n .. + 3 (the wave's own LDS accesses are in order).  Weights take the scores' places, `ml` the maximum and sum of every head.
+// SCALED: the scale is applied here.
+template <bool SCALED>
 __device__ __forceinline__ void softmax_pass(float scale, uint32_t cnt, uint32_t slots, uint32_t n, uint32_t kq, float* lds, uint32_t pitch,
                                              uint32_t R4, float* ml) {
   const uint32_t whole = cnt & ~63u;                       // tokens of blocks that need no mask
@@ -702,14 +704,21 @@ __device__ __forceinline__ void softmax_pass(float scale, uint32_t cnt, uint32_t
     };
     for (uint32_t t = 0; t < whole; t += 64u) top(t + 4u * n, false);
     for (uint32_t t = whole + 4u * n; t < slots; t += 64u) top(t, true);
-    m = row_max16(m) * scale;
+    const float largest = row_max16(m);
+    m = largest * scale;
+    // Weights are 2^(score * scale - m).  With the difference to the largest score taken first, `rest` is what rounding m itself left over,
+    // common to all of them, and a weight of 1 stays one of 2^rest.  As one rounding of score * scale - m that rest decided everything where
+    // m is large: at 2^26 it is half an ulp, 4, and takes the weights out of fp16's range.  From 2^22 on m stands for the
+    // largest score as it is, and a maximum that fp32 does not hold leaves no weights.  One subtraction a weight, 0.4 % of a call; a second
+    // way for large m, behind a branch, cost the short calls 1 .. 2 %.
+    const float rest = fabsf(m) < 4194304.0f ? __builtin_fmaf(largest, scale, -m) : m - m;
     float l = 0.f;
     const auto weigh = [&](uint32_t t, bool masked) {
       const f32x4 sv = *reinterpret_cast<const f32x4*>(row_w + t);
       float ps[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float x = __builtin_fmaf(sv[i], scale, -m);
+        const float x = SCALED ? __builtin_fmaf(sv[i] - largest, scale, rest) : sv[i] - m;
         const float p = __builtin_amdgcn_exp2f(!masked || t + i < cnt ? x : -INFINITY);
         l += p;
         ps[i] = p * 16384.0f;
@@ -890,7 +899,7 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
   if constexpr (W == 2 && !KC) build_select_table(reinterpret_cast<u32x2*>(table), lane);
 
   const float scale = KC ? 1.0f : a.scale_log2;            // not negative; scores of keys grouped per channel are scaled already
-  softmax_pass(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
+  softmax_pass<!KC>(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
 
   // ---- values: one sweep over the task's rows per slab of 128 output dimensions (the weights stay in LDS)
   constexpr int kBlocks = ValueGeo<HB, DS>::kBlocks, kSums = ValueGeo<HB, DS>::kSums;
@@ -916,7 +925,7 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
           if (__builtin_amdgcn_ballot_w64(!(l == l)) != 0ull) {
             const RowStream keys = row_stream<W, G, DS>(a.card, g, c, k_row0 + j0, cnt, row, span);
             scores_apart<W, G, HB>(keys, bounded(reinterpret_cast<const uint8_t*>(a.q + (uint64_t)pair * R * D), R * D * 2u), a.q_flip, rounds, n, kq, lds, pitch, R4);
-            softmax_pass(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
+            softmax_pass<!KC>(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
           }
         }
 #pragma unroll 1

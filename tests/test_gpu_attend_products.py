@@ -1,10 +1,11 @@
 """The products of attention over a card where their packing could show: a value that is no number, or an infinity, reaches its own
 output dimension and no other (the value product pairs neighbouring dimensions), such a key its own token's score and no other (with 64
 dimensions the score product pairs tokens), scales of either sign and zero (the sign is
-taken into q), rows that end inside a round at every width, and head counts at the edges of the three row layouts.
+taken into q), scores far apart, rows that end inside a round at every width, and head counts at the edges of the three row layouts.
 Tolerances: the bounds of test_gpu_attend.py."""
 import numpy as np
 import pytest
+import torch
 
 import qkv_synth
 from oracle import attend_ref, ref
@@ -123,3 +124,38 @@ def test_head_counts_at_the_edges_of_the_layouts(D, rep):
     T = 257
     bits = qkv_synth.make_bits_uniform_choice(T, D + 3 * rep).numpy()
     check(1, 2, rep, T, 64, bits, D + 5 * rep, "attend D=%d rep=%d" % (D, rep), D=D)
+
+
+@pytest.mark.parametrize("size", ["scale 1e7", "scale -3e8", "scale 1e12", "scale 1e30", "scale 1e35", "values"])
+@pytest.mark.parametrize("D,rep,T", [(64, 1, 500), (64, 9, 90), (128, 4, 1100), (128, 6, 33), (256, 5, 300)])
+def test_scores_far_apart(size, D, rep, T):
+    """Scores whose fp32 spacing is larger than 1: one token decides, or two alike do, whatever the maximum rounds to."""
+    H = 2
+    rng = np.random.default_rng(D + rep + T)
+    bits = qkv_synth.make_bits_uniform_choice(T, 5 + D + rep).numpy() if size.startswith("scale") else np.full(T, 16, np.uint8)
+    bits[[2, T - 2]] = 16
+    K, V = qkv_synth.make_kv(1, H, T, D, 80 + rep, "llama")
+    q = rng.standard_normal((1, H * rep, D)).astype(np.float16)
+    scale = float(size.split()[1]) if size.startswith("scale") else D ** -0.5
+    if size == "values":
+        K, q = (K.float() * 900).clamp(-60000, 60000).half(), (q.astype(np.float32) * 9000).astype(np.float16)
+    K[0, 1, 2] = torch.from_numpy(q[0, rep] * np.float16(np.sign(scale) * (8 if size.startswith("scale") else 1)))
+    K[0, 1, T - 2] = K[0, 1, 2]                           # two raw rows alike, the largest score of the second kv head's first head
+    rd = ref.make_desc(1, H, T, D, 32)
+    card = ref.quantize_pack(rd, K.numpy(), V.numpy(), bits, [int((bits == w).sum()) for w in (2, 4, 8, 16)])
+    out, lse, st = run_gpu(card, 1, H, T, D, 32, q, scale)
+    assert st == 0
+    want_o, want_lse = attend_ref.card_attend(card, rd, q, scale)
+    kq, vq = (x.view(np.float16).astype(np.float64)[0] for x in ref.unpack_dequant(card, rd))
+    clear = 0
+    for hq in range(H * rep):
+        s = scale * (kq[hq // rep] @ q[0, hq].astype(np.float64))
+        ds = D * 2.0 ** -24 * abs(scale) * float((np.abs(kq[hq // rep]) @ np.abs(q[0, hq].astype(np.float64))).max())
+        s = np.sort(np.delete(s, 2)) if hq == rep else np.sort(s)
+        if s[-1] - s[-2] < 2 * ds + 64:                   # the definition itself decides closer than fp32 sums can
+            continue
+        clear += 1
+        print("[case] %s D=%d rep=%d head %d: largest score %.3g" % (size, D, rep, hq, s[-1]), flush=True)
+        assert np.abs(out[0, hq] - want_o[0, hq]).max() <= ((T + 8) * 2.0 ** -24 + 2.0 ** -21) * np.abs(vq).max()
+        assert abs(lse[0, hq] - want_lse[0, hq]) <= ds + 2.0 ** -22 * abs(want_lse[0, hq])
+    assert clear > rep
