@@ -10,7 +10,7 @@
 //
 // Work decomposition.  A task is up to `chunk` consecutive rows of one width's
 // segment for one (layer, kv head), for all R query heads.  A wave takes every a.waves-th task of a pair and leaves an unnormalised
-// partial (running maximum m, sum l, sum of p.V^) in a workspace, which it finds there again after its next task; a second
+// partial (running maximum m, sum l, sum of p.V^) in a workspace, where it finds the sums of p.V^ again after its next task; a second
 // kernel merges the partials of each (layer, query head).  Inside a task, in rounds of 2048 values (16 tokens of 128 dimensions, 32 of 64):
 //   scores   a lane reads a span of 32 codes and its pair, decodes it to four MFMA operands of 8 dimensions,
 //            and four MFMAs accumulate q.K^ for the round's tokens and the kv head's query
@@ -387,6 +387,14 @@ __device__ inline void operands_from_tile(const uint8_t* tile, const uint8_t* ta
 }
 
 // ---- cross-lane helpers ------------------------------------------------------------------------
+
+// What lanes of the wave wrote to LDS before is what others read behind it: the hardware keeps one wave's LDS accesses in order,
+// and this, which is no instruction, keeps the compiler to it.
+__device__ inline void lds_handover() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
 template <int CTRL>
 __device__ inline float dpp_move(float v) {
@@ -791,9 +799,11 @@ __device__ __forceinline__ void scores_apart(const RowStream& keys, __amdgpu_buf
 //
 // DS = head_dim / 32 spans per token.  The lane mapping covers a slab of 128 dimensions (4 spans); head_dim 256 is two
 // slabs (the score of a round adds both up before it is stored, the value pass sweeps the task once per slab).
-template <int W, int G, int HB, int DS, bool KC>
+// TURNS: a wave's later tasks add to the partial that the earlier ones left: its sums in part_o, where every lane finds its own, its
+// maximum and sum of every head in LDS (`run`), since one lane writes them and sixteen read them.
+template <int W, int G, int HB, int DS, bool KC, bool TURNS>
 __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom& g, int c, uint32_t pair, uint32_t j0, uint32_t j1,
-                                   uint32_t lane, float* lds, uint8_t* tile, uint8_t* table, float* ml, float* part_o, float* part_ml, bool first) {
+                                   uint32_t lane, float* lds, uint8_t* tile, uint8_t* table, float* ml, float* run, float* part_o, float* part_ml, bool first) {
   const uint32_t n = lane & 15u, kq = lane >> 4;          // also (a, kt) of the value pass
   const uint32_t R = a.rep, R4 = HB == 0 ? 4u : ((R + 3u) & ~3u);
   const uint32_t pitch = a.chunk;                          // of a head's scores in LDS
@@ -899,7 +909,9 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
   if constexpr (W == 2 && !KC) build_select_table(reinterpret_cast<u32x2*>(table), lane);
 
   const float scale = KC ? 1.0f : a.scale_log2;            // not negative; scores of keys grouped per channel are scaled already
+  lds_handover();                                          // scores
   softmax_pass<!KC>(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
+  lds_handover();                                          // weights, maxima and sums, the table
 
   // ---- values: one sweep over the task's rows per slab of 128 output dimensions (the weights stay in LDS)
   constexpr int kBlocks = ValueGeo<HB, DS>::kBlocks, kSums = ValueGeo<HB, DS>::kSums;
@@ -925,7 +937,9 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
           if (__builtin_amdgcn_ballot_w64(!(l == l)) != 0ull) {
             const RowStream keys = row_stream<W, G, DS>(a.card, g, c, k_row0 + j0, cnt, row, span);
             scores_apart<W, G, HB>(keys, bounded(reinterpret_cast<const uint8_t*>(a.q + (uint64_t)pair * R * D), R * D * 2u), a.q_flip, rounds, n, kq, lds, pitch, R4);
+            lds_handover();
             softmax_pass<!KC>(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
+            lds_handover();
           }
         }
 #pragma unroll 1
@@ -961,10 +975,9 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
           else o[e] = acc[x >> 1][m][2 * (x & 1) + h] * kUnscale;
         }
         f32x4* dst = reinterpret_cast<f32x4*>(part_o + (r * D + d0));
-        float2* dst_ml = reinterpret_cast<float2*>(part_ml + 2u * r);
         float2 now = *reinterpret_cast<const float2*>(ml + 2u * r);
-        if (!first) {                                      // the wave's earlier tasks have left theirs here
-          const float2 old = *dst_ml;
+        if (TURNS && !first) {                             // the wave's earlier tasks have left theirs here
+          const float2 old = *reinterpret_cast<const float2*>(run + 2u * r);
           const f32x4 o0 = dst[0], o1 = DS != 2 ? dst[1] : (f32x4){0.f, 0.f, 0.f, 0.f};
           // a task whose weights do not add up to a positive number counts for nothing, here as in the merge
           const bool have = old.y > 0.f, add = now.y > 0.f;
@@ -976,10 +989,11 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
         }
         dst[0] = (f32x4){o[0], o[1], o[2], o[3]};
         if constexpr (DS != 2) dst[1] = (f32x4){o[4], o[5], o[6], o[7]};
-        if (n == 0 && sl == S - 1) *dst_ml = now;
+        if (n == 0 && sl == S - 1) *reinterpret_cast<float2*>((TURNS ? run : part_ml) + 2u * r) = now;
       }
     }
   }
+  if constexpr (TURNS) lds_handover();
 }
 
 // How a card's rows are cut into the tasks of a (layer, kv head).
@@ -1082,6 +1096,7 @@ void attend_kernel(AttendArgs a) {
   // then the rows' pairs (512 bytes), then at 2 bits the 2 KiB selector table
   __shared__ __attribute__((aligned(16))) uint8_t tiles[kTileBytes];
   __shared__ __attribute__((aligned(16))) float mls[32];      // the task's maximum and sum of every head
+  __shared__ __attribute__((aligned(16))) float runs[TURNS ? 32 : 2];      // and the wave's, over its tasks so far
   CardGeom g;
   bool ok = card_geometry_from_header(a.card, a.card_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size,
                                       a.tokens, g, KC ? QKV_FLAG_KEYS_PER_CHANNEL : 0u);
@@ -1122,14 +1137,17 @@ void attend_kernel(AttendArgs a) {
     const bool first = !TURNS || t == tau;
     if (cls == 0) {
       if (KC) build_select_table(reinterpret_cast<u32x2*>(my_table), ln);
-      attend_task<2, G, HB, DS, KC>(a, g, 0, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, part_o, part_ml, first);
+      attend_task<2, G, HB, DS, KC, TURNS>(a, g, 0, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, runs, part_o, part_ml, first);
     }
-    if (cls == 1) attend_task<4, G, HB, DS, KC>(a, g, 1, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, part_o, part_ml, first);
-    if (cls == 2) attend_task<8, G, HB, DS, KC>(a, g, 2, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, part_o, part_ml, first);
+    if (cls == 1) attend_task<4, G, HB, DS, KC, TURNS>(a, g, 1, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, runs, part_o, part_ml, first);
+    if (cls == 2) attend_task<8, G, HB, DS, KC, TURNS>(a, g, 2, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, runs, part_o, part_ml, first);
     if constexpr (!KC) {                       // a card grouped per channel has no raw rows
-      if (cls == 3) attend_task<16, G, HB, DS, false>(a, g, 3, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, part_o, part_ml, first);
+      if (cls == 3) attend_task<16, G, HB, DS, false, TURNS>(a, g, 3, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, runs, part_o, part_ml, first);
     }
     if (!TURNS) break;                         // no more tasks than waves
+  }
+  if constexpr (TURNS) {
+    if (threadIdx.x < a.rep) reinterpret_cast<float2*>(part_ml)[threadIdx.x] = reinterpret_cast<const float2*>(runs)[threadIdx.x];
   }
 }
 
