@@ -258,14 +258,17 @@ __device__ inline void order_q2(u32x4 (&raw)[4]) {
 // cross LDS, never decoded values.
 
 // Rows of 16 spans, or 32 of 8 bytes at head_dim 64.  The pitch keeps the rows that a read instruction touches (4 apart) on
-// different banks.  Behind the rows, as [span][row]: the 64 pairs as two floats (2-bit rows: 64 four-value tables), and
+// different banks and every span where its store of 8 (2 bits) or 16 bytes may lie (4 bits, 64 dimensions: 48 bytes; with 40, every odd
+// row's store 8 bytes off, 16 shapes took 1.6 % longer).  Behind the rows, as [span][row]: the 64 pairs as two floats (2-bit rows: 64 four-value tables), and
 // at 2 bits the 2 KiB selector table.
 template <int W, int ROWS> struct TileGeo {
-  static constexpr uint32_t kRowBytes = ROWS == 16 ? ((W == 2) ? 40u : (W == 4) ? 80u : 128u) : ((W == 2) ? 24u : (W == 4) ? 40u : 80u);
+  static constexpr uint32_t kRowBytes = ROWS == 16 ? ((W == 2) ? 40u : (W == 4) ? 80u : 128u) : ((W == 2) ? 24u : (W == 4) ? 48u : 80u);
   static constexpr uint32_t kPairsAt = (uint32_t)ROWS * kRowBytes;
+  static_assert(kRowBytes % (W == 2 ? 8u : 16u) == 0u && kPairsAt % 16u == 0u, "stage_span stores whole spans, pairs are read four words at a time");
 };
 constexpr uint32_t kTableAt = 32u * 24u + 512u;          // the selector table: behind the larger of the two tiles of 2-bit rows
 constexpr uint32_t kTileBytes = kTableAt + 2048u;
+static_assert(TileGeo<8, 32>::kPairsAt + 512u <= kTileBytes && TileGeo<4, 32>::kPairsAt + 512u <= kTileBytes && TileGeo<8, 16>::kPairsAt + 512u <= kTileBytes, "");
 
 // Loader side: a lane drops its fetched span `span` of row `row`, and the span's pair, into the tile.
 template <int W, int G, int ROWS>
@@ -1092,7 +1095,7 @@ template <int G, int HB, int DS, bool KC, bool TURNS>
 __global__ __launch_bounds__(kWaveSize) __attribute__((amdgpu_waves_per_eu(4)))
 void attend_kernel(AttendArgs a) {
   __shared__ __attribute__((aligned(16))) float lds[kLdsFloatsPerWave];
-  // the value pass's LDS, 3.25 KiB: a round's packed rows (640 / 1280 / 2048 bytes at 2 / 4 / 8 bits; 64 dimensions 768 / 1280 / 2560),
+  // the value pass's LDS, 3.25 KiB: a round's packed rows (640 / 1280 / 2048 bytes at 2 / 4 / 8 bits; 64 dimensions 768 / 1536 / 2560),
   // then the rows' pairs (512 bytes), then at 2 bits the 2 KiB selector table
   __shared__ __attribute__((aligned(16))) uint8_t tiles[kTileBytes];
   __shared__ __attribute__((aligned(16))) float mls[32];      // the task's maximum and sum of every head
