@@ -49,6 +49,8 @@ __device__ inline uint64_t load_widths(const uint8_t* __restrict__ bits, uint32_
   return w;
 }
 
+// INCOMING: there is a card to look at, and one workgroup more than the tokens need.
+template <bool INCOMING>
 __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __restrict__ bits, CardGeom g,
                                                            qkv_card_header_t header, PadTable pads,
                                                            uint8_t* __restrict__ card, bool aligned,
@@ -60,10 +62,12 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
   const uint32_t lane = tid & 63u, wave = tid >> 6;
   const uint32_t T = g.tokens;
   // Where there is an incoming card to look at, a last workgroup, which owns no tokens, does that and writes the header and the pad
-  // bytes while the others write the tables (behind the first workgroup's own tables: requantization of 8K tokens 160.3 us,
-  // like this 159.4); otherwise the first one does, which has only the header to add.
-  const bool head = status_in != nullptr && blockIdx.x == gridDim.x - 1u;
-  const uint32_t block_t0 = blockIdx.x * kPerBlock;       // < T for every workgroup but the last
+  // bytes while the others write the tables (whole requantization, behind the first workgroup's own tables and like this: 256 tokens of
+  // 2 pairs 11.9 and 10.7 us, 2048 of 256 48.1 and 47.3, 8192 of 256 152.1 and 151.6); otherwise the first one does, which has
+  // only the header to add.  Two instances: one kernel that tells them apart as it runs takes longer to plan a card (8192 tokens 5.51 us, like
+  // this 5.45) and to forward one (1000 tokens of 8 pairs 10.94 and 10.85).
+  const bool head = INCOMING && blockIdx.x == gridDim.x - 1u;
+  const uint32_t block_t0 = blockIdx.x * kPerBlock;       // < T for every workgroup that owns tokens
   const uint32_t t0 = block_t0 + tid * kPerThread;
 
   if (head) {
@@ -104,7 +108,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
     if (tot0 != g.n[0] || tot1 != g.n[1] || tot2 != g.n[2] || tot3 != g.n[3]) status |= QKV_STATUS_BAD_COUNTS;
     write_header_and_pads(card, header, pads, status, tid);
   };
-  if (head) {
+  if (head) {                                             // at once: behind a skipped scan of slots 1 us more
     write_head();
     return;
   }
@@ -162,7 +166,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const uint8_t* __res
       }
     }
   }
-  if (status_in == nullptr && blockIdx.x == 0) write_head();
+  if (!INCOMING && blockIdx.x == 0) write_head();
 }
 
 }  // namespace
@@ -172,8 +176,12 @@ hipError_t launch_classify(const uint8_t* bits, const CardGeom& geom, const qkv_
                            uint32_t* status_in) {
   const bool aligned = reinterpret_cast<uintptr_t>(bits) % 8 == 0;
   const uint32_t blocks = (geom.tokens + kPerBlock - 1) / kPerBlock;
-  hipLaunchKernelGGL(classify_kernel, dim3(blocks + (status_in ? 1u : 0u)), dim3(kThreads), 0, stream, bits, geom, header, make_pad_table(geom), card, aligned,
-                     card_in, card_in_bytes, status_in);
+  if (status_in)
+    hipLaunchKernelGGL(classify_kernel<true>, dim3(blocks + 1u), dim3(kThreads), 0, stream, bits, geom, header, make_pad_table(geom), card, aligned,
+                       card_in, card_in_bytes, status_in);
+  else
+    hipLaunchKernelGGL(classify_kernel<false>, dim3(blocks), dim3(kThreads), 0, stream, bits, geom, header, make_pad_table(geom), card, aligned,
+                       card_in, card_in_bytes, status_in);
   return hipGetLastError();
 }
 
