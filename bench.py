@@ -50,7 +50,7 @@ MEASURED_ATTEND = {
                       "lds_active_cycles": 15047633, "lds_bank_conflict_cycles": 7858129, "sources": "1566b12c835b72dc",
                       "profile": "profiles/card_attend_llama8b_8k_b3.txt"},
 }
-ATTEND_SOURCES = ["attend.hip", "qkv_decode.h", "qkv_common.h"]
+ATTEND_SOURCES = ["attend.hip", "attend_cut.h", "qkv_decode.h", "qkv_common.h"]
 
 
 def kernel_sources_digest(names=KERNEL_SOURCES):

@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "attend_cut.h"
 #include "qkv_common.h"
 
 namespace qkv {

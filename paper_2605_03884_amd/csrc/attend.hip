@@ -40,6 +40,7 @@
 #include <atomic>
 #include <cmath>
 
+#include "attend_cut.h"
 #include "qkv_common.h"
 #include "qkv_decode.h"
 
@@ -49,11 +50,6 @@ namespace {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// Tokens of a group of rounds whose loads are in flight together (Prefetch), by class, at 64, 128 and 256 dimensions (there a
-// multiple of them): what makes tasks of different widths last about as long.
-constexpr uint32_t kUnit[3][4] = {{64u, 64u, 32u, 32u}, {64u, 48u, 32u, 16u}, {64u, 32u, 32u, 16u}};
-constexpr int kLdsFloatsPerWave = 1536;      // scores of one task: chunk tokens x padded query heads (6 KiB)
 
 struct AttendArgs {
   const uint8_t* card;
@@ -584,10 +580,18 @@ __device__ inline SpanData<W, G> fetch_value(const RowStream& s, uint32_t rd) {
 }
 
 // Rounds whose loads are in flight ahead of the arithmetic: as many as the registers allow (a fetched span is 3 / 5 / 9 / 16
-// registers at 2 / 4 / 8 / 16 bits; two slabs in flight cost twice that).  Their tokens divide 192 and are 96 at most.
+// registers at 2 / 4 / 8 / 16 bits; two slabs in flight cost twice that).  Their tokens, 64 at most, divide the units that tasks are
+// made of, so that a padded round stays inside its task's LDS.
 template <int W, int DS> struct Prefetch {
   static constexpr int kRounds = DS != 4 ? (W <= 4 ? 2 : 1) : W == 2 ? 4 : W == 4 ? 3 : W == 8 ? 2 : 1;
+  static constexpr uint32_t kTokens = (uint32_t)kRounds * RoundGeo<DS>::kTokens;
 };
+template <int DS> constexpr bool whole_groups() {
+  const uint32_t* unit = kUnit[DS / 4];
+  return unit[0] % Prefetch<2, DS>::kTokens == 0u && unit[1] % Prefetch<4, DS>::kTokens == 0u && unit[2] % Prefetch<8, DS>::kTokens == 0u &&
+         unit[3] % Prefetch<16, DS>::kTokens == 0u;
+}
+static_assert(whole_groups<2>() && whole_groups<4>() && whole_groups<8>(), "a task is a whole number of groups of rounds");
 
 // How the value pass fills its MFMAs (see attend_task) and what it accumulates.
 template <int HB, int DS> struct ValueGeo {
@@ -999,93 +1003,14 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
   if constexpr (TURNS) lds_handover();
 }
 
-// How a card's rows are cut into the tasks of a (layer, kv head).
-//
-// Where it can be, all tasks get the same number of units: a unit is one group of rounds whose loads are in flight
-// together - fewer tokens at larger widths - so a task lasts about as long whatever its width.  s units a task make at
-// most k - 1 + (sum u_c - (k - 1)) / s tasks (rounded up) of the k classes present, so s >= (sum u_c - (k - 1)) / (n - (k - 1)) keeps
-// them within n.  In this order, with n the waves of a pair:
-//   one turn of even tasks; then with no more than `rows` rows each, the length that the workspace's partials go by (a chip that
-//   is not full is bound by latency, and a wide row takes little longer than a narrow one); then as many rows as that of any width;
-//   up to three turns of even tasks, where LDS holds three units or more: the waves run in step, and one that got two long tasks
-//   while others have one holds up the call;
-//   beyond, the longest tasks that LDS holds: a task's start and end cost about 3 us that four waves a SIMD do not quite hide (32K
-//   tokens of 2 bits with tasks of 192 rows 218 us, of 384 199).
-// Whole call, us, with one task a wave, more of them than wave slots, and like this: 8192 tokens at budget 3 of 256 pairs 72 and 65, 224
-// pairs 65 and 59, 9000 tokens 77 and 71, 5000 tokens 48.6 and 40; 512 pairs, 9000 tokens 140 and 137.
-struct TaskCut {
-  uint32_t tasks[4];       // of each class
-  uint32_t step[4];        // rows of a task
-  // Class of task `tau` and its rows [j0, j1); -1: there is no such task.
-  __device__ inline int find(const CardGeom& g, uint32_t tau, uint32_t& j0, uint32_t& j1) const {
-    int cls = -1;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (cls < 0) {
-        if (tau < tasks[c]) {
-          cls = c;
-          j0 = tau * step[c];
-          j1 = min(g.n[c], j0 + step[c]);
-        } else {
-          tau -= tasks[c];
-        }
-      }
-    }
-    return cls;
+// The lanes of a wave, for cut_tasks.
+struct WaveLanes {
+  __device__ inline uint32_t value(uint32_t v, uint32_t lane) const { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
+  __device__ inline uint32_t quad_sum(uint32_t v) const {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);        // quad_perm 1 0 3 2
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);  // quad_perm 2 3 0 1
   }
 };
-
-__device__ inline uint32_t divide_up(uint32_t a, uint32_t b) { return (a + b - 1u) / b; }
-__device__ inline uint32_t lane_value(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
-
-// Every wave goes through this between the header and its first load, and a division is a chain of some thirty dependent
-// instructions: lane 4 k + c works on class c of candidate k, so that all that can be divided at the same time is.
-template <int DS, bool KC>
-__device__ __forceinline__ TaskCut cut_tasks(const AttendArgs& a, const CardGeom& g, uint32_t lane) {
-  uint32_t units[4], sum = 0, present = 0, most = ~0u, room = ~0u;      // units of every class present that fit `rows`, and LDS
-  const uint32_t c = lane & 3u, k = lane >> 2;
-  uint32_t my_unit = 0, my_units = 0, my_fit = 0, my_fit_rows = 0;
-#pragma unroll
-  for (uint32_t x = 0; x < 4u; ++x) {
-    const uint32_t unit = KC ? a.unit[x] : kUnit[DS / 4][x];
-    units[x] = KC ? (g.n[x] == 0u ? 0u : divide_up(g.n[x], unit)) : divide_up(g.n[x], unit);
-    sum += units[x];
-    present += (uint32_t)(g.n[x] != 0u);
-    most = g.n[x] == 0u ? most : min(most, a.fit_rows[x]);
-    room = g.n[x] == 0u ? room : min(room, a.fit[x]);
-    my_unit = c == x ? unit : my_unit;
-    my_units = c == x ? units[x] : my_units;
-    my_fit = c == x ? a.fit[x] : my_fit;
-    my_fit_rows = c == x ? a.fit_rows[x] : my_fit_rows;
-  }
-  const uint32_t spare = present - 1u;                   // every class but one may end with a partly filled task
-  const uint32_t even = a.waves > spare ? a.waves - spare : 1u;
-  const uint32_t first = divide_up(sum - spare, k == 0u ? even : room);
-  const uint32_t share = a.waves > spare ? max(1u, lane_value(first, 0u)) : ~0u;
-  const uint32_t least = lane_value(first, 4u) + spare;
-  // candidates: one turn of even tasks, of as many rows as `rows`; any number of turns of the longest tasks; and how many turns even ones take
-  const uint32_t own = k == 0u ? min(share, my_fit_rows) : k == 1u ? my_fit_rows : k == 2u ? my_fit : a.waves;
-  uint32_t tasks = divide_up(k < 3u ? my_units : least, own), step = own * my_unit;
-  uint32_t total = tasks + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)tasks, 0xB1, 0xF, 0xF, false);        // quad_perm 1 0 3 2
-  total += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)total, 0x4E, 0xF, 0xF, false);                        // quad_perm 2 3 0 1
-  uint32_t best = 0u;
-  if (share > most && lane_value(total, 0u) > a.waves) {
-    const uint32_t turns = lane_value(tasks, 12u);
-    best = lane_value(total, 4u) <= a.waves ? 4u : 8u;
-    if (best == 8u && turns <= 3u && room >= 3u) {
-      const uint32_t shorter = max(1u, divide_up(sum - spare, turns * a.waves - spare));
-      tasks = divide_up(my_units, shorter);
-      step = shorter * my_unit;
-    }
-  }
-  TaskCut cut;
-#pragma unroll
-  for (uint32_t x = 0; x < 4u; ++x) {
-    cut.tasks[x] = lane_value(tasks, best + x);
-    cut.step[x] = lane_value(step, best + x);
-  }
-  return cut;
-}
 
 // KC: the card's key planes are grouped per channel (a uniform card at 2, 4 or 8 bits, group size 32).
 // TURNS: there may be more tasks than waves.  An instance of its own, because what a loop around the tasks keeps in registers and
@@ -1122,7 +1047,7 @@ void attend_kernel(AttendArgs a) {
   uint8_t* my_tile = tiles;
   uint8_t* my_table = my_tile + kTableAt;
   float* my_ml = mls;
-  const TaskCut cut = cut_tasks<DS, KC>(a, g, threadIdx.x & 63u);
+  const TaskCut cut = cut_tasks<DS, KC>(a, g, threadIdx.x & 63u, WaveLanes());
   const uint32_t tasks = cut.tasks[0] + cut.tasks[1] + cut.tasks[2] + cut.tasks[3];
   if (one) *a.valid = min(tasks, a.waves);
   if (tau >= min(tasks, a.waves)) return;      // a spare wave: the merge knows
@@ -1147,7 +1072,7 @@ void attend_kernel(AttendArgs a) {
     if constexpr (!KC) {                       // a card grouped per channel has no raw rows
       if (cls == 3) attend_task<16, G, HB, DS, false, TURNS>(a, g, 3, pair, j0, j1, ln, my_lds, my_tile, my_table, my_ml, runs, part_o, part_ml, first);
     }
-    if (!TURNS) break;                         // no more tasks than waves
+    if (!TURNS) break;                         // no more tasks than waves (see cut_parameters)
   }
   if constexpr (TURNS) {
     if (threadIdx.x < a.rep) reinterpret_cast<float2*>(part_ml)[threadIdx.x] = reinterpret_cast<const float2*>(runs)[threadIdx.x];
@@ -1227,48 +1152,6 @@ __global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(AttendArgs 
 
 }  // namespace
 
-constexpr uint64_t kWaveSlots = 256u * 4u * 4u;        // four waves on each of the four SIMDs of 256 compute units
-
-// Tokens per task and tasks per (layer, kv head) for a given shape.  The scores of one task (tokens x
-// query heads padded to a multiple of 4) must fit the wave's 6 KiB of LDS.  Tasks are processed in groups
-// of 4, 3, 2 or 1 rounds of 16 tokens, depending on the width, and a task size that all of these divide
-// keeps the padded rounds inside the task's LDS: multiples of 192 tokens, or 64 tokens when fewer than
-// 192 fit (a 64-token task pads to 96 at most).  The larger size means fewer partials and less per-task
-// work (90 us against 96 us at 8K tokens x 256 pairs); the smaller one is taken when the larger would
-// not even fill the chip's wave slots once (one wave per task, four waves per SIMD, 256 compute units).
-void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk, uint32_t* max_tasks) {
-  const uint32_t r4 = (rep + 3u) & ~3u;
-  const uint32_t room = kLdsFloatsPerWave / r4;                 // tokens whose scores fit, 96 at least
-  const uint32_t limit = room >= 192u ? room / 192u * 192u : 64u;
-  uint32_t c = limit;
-  while (c > 192u && pairs * ((tokens + c - 1) / c + 2u) < kWaveSlots) c -= 192u;
-  *chunk = c;
-  *max_tasks = (uint32_t)((tokens + *chunk - 1) / *chunk) + 3u;   // every class may end with a partly filled task
-}
-
-// The number of tasks that short sequences are better cut into, where the workspace has room for their partials: one
-// per wave slot of the chip, but no more than there are units of work at a middling mix of widths (an empty task still
-// costs its dispatch).  Only up to 4 query heads per kv head and head_dim 128: beyond, a task's fixed part and the merge are
-// heavier, and the rule would need a line of its own.  Attention and merge, us, with the least number of tasks and cut like
-// this (a pair's waves one after the other): 256 pairs, 8 heads, 300 tokens 20.2 and 18.8, 1000 29.6 and 25.0,
-// 4000 55.2 and 55.4; 16 heads, 2000 tokens 51.5 and 53.8; 32 pairs, 8 heads, 1000 tokens 18.6 and 15.3, 4000 20.9 and 23.8;
-// head_dim 256, 4 heads, 1000 23.7 and 19.2, 4000 29.9 and 35.5.
-// And no more than 96: with few pairs the merge, a few workgroups that go through all partials, takes longer than what shorter
-// tasks save.  Whole call, 4 heads and a mean over widths, us, with at most 1368 / 192 / 96 / 64: 1 pair, 8192 tokens 16 / 16 / 15 / 15,
-// 32768 40 / 22 / 23 / 22, 65536 73 / 32 / 33 / 32; 8 pairs, 8192 19 / 19 / 17 / 17, 24000 39 / 26 / 23 / 23; 16 pairs, 12000 24 / 22 / 20 / 19.
-// Not beyond the fixed scratch array, so that the call that uses it cuts its tasks - and rounds its sums - like the
-// one with a workspace.
-uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t head_dim, uint32_t max_tasks) {
-  if (rep > 4u || head_dim > 128u) return max_tasks;
-  uint64_t want = kWaveSlots / pairs;
-  const uint64_t useful = tokens / 48u + 3u;
-  if (want > useful) want = useful;
-  if (want > 96u) want = 96u;
-  const uint64_t fits = (QKV_ATTEND_STATIC_SCRATCH_BYTES / sizeof(float) - 4u) / (pairs * rep * (head_dim + 2u));
-  if (want > fits) want = fits;
-  return want > max_tasks ? (uint32_t)want : max_tasks;
-}
-
 // ---- scratch for callers that cannot allocate -------------------------------------------------
 //
 // qkv_card_attend_static keeps the partials in this array instead of a caller's workspace.  Every
@@ -1311,18 +1194,6 @@ static uint32_t merge_threads(uint32_t workgroups, uint32_t tasks, uint32_t head
   return workgroups <= 2048u || tasks * head_dim / 4u > 256u ? 128u : 64u;
 }
 
-// Waves per pair: all pairs' first waves are dealt out first, then all second ones: the holes that waves without a task leave are
-// then one piece at the end (a pair's waves one after the other: 2000 tokens of 256 pairs 41.4 us, like this 26.8).  As many turns of the chip's wave slots as leave no more than a tenth of the last one empty, one if that
-// does, but no more than `most`, the partials a pair has room for.
-static uint32_t waves_per_pair(uint64_t pairs, uint32_t most) {
-  uint64_t w = 0;
-  for (uint64_t turns = 1; turns <= 8u; ++turns) {
-    w = turns * kWaveSlots / pairs;
-    if (w >= most || 10u * w * pairs >= 9u * turns * kWaveSlots) break;
-  }
-  return (uint32_t)std::min<uint64_t>(most, w == 0u ? 1u : w);
-}
-
 hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, const void* q,
                          uint32_t q_heads, float softmax_scale, float* out, float* lse, float* workspace,
                          uint64_t workspace_bytes, uint32_t* status, bool keys_per_channel, hipStream_t stream) {
@@ -1339,26 +1210,7 @@ hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeo
   if (a.q_flip != 0u) a.scale_log2 = -a.scale_log2;
   const uint64_t pairs = (uint64_t)expect.layers * expect.kv_heads;
   const uint32_t D = expect.head_dim;
-  uint32_t partials = 0;                       // the workspace has room for, of a pair
-  attend_plan(expect.tokens, a.rep, pairs, &a.rows, &partials);
-  const uint32_t more = attend_more_tasks(expect.tokens, a.rep, pairs, D, partials);
-  if (workspace_bytes >= (pairs * more * a.rep * (D + 2u) + 4u) * sizeof(float)) partials = more;
-  // with keys grouped per channel every task has a wave of its own: there is no register left for more (a.rows and the
-  // partials go together, so that there are no more tasks than waves)
-  a.waves = keys_per_channel ? partials : waves_per_pair(pairs, partials);
-  a.chunk = kLdsFloatsPerWave / ((a.rep + 3u) & ~3u) / 16u * 16u;
-  // a group of rounds whose loads are in flight together; keys grouped per channel are scored 128 tokens at a time, in whole
-  // blocks of 32: as many groups as are whole blocks, 128 tokens where LDS holds a multiple
-  const uint32_t* unit = kUnit[D / 128u];
-  for (int c = 0; c < 4; ++c) a.unit[c] = unit[c];
-  if (keys_per_channel) {
-    a.unit[0] = a.unit[1] = a.unit[2] = a.rows % 128u == 0u || (a.chunk >= 128u && expect.tokens <= 128u * (uint64_t)partials) ? 128u : 64u;
-    if (D == 128u) a.unit[1] = 96u;
-  }
-  for (int c = 0; c < 4; ++c) {
-    a.fit[c] = a.chunk / a.unit[c];
-    a.fit_rows[c] = std::max(1u, a.rows / a.unit[c]);
-  }
+  const uint32_t partials = cut_parameters(a, expect.tokens, a.rep, pairs, D, keys_per_channel, workspace_bytes / sizeof(float));
   a.part_o = workspace;
   a.part_ml = workspace + pairs * a.waves * a.rep * D;
   a.valid = reinterpret_cast<uint32_t*>(workspace + pairs * a.waves * a.rep * (D + 2u));

@@ -160,8 +160,6 @@ hipError_t launch_assign_plan(const float* scores, const uint32_t cuts[3], uint8
 hipError_t launch_assign_long(const float* scores, uint32_t tokens, const uint32_t cuts[3], uint8_t* bits, hipStream_t stream);
 hipError_t launch_assign_plan_long(const float* scores, const uint32_t cuts[3], uint8_t* bits, const CardGeom& geom,
                                    const qkv_card_header_t& header, uint8_t* card, hipStream_t stream);
-void attend_plan(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t* chunk, uint32_t* max_tasks);
-uint32_t attend_more_tasks(uint64_t tokens, uint32_t rep, uint64_t pairs, uint32_t head_dim, uint32_t max_tasks);
 hipError_t launch_attend(const uint8_t* card, uint64_t card_bytes, const CardGeom& expect, const void* q,
                          uint32_t q_heads, float softmax_scale, float* out, float* lse, float* workspace,
                          uint64_t workspace_bytes, uint32_t* status, bool keys_per_channel, hipStream_t stream);
