@@ -417,8 +417,10 @@ int qkv_requantize(const void* card_in_dev, uint64_t card_in_bytes, const qkv_de
  * the softmax and the weighted sum run in fp32; against the float64 definition a score is off
  * by at most head_dim * 2^-24 * softmax_scale * sum_i |q_i K^_ti| (summation order only), which
  * for caches of ordinary magnitude leaves out within a few units in 1e-6 of max|V^|.
+ * Raw rows may hold anything: a score of -inf has a weight of zero, a value that is infinite or no number
+ * makes its own dimension of out one; a head with a score that is +inf or no number has unspecified results.
  *   card_dev, card_bytes, expect, status_dev: as for qkv_unpack_dequant; head_dim 64, 128 or 256
- *             (the kernel is laid out for 128: at 64 half of its lanes idle, at 256 it takes the
+ *             (the kernel is laid out for 128: at 64 it takes twice the tokens at a time, at 256 the
  *             head dimension in two halves), keys grouped per token.
  *   q_dev:    device, fp16 [layers][q_heads][head_dim], 16-byte aligned.  q_heads is a multiple
  *             of kv_heads, at most 16 query heads per kv head.
@@ -475,7 +477,7 @@ int qkv_card_attend_kc(const void* card_dev, uint64_t card_bytes, const qkv_desc
  *   - All calls on one GPU share the array: two calls that overlap in time on the same GPU (on
  *     different streams, or from different threads) race and give wrong results.  Calls on one
  *     stream are ordered by the stream.  Nothing in the array needs clearing between calls: every
- *     partial a call reads it has written itself.
+ *     partial that counts has been written by the call itself.
  *   - The first call on a GPU looks the array's device address up with the runtime; make that
  *     first call outside a graph capture.
  */

@@ -25,9 +25,9 @@
 // 2-bit spans, most of a card at low budgets, are not decoded by arithmetic: a group has only
 // four decoded values, which are computed once and picked by v_perm_b32.  Rounds are taken in whole groups of 4 / 3 / 2 /
 // 1 (at 2 / 4 / 8 / 16 bits; 64 and 256 dimensions: 2 / 2 / 1 / 1) without a branch in between; rounds past a task's end see zeros and
-// count as -inf.  88 .. 128 registers and 9.5 KiB of LDS per wave: four waves per SIMD.
+// count as -inf.  86 .. 125 registers and 9.5 KiB of LDS per wave: four waves per SIMD.
 //
-// Vector instructions of a round of 16 tokens x 128 dimensions with up to 4 query heads, at 2 / 4 / 8 bits: scores 61 / 85 / 80, softmax 9,
+// Vector instructions of a round of 16 tokens x 128 dimensions with up to 4 query heads, at 2 / 4 / 8 bits: scores 61 / 85 / 80, softmax 10,
 // values 38 / 91 / 88, and 8 MFMAs of 16 cycles; at 2 bits the vector pipes are then about 70 % and LDS, most of it the value
 // pass's look-ups, 65 % busy.  With v_mfma_f32_4x4x4_16b_f16, whose operands are four tokens of one dimension,
 // values had to be turned from pairs of dimensions into pairs of tokens, sums added up across lanes, high and low parts of
@@ -803,6 +803,9 @@ __device__ __forceinline__ void scores_apart(const RowStream& keys, __amdgpu_buf
 //            the low parts, HB = 2 (9 .. 16 heads) two blocks of 8 heads with 64 dimensions; with more, where two blocks'
 //            sums leave room for three waves a SIMD only (16 heads, 3622 tokens of 256 pairs: 75.3 -> 81.7 us), the
 //            pairs are turned and v_mfma_f32_16x16x16_f16 has the 16 heads as rows.
+// No accumulator sees both shapes: the compiler (ROCm 7.2) puts nothing between a 16 x 16 x 16 and a 16 x 16 x 32 product that start from each
+// other's result, and one right behind the other, in either order, left 128 of 256 sums wrong in a program of just the two (with
+// other products in between, none).
 //
 // DS = head_dim / 32 spans per token.  The lane mapping covers a slab of 128 dimensions (4 spans); head_dim 256 is two
 // slabs (the score of a round adds both up before it is stored, the value pass sweeps the task once per slab).
