@@ -387,6 +387,13 @@ __device__ inline void operands_from_tile(const uint8_t* tile, const uint8_t* ta
 
 // ---- cross-lane helpers ------------------------------------------------------------------------
 
+// The lane's number, worked out where it is asked for: what depends on it is not kept in registers from further up.
+__device__ inline uint32_t lane_anew() {
+  uint32_t lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
+  return lane;
+}
+
 // What lanes of the wave wrote to LDS before is what others read behind it: the hardware keeps one wave's LDS accesses in order,
 // and this, which is no instruction, keeps the compiler to it.
 __device__ inline void lds_handover() {
@@ -783,6 +790,41 @@ __device__ __forceinline__ void scores_apart(const RowStream& keys, __amdgpu_buf
   }
 }
 
+// The kernel's arguments, read where they are asked for: none of them is kept in registers from further up.
+typedef const __attribute__((address_space(4))) AttendArgs* ArgsAnew;
+__device__ inline ArgsAnew args_anew() {
+  ArgsAnew at = (ArgsAnew)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(at));
+  return at;
+}
+
+// Where a task's sums over values are no numbers: if a head's weights do not add up to one, its scores may be their neighbours' doing, and
+// scores and softmax are worked out again.  Lane, arguments and the card's geometry are asked for anew, since what this rarely taken
+// way keeps in registers is missed by the other (several tasks a wave, 64 dimensions: 3 % of a call).
+template <int W, int G, int HB>
+__device__ __forceinline__ void score_again(uint32_t pair, uint32_t j0, uint32_t cnt, uint32_t rounds, uint32_t slots, float* lds, float* ml) {
+  constexpr int c = W == 2 ? 0 : W == 4 ? 1 : W == 8 ? 2 : 3;
+  const uint32_t lane = lane_anew(), n = lane & 15u, kq = lane >> 4;
+  const ArgsAnew a = args_anew();
+  const uint32_t R = a->rep, R4 = HB == 0 ? 4u : ((R + 3u) & ~3u), pitch = a->chunk;
+  const float l = ml[2u * min(n, R - 1u) + 1u];
+  if (__builtin_amdgcn_ballot_w64(!(l == l)) == 0ull) return;
+  const qkv_card_header_t* header = reinterpret_cast<const qkv_card_header_t*>(a->card);
+  CardGeom g;                                              // what row_stream asks for
+  if constexpr (W == 16) {
+    g.off_fp16 = header->off_fp16;
+  } else {
+    g.off_codes[c] = header->off_codes[c];
+    g.off_meta[c] = header->off_meta[c];
+  }
+  const RowStream keys = row_stream<W, G, 2>(a->card, g, c, (uint64_t)pair * header->count[c] + j0, cnt, RoundGeo<2>::row(n, kq), RoundGeo<2>::span(kq));
+  const __amdgpu_buffer_rsrc_t q_rows = bounded(reinterpret_cast<const uint8_t*>(a->q + (uint64_t)pair * R * 64u), R * 128u);
+  scores_apart<W, G, HB>(keys, q_rows, a->q_flip, rounds, n, kq, lds, pitch, R4);
+  lds_handover();
+  softmax_pass<true>(a->scale_log2, cnt, slots, n, kq, lds, pitch, R4, ml);
+  lds_handover();
+}
+
 // One task: rows [j0, j1) of class c for the pair (layer, kv head) = pair.
 // lds: scores / weights as [head][pitch] floats (R4 * pitch <= kLdsFloatsPerWave);
 // tile: a round's packed rows followed by the rows' pairs.
@@ -941,17 +983,8 @@ __device__ __forceinline__ void attend_task(const AttendArgs& a, const CardGeom&
         for (int m = 0; m < kSums; ++m)
 #pragma unroll
           for (int i = 0; i < 4; ++i) finite = __builtin_fmaf(acc[b][m][i], 0.0f, finite);
-      if (__builtin_amdgcn_ballot_w64(finite != 0.0f) != 0ull) {
-        if constexpr (DS == 2 && !KC) {                      // sums of a head that are no numbers may be a score's doing
-          const float l = ml[2u * min(n, R - 1u) + 1u];
-          if (__builtin_amdgcn_ballot_w64(!(l == l)) != 0ull) {
-            const RowStream keys = row_stream<W, G, DS>(a.card, g, c, k_row0 + j0, cnt, row, span);
-            scores_apart<W, G, HB>(keys, bounded(reinterpret_cast<const uint8_t*>(a.q + (uint64_t)pair * R * D), R * D * 2u), a.q_flip, rounds, n, kq, lds, pitch, R4);
-            lds_handover();
-            softmax_pass<!KC>(scale, cnt, slots, n, kq, lds, pitch, R4, ml);
-            lds_handover();
-          }
-        }
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(finite != 0.0f) != 0ull, 0)) {
+        if constexpr (DS == 2 && !KC) score_again<W, G, HB>(pair, j0, cnt, rounds, slots, lds, ml);
 #pragma unroll 1
         for (uint32_t odd = 0; odd < 2u; ++odd) {
           f32x4 one[kBlocks][kSums];
@@ -1061,8 +1094,7 @@ void attend_kernel(AttendArgs a) {
   for (uint32_t t = tau; t < tasks; t += a.waves) {
     // the lane's number, worked out anew each time: it and what depends on it alone (q in two orders, offsets at four widths) would
     // otherwise be kept in registers that the loop does not have
-    uint32_t ln = threadIdx.x;
-    if (TURNS) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(ln));
+    const uint32_t ln = TURNS ? lane_anew() : threadIdx.x;
     uint32_t j0 = 0, j1 = 0;
     const int cls = cut.find(g, t, j0, j1);
     const bool first = !TURNS || t == tau;

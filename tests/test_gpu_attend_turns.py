@@ -48,3 +48,31 @@ def test_several_tasks_a_wave(L, H, T, D, rep, budget):
         e = D * 2.0 ** -24 * D ** -0.5 * float((q[l].double().abs().view(H, rep, D) @ k[l].double().abs().transpose(1, 2).contiguous()).max())
         assert float((out[l].view(H, rep, D).double() - want).abs().max()) <= (2 * e + 1e-5) * float(v[l].abs().max())
         assert float((lse[l].view(H, rep).double() - want_lse).abs().max()) <= e + 1e-5
+
+
+@pytest.mark.parametrize("L,H,T,D,rep", [(35, 8, 6100, 64, 3), (40, 8, 9000, 64, 8), (35, 8, 2100, 64, 16), (35, 8, 4200, 128, 4)])
+def test_an_infinite_key_in_a_later_task(L, H, T, D, rep):
+    """Scores of -inf in rows of every raw task of one pair: a weight of zero, and nothing else of the wave's tasks is lost."""
+    print("[case] L=%d H=%d T=%d D=%d rep=%d" % (L, H, T, D, rep), flush=True)
+    desc = qkv.Desc.make(L, H, T, D, 64)
+    gen = torch.Generator(device=DEV).manual_seed(T + rep)
+    bits, counts = qkv.assign_bits(torch.rand((T,), device=DEV, generator=gen), 7.0)
+    k, v = (torch.randn((L, H, T, D), dtype=torch.float16, device=DEV, generator=gen) for _ in range(2))
+    q = torch.randn((L, H * rep, D), dtype=torch.float16, device=DEV, generator=gen)
+    raw = (bits == 16).nonzero().flatten()[7::50]
+    k[L - 1, H - 1, raw, 3] = float("inf")
+    q[L - 1, (H - 1) * rep:, 3] = -q[L - 1, (H - 1) * rep:, 3].abs() - 0.01
+    card = torch.empty(qkv.card_bytes(desc, counts), dtype=torch.uint8, device=DEV)
+    qkv.quantize_pack(desc, k, v, bits, counts, card)
+    qkv.unpack_dequant(card, desc, k, v)
+    out, lse = torch.full((L, H * rep, D), float("nan"), device=DEV), torch.full((L, H * rep), float("nan"), device=DEV)
+    qkv.card_attend(card, desc, q, D ** -0.5, out, lse=lse)
+    torch.cuda.synchronize()
+    keep = torch.ones(T, dtype=torch.bool, device=DEV)
+    keep[raw] = False                                     # tokens whose weight is zero, in that pair only
+    for l, h, rows in ((0, 0, keep | True), (L - 1, H - 2, keep | True), (L - 1, H - 1, keep)):
+        kk, vv, qq = k[l, h:h + 1, rows], v[l, h:h + 1, rows], q[l, h * rep:(h + 1) * rep]
+        want, want_lse = dense_attention(qq, kk, vv, 1, rep, D)
+        e = D * 2.0 ** -24 * D ** -0.5 * float((qq.double().abs() @ kk[0].double().abs().T.contiguous()).max())
+        assert float((out[l, h * rep:(h + 1) * rep].double() - want[0]).abs().max()) <= (2 * e + 1e-5) * float(vv.abs().max())
+        assert float((lse[l, h * rep:(h + 1) * rep].double() - want_lse[0]).abs().max()) <= e + 1e-5
