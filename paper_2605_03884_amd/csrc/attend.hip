@@ -332,6 +332,18 @@ template <int W>
 __device__ inline void pieces_from_tile64(const uint8_t* tile, const uint8_t* table, uint32_t a, uint32_t kt, uint32_t (&t)[4][4]) {
   constexpr uint32_t kRowBytes = TileGeo<W, 32>::kRowBytes;
   const uint32_t* pairs_lds = reinterpret_cast<const uint32_t*>(tile + TileGeo<W, 32>::kPairsAt);
+  // 2 bits: all codes, then all look-ups, then the selections.  Left to itself the compiler now and then waits for every look-up by
+  // itself (uniform 2-bit cards, several tasks a wave: 6 % of a call).
+  uint32_t piece[8];
+  u32x2 select[8];
+  if constexpr (W == 2) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) piece[i] = tile[(16u * (i >> 2) + 4u * kt + (i & 3)) * kRowBytes + a];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) select[i] = *reinterpret_cast<const u32x2*>(table + 8u * piece[i]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const uint32_t row = 16u * u + 4u * kt, at = (a >> 3) * 32u + row;
@@ -341,10 +353,8 @@ __device__ inline void pieces_from_tile64(const uint8_t* tile, const uint8_t* ta
       const uint32_t xl[4] = {x01.x, x01.z, x23.x, x23.z}, xh[4] = {x01.y, x01.w, x23.y, x23.w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const uint32_t piece = tile[(row + i) * kRowBytes + a];
-        const u32x2 s = *reinterpret_cast<const u32x2*>(table + 8u * piece);
-        t[i][2 * u] = __builtin_amdgcn_perm(xh[i], xl[i], s.x);
-        t[i][2 * u + 1] = __builtin_amdgcn_perm(xh[i], xl[i], s.y);
+        t[i][2 * u] = __builtin_amdgcn_perm(xh[i], xl[i], select[4 * u + i].x);
+        t[i][2 * u + 1] = __builtin_amdgcn_perm(xh[i], xl[i], select[4 * u + i].y);
       }
     } else {
       const u32x4* pr = reinterpret_cast<const u32x4*>(pairs_lds) + at / 2u;
