@@ -740,10 +740,10 @@ __device__ __forceinline__ void softmax_pass(float scale, uint32_t cnt, uint32_t
     m = largest * scale;
     // Weights are 2^(score * scale - m).  With the difference to the largest score taken first, `rest` is what rounding m itself left over,
     // common to all of them, and a weight of 1 stays one of 2^rest.  As one rounding of score * scale - m that rest decided everything where
-    // m is large: at 2^26 it is half an ulp, 4, and takes the weights out of fp16's range.  From 2^22 on m stands for the
-    // largest score as it is, and a maximum that fp32 does not hold leaves no weights.  One subtraction a weight, 0.4 % of a call; a second
-    // way for large m, behind a branch, cost the short calls 1 .. 2 %.
-    const float rest = fabsf(m) < 4194304.0f ? __builtin_fmaf(largest, scale, -m) : m - m;
+    // m is large: at 2^26 it is half an ulp, 4, and takes the weights out of fp16's range.  From 2^22 on, where it can be more than 1/4,
+    // it is cut off: m is no nearer to the largest score than that anyway.  One subtraction a weight, 0.3 % of a call (short cards
+    // of 16 heads 1 %); a second way for large m, behind a branch, cost the short calls 1 .. 2 %.
+    const float rest = __builtin_amdgcn_fmed3f(__builtin_fmaf(largest, scale, -m), -0.25f, 0.25f);
     float l = 0.f;
     const auto weigh = [&](uint32_t t, bool masked) {
       const f32x4 sv = *reinterpret_cast<const f32x4*>(row_w + t);
