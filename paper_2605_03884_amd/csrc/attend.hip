@@ -25,7 +25,7 @@
 // 2-bit spans, most of a card at low budgets, are not decoded by arithmetic: a group has only
 // four decoded values, which are computed once and picked by v_perm_b32.  Rounds are taken in whole groups of 4 / 3 / 2 /
 // 1 (at 2 / 4 / 8 / 16 bits; 64 and 256 dimensions: 2 / 2 / 1 / 1) without a branch in between; rounds past a task's end see zeros and
-// count as -inf.  86 .. 125 registers and 9.5 KiB of LDS per wave: four waves per SIMD.
+// count as -inf.  96 .. 127 registers and 9.5 KiB of LDS per wave: four waves per SIMD.
 //
 // Vector instructions of a round of 16 tokens x 128 dimensions with up to 4 query heads, at 2 / 4 / 8 bits: scores 61 / 85 / 80, softmax 10,
 // values 38 / 91 / 88, and 8 MFMAs of 16 cycles; at 2 bits the vector pipes are then about 70 % and LDS, most of it the value
