@@ -47,7 +47,7 @@ KERNEL_SOURCES = ["pack.hip", "unpack.hip", "qkv_encode.h", "qkv_decode.h", "qkv
 VECTOR_PEAK_TLANEOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 MEASURED_ATTEND = {
     "llama8b_8k_b3": {"valu_instructions": 19688194, "mfma_instructions": 1060864, "lds_instructions": 2209792,
-                      "lds_active_cycles": 15072209, "lds_bank_conflict_cycles": 7858129, "sources": "b6b0b7f1cd6a0d3b",
+                      "lds_active_cycles": 15072209, "lds_bank_conflict_cycles": 7858129, "sources": "eeb7963229862326",
                       "profile": "profiles/card_attend_llama8b_8k_b3.txt"},
 }
 ATTEND_SOURCES = ["attend.hip", "attend_cut.h", "qkv_decode.h", "qkv_common.h"]

@@ -800,7 +800,8 @@ __device__ __forceinline__ void scores_apart(const RowStream& keys, __amdgpu_buf
   }
 }
 
-// The kernel's arguments, read where they are asked for: none of them is kept in registers from further up.
+// attend_kernel's arguments (one AttendArgs, so they lie where its argument segment begins), read where they are asked for: none of
+// them is kept in registers from further up.
 typedef const __attribute__((address_space(4))) AttendArgs* ArgsAnew;
 __device__ inline ArgsAnew args_anew() {
   ArgsAnew at = (ArgsAnew)__builtin_amdgcn_kernarg_segment_ptr();
