@@ -160,45 +160,6 @@ __device__ inline SpanData<W, G> fetch_span(const RowStream& s, uint32_t rd) {
   return d;
 }
 
-// Codes that sit in the two halves of a word are fp16 numbers already, code * 2^-24: v_fma_mix_f32 reads either half and
-// rounds code * scale + zero to fp32 (scale24 = scale * 2^24), so a code costs no conversion of its own - 2.4 vector
-// instructions a value at 4 bits where picking bytes apart and converting them takes 2.9.
-__device__ inline float fma_low(uint32_t codes, float scale24, float zero) {
-  float r;
-  asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(codes), "v"(scale24), "v"(zero));
-  return r;
-}
-__device__ inline float fma_high(uint32_t codes, float scale24, float zero) {
-  float r;
-  asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(codes), "v"(scale24), "v"(zero));
-  return r;
-}
-__device__ inline uint32_t pack_halves(float a, float b) {
-  const f32x2 v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
-}
-
-// 8 values at 4 bits (one word) or 4 at 8 bits (one word), two neighbours to a word.
-template <int W>
-__device__ inline void decode_word(uint32_t w, float scale24, float zero, uint32_t* out) {
-  static_assert(W == 4 || W == 8, "");
-  if constexpr (W == 4) {
-    float x[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t codes = (w >> (4 * i)) & 0x000F000Fu;                 // values i and 4 + i
-      x[i] = fma_low(codes, scale24, zero);
-      x[4 + i] = fma_high(codes, scale24, zero);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) out[i] = pack_halves(x[2 * i], x[2 * i + 1]);
-  } else {
-    const uint32_t even = w & 0x00FF00FFu, odd = (w >> 8) & 0x00FF00FFu;
-    out[0] = pack_halves(fma_low(even, scale24, zero), fma_low(odd, scale24, zero));
-    out[1] = pack_halves(fma_high(even, scale24, zero), fma_high(odd, scale24, zero));
-  }
-}
-
 // The 32 values of a fetched span as 16 packed fp16 pairs (2 bits: see decode_fetched_bytes).
 template <int W, int G>
 __device__ inline void decode_fetched(const SpanData<W, G>& d, uint32_t (&out)[16]) {

@@ -8,9 +8,11 @@
 // dense values only ever exist in registers.  The result is, byte for byte, the card that creation
 // would build from the injected cache.
 //
-// Work decomposition: a workgroup takes a window of up to 256 consecutive rows of one outgoing segment: of one
-// plane, done for one or two planes, or, in short cards, of the segment as it lies, across planes (a rule in
-// launch_requant).  It looks the window's tokens up once (token through the outgoing card's
+// Work decomposition, two of them (the line between them stands in launch_requant).
+//
+// Windows of a width: a workgroup takes a window of up to 256 consecutive rows of one outgoing segment: of one
+// plane, done for one or two planes, or, in short cards, of the segment as it lies, across planes.
+// It looks the window's tokens up once (token through the outgoing card's
 // order[], written by the classification kernel just before, old width and slot through the incoming
 // card's tables), sorts them by old width into a list in LDS and cuts the list into rounds of at most 64
 // spans of one old width; the four waves deal the rounds of all planes among themselves, each with the
@@ -18,15 +20,21 @@
 // whatever its size: rows that leave for different widths share lines, and windows that run at the
 // same time find them in cache (nontemporal loads cost 26 % at 32K tokens).
 //
+// Windows of tokens (long cards): a workgroup takes 512 rows (plane, token) and sorts them by pair of old and new width.  Tokens
+// in a row lie in a row in every segment of either card, so a window reads and writes every line once; its rounds are dealt out in the order
+// of their middle rows, so that what shares a line is done at about the same time (16384 tokens of 512 planes, 6 to 4: rows past the L2 read
+// 1.33 GB with windows of a width and 0.97, written 0.85 and 0.71, whole call 419 us and 375; in the order of the pairs it is a tenth slower than
+// with windows of a width).  Vector issue is then 90 % of the kernel's time at 3 to 6 bits; beyond 32K tokens reading and
+// writing at once is (reading alone 393 us, writing alone 261, both 740).
+//
 // Spans that were 2-bit (most of a card at low budgets) are not expanded to 32 values at all: a group
 // has four decoded values, in order, so its extrema follow from which codes occur, the quantizer runs
 // on the four values, and the new codes are the old ones relabelled.
 //
-// What bounds it: vector instruction issue (about 70 % busy at 8K tokens), then requests for parts of lines.
-// Whole call, 8K tokens, budget 3 to 2.5, with the new widths' assignment: 199 us before (64 rows of one plane
-// sorted per wave, every span expanded to 32 values), 160 us now; 32K tokens, 6 to 4: 1162 and 840 us.
-// Windows of 512 rows: 171 and 936 us; without the next round's loads in flight: 172 and 877 us; a window
-// of 256 tokens over all widths at once, four waves dealing 16 width pairs: 221 and 1137 us.
+// Whole call with the new widths' assignment, 8K tokens, budget 3 to 2.5: 199 us with 64 rows of one plane sorted per wave and every span
+// expanded to 32 values, 160 with windows of a width, 146 with windows of tokens; 32K tokens, 6 to 4: 1162, 840 and 757 us.
+// Windows of a width: of 512 rows 171 and 936 us; without the next round's loads in flight 172 and 877; of 256 tokens over all
+// widths at once, in the order of the pairs, 221 and 1137.
 //
 // The incoming card is untrusted: header and offsets are rebuilt and checked on the device, table
 // entries are bounded before they are used.
@@ -61,11 +69,12 @@ struct RequantArgs {
 // Bits chosen from a where mask is 1, from b where it is 0: one instruction.
 __device__ inline uint32_t bit_select(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
-// Whether relabel_span2 applies to every lane's pair: a scale that is no negative number, and finite values.
+// Whether relabel_span2 applies to every lane's pair: a scale that is no negative number, and finite values (no other zero has a
+// finite fourth value).
 __device__ inline bool can_relabel(uint32_t old_pair) {
   const float s = half_bits_to_float(old_pair & 0xFFFFu), z = half_bits_to_float(old_pair >> 16);
   const uint32_t x3 = decode_pair(2.0f, 3.0f, s, z) >> 16;
-  const bool odd = (old_pair & 0xFFFFu) > 0x7BFFu || (x3 & 0x7C00u) == 0x7C00u || (old_pair & 0x7C000000u) == 0x7C000000u;
+  const bool odd = (old_pair & 0xFFFFu) > 0x7BFFu || (x3 & 0x7C00u) == 0x7C00u;
   return __builtin_amdgcn_ballot_w64(odd) == 0ull;
 }
 
@@ -171,35 +180,68 @@ __device__ __forceinline__ void decode_old(const OldSpan& d, uint32_t (&w)[16]) 
   uint32_t cw[W];
 #pragma unroll
   for (int i = 0; i < W; ++i) cw[i] = d.cw[i];
-  decode_span<W>(cw, half_bits_to_float(d.pair & 0xFFFFu), half_bits_to_float(d.pair >> 16), w);
+  const float scale = half_bits_to_float(d.pair & 0xFFFFu), zero = half_bits_to_float(d.pair >> 16);
+  if constexpr (W == 2) {
+    decode_span<W>(cw, scale, zero, w);
+  } else {
+#pragma unroll
+    for (int i = 0; i < W; ++i) decode_word<W>(cw[i], scale * 16777216.0f, zero, w + 16 / W * i);
+  }
+}
+
+// Exchanges between the lanes l and l ^ 1: the odd lane's a becomes the even lane's b, and the other way round.
+__device__ __forceinline__ void swap_between(uint32_t& a, uint32_t& b, bool odd) {
+  const uint32_t from_a = dpp<kQuadXor1>(a), from_b = dpp<kQuadXor1>(b);
+  a = odd ? from_b : a;
+  b = odd ? b : from_a;
+}
+
+// Stores the N * 4 bytes of every lane at a place of its own.  Lane 2k + 1's place follows lane 2k's (a row has two spans at least), so
+// they exchange every other sixteen bytes and each store writes 32 bytes in a row instead of 16 (32K tokens, 4 bits to 16: 1727 us and 1528;
+// within fours of lanes and 64 bytes in a row 1187, but 8 registers more than eight waves a SIMD leave, which costs narrow rows more).
+template <int N>
+__device__ __forceinline__ void store_in_twos(uint8_t* dst, uint32_t (&w)[N], uint32_t lane) {
+  const bool odd = (lane & 1u) != 0u;
+#pragma unroll
+  for (int j = 0; j < N; j += 8) {
+#pragma unroll
+    for (int k = j; k < j + 4; ++k) swap_between(w[k], w[k + 4], odd);
+  }
+  u32x4* d = reinterpret_cast<u32x4*>(dst - (odd ? N * 4 - 16 : 0));
+#pragma unroll
+  for (int j = 0; j < N; j += 8) {
+    d[j / 4] = (u32x4){w[j], w[j + 1], w[j + 2], w[j + 3]};
+    d[(N + j) / 4] = (u32x4){w[j + 4], w[j + 5], w[j + 6], w[j + 7]};
+  }
 }
 
 // Stores the codes and the pair of span gsp of the outgoing class with width W.  Plain stores: the rows of a line may
 // leave in different rounds, and the L2 puts the line together.
 template <int W, int G>
-__device__ __forceinline__ void store_span(const RequantArgs& a, uint64_t gsp, uint32_t q, bool live, const uint32_t (&codes)[W], uint32_t pair) {
+__device__ __forceinline__ void store_span(uint8_t* card, const CardGeom& out, uint64_t gsp, uint32_t lane, bool live, uint32_t (&codes)[W], uint32_t pair) {
   constexpr int GS = G / 32, C = W == 2 ? 0 : W == 4 ? 1 : 2;
-  if (!live) return;
-  uint8_t* dst = a.card_out + a.out.off_codes[C] + gsp * (4u * W);
-  if (W == 2) *reinterpret_cast<u32x2*>(dst) = (u32x2){codes[0], codes[1]};
-  if (W >= 4) *reinterpret_cast<u32x4*>(dst) = (u32x4){codes[0], codes[1], codes[2], codes[3]};
-  if (W == 8) *reinterpret_cast<u32x4*>(dst + 16) = (u32x4){codes[4], codes[5], codes[6], codes[7]};
-  if ((q & (GS - 1)) == 0) reinterpret_cast<uint32_t*>(a.card_out + a.out.off_meta[C])[gsp / GS] = pair;
+  if (!live) return;                                                   // both lanes of a pair are: they belong to one row
+  uint8_t* dst = card + out.off_codes[C] + gsp * (4u * W);
+  if constexpr (W == 2) *reinterpret_cast<u32x2*>(dst) = (u32x2){codes[0], codes[1]};
+  if constexpr (W == 4) *reinterpret_cast<u32x4*>(dst) = (u32x4){codes[0], codes[1], codes[2], codes[3]};
+  if constexpr (W == 8) store_in_twos<8>(dst, codes, lane);
+  if ((lane & (GS - 1)) == 0) reinterpret_cast<uint32_t*>(card + out.off_meta[C])[gsp / GS] = pair;
 }
 
 template <int W, int G>
-__device__ __forceinline__ void relabel_store(const RequantArgs& a, const OldSpan& d, uint64_t gsp, uint32_t q, bool live) {
+__device__ __forceinline__ void relabel_store(uint8_t* card, const CardGeom& out, uint32_t cw0, uint32_t cw1, uint32_t old_pair, uint64_t gsp,
+                                              uint32_t lane, bool live) {
   uint32_t codes[W];
-  const uint32_t cw[2] = {d.cw[0], d.cw[1]};
-  const uint32_t pair = relabel_span2<W, G / 32>(cw, d.pair, codes);
-  store_span<W, G>(a, gsp, q, live, codes, pair);
+  const uint32_t cw[2] = {cw0, cw1};
+  const uint32_t pair = relabel_span2<W, G / 32>(cw, old_pair, codes);
+  store_span<W, G>(card, out, gsp, lane, live, codes, pair);
 }
 
 template <int W, int G>
-__device__ __forceinline__ void quantize_store(const RequantArgs& a, const uint32_t (&w)[16], uint64_t gsp, uint32_t q, bool live) {
+__device__ __forceinline__ void quantize_store(uint8_t* card, const CardGeom& out, const uint32_t (&w)[16], uint64_t gsp, uint32_t lane, bool live) {
   uint32_t codes[W];
   const uint32_t pair = quantize_span<W, G / 32>(w, codes);            // every lane takes part: groups span lanes
-  store_span<W, G>(a, gsp, q, live, codes, pair);
+  store_span<W, G>(card, out, gsp, lane, live, codes, pair);
 }
 
 // A round: up to 64 spans of rows list[first .. first + rows) of old class `co`.
@@ -332,7 +374,7 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
     bool done = false;
     if constexpr (C < 3) {
       if (d.co == 0u && can_relabel(o.pair)) {
-        relabel_store<(2 << C), G>(a, o, gsp, q, live);
+        relabel_store<(2 << C), G>(a.card_out, out, o.cw[0], o.cw[1], o.pair, gsp, lane, live);
         done = true;
       }
     }
@@ -346,11 +388,9 @@ __device__ __forceinline__ void requant_window(const RequantArgs& a, const CardG
         for (int j = 0; j < 16; ++j) w[j] = d.co == 3u ? o.cw[j] : 0u;
       }
       if constexpr (C < 3) {
-        quantize_store<(2 << C), G>(a, w, gsp, q, live);
+        quantize_store<(2 << C), G>(a.card_out, out, w, gsp, lane, live);
       } else if (live) {
-        u32x4* dst = reinterpret_cast<u32x4*>(a.card_out + out.off_fp16 + gsp * 64u);
-#pragma unroll
-        for (int h = 0; h < 4; ++h) dst[h] = (u32x4){w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]};
+        store_in_twos<16>(a.card_out + out.off_fp16 + gsp * 64u, w, lane);
       }
     }
     if (!more) break;
@@ -380,6 +420,229 @@ __global__ __launch_bounds__(kBlockThreads) void requant_kernel(RequantArgs a) {
   else requant_window<3, G>(a, in, k - a.windows[2], across, p0, p1, sh);
 }
 
+
+// ---- long cards of narrow rows ----
+
+// A span as it lies in the incoming card, for the kernel below: its codes (or its 32 raw values) and its pair.  2-bit codes are the first
+// half of c[0]; behind them are whatever bytes follow in the card.
+struct WideSpan {
+  u32x4 c[4];
+  uint32_t pair;
+};
+typedef u32x4 __attribute__((aligned(8))) u32x4_a8;
+
+template <int W>
+__device__ __forceinline__ void decode_wide(const WideSpan& d, uint32_t (&w)[16]) {
+  OldSpan o;
+#pragma unroll
+  for (int i = 0; i < W; ++i) o.cw[i] = d.c[i / 4][i % 4];
+  o.pair = d.pair;
+  decode_old<W>(o, w);
+}
+
+constexpr uint32_t kTokenThreads = 512, kTokenWaves = kTokenThreads / kWaveSize;
+constexpr uint32_t kTokenRows = kTokenThreads;   // rows (plane, token) that a workgroup looks up and sorts: one a thread
+constexpr uint32_t kPairs = 20;               // pairs of an old class - 0 .. 3, and 4: not placed by the incoming tables - and a new one
+constexpr uint32_t kNoRow = 31;
+
+struct TokenArgs {
+  const uint8_t* card_in;
+  uint64_t card_in_bytes;
+  uint32_t layers, kv_heads, head_dim, group_size;
+  uint64_t tokens;
+  CardGeom out;                 // the outgoing card's geometry (host-known counts)
+  uint8_t* card_out;
+  uint32_t* status;             // may be null; holds the verdict on the incoming header already (classify_kernel)
+  uint32_t rows;                // planes / group_planes * tokens
+  uint32_t group_planes;        // planes that a workgroup does one after the other, with one look-up and sort
+};
+
+struct TokenShared {
+  static constexpr uint32_t kRounds = kTokenRows * 8u / kWaveSize + kPairs;      // 8 spans a row at most
+  u32x2 list[kTokenRows];                           // row of the old class's segment, row of the new one's; sorted by pair of classes
+  uint32_t counts[kTokenWaves][32];
+  uint32_t found[kRounds];                     // rounds: pair | rows << 8 | first place in the list << 16
+  u32x4 place[kRounds / 4 + 1];                // where in the window a round's middle row is << 12 | its number
+  uint32_t rounds[kRounds];                    // the same as found, by place
+  u32x4 sections[8];                           // where the codes and the pairs of an old class begin
+  uint32_t n_old[8];
+};
+
+template <int G>
+__global__ __launch_bounds__(kTokenThreads) void requant_tokens_kernel(TokenArgs a) {
+  __shared__ TokenShared sh;
+  CardGeom in;
+  if (!card_geometry_from_header(a.card_in, a.card_in_bytes, a.layers, a.kv_heads, a.head_dim, a.group_size, a.tokens, in))
+    return;                                   // uniform over the grid
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const CardGeom& out = a.out;
+  const uint32_t spr_shift = out.lpr_shift - 2u;                       // log2(spans per row)
+  const uint32_t T = out.tokens;
+
+  if (tid == 0) {                             // a choice among the members of `in` would be loaded from scratch memory, by index
+    const auto at = [](uint64_t codes, uint64_t pairs) {
+      return (u32x4){(uint32_t)codes, (uint32_t)(codes >> 32), (uint32_t)pairs, (uint32_t)(pairs >> 32)};
+    };
+#pragma unroll
+    for (int c = 0; c < 3; ++c) sh.sections[c] = at(in.off_codes[c], in.off_meta[c]);
+    sh.sections[3] = at(in.off_fp16, in.off_fp16);
+    sh.sections[4] = at(0u, 0u);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sh.n_old[c] = in.n[c];
+    sh.n_old[4] = 0u;
+  }
+
+  // ---- look the rows up and sort them by pair of classes
+  uint32_t pair_of = kNoRow, rank;
+  u32x2 entry = {};
+  {
+    // Workgroups are dealt out strictly in turn, to the eight XCDs and to the parts of each: where a plane's windows are a multiple
+    // of that, the same tokens of all planes meet on the same compute units, and where widths go with the tokens some have all of the
+    // wide rows (16384 tokens sorted by width, 6 to 4: 511 us, with every 64 workgroups in an order of their own 343).
+    uint32_t window = blockIdx.x;
+    if ((window | 63u) < gridDim.x) window = (window & ~63u) | ((window * 21u + (window >> 6) * 13u) & 63u);
+    const uint32_t r0 = window * kTokenRows, rows = min(kTokenRows, a.rows - r0);
+    const uint32_t group0 = r0 / T, t0 = r0 - group0 * T;
+    const bool as_counted = (reinterpret_cast<const uint32_t*>(a.card_out)[48] & QKV_STATUS_BAD_COUNTS) == 0u;
+    bool bad = false;
+    if (tid < rows) {
+      uint32_t group = 0, t = t0 + tid;
+      if (T >= kTokenRows) { if (t >= T) { group = 1u; t -= T; } }
+      else { group = t / T; t -= group * T; }
+      const uint32_t plane = (group0 + group) * a.group_planes;
+      uint32_t cn, sn;
+      if (as_counted) {
+        cn = class_of(a.card_out[out.off_bits + t]);
+        sn = reinterpret_cast<const uint32_t*>(a.card_out + out.off_slot)[t];
+      } else {                                                         // rows as the caller's counts say, tokens as order[] says
+        cn = t < out.base[1] ? 0u : t < out.base[2] ? 1u : t < out.base[3] ? 2u : 3u;
+        sn = t - (cn == 0u ? out.base[0] : cn == 1u ? out.base[1] : cn == 2u ? out.base[2] : out.base[3]);
+        t = min(reinterpret_cast<const uint32_t*>(a.card_out + out.off_order)[t], T - 1u);
+      }
+      const uint32_t n_new = cn == 0u ? out.n[0] : cn == 1u ? out.n[1] : cn == 2u ? out.n[2] : out.n[3];
+      const uint32_t width = a.card_in[in.off_bits + t];
+      const uint32_t so = reinterpret_cast<const uint32_t*>(a.card_in + in.off_slot)[t];
+      const uint32_t n_old = width == 2 ? in.n[0] : width == 4 ? in.n[1] : width == 8 ? in.n[2] : width == 16 ? in.n[3] : 0u;
+      const uint32_t co = so < n_old ? class_of(width) : 4u;
+      bad = co == 4u;
+      if (sn < n_new) pair_of = co * 4u + cn;
+      entry = (u32x2){plane * n_old + so, plane * n_new + sn};
+    }
+    if (bad && a.status) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
+    uint64_t same = ~0ull;                                             // lanes with this lane's pair
+#pragma unroll
+    for (uint32_t bit = 1; bit < 32u; bit <<= 1) {
+      const uint64_t m = __builtin_amdgcn_ballot_w64((pair_of & bit) != 0u);
+      same &= (pair_of & bit) ? m : ~m;
+    }
+    rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+    if (lane < 32u) sh.counts[wave][lane] = 0u;
+    if (rank == 0u) sh.counts[wave][pair_of] = (uint32_t)__builtin_popcountll(same);
+  }
+  __syncthreads();
+  const uint32_t per_shift = 6u - spr_shift, per_round = 1u << per_shift;     // rows of a round
+  uint32_t n_rounds;
+  {
+    uint32_t total = 0, lower = 0;                                     // lane = pair: its rows in the window, and in front of this wave's
+#pragma unroll
+    for (uint32_t w = 0; w < kTokenWaves; ++w) {
+      const uint32_t n = lane < kPairs ? sh.counts[w][lane] : 0u;
+      total += n;
+      lower += w < wave ? n : 0u;
+    }
+    const uint32_t start = wave_inclusive_scan(total) - total;         // first place in the list
+    const uint32_t own = (total + per_round - 1u) >> per_shift;
+    const uint32_t inc = wave_inclusive_scan(own);
+    n_rounds = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    if (wave == 0 && lane < 4u) reinterpret_cast<uint32_t*>(sh.place)[n_rounds + lane] = ~0u;
+    const int from = (int)(pair_of * 4u);
+    const uint32_t first = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)start);
+    const uint32_t rel = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)lower) + rank;
+    const uint32_t info = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)((inc - own) | (total << 16)));
+    if (pair_of < kPairs) {
+      const uint32_t begin = rel & ~(per_round - 1u), rows = min(per_round, (info >> 16) - begin);
+      sh.list[first + rel] = entry;
+      if (rel == begin + rows / 2u) {
+        const uint32_t r = (info & 0xFFFFu) + (rel >> per_shift);
+        sh.found[r] = pair_of | (rows << 8) | ((first + begin) << 16);
+        reinterpret_cast<uint32_t*>(sh.place)[r] = (tid << 12) | r;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < n_rounds) {
+    const uint32_t mine = reinterpret_cast<const uint32_t*>(sh.place)[tid];
+    uint32_t before = 0;
+    for (uint32_t j = 0; j < (n_rounds + 3u) / 4u; ++j) {
+      const u32x4 p = sh.place[j];
+      before += (uint32_t)(p.x < mine) + (uint32_t)(p.y < mine) + (uint32_t)(p.z < mine) + (uint32_t)(p.w < mine);
+    }
+    sh.rounds[before] = sh.found[tid];
+  }
+  __syncthreads();
+  if (n_rounds == 0u) return;                                          // only where the caller's counts are wrong
+
+  const uint32_t q = lane & ((1u << spr_shift) - 1u), row_of_lane = lane >> spr_shift;
+  uint32_t r = wave, p = 0;
+  while (r >= n_rounds) { r -= n_rounds; ++p; }
+  if (p >= a.group_planes) return;
+  uint32_t d, row_out;
+  WideSpan o = {};
+  const auto fetch = [&]() {
+    d = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.rounds[r]);
+    const u32x2 e = sh.list[(d >> 16) + min(row_of_lane, ((d >> 8) & 255u) - 1u)];   // lanes past the round's rows repeat its last one
+    const uint32_t co = (d >> 2) & 7u, cn = d & 3u;
+    row_out = e.y + p * (cn == 0u ? out.n[0] : cn == 1u ? out.n[1] : cn == 2u ? out.n[2] : out.n[3]);
+    // One sequence of loads for all classes, each into registers of its own: out of branches that load into the same ones they
+    // came with copies behind each, and waits in front of the copies.  Raw rows have no pair and load their own start in its place; rows
+    // that the incoming tables don't place load the card's.
+    const uint64_t gsp = co < 4u ? ((uint64_t)(e.x + p * sh.n_old[co]) << spr_shift) + q : 0u;
+    const u32x4 at = sh.sections[co];
+    const uint64_t codes = (uint64_t)at.x | (uint64_t)at.y << 32, meta = (uint64_t)at.z | (uint64_t)at.w << 32;
+    const uint8_t* src = a.card_in + codes + (gsp << (3u + co));
+    o.c[0] = *reinterpret_cast<const u32x4_a8*>(src);
+    o.pair = *reinterpret_cast<const uint32_t*>(co < 3u ? a.card_in + meta + gsp / (G / 32) * 4u : src);
+    if (co >= 2u) o.c[1] = reinterpret_cast<const u32x4*>(src)[1];
+    if (co == 3u) {
+      o.c[2] = reinterpret_cast<const u32x4*>(src)[2];
+      o.c[3] = reinterpret_cast<const u32x4*>(src)[3];
+    }
+  };
+  fetch();
+  while (true) {
+    const uint32_t co = (d >> 2) & 7u, cn = d & 3u;
+    const bool live = row_of_lane < ((d >> 8) & 255u);
+    const uint64_t gsp = ((uint64_t)row_out << spr_shift) + q;
+    const bool relabel = co == 0u && cn != 3u && can_relabel(o.pair);
+    uint32_t w[16];
+    if (relabel) { w[0] = o.c[0].x; w[1] = o.c[0].y; w[2] = o.pair; }
+    else if (co == 0u) decode_wide<2>(o, w);
+    else if (co == 1u) decode_wide<4>(o, w);
+    else if (co == 2u) decode_wide<8>(o, w);
+    else {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) w[j] = co == 3u ? o.c[j / 4][j % 4] : 0u;
+    }
+    // The next round's loads go to the registers that this round's came to, once it is decoded: copies of them, with the loads
+    // in front of the decoding, were a fifth of the loop's vector instructions.
+    r += kTokenWaves;
+    while (r >= n_rounds) { r -= n_rounds; ++p; }
+    const bool more = p < a.group_planes;
+    if (more) fetch();
+    if (relabel) {
+      if (cn == 0u) relabel_store<2, G>(a.card_out, out, w[0], w[1], w[2], gsp, lane, live);
+      else if (cn == 1u) relabel_store<4, G>(a.card_out, out, w[0], w[1], w[2], gsp, lane, live);
+      else relabel_store<8, G>(a.card_out, out, w[0], w[1], w[2], gsp, lane, live);
+    }
+    else if (cn == 0u) quantize_store<2, G>(a.card_out, out, w, gsp, lane, live);
+    else if (cn == 1u) quantize_store<4, G>(a.card_out, out, w, gsp, lane, live);
+    else if (cn == 2u) quantize_store<8, G>(a.card_out, out, w, gsp, lane, live);
+    else if (live) store_in_twos<16>(a.card_out + out.off_fp16 + gsp * 64u, w, lane);
+    if (!more) break;
+  }
+}
+
 }  // namespace
 
 hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const CardGeom& out, uint8_t* card_out,
@@ -402,6 +665,33 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
   // values 700 tokens 122 and 131.  64 planes of 6000 tokens 23.1 and 21.0, 16 of 32768 27.0 and 27.1.  Smaller windows
   // while there are few: 200 tokens, 6 to 4, 11.6 with 128 rows and 12.1 with 256, 64 tokens 7.4 with 64 rows and 8.0 with 128.
   const uint64_t rows = (uint64_t)out.planes * out.tokens;
+  const uint64_t values = rows * out.head_dim;
+  // Long cards: the windows of tokens, unless a head has 64 dimensions (windows of half the bytes, and as many rounds that are not
+  // full) or rows are wide (whole lines that nobody else reads: nothing to gain).  Whole call, us, with windows of a width and of tokens:
+  // 512 planes of 128 values, 1500 tokens, 3 to 2.5 33.7 and 35.3, 2000 43.4 and 41.8, 6 to 4 62.4 and 59.7, 16000 410 and 371;
+  // 256 planes of 256 values, 1500 tokens, 6 to 4 46.6 and 46.2, 2000 58.9 and 57.2, 16000 395 and 356; 512 of 64, 5000 tokens, 6 to 4
+  // 85.1 and 85.9, 16000, 8 to 5, 253 and 267; 512 of 128, 16384 tokens, 16 to 4 541 and 567, 8 to 8 568 and 588, 8 to 6 511 and 498.
+  if (out.head_dim >= 128u && values >= 131072000ull && 2u * card_in_bytes <= 3u * values && out.total <= values) {
+    TokenArgs t;
+    t.card_in = card_in; t.card_in_bytes = card_in_bytes;
+    t.layers = out.layers; t.kv_heads = out.kv_heads; t.head_dim = out.head_dim; t.group_size = out.group_size;
+    t.tokens = out.tokens;
+    t.out = out;
+    t.card_out = card_out;
+    t.status = status;
+    // Two planes with one look-up and sort while the cards sit in the memory-side cache; larger ones want the planes that are worked on at a
+    // time to be neighbours (8192 tokens, 3 to 2.5: 151 us with one plane and 138 with two; 5 to 3 172 and 178; 32768, 6 to 4: 745 and 790).
+    // A card has an even number of planes, and a grid fewer than 2^32 threads.
+    t.group_planes = card_in_bytes + out.total <= kCacheResidentCardBytes || rows >= (1ull << 31) ? 2u : 1u;
+    t.rows = out.planes / t.group_planes * out.tokens;
+    const dim3 grid((t.rows + kTokenRows - 1u) / kTokenRows), block(kTokenThreads);
+    switch (out.group_size) {
+      case 32: hipLaunchKernelGGL(requant_tokens_kernel<32>, grid, block, 0, stream, t); break;
+      case 64: hipLaunchKernelGGL(requant_tokens_kernel<64>, grid, block, 0, stream, t); break;
+      default: hipLaunchKernelGGL(requant_tokens_kernel<128>, grid, block, 0, stream, t); break;
+    }
+    return hipGetLastError();
+  }
   const bool cached = card_in_bytes + out.total <= (192ull << 20);
   const bool across = rows < 1536u * kWindow || (cached ? out.tokens < 1536u : (uint64_t)out.tokens * out.head_dim < 900u * 128u);
   a.window = !across || rows > 512u * kWindow ? kWindow : rows > 128u * kWindow ? kWindow / 2u : kWindow / 4u;

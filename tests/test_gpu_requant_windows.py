@@ -134,3 +134,49 @@ def test_two_bit_groups_of_any_content(kind, G):
     card[off["meta2"]:off["meta2"] + 4 * n_pairs] = np.stack([scale, zeros], axis=1).reshape(-1).view(np.uint8)
     for width in (2, 4, 8, 16):
         hop(card, rd, np.full(T, width, np.uint8), "2-bit, %s, G=%d to %d bits" % (kind, G, width))
+
+
+@pytest.mark.parametrize("L,H,T,D,G,order", [(32, 8, 2001, 128, 32, "drawn"), (32, 8, 2048, 128, 64, "sorted"), (16, 8, 2049, 256, 128, "drawn"),
+                                             (16, 8, 2100, 256, 32, "sorted"), (1, 1, 512003, 128, 128, "drawn"), (1024, 5, 101, 128, 32, "drawn"),
+                                             (64, 1, 8191, 128, 32, "one width")])
+def test_windows_of_tokens(L, H, T, D, G, order):
+    """At least 131072000 values of 128 or 256 dimensions: windows of 512 rows inside a plane, across the ends of planes and over many
+    short ones, against injection and creation on the GPU; with an entry of the incoming tables out of range the token's rows are
+    those of zeros, and with counts that are not those of the widths the card is what creation makes of the same counts."""
+    assert 2 * L * H * T * D >= 131072000 and D >= 128
+    print("[case] windows of tokens L=%d H=%d T=%d D=%d G=%d %s" % (L, H, T, D, G, order), flush=True)
+    rng = np.random.default_rng(T)
+    a, b = draw_bits(T, rng, [0.4, 0.3, 0.2, 0.1]), draw_bits(T, rng, [0.62, 0.26, 0.08, 0.04])
+    if order == "sorted":
+        a = np.sort(a)
+    if order == "one width":
+        a[:] = 4
+    ca, cb = ref.count_bits(a).tolist(), ref.count_bits(b).tolist()
+    a, b = torch.from_numpy(a).to(DEV), torch.from_numpy(b).to(DEV)
+    desc = qkv.Desc.make(L, H, T, D, G)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T)
+    k = torch.randn((L, H, T, D), dtype=torch.float16, device=DEV, generator=g)
+    v = torch.randn((L, H, T, D), dtype=torch.float16, device=DEV, generator=g)
+    card = torch.empty(qkv.card_bytes(desc, ca), dtype=torch.uint8, device=DEV)
+    qkv.quantize_pack(desc, k, v, a, ca, card)
+    qkv.unpack_dequant(card, desc, k, v)
+    status = torch.full((1,), 0x7777, dtype=torch.int32, device=DEV)
+
+    def compare(counts, want_status):
+        out = torch.full((qkv.card_bytes(desc, counts),), 0xA5, dtype=torch.uint8, device=DEV)
+        want = torch.full_like(out, 0xA5)
+        qkv.quantize_pack(desc, k, v, b, counts, want)
+        qkv.requantize(card, desc, b, counts, out, status=status)
+        assert int(status.item()) == want_status
+        assert torch.equal(out, want)
+
+    compare(cb, 0)
+    wrong = list(cb)
+    wrong[0], wrong[1] = wrong[0] - 3, wrong[1] + 3
+    compare(wrong, 0)
+    off = ref.card_offsets(ref.make_desc(L, H, T, D, G), ca)
+    lost = T // 2
+    card[off["slot"]:off["slot"] + 4 * T].view(torch.int32)[lost] = 1 << 30
+    k[:, :, lost], v[:, :, lost] = 0, 0
+    compare(cb, qkv.STATUS_BAD_ORDER)
