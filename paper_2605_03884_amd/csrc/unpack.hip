@@ -123,16 +123,28 @@ __device__ inline void report_status(const uint8_t* card, const CardGeom& g, boo
   }
 }
 
+// Plane and row within it of row `lane` of a tile that starts at row r0 of a segment with n rows a plane.  r0 is uniform, and so is its
+// division; the lane's own is a comparison where a tile has no more rows than a plane, a division a lane only in the shortest cards.
+__device__ inline void plane_and_row(uint32_t r0, uint32_t n, uint32_t lane, uint32_t tile_rows, uint32_t& p, uint32_t& j) {
+  p = r0 / n;
+  j = r0 - p * n + lane;
+  if (n >= tile_rows) {
+    if (j >= n) { j -= n; ++p; }
+  } else {
+    const uint32_t more = j / n;
+    p += more;
+    j -= more * n;
+  }
+}
+
 // Address of the output row that row `lane` of the tile starting at segment row r0 goes to;
 // 0 for rows past the segment's end and for corrupt order[] entries.
 __device__ inline uint64_t tile_row_address(const UnpackArgs& a, const CardGeom& g, int c, uint32_t r0, uint32_t n_rows,
                                             uint32_t lane, uint32_t tile_rows, uint32_t& bad) {
   uint64_t addr = 0;
-  const uint32_t r = r0 + lane;
-  if (lane < tile_rows && r < n_rows) {
-    const uint32_t n = g.n[c];
-    const uint32_t p = r / n;
-    const uint32_t j = r - p * n;
+  if (lane < tile_rows && r0 + lane < n_rows) {
+    uint32_t p, j;
+    plane_and_row(r0, g.n[c], lane, tile_rows, p, j);
     const uint32_t t = reinterpret_cast<const uint32_t*>(a.card + g.off_order)[g.base[c] + j];
     const uint32_t lh = g.planes >> 1;
     const uint32_t row_bytes = g.head_dim * 2u;
@@ -185,11 +197,11 @@ __device__ inline void store_tile(uint64_t my_row_addr, uint32_t lane, uint32_t 
 // Decodes the tile of class c that starts at segment row r0 (rows at or past n_rows are skipped) and stores
 // it to the row addresses that row_address() gives (lane i: row r0 + i).  ROPE: rotate every row with `rope`.
 // The addresses take two dependent trips to the tables, so the tile's own loads are issued before them (one layer
-// of 3877 tokens, keys realigned: 10.1 us with the addresses first, 8.4 us; all tiles' rows of 8K tokens injected without
+// of 3877 tokens, keys realigned, in the former order of the tiles: 10.1 us with the addresses first, 8.4 us; all tiles' rows of 8K tokens injected without
 // realignment: 281 and 269 us) - except with rows_first, where the card streams and the wider loads in flight only crowd the
 // writes out: raw rows of a uniform card too large to stay in cache (8K tokens of 16 bits: 378 us with the addresses first,
-// 386), uniform cards injected into more layers than a call for few takes (8K of 8 bits 285 and 301, of 4 bits 235 and 249; 32K of
-// 4 bits 985 and 1045), and cards of 4 and 8 bits with keys per channel from 512 MB of cache on
+// 386), uniform cards of 4 and 8 bits injected into more layers than a call for few takes (8K of 8 bits 285 and 301, of 4 bits 235 and 249; 32K of
+// 4 bits 985 and 1045; of 2 bits the other way round, 8K 232 and 215), and cards of 4 and 8 bits with keys per channel from 512 MB of cache on
 // (32K tokens of 4 bits, 941 and 1026; below, 64 planes of 8K tokens of 8 bits, 66.9 and 63.6), key tiles that are rotated
 // apart (32K of 4 bits 1164 and 1077).
 template <int W, int G, bool KEEP, bool ROPE, typename ROWS>
@@ -312,21 +324,29 @@ __device__ inline void unpack_tile_kc(const uint8_t* card, const CardGeom& g, in
   store_tile(my_row, lane, lpr_shift, data);
 }
 
-template <bool KEEP, bool ROPE, typename ROWS>
+// FEW: in a grid of half a chip, as a call for few layers has it, the loads are taken one by one behind a test each, in large ones without; raw
+// rows of a uniform card, where everything in flight is loads and stores of whole rows, in two halves.  (32 calls, a layer of 3877 tokens each,
+// 16 bits, realigned: 265 us before, 281 without tests, 249 with; 8 bits on average 259, 251 and 246.  All of 8K tokens of 16 bits injected
+// in a call 371 us before, 377 at once, 350 in halves; 32K tokens at 4 bits on average unpacked 986 with tests, 970 without.)
+template <bool KEEP, bool ROPE, bool FEW, typename ROWS>
 __device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_t r0, uint32_t n_rows, const ROWS& row_address,
                                  bool rows_first, uint32_t lane, const RopeLane& rope) {
   const uint32_t lpr_shift = g.lpr_shift;
   const uint32_t row_bytes = g.head_dim * 2u;
   const uint8_t* src = card + g.off_fp16 + (uint64_t)r0 * row_bytes;
-  const uint64_t seg_left = ((uint64_t)n_rows - r0) * row_bytes;   // bytes from the tile start to the segment end
+  const uint32_t last = min(n_rows - r0, (uint32_t)kTileChunks >> lpr_shift) * row_bytes - 16u;   // where the tile's last chunk begins
   uint64_t my_row = 0;
   if (rows_first) my_row = row_address();
-  u32x4 data[kTileIters];
+  u32x4 data[kTileIters] = {};
 #pragma unroll
   for (int k = 0; k < kTileIters; ++k) {
-    const uint64_t off = (uint64_t)(k * kWaveSize + lane) * 16u;
-    data[k] = (u32x4)(0u);
-    if (off < seg_left) data[k] = card_load<KEEP>(reinterpret_cast<const u32x4*>(src + off));
+    const uint32_t off = (uint32_t)(k * kWaveSize + lane) * 16u;
+    if constexpr (FEW) {
+      if (off <= last) data[k] = card_load<KEEP>(reinterpret_cast<const u32x4*>(src + off));
+    } else {
+      data[k] = card_load<KEEP>(reinterpret_cast<const u32x4*>(src + min(off, last)));               // past it: that once more, no row is theirs
+      if (k == 3 && g.n[3] == g.tokens) asm volatile("" :: "v"(data[0]), "v"(data[1]), "v"(data[2]), "v"(data[3]));
+    }
   }
   if (!rows_first) my_row = row_address();
   if (ROPE) {
@@ -349,30 +369,29 @@ __global__ void unpack_status_kernel(UnpackArgs a) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *a.status = ok ? 0u : QKV_STATUS_BAD_HEADER;
 }
 
-// The tiles of width class C, dealt to the waves round-robin from the segment's end, continuing where
-// the previous class stopped.
+// Tile k of width class C, from the segment's end.  False, and k lowered by the class's tiles, if there are fewer: the grid has a wave for
+// every tile, whatever the split of the tokens.
 template <int C, int G, bool KEEP, bool KC>
-__device__ inline void unpack_class(const UnpackArgs& a, const CardGeom& g, uint32_t gw, uint32_t n_waves, uint32_t lane,
-                                    u32x4* lds, uint32_t& cum, uint32_t& bad) {
+__device__ inline bool unpack_class(const UnpackArgs& a, const CardGeom& g, uint32_t& k, uint32_t lane, u32x4* lds, uint32_t& bad) {
   const uint32_t n_rows = g.planes * g.n[C];
-  if (n_rows == 0) return;
   const uint32_t tile_rows = kTileChunks >> g.lpr_shift;
   const uint32_t tiles = (n_rows + tile_rows - 1) / tile_rows;
-  const uint32_t first = (gw + n_waves - cum) % n_waves;
-  const RopeLane no_rope = {};
-  for (uint32_t i = first; i < tiles; i += n_waves) {
-    const uint32_t r0 = (tiles - 1 - i) * tile_rows;
-    const auto my_row = [&] { return tile_row_address(a, g, C, r0, n_rows, lane, tile_rows, bad); };
-    if constexpr (C == 3) {
-      copy_tile<KEEP, false>(a.card, g, r0, n_rows, my_row, true, lane, no_rope);
-    } else {
-      constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
-      const bool rows_first = KC && C >= 1 && a.rows_first != 0u;
-      if (KC && r0 < (n_rows >> 1)) unpack_tile_kc<W, KEEP, false>(a.card, g, C, r0, n_rows >> 1, my_row, rows_first, lane, lds, no_rope);   // key rows
-      else unpack_tile<W, G, KEEP, false>(a.card, g, C, r0, n_rows, my_row, rows_first, lane, lds, no_rope);
-    }
+  if (k >= tiles) {
+    k -= tiles;
+    return false;
   }
-  cum = (cum + tiles) % n_waves;
+  const RopeLane no_rope = {};
+  const uint32_t r0 = (tiles - 1 - k) * tile_rows;
+  const auto my_row = [&] { return tile_row_address(a, g, C, r0, n_rows, lane, tile_rows, bad); };
+  if constexpr (C == 3) {
+    copy_tile<KEEP, false, false>(a.card, g, r0, n_rows, my_row, true, lane, no_rope);
+  } else {
+    constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
+    const bool rows_first = KC && C >= 1 && a.rows_first != 0u;
+    if (KC && r0 < (n_rows >> 1)) unpack_tile_kc<W, KEEP, false>(a.card, g, C, r0, n_rows >> 1, my_row, rows_first, lane, lds, no_rope);   // key rows
+    else unpack_tile<W, G, KEEP, false>(a.card, g, C, r0, n_rows, my_row, rows_first, lane, lds, no_rope);
+  }
+  return true;
 }
 
 // KC: a uniform card whose key planes (the first half of every segment) are grouped per channel.
@@ -392,10 +411,10 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = threadIdx.x >> 6;
   const uint32_t gw = (blockIdx.x - a.check_blocks) * kWavesPerBlock + wave;
-  const uint32_t n_waves = (gridDim.x - a.check_blocks) * kWavesPerBlock;
   u32x4* my_lds = lds[wave];
 
   uint32_t bad = 0;
+  uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane((int)gw);
   if (!KC) {
     // Plane by plane, from the last plane to the first; inside a plane the raw rows' tiles first, the 2-bit rows'
     // last, each width from its last tile down - the card is still walked from its end, which is what the memory-
@@ -410,16 +429,15 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
     const uint32_t tp0 = (g.n[0] + tile_rows - 1) / tile_rows, tp1 = (g.n[1] + tile_rows - 1) / tile_rows,
                    tp2 = (g.n[2] + tile_rows - 1) / tile_rows, tp3 = (g.n[3] + tile_rows - 1) / tile_rows;
     const uint32_t per_plane = tp0 + tp1 + tp2 + tp3;
-    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)gw);
-    const uint32_t pr = s / per_plane;
+    const uint32_t pr = k / per_plane;
     if (pr >= g.planes) return;
     const uint32_t p = g.planes - 1u - pr;
-    uint32_t k = s - pr * per_plane;
+    k -= pr * per_plane;
     const RopeLane no_rope = {};
     if (k < tp3) {
       const uint32_t r0 = p * g.n[3] + (tp3 - 1u - k) * tile_rows, end = (p + 1u) * g.n[3];
       const auto my_row = [&] { return tile_row_address(a, g, 3, r0, end, lane, tile_rows, bad); };
-      copy_tile<KEEP, false>(a.card, g, r0, end, my_row, !KEEP && g.n[3] == g.tokens, lane, no_rope);
+      copy_tile<KEEP, false, false>(a.card, g, r0, end, my_row, !KEEP && g.n[3] == g.tokens, lane, no_rope);
     } else if ((k -= tp3) < tp2) {
       const uint32_t r0 = p * g.n[2] + (tp2 - 1u - k) * tile_rows, end = (p + 1u) * g.n[2];
       const auto my_row = [&] { return tile_row_address(a, g, 2, r0, end, lane, tile_rows, bad); };
@@ -440,11 +458,8 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
   // The card is walked from its end to its start: right after packing, its tail is what the
   // 256 MB memory-side cache still holds (a card of 302 MB unpacks in 212 us this way, 264 us
   // front to back; cards that fit, or that are several times larger, are indifferent).
-  uint32_t cum = 0;
-  unpack_class<3, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
-  unpack_class<2, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
-  unpack_class<1, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
-  unpack_class<0, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
+  (void)(unpack_class<3, G, KEEP, KC>(a, g, k, lane, my_lds, bad) || unpack_class<2, G, KEEP, KC>(a, g, k, lane, my_lds, bad) ||
+         unpack_class<1, G, KEEP, KC>(a, g, k, lane, my_lds, bad) || unpack_class<0, G, KEEP, KC>(a, g, k, lane, my_lds, bad));
   if (bad && a.status && a.check_blocks == 0u) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
 }
 
@@ -454,11 +469,8 @@ template <typename ARGS>
 __device__ inline uint64_t inject_row_address(const ARGS& a, const CardGeom& g, int c, uint32_t kv, uint32_t r0,
                                               uint32_t seg_hi, uint32_t lane, uint32_t tile_rows, uint32_t& bad) {
   uint64_t addr = 0;
-  const uint32_t r = r0 + lane;
-  if (lane < tile_rows && r < seg_hi) {
-    const uint32_t n = g.n[c];
-    const uint32_t p = r / n;
-    const uint32_t j = r - p * n;
+  if (lane < tile_rows && r0 + lane < seg_hi) {
+    const uint32_t p = (r0 + lane) / g.n[c], j = r0 + lane - p * g.n[c];
     const uint32_t t = reinterpret_cast<const uint32_t*>(a.card + g.off_order)[g.base[c] + j];
     const uint32_t pl = p - kv * (g.planes >> 1);
     const uint32_t layer = pl / a.kv_heads;
@@ -473,34 +485,34 @@ __device__ inline uint64_t inject_row_address(const ARGS& a, const CardGeom& g, 
   return addr;
 }
 
-// One (class, K or V) range of the card's rows for the layer range: its tiles are dealt to the
-// waves round-robin, continuing where the previous range stopped.  (K and V as separate
-// instances of this code measure faster than one instance looping over both.)
+// Tile k of one (class, K or V) range of the card's rows for the layer range.  False, and k lowered by the range's tiles, if there are
+// fewer: the grid has a wave for every tile, whatever the split of the tokens.  (With the tiles dealt round-robin over the grid, two
+// remainders a range stood in front of the first load, 750 dependent instructions for the rows of 2 bits.  K and V as separate
+// instances of this code measure faster than one instance for both.)
 template <int C, int KV, int G, bool KEEP, bool ROPE, bool KC, typename ARGS>
-__device__ inline void inject_range(const ARGS& a, const CardGeom& g, const RopeLane& rope, uint32_t gw,
-                                    uint32_t n_waves, uint32_t lane, u32x4* lds, uint32_t& cum, uint32_t& bad) {
+__device__ inline bool inject_range(const ARGS& a, const CardGeom& g, const RopeLane& rope, uint32_t& k, uint32_t lane, u32x4* lds, uint32_t& bad) {
   const uint32_t n = g.n[C];
-  if (n == 0) return;
   const uint32_t tile_rows = kTileChunks >> g.lpr_shift;
   const uint32_t seg_lo = ((uint32_t)KV * (g.planes >> 1) + a.layer_begin * a.kv_heads) * n;
   const uint32_t seg_rows = a.layer_count * a.kv_heads * n;
   const uint32_t seg_hi = seg_lo + seg_rows;
   const uint32_t tiles = (seg_rows + tile_rows - 1) / tile_rows;
+  if (k >= tiles) {
+    k -= tiles;
+    return false;
+  }
   constexpr bool rot = KV == 0 && ROPE;            // only keys depend on the position
   constexpr bool many = ARGS::kLayers > kFewLayers;
-  const uint32_t first = (gw + n_waves - cum) % n_waves;
-  for (uint32_t i = first; i < tiles; i += n_waves) {
-    const uint32_t r0 = seg_lo + (tiles - 1 - i) * tile_rows;
-    const auto my_row = [&] { return inject_row_address(a, g, C, (uint32_t)KV, r0, seg_hi, lane, tile_rows, bad); };
-    if (C == 3) {
-      copy_tile<KEEP, rot>(a.card, g, r0, seg_hi, my_row, !KEEP && n == g.tokens, lane, rope);
-    } else {
-      constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
-      if (KC && KV == 0) unpack_tile_kc<W, KEEP, rot>(a.card, g, C, r0, (g.planes >> 1) * n, my_row, many && C >= 1 && !rot, lane, lds, rope);
-      else unpack_tile<W, G, KEEP, rot>(a.card, g, C, r0, seg_hi, my_row, many && n == g.tokens, lane, lds, rope);
-    }
+  const uint32_t r0 = seg_lo + (tiles - 1 - k) * tile_rows;
+  const auto my_row = [&] { return inject_row_address(a, g, C, (uint32_t)KV, r0, seg_hi, lane, tile_rows, bad); };
+  if (C == 3) {
+    copy_tile<KEEP, rot, !many>(a.card, g, r0, seg_hi, my_row, !KEEP && n == g.tokens, lane, rope);
+  } else {
+    constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
+    if (KC && KV == 0) unpack_tile_kc<W, KEEP, rot>(a.card, g, C, r0, (g.planes >> 1) * n, my_row, many && C >= 1 && !rot, lane, lds, rope);
+    else unpack_tile<W, G, KEEP, rot>(a.card, g, C, r0, seg_hi, my_row, many && n == g.tokens && C >= 1, lane, lds, rope);
   }
-  cum = (cum + tiles) % n_waves;
+  return true;
 }
 
 template <int G, bool KEEP, bool ROPE, bool KC, bool FEW>
@@ -518,8 +530,7 @@ __global__ __launch_bounds__(kBlockThreads, ROPE && !KC ? 4 : 1) void inject_ker
   if (!shape_ok) return;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = threadIdx.x >> 6;
-  const uint32_t gw = (blockIdx.x - a.check_blocks) * kWavesPerBlock + wave;
-  const uint32_t n_waves = (gridDim.x - a.check_blocks) * kWavesPerBlock;
+  uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane((int)((blockIdx.x - a.check_blocks) * kWavesPerBlock + wave));
   u32x4* my_lds = lds[wave];
 
   // chunk 64 k + lane of a tile is chunk (lane mod chunks-per-row) of its row, whatever k
@@ -535,15 +546,11 @@ __global__ __launch_bounds__(kBlockThreads, ROPE && !KC ? 4 : 1) void inject_ker
   }
 
   // from the card's end to its start, as the dense kernel does
-  uint32_t bad = 0, cum = 0;
-  inject_range<3, 1, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
-  inject_range<3, 0, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
-  inject_range<2, 1, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
-  inject_range<2, 0, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
-  inject_range<1, 1, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
-  inject_range<1, 0, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
-  inject_range<0, 1, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
-  inject_range<0, 0, G, KEEP, ROPE, KC>(a, g, rope, gw, n_waves, lane, my_lds, cum, bad);
+  uint32_t bad = 0;
+  (void)(inject_range<3, 1, G, KEEP, ROPE, KC>(a, g, rope, k, lane, my_lds, bad) || inject_range<3, 0, G, KEEP, ROPE, KC>(a, g, rope, k, lane, my_lds, bad) ||
+         inject_range<2, 1, G, KEEP, ROPE, KC>(a, g, rope, k, lane, my_lds, bad) || inject_range<2, 0, G, KEEP, ROPE, KC>(a, g, rope, k, lane, my_lds, bad) ||
+         inject_range<1, 1, G, KEEP, ROPE, KC>(a, g, rope, k, lane, my_lds, bad) || inject_range<1, 0, G, KEEP, ROPE, KC>(a, g, rope, k, lane, my_lds, bad) ||
+         inject_range<0, 1, G, KEEP, ROPE, KC>(a, g, rope, k, lane, my_lds, bad) || inject_range<0, 0, G, KEEP, ROPE, KC>(a, g, rope, k, lane, my_lds, bad));
   if (bad && a.status && a.check_blocks == 0u) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
 }
 
