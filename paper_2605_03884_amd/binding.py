@@ -71,6 +71,13 @@ class Inject(ctypes.Structure):
     ]
 
 
+class _InjectByAddress(ctypes.Structure):
+    """qkv_inject_t with the tables' addresses as numbers."""
+    _fields_ = [(name, ctypes.c_size_t if name in ("k_layers", "v_layers") else kind) for name, kind in Inject._fields_]
+
+
+_pointer_tables = [ctypes.c_void_p * (2 * count) for count in range(5)]
+
 _lib = None
 
 
@@ -117,7 +124,7 @@ def lib():
     L.qkv_card_fill.restype = ctypes.c_int
     L.qkv_card_fill.argtypes = [ctypes.POINTER(Desc), vp, vp, i64p, vp, ctypes.c_uint64, vp]
     L.qkv_inject_layers.restype = ctypes.c_int
-    L.qkv_inject_layers.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(Desc), ctypes.POINTER(Inject), vp, vp]
+    L.qkv_inject_layers.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(Desc), vp, vp, vp]           # Inject or _InjectByAddress
     L.qkv_quantize_pack_kc.restype = ctypes.c_int
     L.qkv_quantize_pack_kc.argtypes = [ctypes.POINTER(Desc), vp, vp, vp, i64p, vp, ctypes.c_uint64, vp]
     L.qkv_unpack_dequant_kc.restype = ctypes.c_int
@@ -158,9 +165,11 @@ def _counts(counts):
     return _Counts(*map(int, counts))
 
 
-# The current stream's handle without the object torch.cuda.current_stream() builds (2.9 us of a call's 8).  Not part of
-# torch's public interface: where a torch lacks it, the object is asked.
+# The current stream's handle without the object torch.cuda.current_stream() builds (2.9 us of a call's 8), and the current device without
+# torch.cuda.current_device()'s look whether CUDA is set up (0.2 us), which the tensors of a call have seen to.  Not part of
+# torch's public interface: where a torch lacks them, the public calls are made.
 _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 
 
 def _stream(stream):
@@ -168,7 +177,7 @@ def _stream(stream):
     if stream is None:
         if _current_raw_stream is None:
             return torch.cuda.current_stream().cuda_stream
-        return _current_raw_stream(torch.cuda.current_device())
+        return _current_raw_stream(_current_device())
     return stream.cuda_stream
 
 
@@ -347,25 +356,28 @@ def inject_layers(card, expect, k_layers, v_layers, layer_begin=0, rope_base=0.0
     count = len(k_layers)
     if count != len(v_layers) or count < 1:
         raise ValueError("k_layers and v_layers must be lists of the same, non-zero length")
-    ref_strides = k_layers[0].stride()
-    heads, tokens, dim = expect.kv_heads, expect.tokens, expect.head_dim
+    strides = k_layers[0].stride()
+    heads, tokens, dim, half = expect.kv_heads, expect.tokens, expect.head_dim, torch.float16
     pointers = []
     for tensors in (k_layers, v_layers):
         for t in tensors:
             shape = t.shape
-            if not t.is_cuda or t.dtype != torch.float16 or len(shape) != 3:
+            if t.dtype is not half or len(shape) != 3 or not t.is_cuda:
                 raise ValueError("layer tensors must be device float16 [kv_heads, tokens, head_dim]")
             if shape[0] != heads or shape[1] < tokens or shape[2] != dim:
                 raise ValueError("layer tensor shape %s does not hold the card's tokens" % (tuple(shape),))
-            if t.stride() != ref_strides or ref_strides[2] != 1:
+            if t.stride() != strides or strides[2] != 1:
                 raise ValueError("layer tensors must share their strides and have contiguous rows")
             pointers.append(t.data_ptr())
-    table = ctypes.c_void_p * count
-    where = Inject(int(layer_begin), count, table(*pointers[:count]), table(*pointers[count:]),
-                   ref_strides[0], ref_strides[1], float(rope_base), int(rope_delta), 1 if keys_per_channel else 0, 0)
-    sp = _optional_ptr(status, None, "status")
-    _check(lib().qkv_inject_layers(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect), ctypes.byref(where),
-                                   sp, _stream(stream)), "qkv_inject_layers")
+    # One table for both, and its address as a number: a receiver makes this call once a layer, and with two arrays behind
+    # pointer fields the arguments alone took 0.8 us.
+    table = _pointer_tables[count](*pointers) if count < len(_pointer_tables) else (ctypes.c_void_p * (2 * count))(*pointers)
+    at = ctypes.addressof(table)
+    where = _InjectByAddress(int(layer_begin), count, at, at + 8 * count, strides[0], strides[1], float(rope_base), int(rope_delta),
+                             1 if keys_per_channel else 0, 0)
+    _check((_lib or lib()).qkv_inject_layers(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect), ctypes.byref(where),
+                                             None if status is None else _dev_ptr(status, None, "status"), _stream(stream)),
+           "qkv_inject_layers")
 
 
 def card_attend_workspace(expect, q_heads):
