@@ -74,13 +74,14 @@ __global__ __launch_bounds__(256) void controller_kernel(const float* __restrict
 
 // ---- the greedy allocator -----------------------------------------------------------------------
 //
-// Up to 32768 tokens one workgroup does it in one launch, thread i owning KPT consecutive tokens whose scores stay in
-// registers (KPT = 2, 8, 16, 32: a short sequence runs short code).  Three passes over the keys: 12, 10 and 10 bits; every
+// Up to 32768 tokens one workgroup does it in one launch, a thread owning runs of four neighbouring tokens, the next run 256 tokens
+// on, whose scores stay in registers (KPT = 2, 8, 16, 32: a short sequence runs short code).  Three passes over the keys: 12, 10 and 10 bits; every
 // thread holds its buckets' sums and a workgroup-wide prefix finds the bucket, and the last pass counts the levels
-// apart, so that the sweep that ranks equal keys by token is only made when a level is admitted in part.  Bound by
-// instruction issue and barriers on one compute unit: 8192 tokens took 15.5 us with four passes of 8 bits, one wave
-// searching each histogram, and an unconditional ranking sweep; 12.0 now (16384 tokens 33 and
-// 19 us, 32768 50 and 35, by events).
+// apart.  Bound by instruction issue and barriers on one compute unit: of 11.0 us for 8192 tokens the widths took 3.7, with three ranks kept for
+// every token.  Now a token's class is the number of floors that its gains reach, ranks are only kept in the one wave in which a level's
+// share of the last key ends, and class counts come from ballots; the third pass looks once at a token's three keys.  By events, us, before and
+// now: 2048 tokens 5.8 / 5.2, 8192 11.6 / 9.3, 16384 19.6 / 14.5, 32768 36.3 / 25.0; fifty different scores 6.3 / 5.4, 12.5 / 10.1, 20.8 /
+// 16.2, 38.2 / 28.4; 50499 and more, whose last launch has the same floors, 39.3 / 34.4 and 43.3 / 35.7.
 // The first pass's histogram has four copies: with two, scores that crowd together took longer than before (two copies, four, and
 // before, us: a narrow range of 32768 tokens 64 / 47 / 52, normally distributed 52 / 43 / 50, one range of 4096 13.3 / 11.5 /
 // 11.5; uniform 8192 11.4 / 11.7 / 16.0); eight cost more to clear and add up (uniform 8192 12.9).  Up to 2048 tokens two do.
@@ -113,58 +114,65 @@ __device__ inline void split_last_key(uint32_t left, const uint32_t (&n)[3], uin
   for (int l = 0; l < 3; ++l) tied = tied || (quota[l] != 0u && quota[l] != n[l]);
 }
 
-// Class of a token, and its share of the equal keys seen so far (run).
-__device__ inline uint32_t greedy_class(float score, uint32_t kstar, const uint32_t (&quota)[3], bool tied, uint32_t (&run)[3]) {
-  bool taken[3];
+// What an upgrade's gain must reach, as bits: taken if its bits are >= floor[level], so a token's class is the number of levels whose floor
+// it reaches - a level's gain is at most that of the level before, and a level with a share of the last key has all of the level before it
+// admitted.  (A key of 0 does not occur: the largest gain is infinity.)
+__device__ inline void gain_floors(uint32_t kstar, const uint32_t (&quota)[3], uint32_t (&floor)[3]) {
 #pragma unroll
-  for (int l = 0; l < 3; ++l) {
-    const uint32_t key = gain_key(score, l);
-    const bool is_eq = key == kstar;
-    taken[l] = key < kstar || (is_eq && (tied ? run[l] < quota[l] : quota[l] != 0u));
-    run[l] += is_eq;
-  }
-  return taken[0] ? (taken[1] ? (taken[2] ? 3u : 2u) : 1u) : 0u;
+  for (int l = 0; l < 3; ++l) floor[l] = ~kstar + (quota[l] == 0u ? 1u : 0u);
 }
+
+// If a level is admitted in part (tied), it is the last one with a share of the last key: the levels before it are full.
+__device__ inline int level_in_part(const uint32_t (&quota)[3]) { return quota[2] != 0u ? 2 : quota[1] != 0u ? 1 : 0; }
+__device__ inline float per_bit(int level) { return level == 0 ? kPerBit[0] : level == 1 ? kPerBit[1] : kPerBit[2]; }
 
 template <int KPT>
 __global__ __launch_bounds__(kThreads) void greedy_kernel(const float* __restrict__ scores, uint32_t T, uint32_t spare,
                                                           uint8_t* __restrict__ bits, unsigned long long* __restrict__ counts4,
                                                           bool aligned) {
   constexpr uint32_t kCopies = KPT <= 2 ? 2u : 4u;          // of the first pass's histogram, see above
+  constexpr int V = KPT < 4 ? KPT : 4, kChunks = KPT / V;   // a thread's tokens: kChunks times V neighbours
+  typedef float floats __attribute__((ext_vector_type(V)));
   __shared__ __attribute__((aligned(16))) uint32_t hist[kTop * kCopies];    // first pass: bucket d, copy c at [kCopies d + c]
   __shared__ uint32_t tot[3][kSelectWaves];
   __shared__ uint32_t sel_digit, sel_left, sel_same[3];
-  __shared__ uint32_t class_tot[4];
+  __shared__ uint32_t class_tot[3];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint32_t t0 = min(tid * (uint32_t)KPT, T), n_own = min(t0 + (uint32_t)KPT, T) - t0;
-  float mine[KPT];
-  if (KPT % 4 == 0 && aligned && n_own == (uint32_t)KPT) {
+  // token i of a thread is t0 + at(i), one that exists if at(i) < rest
+  const uint32_t wave_t0 = wave * (uint32_t)(kWaveSize * KPT), t0 = wave_t0 + lane * V;
+  const int rest = (int)T - (int)t0;
+  const auto at = [](int i) { return i / V * kWaveSize * V + i % V; };
+  const bool whole = aligned && wave_t0 + (uint32_t)(kWaveSize * KPT) <= T;           // every lane's tokens, vector loads
+  float mine[KPT];                                          // the scores, negative ones and NaN as 0
+  if (whole) {
+    floats f[kChunks];
 #pragma unroll
-    for (int i = 0; i < KPT; i += 4) {
-      const float4 f = *reinterpret_cast<const float4*>(scores + t0 + i);
-      mine[i] = f.x; mine[i + 1] = f.y; mine[i + 2] = f.z; mine[i + 3] = f.w;
-    }
+    for (int c = 0; c < kChunks; ++c) f[c] = *reinterpret_cast<const floats*>(scores + t0 + c * kWaveSize * V);
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) mine[i] = f[i / V][i % V];
   } else {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) mine[i] = (uint32_t)i < n_own ? scores[t0 + i] : 0.0f;
+    for (int i = 0; i < KPT; ++i) mine[i] = at(i) < rest ? scores[t0 + at(i)] : 0.0f;
   }
-  // f(key, level) for every upgrade of the owned tokens
+  // f(key, level) for every upgrade of the own tokens
   const auto for_each_key = [&](auto&& f) {
 #pragma unroll
     for (int i = 0; i < KPT; ++i) {
-      if ((uint32_t)i >= n_own) continue;
+      if (at(i) >= rest) continue;
 #pragma unroll
       for (int l = 0; l < 3; ++l) f(gain_key(mine[i], l), l);
     }
   };
-  if (tid < 4u) class_tot[tid] = 0;
+  if (tid < 3u) class_tot[tid] = 0;
   // `spare` counts units of 2 bits; the upgrades weigh 1, 2, 4.  If all 7T fit, nothing is selected.
   const bool everything = spare >= 7u * T;
-  uint32_t kstar = 0, quota[3] = {0, 0, 0}, run[3] = {0, 0, 0};
+  uint32_t kstar = 0, quota[3] = {0, 0, 0}, floor[3] = {0, 0, 0};
   bool tied = false;
   if (!everything) {
     for (uint32_t i = tid; i < kTop * kCopies / 4u; i += kThreads) reinterpret_cast<u32x4*>(hist)[i] = (u32x4)(0u);
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) mine[i] = mine[i] > 0.0f ? mine[i] : 0.0f;
     for_each_key([&](uint32_t key, int l) { atomicAdd(&hist[(key >> 20) * kCopies + (lane & (kCopies - 1u))], 1u << l); });
     __syncthreads();
     uint32_t c[4];
@@ -197,7 +205,17 @@ __global__ __launch_bounds__(kThreads) void greedy_kernel(const float* __restric
     if (inc[0] > want1 && inc[0] - own[0] <= want1) { sel_digit = tid; sel_left = want1 - (inc[0] - own[0]); }
     __syncthreads();
     const uint32_t high = (top << 10) | uniform(sel_digit), want2 = uniform(sel_left);
-    for_each_key([&](uint32_t key, int l) { if ((key >> 10) == high) atomicAdd(&hist[(1u + l) * kSub + (key & (kSub - 1u))], 1u); });
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {                             // few keys are left: one look at a token's three, and no more in most waves
+      uint32_t key[3];
+      bool any = false;
+#pragma unroll
+      for (int l = 0; l < 3; ++l) { key[l] = gain_key(mine[i], l); any = any || (key[l] >> 10) == high; }
+      if (__builtin_amdgcn_ballot_w64(any && at(i) < rest) == 0ull) continue;
+#pragma unroll
+      for (int l = 0; l < 3; ++l)
+        if ((key[l] >> 10) == high && at(i) < rest) atomicAdd(&hist[(1u + l) * kSub + (key[l] & (kSub - 1u))], 1u);
+    }
     __syncthreads();
     const uint32_t n0 = hist[kSub + tid], n1 = hist[2u * kSub + tid], n2 = hist[3u * kSub + tid];
     own[0] = n0 + 2u * n1 + 4u * n2;
@@ -210,41 +228,82 @@ __global__ __launch_bounds__(kThreads) void greedy_kernel(const float* __restric
     kstar = (high << 10) | uniform(sel_digit);                  // the key at which the budget runs out
     const uint32_t n[3] = {uniform(sel_same[0]), uniform(sel_same[1]), uniform(sel_same[2])};
     split_last_key(uniform(sel_left), n, quota, tied);
-    if (tied) {                                                 // per level, how many of those keys lie at lower token indices
-      uint32_t eq[3] = {0, 0, 0}, inc3[3], all3[3];
-      for_each_key([&](uint32_t key, int l) { eq[l] += (uint32_t)(key == kstar); });
-      block_scan<3>(eq, inc3, all3, tot, lane, wave);
-#pragma unroll
-      for (int l = 0; l < 3; ++l) run[l] = inc3[l] - eq[l];
-    }
+    gain_floors(kstar, quota, floor);                           // everything: floors of 0, which every gain reaches
   } else {
     __syncthreads();
   }
 
-  uint32_t cls[KPT], cnt[4] = {0, 0, 0, 0};
+  uint32_t reached[3] = {0, 0, 0};                              // the wave's tokens of class >= 1, 2, 3
+  const bool word = V == 4 && whole && (reinterpret_cast<uintptr_t>(bits) & 3u) == 0u;
+  const auto store = [&](int c, const uint32_t (&cls)[V]) {
+    if constexpr (V == 4) {
+      if (word) {
+        *reinterpret_cast<uint32_t*>(bits + t0 + c * kWaveSize * V) = (2u << cls[0]) | ((2u << cls[1]) << 8) | ((2u << cls[2]) << 16) | ((2u << cls[3]) << 24);
+        return;
+      }
+    }
 #pragma unroll
-  for (int i = 0; i < KPT; ++i) {
-    cls[i] = everything ? 3u : greedy_class(mine[i], kstar, quota, tied, run);
-    const bool real = (uint32_t)i < n_own;
-    cnt[0] += (uint32_t)(real && cls[i] == 0u); cnt[1] += (uint32_t)(real && cls[i] == 1u);
-    cnt[2] += (uint32_t)(real && cls[i] == 2u); cnt[3] += (uint32_t)(real && cls[i] == 3u);
+    for (int i = 0; i < V; ++i) if (at(c * V + i) < rest) bits[t0 + at(c * V + i)] = (uint8_t)(2u << cls[i]);
+  };
+  // Where a level is admitted in part, tokens with the last key are taken in their order: a wave has room for all of its own, for
+  // none, or - one wave - for the first of them.
+  uint32_t room = 0;
+  bool split = false;
+  const int part = level_in_part(quota);
+  const float part_bit = per_bit(part);
+  if (tied) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < KPT; ++i)
+      n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(at(i) < rest && __float_as_uint(mine[i] * part_bit) == ~kstar));
+    if (lane == 0u) tot[0][wave] = n;
+    __syncthreads();
+    const uint32_t before = waves_below(scan_wave_totals(tot[0], lane), wave), most = part == 0 ? quota[0] : part == 1 ? quota[1] : quota[2];
+    room = most > before ? most - before : 0u;
+    split = room != 0u && room < n;
+#pragma unroll
+    for (int l = 0; l < 3; ++l) if (l == part && room < n) floor[l] = ~kstar + 1u;
   }
-  if (KPT % 4 == 0 && n_own == (uint32_t)KPT && (reinterpret_cast<uintptr_t>(bits) & 3u) == 0u) {
 #pragma unroll
-    for (int i = 0; i < KPT; i += 4)
-      *reinterpret_cast<uint32_t*>(bits + t0 + i) = (2u << cls[i]) | ((2u << cls[i + 1]) << 8) | ((2u << cls[i + 2]) << 16) | ((2u << cls[i + 3]) << 24);
-  } else {
+  for (int c = 0; c < kChunks; ++c) {
+    uint32_t cls[V];
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) if ((uint32_t)i < n_own) bits[t0 + i] = (uint8_t)(2u << cls[i]);
+    for (int i = 0; i < V; ++i) {
+      cls[i] = 0;
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        const bool taken = __float_as_uint(mine[c * V + i] * kPerBit[l]) >= floor[l];
+        cls[i] += taken;
+        reached[l] += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(taken && at(c * V + i) < rest));
+      }
+    }
+    if (split) {
+      uint32_t rank = 0, n = 0;                                 // the wave's tokens with the last key in front of the thread's
+      bool same[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        same[i] = at(c * V + i) < rest && __float_as_uint(mine[c * V + i] * part_bit) == ~kstar;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(same[i]);
+        rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, rank));
+        n += (uint32_t)__builtin_popcountll(mask);
+      }
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const bool taken = same[i] && rank < room;
+        cls[i] += taken;
+        rank += same[i];
+        const uint32_t more = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(taken));
+#pragma unroll
+        for (int l = 0; l < 3; ++l) reached[l] += l == part ? more : 0u;
+      }
+      room -= min(room, n);
+    }
+    store(c, cls);
   }
   if (counts4 != nullptr) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t inc = wave_inclusive_scan(cnt[k]);
-      if (lane == 63 && inc) atomicAdd(&class_tot[k], inc);
-    }
+    if (lane < 3u) atomicAdd(&class_tot[lane], lane == 0u ? reached[0] : lane == 1u ? reached[1] : reached[2]);
     __syncthreads();
-    if (tid < 4) counts4[tid] = class_tot[tid];
+    if (tid < 4u) counts4[tid] = (tid == 0u ? T : class_tot[tid - 1u]) - (tid == 3u ? 0u : class_tot[tid]);
   }
 }
 
@@ -432,15 +491,25 @@ __global__ __launch_bounds__(kThreads) void greedy_write_kernel(GreedyArgs a) {
   __shared__ GreedyPart part;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, b = blockIdx.x;
   const uint32_t t0 = b * a.per, t1 = min(t0 + a.per, a.tokens);
-  uint32_t kstar = 0, quota[3] = {0, 0, 0}, same[3] = {0, 0, 0};
+  uint32_t kstar = 0, floor[3] = {0, 0, 0};
+  uint32_t same = 0, most = 0;                                // of the level that is admitted in part: tokens with the last key in earlier workgroups, and how many are taken
+  float part_bit = 0.0f;
   bool tied = false;
   if constexpr (!EVERYTHING) {
     if (tid < sizeof(GreedyPart) / 4u) reinterpret_cast<uint32_t*>(&part)[tid] = reinterpret_cast<const uint32_t*>(part_of(a, b))[tid];
     __syncthreads();                                          // read by now: the stores below may go over it
     kstar = uniform(part.kstar);
     tied = uniform(part.tied) != 0u;
+    const uint32_t quota[3] = {uniform(part.quota[0]), uniform(part.quota[1]), uniform(part.quota[2])};
+    gain_floors(kstar, quota, floor);
+    if (tied) {
+      const int level = level_in_part(quota);
+      same = uniform(part.same[level]);
+      most = uniform(part.quota[level]);
+      part_bit = per_bit(level);
 #pragma unroll
-    for (int l = 0; l < 3; ++l) { quota[l] = uniform(part.quota[l]); same[l] = uniform(part.same[l]); }
+      for (int l = 0; l < 3; ++l) if (l == level) ++floor[l];
+    }
   } else if (b == 0 && tid < 4u && a.counts4 != nullptr) {
     a.counts4[tid] = tid == 3u ? a.tokens : 0u;
   }
@@ -455,22 +524,28 @@ __global__ __launch_bounds__(kThreads) void greedy_write_kernel(GreedyArgs a) {
 #pragma unroll
       for (uint32_t i = 0; i < 4u; ++i) s[i] = !EVERYTHING && i < n ? a.scores[t + i] : 0.0f;
     }
-    uint32_t run[3] = {0, 0, 0};
-    if (tied) {
-      uint32_t eq[3] = {0, 0, 0}, inc[3], all[3];
+    uint32_t run = 0;
+    if (tied) {                                               // tokens with the last key, in their order
+      uint32_t eq[1] = {0}, inc[1], all[1];
 #pragma unroll
-      for (uint32_t i = 0; i < 4u; ++i)
-#pragma unroll
-        for (int l = 0; l < 3; ++l) eq[l] += (uint32_t)(i < n && gain_key(s[i], l) == kstar);
-      block_scan<3>(eq, inc, all, tot, lane, wave);
-#pragma unroll
-      for (int l = 0; l < 3; ++l) { run[l] = same[l] + inc[l] - eq[l]; same[l] += all[l]; }
+      for (uint32_t i = 0; i < 4u; ++i) eq[0] += (uint32_t)(i < n && __float_as_uint((s[i] > 0.0f ? s[i] : 0.0f) * part_bit) == ~kstar);
+      block_scan<1>(eq, inc, all, tot, lane, wave);
+      run = same + inc[0] - eq[0];
+      same += all[0];
       __syncthreads();                                        // the wave totals are written again
     }
     uint32_t widths = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < 4u; ++i)
-      widths |= (2u << (EVERYTHING ? 3u : greedy_class(s[i], kstar, quota, tied, run))) << (8u * i);
+    for (uint32_t i = 0; i < 4u; ++i) {
+      uint32_t cls = EVERYTHING ? 3u : 0u;
+      if constexpr (!EVERYTHING) {
+        const float score = s[i] > 0.0f ? s[i] : 0.0f;        // negative and NaN scores count as 0
+#pragma unroll
+        for (int l = 0; l < 3; ++l) cls += (uint32_t)(__float_as_uint(score * kPerBit[l]) >= floor[l]);
+        if (tied && __float_as_uint(score * part_bit) == ~kstar) cls += (uint32_t)(run++ < most);
+      }
+      widths |= (2u << cls) << (8u * i);
+    }
     if (n == 4u && (reinterpret_cast<uintptr_t>(a.bits) & 3u) == 0u) *reinterpret_cast<uint32_t*>(a.bits + t) = widths;
     else for (uint32_t i = 0; i < n; ++i) a.bits[t + i] = (uint8_t)(widths >> (8u * i));
   }

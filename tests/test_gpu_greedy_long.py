@@ -31,3 +31,17 @@ def test_lengths(T, kind):
         assert torch.equal(bits, torch.from_numpy(want).to(DEV)), (budget, shift)
         assert got.cpu().tolist() == counts.tolist(), (budget, shift)
         assert (buf[:8 + shift] == 0x5A).all() and (buf[8 + shift + T:] == 0x5A).all()
+
+
+@pytest.mark.parametrize("T", [600, 5000, 9000, 30000, 40000])
+def test_last_key_shared_by_many(T):
+    """The budget ends among equal keys: in a wave's first, last or middle tokens, on and off the four of a thread, at every level."""
+    scores = np.where(np.arange(T) % 5 == 3, 0.5, 1.0).astype(np.float32)
+    s = torch.from_numpy(scores).to(DEV)
+    for budget in (2.001, 2.002, 2.057, 2.114, 2.228, 2.3, 2.456, 2.911, 3.59, 3.6, 4.3, 5.501, 5.6, 6.777, 9.119, 12.003, 15.999):
+        print("[case] T=%d budget %g" % (T, budget), flush=True)
+        want, counts = ref.assign_bits_greedy(scores, budget)
+        bits, got = qkv.assign_bits_greedy(s, budget)
+        torch.cuda.synchronize()
+        assert torch.equal(bits, torch.from_numpy(want).to(DEV)), budget
+        assert got.cpu().tolist() == counts.tolist(), budget
