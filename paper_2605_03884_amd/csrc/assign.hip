@@ -123,21 +123,17 @@ __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, ui
       const uint32_t pre0 = uniform(sel_prefix[0]), pre1 = uniform(sel_prefix[1]), pre2 = uniform(sel_prefix[2]);
       const uint32_t rep1 = (live[0] && pre1 == pre0) ? 0u : 1u;
       const uint32_t rep2 = (live[0] && pre2 == pre0) ? 0u : (live[1] && pre2 == pre1) ? 1u : 2u;
-      const bool count0 = live[0], count1 = live[1] && rep1 == 1u, count2 = live[2] && rep2 == 2u;
+      // what a key's higher bits are compared with; no key's are all ones after the shift.  The three differ, so a key is counted once.
+      const uint32_t only0 = live[0] ? pre0 >> (shift + 8u) : 0xFFFFFFFFu;
+      const uint32_t only1 = live[1] && rep1 == 1u ? pre1 >> (shift + 8u) : 0xFFFFFFFFu;
+      const uint32_t only2 = live[2] && rep2 == 2u ? pre2 >> (shift + 8u) : 0xFFFFFFFFu;
       uint32_t* hist = hist2 + 768u * (pass & 1);         // cleared during the previous search
-      const uint32_t high_mask = 0xFFFFFFFFu << (shift + 8u);
 #pragma unroll
       for (int i = 0; i < KPT; ++i) {
-        const uint32_t key = keys[i];
-        const bool own = (uint32_t)i < n_own;
-        const bool h0 = own && count0 && ((key ^ pre0) & high_mask) == 0u;
-        const bool h1 = own && count1 && ((key ^ pre1) & high_mask) == 0u;
-        const bool h2 = own && count2 && ((key ^ pre2) & high_mask) == 0u;
-        if (__builtin_amdgcn_ballot_w64(h0 || h1 || h2) != 0ull) {       // many waves hold no key of any bucket
-          const uint32_t d = (key >> shift) & 255u;
-          if (h0) atomicAdd(&hist[d], 1u);
-          if (h1) atomicAdd(&hist[256u + d], 1u);
-          if (h2) atomicAdd(&hist[512u + d], 1u);
+        const uint32_t key = keys[i], high = key >> (shift + 8u);
+        const bool h1 = high == only1, h2 = high == only2, any = (uint32_t)i < n_own && (high == only0 || h1 || h2);
+        if (__builtin_amdgcn_ballot_w64(any) != 0ull) {                        // many waves hold no key of any bucket
+          if (any) atomicAdd(&hist[((key >> shift) & 255u) + (h1 ? 256u : h2 ? 512u : 0u)], 1u);
         }
       }
       __syncthreads();
@@ -203,26 +199,13 @@ __device__ __forceinline__ void ranked_body(const float* __restrict__ scores, ui
       const uint32_t shift = pass == 0u ? 20u : 10u;
       const uint32_t rep1 = pre[1] == pre[0] ? 0u : 1u, rep2 = pre[2] == pre[0] ? 0u : pre[2] == pre[1] ? 1u : 2u;
       uint32_t* hist = wide + pass * 3u * kSub;
-      if (rep1 == 1u && rep2 == 2u) {
+      const uint32_t only1 = rep1 == 1u ? pre[1] : 0xFFFFFFFFu, only2 = rep2 == 2u ? pre[2] : 0xFFFFFFFFu;
 #pragma unroll
-        for (int i = 0; i < KPT; ++i) {
-          const uint32_t key = keys[i], high = key >> shift;
-          const bool own = (uint32_t)i < n_own;
-          const bool h0 = own && high == pre[0], h1 = own && high == pre[1], h2 = own && high == pre[2];
-          if (__builtin_amdgcn_ballot_w64(h0 || h1 || h2) != 0ull) {           // many waves hold no key of any bucket
-            const uint32_t d = (key >> (shift - 10u)) & (kSub - 1u);
-            if (h0) atomicAdd(&hist[d], 1u);
-            if (h1) atomicAdd(&hist[kSub + d], 1u);
-            if (h2) atomicAdd(&hist[2u * kSub + d], 1u);
-          }
-        }
-      } else {
-        const uint32_t only1 = rep1 == 1u ? pre[1] : 0xFFFFFFFFu, only2 = rep2 == 2u ? pre[2] : 0xFFFFFFFFu;
-#pragma unroll
-        for (int i = 0; i < KPT; ++i) {
-          const uint32_t key = keys[i], high = key >> shift, d = (key >> (shift - 10u)) & (kSub - 1u);
-          const bool h0 = high == pre[0], h1 = high == only1, h2 = high == only2;      // one of them at most
-          if ((uint32_t)i < n_own && (h0 || h1 || h2)) atomicAdd(&hist[d + (h1 ? kSub : h2 ? 2u * kSub : 0u)], 1u);
+      for (int i = 0; i < KPT; ++i) {
+        const uint32_t key = keys[i], high = key >> shift;
+        const bool h1 = high == only1, h2 = high == only2, any = (uint32_t)i < n_own && (high == pre[0] || h1 || h2);      // one of them at most
+        if (__builtin_amdgcn_ballot_w64(any) != 0ull) {                        // many waves hold no key of any bucket
+          if (any) atomicAdd(&hist[((key >> (shift - 10u)) & (kSub - 1u)) + (h1 ? kSub : h2 ? 2u * kSub : 0u)], 1u);
         }
       }
       __syncthreads();
