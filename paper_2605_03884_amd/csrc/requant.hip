@@ -32,7 +32,7 @@
 // on the four values, and the new codes are the old ones relabelled.
 //
 // Whole call with the new widths' assignment, 8K tokens, budget 3 to 2.5: 199 us with 64 rows of one plane sorted per wave and every span
-// expanded to 32 values, 160 with windows of a width, 146 with windows of tokens; 32K tokens, 6 to 4: 1162, 840 and 757 us.
+// expanded to 32 values, 160 with windows of a width, 140 .. 146 with windows of tokens; 32K tokens, 6 to 4: 1162, 840 and 719 .. 760 us.
 // Windows of a width: of 512 rows 171 and 936 us; without the next round's loads in flight 172 and 877; of 256 tokens over all
 // widths at once, in the order of the pairs, 221 and 1137.
 //
