@@ -79,6 +79,7 @@ class _InjectByAddress(ctypes.Structure):
 _pointer_tables = [ctypes.c_void_p * (2 * count) for count in range(5)]
 
 _lib = None
+_inject_by_address = None         # qkv_inject_layers for an _InjectByAddress; set with _lib
 
 
 def lib_path():
@@ -87,7 +88,7 @@ def lib_path():
 
 def lib():
     """The loaded library.  Built once by paper_2605_03884_amd.build if it is not there; never replaced by a fallback."""
-    global _lib
+    global _lib, _inject_by_address
     if _lib is not None:
         return _lib
     path = lib_path()
@@ -124,7 +125,10 @@ def lib():
     L.qkv_card_fill.restype = ctypes.c_int
     L.qkv_card_fill.argtypes = [ctypes.POINTER(Desc), vp, vp, i64p, vp, ctypes.c_uint64, vp]
     L.qkv_inject_layers.restype = ctypes.c_int
-    L.qkv_inject_layers.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(Desc), vp, vp, vp]           # Inject or _InjectByAddress
+    L.qkv_inject_layers.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(Desc), ctypes.POINTER(Inject), vp, vp]
+    inject = L["qkv_inject_layers"]                # the same entry point, a prototype of its own
+    inject.restype = ctypes.c_int
+    inject.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(Desc), ctypes.POINTER(_InjectByAddress), vp, vp]
     L.qkv_quantize_pack_kc.restype = ctypes.c_int
     L.qkv_quantize_pack_kc.argtypes = [ctypes.POINTER(Desc), vp, vp, vp, i64p, vp, ctypes.c_uint64, vp]
     L.qkv_unpack_dequant_kc.restype = ctypes.c_int
@@ -149,7 +153,7 @@ def lib():
                                 ctypes.POINTER(ctypes.c_uint32), vp]
     L.qkv_card_flags.restype = ctypes.c_int
     L.qkv_card_flags.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(ctypes.c_uint32), vp]
-    _lib = L
+    _lib, _inject_by_address = L, inject
     return L
 
 
@@ -375,9 +379,10 @@ def inject_layers(card, expect, k_layers, v_layers, layer_begin=0, rope_base=0.0
     at = ctypes.addressof(table)
     where = _InjectByAddress(int(layer_begin), count, at, at + 8 * count, strides[0], strides[1], float(rope_base), int(rope_delta),
                              1 if keys_per_channel else 0, 0)
-    _check((_lib or lib()).qkv_inject_layers(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect), ctypes.byref(where),
-                                             None if status is None else _dev_ptr(status, None, "status"), _stream(stream)),
-           "qkv_inject_layers")
+    if _inject_by_address is None:
+        lib()
+    _check(_inject_by_address(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect), ctypes.byref(where),
+                              None if status is None else _dev_ptr(status, None, "status"), _stream(stream)), "qkv_inject_layers")
 
 
 def card_attend_workspace(expect, q_heads):

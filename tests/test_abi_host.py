@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import paper_2605_03884_amd as qkv
+from paper_2605_03884_amd import binding
 from oracle import ref
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -163,3 +164,20 @@ int main(void) {
     assert int(out[0]) == qkv.version()
     assert int(out[1]) == 267297024                            # the 8K benchmark card, closed form of the layout
     assert out[2].strip() == "card buffer too small"
+
+
+def test_inject_layers_takes_its_own_structure_and_no_other():
+    """The declared prototype: a qkv_inject_t by value or by reference, not a pointer to something else; and the binding's own view of it,
+    with addresses as numbers, has the same layout."""
+    call, desc, where = qkv.lib().qkv_inject_layers, qkv.Desc.make(1, 1, 8, 64, 32), qkv.Inject()
+    null = -1
+    assert call(None, 0, desc, where, None, None) == null
+    assert call(None, 0, ctypes.byref(desc), ctypes.byref(where), None, None) == null
+    for other in (desc, ctypes.byref(desc), 1234, (ctypes.c_uint8 * 128)()):
+        with pytest.raises(ctypes.ArgumentError):
+            call(None, 0, desc, other, None, None)
+    by_address = binding._InjectByAddress
+    assert ctypes.sizeof(by_address) == ctypes.sizeof(qkv.Inject)
+    for name, _ in qkv.Inject._fields_:
+        a, b = getattr(qkv.Inject, name), getattr(by_address, name)
+        assert (a.offset, a.size) == (b.offset, b.size), name
