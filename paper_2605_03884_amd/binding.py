@@ -153,7 +153,8 @@ def lib():
                                 ctypes.POINTER(ctypes.c_uint32), vp]
     L.qkv_card_flags.restype = ctypes.c_int
     L.qkv_card_flags.argtypes = [vp, ctypes.c_uint64, ctypes.POINTER(ctypes.c_uint32), vp]
-    _lib, _inject_by_address = L, inject
+    _inject_by_address = inject                    # before _lib: another thread that finds _lib set finds this too
+    _lib = L
     return L
 
 
