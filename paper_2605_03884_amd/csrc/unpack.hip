@@ -355,34 +355,24 @@ __global__ void unpack_status_kernel(UnpackArgs a) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *a.status = ok ? 0u : QKV_STATUS_BAD_HEADER;
 }
 
-// The tiles of width class C, dealt to the waves round-robin from the segment's end, continuing where
-// the previous class stopped.  (The grid has a wave for every tile, and a tile found by comparisons, as in injection, serves short cards: 16 pairs of
-// 2048 tokens 9.1 us and 8.4; but 256 pairs of 8192 take 237 us for 228 and 32768 tokens 1020 for 955.  Without remainders this
-// form is as fast as it was with them, or 2 % faster.)
-template <int C, int G, bool KEEP, bool KC>
-__device__ inline void unpack_class(const UnpackArgs& a, const CardGeom& g, uint32_t gw, uint32_t n_waves, uint32_t lane,
-                                    u32x4* lds, uint32_t& cum, uint32_t& bad) {
-  const uint32_t n_rows = g.planes * g.n[C];
-  if (n_rows == 0) return;
+// The tiles of a uniform card of width class C with keys per channel, dealt to the waves round-robin from the segment's end.  A tile lies in one plane (kc_shape).
+// The grid has a wave for every tile, so the loop is made once, by the waves that have one.  With a test in its place 4-bit cards of 256 pairs and 32768
+// tokens take 1010 us for 935, with as many waves a SIMD too; 8192 tokens 222 for 228, 16 pairs of 2048 5.7 for 6.6.
+template <int C, bool KEEP>
+__device__ inline void unpack_class(const UnpackArgs& a, const CardGeom& g, uint32_t gw, uint32_t n_waves, uint32_t lane, u32x4* lds, uint32_t& bad) {
+  constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
+  const uint32_t n_rows = g.planes * g.n[C];                     // 0 for the other classes
   const uint32_t tile_rows = kTileChunks >> g.lpr_shift;
   const uint32_t tiles = (n_rows + tile_rows - 1) / tile_rows;
-  const uint32_t first = gw >= cum ? gw - cum : gw + n_waves - cum;
   const RopeLane no_rope = {};
-  for (uint32_t i = first; i < tiles; i += n_waves) {
+  for (uint32_t i = gw; i < tiles; i += n_waves) {
     const uint32_t r0 = (tiles - 1 - i) * tile_rows;
-    const uint32_t p = r0 / g.n[C];                               // a tile lies in one plane (kc_shape)
+    const uint32_t p = r0 / g.n[C];
     const auto my_row = [&] { return tile_row_address(a, g, C, p, r0, lane, tile_rows, bad); };
-    if constexpr (C == 3) {
-      copy_tile<KEEP, false, false>(a.card, g, r0, n_rows, my_row, true, lane, no_rope);
-    } else {
-      constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
-      const bool rows_first = KC && C >= 1 && a.rows_first != 0u;
-      if (KC && r0 < (n_rows >> 1)) unpack_tile_kc<W, KEEP, false>(a.card, g, C, r0, n_rows >> 1, my_row, rows_first, lane, lds, no_rope);   // key rows
-      else unpack_tile<W, G, KEEP, false>(a.card, g, C, r0, n_rows, my_row, rows_first, lane, lds, no_rope);
-    }
+    const bool rows_first = C >= 1 && a.rows_first != 0u;
+    if (r0 < (n_rows >> 1)) unpack_tile_kc<W, KEEP, false>(a.card, g, C, r0, n_rows >> 1, my_row, rows_first, lane, lds, no_rope);   // key rows
+    else unpack_tile<W, 32, KEEP, false>(a.card, g, C, r0, n_rows, my_row, rows_first, lane, lds, no_rope);
   }
-  cum += tiles;
-  cum = cum >= n_waves ? cum - n_waves : cum;
 }
 
 // KC: a uniform card whose key planes (the first half of every segment) are grouped per channel.
@@ -449,12 +439,10 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
   // The card is walked from its end to its start: right after packing, its tail is what the
   // 256 MB memory-side cache still holds (a card of 302 MB unpacks in 212 us this way, 264 us
   // front to back; cards that fit, or that are several times larger, are indifferent).
-  uint32_t cum = 0;
   const uint32_t n_waves = (gridDim.x - a.check_blocks) * kWavesPerBlock;
-  unpack_class<3, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
-  unpack_class<2, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
-  unpack_class<1, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
-  unpack_class<0, G, KEEP, KC>(a, g, gw, n_waves, lane, my_lds, cum, bad);
+  unpack_class<2, KEEP>(a, g, gw, n_waves, lane, my_lds, bad);
+  unpack_class<1, KEEP>(a, g, gw, n_waves, lane, my_lds, bad);
+  unpack_class<0, KEEP>(a, g, gw, n_waves, lane, my_lds, bad);
   if (bad && a.status && a.check_blocks == 0u) atomicOr(a.status, QKV_STATUS_BAD_ORDER);
 }
 
