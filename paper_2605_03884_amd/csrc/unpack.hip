@@ -185,9 +185,10 @@ __device__ inline void store_tile(uint64_t my_row_addr, uint32_t lane, uint32_t 
 // The addresses take two dependent trips to the tables, so the tile's own loads are issued before them (one layer
 // of 3877 tokens, keys realigned, in the former order of the tiles: 10.1 us with the addresses first, 8.4 us; all tiles' rows of 8K tokens injected without
 // realignment: 281 and 269 us) - except with rows_first, where the card streams and the wider loads in flight only crowd the
-// writes out: raw rows of a uniform card too large to stay in cache (8K tokens of 16 bits: 378 us with the addresses first,
-// 386), uniform cards of 4 and 8 bits injected into more layers than a call for few takes (8K of 8 bits 285 and 301, of 4 bits 235 and 249; 32K of
-// 4 bits 985 and 1045; of 2 bits the other way round, 8K 232 and 215), and cards of 4 and 8 bits with keys per channel from 512 MB of cache on
+// writes out: raw rows of a card too large to stay in cache (8K tokens of 16 bits: 378 us with the addresses first, 386; 32K at 12 bits on average
+// 1345 and 1400; injected: of a uniform card), uniform cards of 4 and 8 bits injected into more layers than a call for few takes (8K of 8 bits 285 and 301, of 4 bits
+// 235 and 249; 32K of 4 bits 985 and 1045; of 2 bits the other way round, 8K 232 and 215), and
+// cards of 4 and 8 bits with keys per channel from 512 MB of cache on
 // (32K tokens of 4 bits, 941 and 1026; below, 64 planes of 8K tokens of 8 bits, 66.9 and 63.6), key tiles that are rotated
 // apart (32K of 4 bits 1164 and 1077).
 template <int W, int G, bool KEEP, bool ROPE, typename ROWS>
@@ -310,10 +311,11 @@ __device__ inline void unpack_tile_kc(const uint8_t* card, const CardGeom& g, in
   store_tile(my_row, lane, lpr_shift, data);
 }
 
-// FEW: in a grid of half a chip, as a call for few layers has it, the loads are taken one by one behind a test each, in large ones without; raw
-// rows of a uniform card, where everything in flight is loads and stores of whole rows, in two halves.  (32 calls, a layer of 3877 tokens each,
-// 16 bits, realigned: 265 us before, 281 without tests, 249 with; 8 bits on average 259, 251 and 246.  All of 8K tokens of 16 bits injected
-// in a call 371 us before, 377 at once, 350 in halves; 32K tokens at 4 bits on average unpacked 986 with tests, 970 without.)
+// FEW: in a grid of half a chip, as a call for few layers has it, the loads are taken one by one behind a test each, in large ones without; where a
+// quarter of the tokens or more are raw - most of what is in flight is loads and stores of whole rows - in two halves.  (32 calls, a layer of 3877
+// tokens each, 16 bits, realigned: 265 us before, 281 without tests, 249 with; 8 bits on average 259, 251 and 246.  All of 8K tokens of 16 bits
+// injected in a call 371 us before, 377 at once, 350 in halves; 32K tokens at 4 bits on average unpacked 986 with tests, 970 without, at 12 bits
+// 1358 at once and 1310 in halves, at 15 bits 1493 and 1455, row addresses first in both.)
 template <bool KEEP, bool ROPE, bool FEW, typename ROWS>
 __device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_t r0, uint32_t n_rows, const ROWS& row_address,
                                  bool rows_first, uint32_t lane, const RopeLane& rope) {
@@ -331,7 +333,7 @@ __device__ inline void copy_tile(const uint8_t* card, const CardGeom& g, uint32_
       if (off <= last) data[k] = card_load<KEEP>(reinterpret_cast<const u32x4*>(src + off));
     } else {
       data[k] = card_load<KEEP>(reinterpret_cast<const u32x4*>(src + min(off, last)));               // past it: that once more, no row is theirs
-      if (k == 3 && g.n[3] == g.tokens) asm volatile("" :: "v"(data[0]), "v"(data[1]), "v"(data[2]), "v"(data[3]));
+      if (k == 3 && g.n[3] >= g.tokens >> 2) asm volatile("" :: "v"(data[0]), "v"(data[1]), "v"(data[2]), "v"(data[3]));
     }
   }
   if (!rows_first) my_row = row_address();
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(kBlockThreads) void unpack_kernel(UnpackArgs a) {
     if (k < tp3) {
       const uint32_t r0 = p * g.n[3] + (tp3 - 1u - k) * tile_rows, end = (p + 1u) * g.n[3];
       const auto my_row = [&] { return tile_row_address(a, g, 3, p, r0, lane, tile_rows, bad); };
-      copy_tile<KEEP, false, false>(a.card, g, r0, end, my_row, !KEEP && g.n[3] == g.tokens, lane, no_rope);
+      copy_tile<KEEP, false, false>(a.card, g, r0, end, my_row, !KEEP, lane, no_rope);
     } else if ((k -= tp3) < tp2) {
       const uint32_t r0 = p * g.n[2] + (tp2 - 1u - k) * tile_rows, end = (p + 1u) * g.n[2];
       const auto my_row = [&] { return tile_row_address(a, g, 2, p, r0, lane, tile_rows, bad); };
