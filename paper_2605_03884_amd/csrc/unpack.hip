@@ -186,8 +186,8 @@ __device__ inline void store_tile(uint64_t my_row_addr, uint32_t lane, uint32_t 
 // of 3877 tokens, keys realigned, in the former order of the tiles: 10.1 us with the addresses first, 8.4 us; all tiles' rows of 8K tokens injected without
 // realignment: 281 and 269 us) - except with rows_first, where the card streams and the wider loads in flight only crowd the
 // writes out: raw rows of a card too large to stay in cache (8K tokens of 16 bits: 378 us with the addresses first, 386; 32K at 12 bits on average
-// 1345 and 1400; injected: of a uniform card), uniform cards of 4 and 8 bits injected into more layers than a call for few takes (8K of 8 bits 285 and 301, of 4 bits
-// 235 and 249; 32K of 4 bits 985 and 1045; of 2 bits the other way round, 8K 232 and 215), and
+// 1345 and 1400; injected: of a uniform card), uniform cards injected into more layers than a call for few takes (8K of 8 bits 285 and 301, of 4 bits
+// 235 and 249; 32K of 4 bits 985 and 1045; of 2 bits, 3877 tokens realigned in calls of 8 layers, 106 and 111, 32K 905 and 920), and
 // cards of 4 and 8 bits with keys per channel from 512 MB of cache on
 // (32K tokens of 4 bits, 941 and 1026; below, 64 planes of 8K tokens of 8 bits, 66.9 and 63.6), key tiles that are rotated
 // apart (32K of 4 bits 1164 and 1077).
@@ -495,7 +495,7 @@ __device__ inline bool inject_range(const ARGS& a, const CardGeom& g, const Rope
   } else {
     constexpr int W = C == 0 ? 2 : C == 1 ? 4 : 8;
     if (KC && KV == 0) unpack_tile_kc<W, KEEP, rot>(a.card, g, C, r0, (g.planes >> 1) * n, my_row, many && C >= 1 && !rot, lane, lds, rope);
-    else unpack_tile<W, G, KEEP, rot>(a.card, g, C, r0, seg_hi, my_row, many && n == g.tokens && C >= 1, lane, lds, rope);
+    else unpack_tile<W, G, KEEP, rot>(a.card, g, C, r0, seg_hi, my_row, many && n == g.tokens && (C >= 1 || a.layer_count > kFewLayers), lane, lds, rope);
   }
   return true;
 }
