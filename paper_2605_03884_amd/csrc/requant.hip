@@ -667,11 +667,15 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
   const uint64_t rows = (uint64_t)out.planes * out.tokens;
   const uint64_t values = rows * out.head_dim;
   // Long cards: the windows of tokens, unless a head has 64 dimensions (windows of half the bytes, and as many rounds that are not
-  // full) or rows are wide (whole lines that nobody else reads: nothing to gain).  Whole call, us, with windows of a width and of tokens:
+  // full) or rows are wide (whole lines that nobody else reads: nothing to gain, and more to lose where widths are sorted along the tokens, as
+  // they nearly are where scores follow the position).  Whole call, us, with windows of a width and of tokens:
   // 512 planes of 128 values, 1500 tokens, 3 to 2.5 33.7 and 35.3, 2000 43.4 and 41.8, 6 to 4 62.4 and 59.7, 16000 410 and 371;
   // 256 planes of 256 values, 1500 tokens, 6 to 4 46.6 and 46.2, 2000 58.9 and 57.2, 16000 395 and 356; 512 of 64, 5000 tokens, 6 to 4
-  // 85.1 and 85.9, 16000, 8 to 5, 253 and 267; 512 of 128, 16384 tokens, 16 to 4 541 and 567, 8 to 8 568 and 588, 8 to 6 511 and 498.
-  if (out.head_dim >= 128u && values >= 131072000ull && 2u * card_in_bytes <= 3u * values && out.total <= values) {
+  // 85.1 and 85.9, 16000, 8 to 5, 253 and 267; 512 of 128, 16384 tokens, 16 to 4 541 and 567, 8 to 8 568 and 588, 8 to 6 511 and 498,
+  // 9.5 to 6.5 550 and 551, sorted 9 to 6 433 and 463, 6 to 4 328 and 347, 3 to 2.5 224 and 227.
+  // The incoming card's length is all that is known here of its widths: in a longer buffer it counts as a card of wider rows.
+  const uint64_t bytes = card_in_bytes + out.total;
+  if (out.head_dim >= 128u && values >= 131072000ull && 2u * card_in_bytes <= 3u * values && out.total <= values && bytes <= 2u * values) {
     TokenArgs t;
     t.card_in = card_in; t.card_in_bytes = card_in_bytes;
     t.layers = out.layers; t.kv_heads = out.kv_heads; t.head_dim = out.head_dim; t.group_size = out.group_size;
@@ -679,10 +683,19 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
     t.out = out;
     t.card_out = card_out;
     t.status = status;
-    // Two planes with one look-up and sort while the cards sit in the memory-side cache; larger ones want the planes that are worked on at a
-    // time to be neighbours (8192 tokens, 3 to 2.5: 151 us with one plane and 138 with two; 5 to 3 172 and 178; 32768, 6 to 4: 745 and 790).
+    // Two planes with one look-up and sort where rows are narrow and the look-ups' share is large; wider ones want the planes that are worked on at a
+    // time to be neighbours, unless the cards sit in the memory-side cache.  A row of 256 values has fewer look-ups a byte, and there the chip must
+    // stay full with half the workgroups.  Both cards' bits a value decide (one plane and two, us; 2 to 2 bits 16384 tokens 215 and 175, 3 to 2.5
+    // 8192 151 and 136, 16384 291 and 255, 4 to 2 294 and 265, 5 to 2.5 8192 166 and 161; 6 to 4 2001 tokens 47.3 and 49.1, 8192 197 and 211, 8 to
+    // 5 235 and 256, 8 bits to 4 3000 72.1 and 77.1, 32768, 6 to 4, 745 and 790; between them 5 to 3 8192 170 and 174, 4 to 4 176 and 185, but 2001 44.8
+    // and 43.9; all of 4 bits to 4 again 8192 163 and 149, 16384 317 and 285.  256 values, 3 to 2.5: 2001 tokens 36.3 and 38.4, 6000 91.6 and
+    // 90.0, 8192 123 and 118, 4 to 3 6000 103 and 106).
     // A card has an even number of planes, and a grid fewer than 2^32 threads.
-    t.group_planes = card_in_bytes + out.total <= kCacheResidentCardBytes || rows >= (1ull << 31) ? 2u : 1u;
+    const bool one_width = out.n[0] == out.tokens || out.n[1] == out.tokens || out.n[2] == out.tokens || out.n[3] == out.tokens;
+    const bool two = out.head_dim > 128u ? 16u * bytes <= 15u * values && rows >= 2u * 1024u * kTokenRows
+                                         : 16u * bytes <= 19u * values || (one_width && card_in_bytes <= out.total) ||
+                                           (16u * bytes <= 21u * values && bytes <= (256ull << 20));
+    t.group_planes = two || rows >= (1ull << 31) ? 2u : 1u;
     t.rows = out.planes / t.group_planes * out.tokens;
     const dim3 grid((t.rows + kTokenRows - 1u) / kTokenRows), block(kTokenThreads);
     switch (out.group_size) {

@@ -136,47 +136,79 @@ def test_two_bit_groups_of_any_content(kind, G):
         hop(card, rd, np.full(T, width, np.uint8), "2-bit, %s, G=%d to %d bits" % (kind, G, width))
 
 
-@pytest.mark.parametrize("L,H,T,D,G,order", [(32, 8, 2001, 128, 32, "drawn"), (32, 8, 2048, 128, 64, "sorted"), (16, 8, 2049, 256, 128, "drawn"),
-                                             (16, 8, 2100, 256, 32, "sorted"), (1, 1, 512003, 128, 128, "drawn"), (1024, 5, 101, 128, 32, "drawn"),
-                                             (64, 1, 8191, 128, 32, "one width")])
-def test_windows_of_tokens(L, H, T, D, G, order):
-    """At least 131072000 values of 128 or 256 dimensions: windows of 512 rows inside a plane, across the ends of planes and over many
-    short ones, against injection and creation on the GPU; with an entry of the incoming tables out of range the token's rows are
-    those of zeros, and with counts that are not those of the widths the card is what creation makes of the same counts."""
-    assert 2 * L * H * T * D >= 131072000 and D >= 128
-    print("[case] windows of tokens L=%d H=%d T=%d D=%d G=%d %s" % (L, H, T, D, G, order), flush=True)
-    rng = np.random.default_rng(T)
-    a, b = draw_bits(T, rng, [0.4, 0.3, 0.2, 0.1]), draw_bits(T, rng, [0.62, 0.26, 0.08, 0.04])
-    if order == "sorted":
-        a = np.sort(a)
-    if order == "one width":
-        a[:] = 4
-    ca, cb = ref.count_bits(a).tolist(), ref.count_bits(b).tolist()
-    a, b = torch.from_numpy(a).to(DEV), torch.from_numpy(b).to(DEV)
-    desc = qkv.Desc.make(L, H, T, D, G)
-    g = torch.Generator(device=DEV)
-    g.manual_seed(T)
-    k = torch.randn((L, H, T, D), dtype=torch.float16, device=DEV, generator=g)
-    v = torch.randn((L, H, T, D), dtype=torch.float16, device=DEV, generator=g)
-    card = torch.empty(qkv.card_bytes(desc, ca), dtype=torch.uint8, device=DEV)
-    qkv.quantize_pack(desc, k, v, a, ca, card)
-    qkv.unpack_dequant(card, desc, k, v)
-    status = torch.full((1,), 0x7777, dtype=torch.int32, device=DEV)
+def planes_at_a_time(desc, total_in, counts_out):
+    """How many planes a workgroup of the windows of tokens does with one look-up and sort; 0: the call goes through windows of a width."""
+    total_out = qkv.card_bytes(desc, counts_out)
+    rows = 2 * desc.layers * desc.kv_heads * desc.tokens
+    values, both = rows * desc.head_dim, total_in + total_out
+    if desc.head_dim < 128 or values < 131072000 or 2 * total_in > 3 * values or total_out > values or both > 2 * values:
+        return 0
+    if desc.head_dim > 128:
+        return 2 if 16 * both <= 15 * values and rows >= 2 * 1024 * 512 else 1
+    one_width = desc.tokens in counts_out
+    return 2 if 16 * both <= 19 * values or (one_width and total_in <= total_out) or (16 * both <= 21 * values and both <= 256 << 20) else 1
 
-    def compare(counts, want_status):
-        out = torch.full((qkv.card_bytes(desc, counts),), 0xA5, dtype=torch.uint8, device=DEV)
-        want = torch.full_like(out, 0xA5)
-        qkv.quantize_pack(desc, k, v, b, counts, want)
-        qkv.requantize(card, desc, b, counts, out, status=status)
-        assert int(status.item()) == want_status
+
+MIXES = {"wide": [0.4, 0.3, 0.2, 0.1], "middle": [0.62, 0.26, 0.08, 0.04], "narrow": [0.85, 0.1, 0.04, 0.01], "of 2": [1, 0, 0, 0], "of 4": [0, 1, 0, 0]}
+
+
+class LongCard:
+    """A card long enough for the windows of tokens, made on the GPU, and what creation makes of it after injection."""
+
+    def __init__(self, L, H, T, D, G, old, new, order="drawn", planes=None):
+        print("[case] windows of tokens L=%d H=%d T=%d D=%d G=%d %s to %s %s" % (L, H, T, D, G, old, new, order), flush=True)
+        self.shape, rng = (L, H, T, D, G), np.random.default_rng(T)
+        a, b = draw_bits(T, rng, MIXES[old]), draw_bits(T, rng, MIXES[new])
+        if order == "sorted":
+            a = np.sort(a)
+        self.ca, self.cb = ref.count_bits(a).tolist(), ref.count_bits(b).tolist()
+        self.desc = qkv.Desc.make(L, H, T, D, G)
+        self.off = ref.card_offsets(ref.make_desc(L, H, T, D, G), self.ca)
+        self.a, self.b = torch.from_numpy(a).to(DEV), torch.from_numpy(b).to(DEV)
+        g = torch.Generator(device=DEV)
+        g.manual_seed(T)
+        self.k = torch.randn((L, H, T, D), dtype=torch.float16, device=DEV, generator=g)
+        self.v = torch.randn((L, H, T, D), dtype=torch.float16, device=DEV, generator=g)
+        self.card = torch.empty(qkv.card_bytes(self.desc, self.ca), dtype=torch.uint8, device=DEV)
+        taken = planes_at_a_time(self.desc, self.card.numel(), self.cb)
+        assert taken == planes if planes else taken > 0
+        qkv.quantize_pack(self.desc, self.k, self.v, self.a, self.ca, self.card)
+        qkv.unpack_dequant(self.card, self.desc, self.k, self.v)
+        self.status = torch.full((1,), 0x7777, dtype=torch.int32, device=DEV)
+
+    def requantize(self, counts):
+        out = torch.full((qkv.card_bytes(self.desc, counts),), 0xA5, dtype=torch.uint8, device=DEV)
+        qkv.requantize(self.card, self.desc, self.b, counts, out, status=self.status)
+        return out
+
+    def compare(self, counts, want_status):
+        want = torch.full((qkv.card_bytes(self.desc, counts),), 0xA5, dtype=torch.uint8, device=DEV)
+        qkv.quantize_pack(self.desc, self.k, self.v, self.b, counts, want)
+        out = self.requantize(counts)
+        assert int(self.status.item()) == want_status
         assert torch.equal(out, want)
 
-    compare(cb, 0)
-    wrong = list(cb)
-    wrong[0], wrong[1] = wrong[0] - 3, wrong[1] + 3
-    compare(wrong, 0)
-    off = ref.card_offsets(ref.make_desc(L, H, T, D, G), ca)
-    lost = T // 2
-    card[off["slot"]:off["slot"] + 4 * T].view(torch.int32)[lost] = 1 << 30
-    k[:, :, lost], v[:, :, lost] = 0, 0
-    compare(cb, qkv.STATUS_BAD_ORDER)
+
+@pytest.mark.parametrize("L,H,T,D,G,old,new,order,planes", [
+    (32, 8, 2001, 128, 32, "wide", "middle", "drawn", 1), (32, 8, 2048, 128, 64, "wide", "middle", "sorted", 2),
+    (16, 8, 2049, 256, 128, "wide", "middle", "drawn", 1), (16, 8, 2100, 256, 32, "wide", "middle", "sorted", 1),
+    (1, 1, 512003, 128, 128, "wide", "middle", "drawn", 2), (1024, 5, 101, 128, 32, "wide", "middle", "drawn", 1),
+    (64, 1, 8191, 128, 32, "of 4", "middle", "drawn", 2), (32, 8, 7001, 128, 32, "wide", "middle", "drawn", 1),
+    (32, 8, 8191, 128, 32, "middle", "narrow", "drawn", 2), (32, 8, 8193, 128, 32, "of 4", "of 4", "drawn", 2),
+    (16, 8, 4101, 256, 128, "middle", "narrow", "sorted", 2), (4, 2, 65537, 128, 64, "of 2", "wide", "drawn", 2)])
+def test_windows_of_tokens(L, H, T, D, G, old, new, order, planes):
+    """At least 131072000 values of 128 or 256 dimensions in narrow rows: windows of 512 rows inside a plane, across the ends of planes and over
+    many short ones, one and two planes at a time, below and above 512 MiB, against injection and creation on the GPU; with an entry
+    of the incoming tables out of range, or a width that is none, the token's rows are those of zeros, and with counts that are not those of
+    the widths the card is what creation makes of the same counts."""
+    c = LongCard(L, H, T, D, G, old, new, order, planes)
+    c.compare(c.cb, 0)
+    wrong = list(c.cb)
+    at = 0 if wrong[0] >= 3 else 1
+    wrong[at], wrong[at + 1] = wrong[at] - 3, wrong[at + 1] + 3
+    c.compare(wrong, 0)
+    slots = c.card[c.off["slot"]:c.off["slot"] + 4 * T].view(torch.int32)
+    for lost, spoil in ((T // 2, lambda t: slots[t:t + 1].fill_(1 << 30)), (T // 3, lambda t: c.card[c.off["bits"] + t:c.off["bits"] + t + 1].fill_(7))):
+        spoil(lost)
+        c.k[:, :, lost], c.v[:, :, lost] = 0, 0
+        c.compare(c.cb, qkv.STATUS_BAD_ORDER)
