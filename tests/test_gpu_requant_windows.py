@@ -136,6 +136,33 @@ def test_two_bit_groups_of_any_content(kind, G):
         hop(card, rd, np.full(T, width, np.uint8), "2-bit, %s, G=%d to %d bits" % (kind, G, width))
 
 
+@pytest.mark.parametrize("G", [32, 64, 128])
+@pytest.mark.parametrize("old", [4, 8])
+def test_wider_groups_of_any_content(old, G):
+    """4- and 8-bit cards with drawn pairs and codes; every decoded value stays finite."""
+    T, D, P = 96, 128, 2
+    rng = np.random.default_rng(old + G)
+    rd = ref.make_desc(1, 1, T, D, G)
+    zero = np.zeros((1, 1, T, D), np.uint16)
+    counts = [T * (w == old) for w in (2, 4, 8, 16)]
+    card = ref.quantize_pack(rd, zero, zero, np.full(T, old, np.uint8), counts)
+    off = ref.card_offsets(rd, counts)
+    n_codes, n_pairs = P * T * D * old // 8, P * T * D // G
+    card[off["codes%d" % old]:off["codes%d" % old] + n_codes] = rng.integers(0, 256, n_codes).astype(np.uint8)
+    scale, zeros = drawn_pairs(rng, n_pairs)
+    card[off["meta%d" % old]:off["meta%d" % old] + 4 * n_pairs] = np.stack([scale, zeros], axis=1).reshape(-1).view(np.uint8)
+    for width in (2, 4, 8, 16):
+        hop(card, rd, np.full(T, width, np.uint8), "%d-bit, any pairs, G=%d to %d bits" % (old, G, width))
+
+
+def drawn_pairs(rng, n):
+    """Scales of every kind - ordinary, subnormal, zero, negative - and zeros of any size; 255 steps from any zero stay finite."""
+    scale = np.abs(rng.standard_normal(n) * 10.0 ** rng.integers(-3, 2, n)).astype(np.float16)
+    low = (rng.integers(1, 1024, n) * 2.0 ** -24).astype(np.float16)
+    zeros = (rng.standard_normal(n) * 10.0 ** rng.integers(-6, 4, n)).astype(np.float16)
+    return np.choose(rng.integers(0, 4, n), [scale, low, np.zeros_like(scale), -scale]), zeros
+
+
 def planes_at_a_time(desc, total_in, counts_out):
     """How many planes a workgroup of the windows of tokens does with one look-up and sort; 0: the call goes through windows of a width."""
     total_out = qkv.card_bytes(desc, counts_out)
@@ -212,3 +239,36 @@ def test_windows_of_tokens(L, H, T, D, G, old, new, order, planes):
         spoil(lost)
         c.k[:, :, lost], c.v[:, :, lost] = 0, 0
         c.compare(c.cb, qkv.STATUS_BAD_ORDER)
+
+
+@pytest.mark.parametrize("G,new", [(32, "wide"), (64, "middle"), (128, "of 4"), (32, "of 2")])
+def test_windows_of_tokens_any_pairs(G, new):
+    """Pairs that creation would never write, ordinary ones among them, at every width: 2-bit rows that can't be relabelled, and the wider decoders."""
+    c = LongCard(32, 8, 2003, 128, G, "wide", new)
+    rng = np.random.default_rng(G)
+    for i, width in enumerate((2, 4, 8)):
+        n = 2 * 32 * 8 * c.ca[i] * (128 // G)
+        scale, zeros = drawn_pairs(rng, n)
+        at = c.off["meta%d" % width]
+        mine = torch.from_numpy(np.stack([scale, zeros], axis=1).reshape(-1).view(np.int32)).to(DEV)
+        pairs = c.card[at:at + 4 * n].view(torch.int32)
+        pairs.copy_(torch.where(torch.arange(n, device=DEV) % 5 == 0, pairs, mine))
+    qkv.unpack_dequant(c.card, c.desc, c.k, c.v)
+    assert torch.isfinite(c.k).all() and torch.isfinite(c.v).all()
+    c.compare(c.cb, 0)
+
+
+def test_windows_of_tokens_refused_card():
+    """A header that is none, and a card with keys per channel: nothing is written but the front matter."""
+    c = LongCard(32, 8, 2001, 128, 32, "wide", "middle")
+    out = ref.card_offsets(ref.make_desc(*c.shape), c.cb)
+    per_plane = [c.cb[0] * 32, c.cb[0] * 16, c.cb[1] * 64, c.cb[1] * 16, c.cb[2] * 128, c.cb[2] * 16, c.cb[3] * 256]
+    for byte, value in ((3, 0), (188, qkv.FLAG_KEYS_PER_CHANNEL)):
+        was = int(c.card[byte].item())
+        c.card[byte] = value
+        got = c.requantize(c.cb)
+        assert int(c.status.item()) == qkv.STATUS_BAD_HEADER
+        for name, n in zip(("codes2", "meta2", "codes4", "meta4", "codes8", "meta8", "fp16"), per_plane):
+            assert (got[out[name]:out[name] + 512 * n] == 0xA5).all(), name
+        c.card[byte] = was
+    c.compare(c.cb, 0)
