@@ -171,8 +171,8 @@ def _counts(counts):
 
 
 # The current stream's handle without the object torch.cuda.current_stream() builds (2.9 us of a call's 8), and the current device without
-# torch.cuda.current_device()'s look whether CUDA is set up (0.2 us), which the tensors of a call have seen to.  Not part of
-# torch's public interface: where a torch lacks them, the public calls are made.
+# torch.cuda.current_device()'s look from Python whether CUDA is set up (0.2 us), which the native call makes by itself: in a forked child
+# too it asks torch's initialization, which refuses.  Not part of torch's public interface: where a torch lacks them, the public calls are made.
 _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 
@@ -305,7 +305,8 @@ def quantize_pack_kc(desc, k, v, bits, counts, card, stream=None):
 
 
 def requantize(card_in, desc, bits, counts, card_out, status=None, card_in_nbytes=None, stream=None):
-    """The card that quantize_pack would build from unpack_dequant(card_in), at the new widths, card to card."""
+    """The card that quantize_pack would build from unpack_dequant(card_in), at the new widths, card to card.  Where card_in is a buffer
+    longer than its card, card_in_nbytes should name the card's own length: the kernel is chosen by it."""
     n = card_in.numel() if card_in_nbytes is None else int(card_in_nbytes)
     sp = _optional_ptr(status, None, "status")
     _check(lib().qkv_requantize(_dev_ptr(card_in, torch.uint8, "card_in"), n, ctypes.byref(desc),
@@ -382,7 +383,7 @@ def inject_layers(card, expect, k_layers, v_layers, layer_begin=0, rope_base=0.0
                              1 if keys_per_channel else 0, 0)
     if _inject_by_address is None:
         lib()
-    _check(_inject_by_address(_dev_ptr(card, torch.uint8, "card"), n, ctypes.byref(expect), ctypes.byref(where),
+    _check(_inject_by_address(_dev_ptr(card, torch.uint8, "card"), n, expect, where,          # structures themselves: 0.3 us less than by byref()
                               None if status is None else _dev_ptr(status, None, "status"), _stream(stream)), "qkv_inject_layers")
 
 
