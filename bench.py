@@ -33,7 +33,7 @@ MALL_BYTES = 256 << 20    # memory-side cache: a working set below this is serve
 # taken: `sources` is a digest of the kernel sources at that time, and the figures are reported only while
 # the sources still have that digest (else `traffic` is null and says why).
 MEASURED_TRAFFIC = {
-    "llama8b_8k_b3": {"pack": 1341417132, "unpack": 1346941541, "sources": "2ac64f0c897e77ca",
+    "llama8b_8k_b3": {"pack": 1341416556, "unpack": 1346953653, "sources": "d726175ab8096a47",
                       "profile": "profiles/pack_unpack_llama8b_8k_b3_hbm_traffic.txt"},
 }
 KERNEL_SOURCES = ["pack.hip", "unpack.hip", "qkv_encode.h", "qkv_decode.h", "qkv_common.h"]

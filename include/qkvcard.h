@@ -389,7 +389,8 @@ int qkv_inject_layers(const void* card_dev, uint64_t card_bytes, const qkv_desc_
  * qkv_quantize_pack would build from the cache qkv_unpack_dequant rebuilds - byte for byte -
  * but moves only the two cards' bytes: every span is decoded and quantized again in registers.
  *   card_in_dev, card_in_bytes: the incoming card (device, 256-byte aligned, per-token groups);
- *               validated on the device like qkv_unpack_dequant does.
+ *               validated on the device like qkv_unpack_dequant does.  Where the card sits in a longer buffer, its own
+ *               length is the better argument: results are the same, but the kernel is chosen by it.
  *   desc:       host; shape of both cards (must match the incoming header) and the identifiers
  *               and position offset that go into the outgoing header.
  *   bits_dev, counts: the new widths, as for qkv_quantize_pack.

@@ -3,8 +3,9 @@
 //
 // An agent that forwards a card at new bit widths would otherwise rebuild the dense fp16 cache
 // (injection) and build the next card from it (card creation): 2 x (dense + card) bytes of traffic.
-// Here every span of 32 values is read from the incoming card, decoded with the injection kernel's
-// decoder, quantized with the card-creation kernel's quantizer and stored into the outgoing card; the
+// Here every span of 32 values is read from the incoming card, decoded to what injection would write - 2-bit codes
+// with its decoder, 4- and 8-bit codes with the attention kernel's, whose roundings are the same -, quantized with the
+// card-creation kernel's quantizer and stored into the outgoing card; the
 // dense values only ever exist in registers.  The result is, byte for byte, the card that creation
 // would build from the injected cache.
 //
@@ -24,15 +25,15 @@
 // in a row lie in a row in every segment of either card, so a window reads and writes every line once; its rounds are dealt out in the order
 // of their middle rows, so that what shares a line is done at about the same time (16384 tokens of 512 planes, 6 to 4: rows past the L2 read
 // 1.33 GB with windows of a width and 0.97, written 0.85 and 0.71, whole call 419 us and 375; in the order of the pairs it is a tenth slower than
-// with windows of a width).  Vector issue is then 90 % of the kernel's time at 3 to 6 bits; beyond 32K tokens reading and
-// writing at once is (reading alone 393 us, writing alone 261, both 740).
+// with windows of a width).  Vector issue is then 82 % of the kernel's time at 8K tokens, 3 to 2.5; at 32K, 6 to 4, it is 81 %, and reading and
+// writing at once takes as long as the kernel (reading alone 393 us, writing alone 261, both 740).
 //
 // Spans that were 2-bit (most of a card at low budgets) are not expanded to 32 values at all: a group
 // has four decoded values, in order, so its extrema follow from which codes occur, the quantizer runs
 // on the four values, and the new codes are the old ones relabelled.
 //
 // Whole call with the new widths' assignment, 8K tokens, budget 3 to 2.5: 199 us with 64 rows of one plane sorted per wave and every span
-// expanded to 32 values, 160 with windows of a width, 140 .. 146 with windows of tokens; 32K tokens, 6 to 4: 1162, 840 and 719 .. 760 us.
+// expanded to 32 values, 160 with windows of a width, 144 .. 146 with windows of tokens; 32K tokens, 6 to 4: 1162, 840 and 753 .. 764 us.
 // Windows of a width: of 512 rows 171 and 936 us; without the next round's loads in flight 172 and 877; of 256 tokens over all
 // widths at once, in the order of the pairs, 221 and 1137.
 //
@@ -659,11 +660,13 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
   // hundred tokens most rounds are then partly empty.  Short cards' windows run across planes instead, every one
   // full, at the price of a division per row and of a plane's widths being read at different times, which costs more
   // the less of the cards the 256 MB memory-side cache holds.  Where windows of a plane would be fewer than fill the
-  // chip, longer cards' run across planes too.  Kernel alone, us, with windows of a plane and across planes: 512 planes of
-  // 128 values, 200 tokens, budget 3 to 2.5, 17.0 and 9.0; 500 20.0 and 14.2; 1000 25.5 and 21.5; 1500, 6 to 4, 37.1
-  // and 36.4; 2000, 6 to 4, 45.3 and 47.4.  2048 planes, 850 tokens, 6 to 4 (310 MB) 85.9 and 86.5, 1400 143 and 155; of 256
-  // values 700 tokens 122 and 131.  64 planes of 6000 tokens 23.1 and 21.0, 16 of 32768 27.0 and 27.1.  Smaller windows
-  // while there are few: 200 tokens, 6 to 4, 11.6 with 128 rows and 12.1 with 256, 64 tokens 7.4 with 64 rows and 8.0 with 128.
+  // chip, longer cards' run across planes too.  Of the shapes that come here, whole call with the classification, us, with windows of a plane
+  // and across planes: 512 planes of 128 values, 200 tokens, budget 3 to 2.5, 19.9 and 13.9; 500 26.3 and 19.2; 1000 31.0 and 26.2;
+  // 1400, 6 to 4, 40.7 and 40.1; 1900 50.9 and 51.1; wide rows, 4000 tokens, 5 to 8 142 and 159, 9.5 to 6.5 148 and 155, 8 bits to 8 126 and 118.  512 planes of
+  // 64 values, 1500 tokens, 3 to 2.5 31.5 and 26.8, 1800 34.5 and 30.2, 6 to 4 33.6 and 32.6, 4000 57.9 and 58.6, 8192 124 and 130.  1024
+  // planes of 256 values, 9.5 to 6.5, 400 tokens 47.6 and 49.0, 900 131 and 139.  64 planes of 6000 tokens of 128 values 24.4 and 22.7, 16 of 32768
+  // 29.9 and 29.5.  Smaller windows while there are few (kernel alone): 200 tokens, 6 to 4, 11.6 with 128 rows and 12.1 with 256, 64 tokens 7.4
+  // with 64 rows and 8.0 with 128.
   const uint64_t rows = (uint64_t)out.planes * out.tokens;
   const uint64_t values = rows * out.head_dim;
   // Long cards: the windows of tokens, unless a head has 64 dimensions (windows of half the bytes, and as many rounds that are not
@@ -717,9 +720,10 @@ hipError_t launch_requant(const uint8_t* card_in, uint64_t card_in_bytes, const 
   a.stride = 1u;
   if (!across) {
     // A workgroup's look-ups are worth sharing between planes while the chip stays full several times over and both cards
-    // sit in the memory-side cache (8K tokens, budget 3 to 2.5: 161.7 us with two planes, 165.4 with one); larger cards
-    // want a plane's windows, which share lines of the incoming card, to run at the same time (32K, 6 to 4: 853 us with
-    // one plane, 951 with four).
+    // sit in the memory-side cache (512 planes of 64 values, 8192 tokens, 3 to 2.5: 76.1 us with two planes, 94.3 with one, 6 to 4 124 and 127, but 8 to 5
+    // 144 and 136; 20000 tokens, 3 to 2.5, 200 and 245); larger cards of wide rows want a plane's windows, which share lines of the
+    // incoming card, to run at the same time (60000 tokens, 8 to 5: 950 us with two planes, 898 with one; 512 of 128 values, 8192
+    // tokens, 9.5 to 6.5, 309 and 285).
     const bool resident = out.total <= kCacheResidentCardBytes && card_in_bytes <= kCacheResidentCardBytes;
     uint32_t group = resident ? kMaxPlanes : 1u;
     while (group > 1u && blocks * ((out.planes + group - 1u) / group) < 8192u) group /= 2u;
