@@ -1,10 +1,13 @@
-"""Uniform cards, whose tiles look their row addresses up before or after they load: injection into more and into fewer layers than
-the line between them, raw rows of a card beyond 512 MiB, keys per channel beyond 512 MiB of cache.  Unpacking at small
+"""Cards whose tiles look their row addresses up before or after they load: uniform ones injected into more and into fewer layers than
+the line between them, raw rows beyond 512 MiB, of any share of the tokens, keys per channel beyond 512 MiB of cache.  Unpacking at small
 sizes is compared with the oracle elsewhere; here the calls must agree with it, or with the raw rows themselves."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2605_03884_amd as qkv
+import qkv_synth
+from oracle import ref
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -60,6 +63,35 @@ def test_raw_rows_of_a_large_card():
     k2.zero_(), v2.zero_()
     qkv.inject_layers(card, desc, list(k2), list(v2), status=status)
     assert int(status.item()) == 0 and torch.equal(k, k2) and torch.equal(v, v2)
+
+
+@pytest.mark.parametrize("raw", [0, 1, 32, 33, 34, 132, 133])
+@pytest.mark.parametrize("D,G", [(64, 32), (128, 64), (256, 128)])
+def test_streamed_cards_of_mixed_widths(D, G, raw):
+    """A buffer beyond 512 MiB makes the card in it one that is streamed.  Raw tokens below, at and above a quarter, where their loads go out in halves."""
+    L, H, T = 6, 2, 133
+    print("[case] streamed D=%d, %d raw tokens of %d" % (D, raw, T), flush=True)
+    rng = np.random.default_rng(D + raw)
+    bits = np.concatenate([np.full(raw, 16, np.uint8), rng.choice(np.array([2, 4, 8], np.uint8), T - raw)])
+    rng.shuffle(bits)
+    K, V = qkv_synth.make_kv(L, H, T, D, 7 + raw, "llama")
+    rd = ref.make_desc(L, H, T, D, G)
+    card = ref.quantize_pack(rd, K.numpy().view(np.uint16), V.numpy().view(np.uint16), bits, ref.count_bits(bits).tolist())
+    want = [torch.from_numpy(x.reshape(L, H, T, D).view(np.int16)).to(DEV) for x in ref.unpack_dequant(card, rd)]
+    buffer = torch.empty((512 << 20) + 4096, dtype=torch.uint8, device=DEV)
+    buffer[:card.size] = torch.from_numpy(card).to(DEV)
+    desc = qkv.Desc.make(L, H, T, D, G)
+    status = torch.ones(1, dtype=torch.int32, device=DEV)
+    k, v = [torch.full((L, H, T, D), 7.0, dtype=torch.float16, device=DEV) for _ in range(2)]
+    qkv.unpack_dequant(buffer, desc, k, v, status=status)
+    assert int(status.item()) == 0
+    assert torch.equal(k.view(torch.int16), want[0]) and torch.equal(v.view(torch.int16), want[1])
+    for many in (L, 3):
+        k.fill_(7.0), v.fill_(7.0)
+        for begin in range(0, L, many):
+            qkv.inject_layers(buffer, desc, list(k[begin:begin + many]), list(v[begin:begin + many]), begin, status=status)
+        assert int(status.item()) == 0
+        assert torch.equal(k.view(torch.int16), want[0]) and torch.equal(v.view(torch.int16), want[1])
 
 
 @pytest.mark.parametrize("width", [2, 4, 8])
